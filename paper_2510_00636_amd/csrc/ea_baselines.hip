@@ -58,7 +58,12 @@ __device__ __forceinline__ float row_sum16(float x) {
 }
 
 constexpr int kBaseRowsPerWg = 128;     // 16 rows at a time, 8 rounds
-constexpr int kKeydiffRowsPerWg = 1024; // KeyDiff's second pass: the anchor is rebuilt once per workgroup
+// KeyDiff: how many workgroups its passes are cut into, as far as the heads are long enough.  The
+// first pass is bound by the loads a CU keeps in flight: 8 heads x 65536 rows at d = 128 took 121 us in
+// both passes with 4096 rows per workgroup of the first (128 workgroups, 1.6 TB/s), 56 us with 512.
+constexpr int kKeydiffWgs = 1024;
+constexpr int kKeydiffMaxRows = 1024;   // second pass: every workgroup adds up the head's partial sums, 512
+                                        // bytes per chunk at d = 128, which this many rows pay for
 
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void k_knorm(const void* __restrict__ k, long long n, long long n_cap,
@@ -134,7 +139,7 @@ __global__ __launch_bounds__(256) void k_keydiff_partial(const void* __restrict_
 // KeyDiff pass 2: the anchor a (partials added in chunk order), then 1 - cos(k_i, a) per row
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void k_keydiff_score(const void* __restrict__ k, long long n,
-                                                       long long n_cap, int units, int nchunk,
+                                                       long long n_cap, int units, int nchunk, int rows_per_wg,
                                                        const float* __restrict__ partial,
                                                        float* __restrict__ scores) {
   typedef RowPiece<D, BF16> RP;
@@ -142,10 +147,31 @@ __global__ __launch_bounds__(256) void k_keydiff_score(const void* __restrict__ 
   __shared__ float s_inv;
   const int tid = threadIdx.x, l = tid & 15, rw = tid >> 4;
   const int unit = blockIdx.x % units;
-  const long long r0 = (long long)(blockIdx.x / units) * kKeydiffRowsPerWg;
+  const long long r0 = (long long)(blockIdx.x / units) * rows_per_wg;
+  // the partials, four channels per thread: 1024 / D lanes share a channel group, each adds every
+  // (1024 / D)-th chunk in increasing order, eight loads in flight, and lane sums are added in lane
+  // order: the same bits on every run
+  constexpr int CG = D / 4, SH = 256 / CG;
+  __shared__ float4 s_sum[SH][CG];
+  {
+    const int cg = tid % CG, sh = tid / CG;
+    const float4* pp = reinterpret_cast<const float4*>(partial + (size_t)unit * nchunk * D) + cg;
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int q0 = sh; q0 < nchunk; q0 += 8 * SH) {
+      float4 x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = pp[(size_t)min(q0 + u * SH, nchunk - 1) * CG];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (q0 + u * SH < nchunk) { t.x += x[u].x; t.y += x[u].y; t.z += x[u].z; t.w += x[u].w; }
+    }
+    s_sum[sh][cg] = t;
+  }
+  __syncthreads();
   for (int c = tid; c < D; c += 256) {
     float s = 0.f;
-    for (int q = 0; q < nchunk; ++q) s += partial[((size_t)unit * nchunk + q) * D + c];
+#pragma unroll
+    for (int q = 0; q < SH; ++q) s += reinterpret_cast<const float*>(&s_sum[q][c / 4])[c % 4];
     s_a[c] = s / (float)n;
   }
   __syncthreads();
@@ -167,7 +193,7 @@ __global__ __launch_bounds__(256) void k_keydiff_score(const void* __restrict__ 
       const int c = RP::W * l + 16 * RP::W * j + e;
       an[RP::W * j + e] = c < D ? s_a[c] : 0.f;
     }
-  for (int it0 = 0; it0 < kKeydiffRowsPerWg / 16 && r0 + it0 * 16 < n; it0 += 8) {
+  for (int it0 = 0; it0 < rows_per_wg / 16 && r0 + it0 * 16 < n; it0 += 8) {
   RP pp[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) pp[u].load(base, min(r0 + (it0 + u) * 16 + rw, n - 1), l);
@@ -198,13 +224,17 @@ static hipError_t launch_baseline_t(const Dims& d, int kind, const void* k, int6
   if (kind == EA_SCORER_KNORM) {
     k_knorm<D, BF16><<<nblk * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), scores);
   } else {
-    int nchunk = (int)((n + 4095) / 4096);
-    if (nchunk > 256) nchunk = 256;
-    const int rows = (int)((n + nchunk - 1) / nchunk);
-    nchunk = (int)((n + rows - 1) / rows);
-    k_keydiff_partial<D, BF16><<<nchunk * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), rows, scratch);
-    const unsigned nblk2 = (unsigned)((n + kKeydiffRowsPerWg - 1) / kKeydiffRowsPerWg);
-    k_keydiff_score<D, BF16><<<nblk2 * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), nchunk, scratch, scores);
+    // both passes: rows per workgroup in multiples of 128 (16 rows at a time, eight loads in flight)
+    const int64_t spread = (n * d.units() / kKeydiffWgs + 127) / 128 * 128;
+    int64_t rows = spread < 128 ? 128 : spread;
+    const int64_t least = ((n + kBaselineChunks - 1) / kBaselineChunks + 127) / 128 * 128;   // the scratch holds that many chunks
+    if (rows < least) rows = least;
+    if (rows > n + 127) rows = n + 127;                     // (one chunk; keeps the count an int)
+    const int nchunk = (int)((n + rows - 1) / rows);
+    k_keydiff_partial<D, BF16><<<nchunk * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), (int)rows, scratch);
+    const int rows2 = spread < 128 ? 128 : spread > kKeydiffMaxRows ? kKeydiffMaxRows : (int)spread;
+    const unsigned nblk2 = (unsigned)((n + rows2 - 1) / rows2);
+    k_keydiff_score<D, BF16><<<nblk2 * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), nchunk, rows2, scratch, scores);
   }
   return hipGetLastError();
 }
