@@ -50,118 +50,207 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 caches: everything in fp64 on the vector units (the 1e-5 score tolerance of this
-// path leaves no room for fp32 accumulation of a d^2-term quadratic form).  One workgroup
-// = (unit, query head, span of keys); 64 keys at a time, K tile in LDS, thread (key, quarter
-// of the output channels).
-template <int D>
-__global__ __launch_bounds__(256) void k_score_f32(const float* __restrict__ k,
-                                                   const float* __restrict__ v, long long n,
+// fp32 caches: everything in fp64 (the 1e-5 score tolerance of this path leaves no room for fp32
+// accumulation of a d^2-term quadratic form), the quadratic form on the fp64 matrix cores.
+//
+// Y = M K^T runs as v_mfma_f64_16x16x4_f64: A = 16 output channels x 4 input channels of M, B = 4
+// input channels x 16 keys.  Lane l = (r = l % 16, q = l / 16) owns the channels q*d/4 .. of key r as
+// B operands; accumulator register v of the lane is row q + 4 v, and row rho of tile jt is the
+// channel (rho % 4)*d/4 + 4 jt + rho / 4, so the lane gets back channels it holds and k.(M k) needs
+// no data movement.  M folds the pair (c, j) and (j, c) of Sigma onto one side at the granularity
+// of the 16-channel blocks fb(c) = (c mod d/4) / 4 (the sum of two fp32 numbers, exact in fp64):
+// (d/16 + 1) / (2 d/16) of the dense work is left.  The rows of M of one output tile, a slab of up
+// to d/16 KiB x 2, are put together in LDS from Sigma by the four wavefronts and then used by each
+// for its KT x 16 keys, which stay in registers as fp32.
+//
+// What bounds it is the matrix cores' fp64 rate (64 cycles per instruction, 33 us of the first shape
+// below) and, at two wavefronts per SIMD, the latency around the slabs.  The vector units' fp64 rate
+// is the same, but the kernel on them that this replaces did the dense product and converted both
+// operands of every multiplication: 28 query heads x 5003 keys at d = 128 338 -> 82 us, 32 x 16000 at
+// d = 64 303 -> 83 us, 16 x 2000 at d = 256 446 -> 72 us, 4 x 1024 at d = 64 27 -> 10 us.
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+template <int D, int KT>
+__global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 5 - KT : 2)) void k_score_f32(const float* __restrict__ k, const float* __restrict__ v, long long n,
                                                    long long n_cap, const float* __restrict__ mu,
-                                                   const float* __restrict__ sigma, int G, int units,
-                                                   int span, int nchunk, double* __restrict__ logits,
-                                                   float* __restrict__ vnorm,
+                                                   const float* __restrict__ sigma, int G, int units, int span,
+                                                   int nchunk, double* __restrict__ logits, float* __restrict__ vnorm,
                                                    double2* __restrict__ part) {
-  constexpr int QW = D / 4;
-  extern __shared__ float s_k[];            // [64][D + 1]
-  __shared__ double s_red[4][64];
-  __shared__ double s_ms[2];
-  const int tid = threadIdx.x, r = tid & 63, qd = tid >> 6;
+  constexpr int QW = D / 4, NT = D / 16;
+  __shared__ double s_a[NT * 4 * 64];       // fragments of a slab, [k-step][lane]
+  __shared__ double s_mu[D];
+  __shared__ double s_ms[4][2];
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int unit = blockIdx.x % units;
   const int t2 = blockIdx.x / units;
   const int gq = t2 % G, chunk = t2 / G;
   const float* S = sigma + ((size_t)unit * G + gq) * D * D;
-  const float* M = mu + ((size_t)unit * G + gq) * D;
   const float* kb = k + (size_t)unit * n_cap * D;
   const float* vb = v + (size_t)unit * n_cap * D;
+  const bool do_v = chunk % G == gq;        // the value norms of a span: dealt to the group's heads in turn
   const long long key_lo = (long long)chunk * span, key_hi = min(key_lo + (long long)span, n);
-  double m_run = -INFINITY, s_run = 0.0;   // thread r < 64 of quarter 0 tracks key slot r
-  for (long long key0 = key_lo; key0 < key_hi; key0 += 64) {
-    __syncthreads();
-    for (int e = tid; e < 64 * D; e += 256) {
-      int rr = e / D, c = e - rr * D;
-      long long row = min(key0 + rr, n - 1);
-      s_k[rr * (D + 1) + c] = kb[row * D + c];
-    }
-    __syncthreads();
-    double y[QW];
-#pragma unroll
-    for (int j = 0; j < QW; ++j) y[j] = 0.0;
-    for (int c = 0; c < D; ++c) {
-      const double kc = (double)s_k[r * (D + 1) + c];
-      const float* Sr = S + (size_t)c * D + qd * QW;
-#pragma unroll
-      for (int j = 0; j < QW; ++j) y[j] = fma(kc, (double)Sr[j], y[j]);
-    }
-    double quad = 0.0, lin = 0.0;
-#pragma unroll
-    for (int j = 0; j < QW; ++j) {
-      const double kj = (double)s_k[r * (D + 1) + qd * QW + j];
-      quad = fma(y[j], kj, quad);
-      lin = fma((double)M[qd * QW + j], kj, lin);
-    }
-    s_red[qd][r] = lin / sqrt((double)D) + quad / (2.0 * D);
-    __syncthreads();
-    if (qd == 0 && key0 + r < n) {
-      double lg = s_red[0][r] + s_red[1][r] + s_red[2][r] + s_red[3][r];
-      logits[((size_t)unit * G + gq) * n + key0 + r] = lg;
-      double mn = fmax(m_run, lg);
-      s_run = s_run * exp(m_run - mn) + exp(lg - mn);
-      m_run = mn;
-    }
-    if (gq == 0) {   // value norms, once per unit
-      __syncthreads();
-      long long row = min(key0 + r, n - 1);
-      double ss = 0.0;
-      for (int j = 0; j < QW; ++j) {
-        double x = (double)vb[row * D + qd * QW + j];
-        ss = fma(x, x, ss);
-      }
-      s_red[qd][r] = ss;
-      __syncthreads();
-      if (qd == 0 && key0 + r < n)
-        vnorm[(size_t)unit * n + key0 + r] =
-            (float)sqrt(s_red[0][r] + s_red[1][r] + s_red[2][r] + s_red[3][r]);
-    }
-  }
-  // reduce the 64 key slots
+  double m_run = -INFINITY, s_run = 0.0;    // of the keys in this lane's slots r
+  if (tid < D) s_mu[tid] = (double)mu[((size_t)unit * G + gq) * D + tid];
   __syncthreads();
-  if (qd == 0) {
-    double m = m_run, s = s_run;
-    for (int o = 32; o >= 1; o >>= 1) {
-      double m2 = __shfl_xor(m, o), s2 = __shfl_xor(s, o);
-      double mn = fmax(m, m2);
-      if (mn == -INFINITY) { s = 0.0; m = mn; }
-      else { s = s * exp(m - mn) + s2 * exp(m2 - mn); m = mn; }
+  // Tile b of slab jt is one wavefront's: M's own side (c_out, c_in .. c_in + 3) and, for b < jt, the
+  // mirrored entries (c_in, c_out ..), which are added to it in LDS.  (A second buffer, filled during the
+  // matrix instructions of the slab in front, costs the third workgroup of a CU and gains nothing.)
+  const int ms = (lane >> 2) & 3, mq = lane & 3;
+  auto build_slab = [&](int jt) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int b = wave; b <= jt; b += 4) {
+      const float4 own = *reinterpret_cast<const float4*>(S + (size_t)((r & 3) * QW + 4 * jt + (r >> 2)) * D + q * QW + 4 * b);
+      const float4 mir = *reinterpret_cast<const float4*>(S + (size_t)(q * QW + 4 * b + ms) * D + mq * QW + 4 * jt);
+      double* at = s_a + b * 256;
+      at[lane] = own.x;
+      at[64 + lane] = own.y;
+      at[128 + lane] = own.z;
+      at[192 + lane] = own.w;
+      if (b < jt) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double* am = at + ms * 64 + q * 16 + mq;
+        am[0] += (double)mir.x;
+        am[4] += (double)mir.y;
+        am[8] += (double)mir.z;
+        am[12] += (double)mir.w;
+      }
     }
-    if (r == 0) part[((size_t)unit * G + gq) * nchunk + chunk] = make_double2(m, s);
+  };
+  for (long long key0 = key_lo; key0 < key_hi; key0 += 64 * KT) {
+    float kf[KT][QW];
+    long long key[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      key[t] = key0 + (wave * KT + t) * 16 + r;
+      const float4* kp = reinterpret_cast<const float4*>(kb + min(key[t], n - 1) * D + q * QW);
+#pragma unroll
+      for (int x = 0; x < QW / 4; ++x) {
+        const float4 f = kp[x];
+        kf[t][4 * x] = f.x; kf[t][4 * x + 1] = f.y; kf[t][4 * x + 2] = f.z; kf[t][4 * x + 3] = f.w;
+      }
+    }
+    double lin[KT], quad[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) { lin[t] = 0.0; quad[t] = 0.0; }
+#pragma unroll
+    for (int x = 0; x < QW; ++x) {
+      const double m = s_mu[q * QW + x];
+#pragma unroll
+      for (int t = 0; t < KT; ++t) lin[t] = fma(m, (double)kf[t][x], lin[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(lin[t]));
+    static_for<NT>([&](auto jt_) {
+      constexpr int jt = decltype(jt_)::value;
+      // (keeps the compiler from holding the keys widened to 64 bits across the slabs: the conversions are
+      // hidden by the matrix instructions, twice the registers are not)
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int x = 0; x < QW; ++x) asm volatile("" : "+v"(kf[t][x]));
+      __syncthreads();                      // the previous slab has been consumed
+      build_slab(jt);
+      __syncthreads();
+      doublex4 acc[KT];
+#pragma unroll
+      for (int t = 0; t < KT; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+      // four k-steps at a time, the next four fragments on their way; nothing moves across the blocks
+      // (left alone, the scheduler widens every key and fetches every fragment of the slab at once)
+      double f[2][4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[0][e] = s_a[e * 64 + lane];
+      static_for<jt + 1>([&](auto b_) {
+        constexpr int b = decltype(b_)::value;
+        if constexpr (b < jt) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) f[(b + 1) & 1][e] = s_a[(4 * (b + 1) + e) * 64 + lane];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < KT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[b & 1][e], (double)kf[t][4 * b + e], acc[t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) quad[t] = fma(acc[t][x], (double)kf[t][4 * jt + x], quad[t]);
+#pragma unroll
+      for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(quad[t]));     // dotted here, not at the end of all slabs
+    });
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      double lg = lin[t] / sqrt((double)D) + quad[t] / (2.0 * D);
+      lg += __shfl_xor(lg, 16);
+      lg += __shfl_xor(lg, 32);
+      if (key[t] < n) {
+        if (q == 0) logits[((size_t)unit * G + gq) * n + key[t]] = lg;
+        const double mn = fmax(m_run, lg);
+        s_run = s_run * exp(m_run - mn) + exp(lg - mn);
+        m_run = mn;
+      }
+      if (do_v) {
+        const float4* vp = reinterpret_cast<const float4*>(vb + min(key[t], n - 1) * D + q * QW);
+        double ss = 0.0;
+#pragma unroll
+        for (int x = 0; x < QW / 4; ++x) {
+          const float4 f = vp[x];
+          ss = fma((double)f.x, (double)f.x, ss);
+          ss = fma((double)f.y, (double)f.y, ss);
+          ss = fma((double)f.z, (double)f.z, ss);
+          ss = fma((double)f.w, (double)f.w, ss);
+        }
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        if (q == 0 && key[t] < n) vnorm[(size_t)unit * n + key[t]] = (float)sqrt(ss);
+      }
+    }
   }
-  (void)s_ms;
+  // (max, sum exp) of the span: the 16 key slots of each wavefront, then the four wavefronts
+  double m = m_run, s = s_run;
+  auto merge = [&](double m2, double s2) {
+    const double mn = fmax(m, m2);
+    if (mn == -INFINITY) s = 0.0;
+    else s = s * exp(m - mn) + s2 * exp(m2 - mn);
+    m = mn;
+  };
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1) merge(__shfl_xor(m, o), __shfl_xor(s, o));
+  if (lane == 0) { s_ms[wave][0] = m; s_ms[wave][1] = s; }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 4; ++w) merge(s_ms[w][0], s_ms[w][1]);
+    part[((size_t)unit * G + gq) * nchunk + chunk] = make_double2(m, s);
+  }
 }
 
 hipError_t launch_score_f32(const Dims& d, const void* k, const void* v, int64_t n, int64_t n_cap,
                             const float* mu, const float* sigma, double* logits, float* vnorm,
                             double2* part, int* nchunk_out, hipStream_t st) {
+  // 64 KT keys per workgroup and step: two key tiles per wavefront halve the reads and the building of
+  // the slabs per key, once that still leaves two workgroups per CU (at d = 256 one tile's keys fill the
+  // registers); spans so that a head has at most 1024 partials
+  const int64_t heads = d.qheads();
+  const int kt = d.D <= 128 && heads * ((n + 127) / 128) >= 2 * (int64_t)device_num_cu() ? 2 : 1;
   int64_t span = (n + 1023) / 1024;
-  span = (span + 63) / 64 * 64;
-  if (span < 64) span = 64;
+  span = (span + 64 * kt - 1) / (64 * kt) * (64 * kt);
   int nchunk = (int)((n + span - 1) / span);
   *nchunk_out = nchunk;
-  int grid = d.units() * d.G * nchunk;
-  size_t lds = (size_t)64 * (d.D + 1) * sizeof(float);
-#define EA_F32(DD)                                                                              \
-  if (d.D == DD) {                                                                              \
-    auto kern = k_score_f32<DD>;                                                                \
-    static LdsOptIn opt;                                                                        \
-    hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);                        \
-    if (e != hipSuccess) return e;                                                              \
-    kern<<<grid, 256, lds, st>>>((const float*)k, (const float*)v, n, n_cap, mu, sigma, d.G,    \
-                                 d.units(), (int)span, nchunk, logits, vnorm, part);            \
-    return hipGetLastError();                                                                   \
+  const int64_t grid = heads * nchunk;
+#define EA_F32(DD, KK)                                                                             \
+  if (d.D == DD && kt == KK) {                                                                     \
+    k_score_f32<DD, KK><<<(unsigned)grid, 256, 0, st>>>((const float*)k, (const float*)v, n, n_cap, mu, sigma, d.G, \
+                                                        d.units(), (int)span, nchunk, logits, vnorm, part); \
+    return hipGetLastError();                                                                      \
   }
-  EA_F32(64)
-  EA_F32(128)
-  EA_F32(256)
+  EA_F32(64, 1)
+  EA_F32(64, 2)
+  EA_F32(128, 1)
+  EA_F32(128, 2)
+  EA_F32(256, 1)
 #undef EA_F32
   return hipErrorInvalidValue;
 }

@@ -27,3 +27,22 @@ def test_keydiff_chunk_edges(n, d, dtype):
     ea.score_baseline(p, ea.SCORER_KEYDIFF, P.to_dev(lay["k"]), n, n, 0, sc, P.workspace(p, n, 1))
     torch.cuda.synchronize()
     assert np.abs(sc.cpu().numpy() - X.keydiff_scores(widen(lay["k"]))).max() <= 2e-6
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("hq,hkv,n", [(4, 2, 1), (4, 2, 63), (6, 2, 65), (4, 1, 1023), (8, 2, 8201)])
+def test_fp32_scores_tile_edges(d, hq, hkv, n):
+    """fp32 caches: heads shorter than a key tile, around 64 and 128 keys, spans of more than one
+    tile and (8 heads x 8201 keys) the two-tile instances, with a Sigma that is not symmetric.  The
+    logits are fp64 sums of the given fp32 numbers, so a score carries the rounding of ||v|| and its
+    own to fp32: 2^-23, and the 2^-22 allowed here."""
+    import torch
+    rng = np.random.default_rng(7 * n + d)
+    cfg = CONFIGS["c1"].with_(head_dim=d, n_q_heads=hq, n_kv_heads=hkv)
+    lay = make_layer(cfg, n=n, window=min(n, 2))
+    a = rng.standard_normal((1, hq, d, d)) / np.sqrt(d)
+    sigma = (a @ a.transpose(0, 1, 3, 2) + 0.05 * rng.standard_normal((1, hq, d, d))).astype(np.float32)
+    mu = rng.standard_normal((1, hq, d)).astype(np.float32)
+    got = P.run_score(cfg, lay, mu, sigma, 0.02, n_cap=n + 3)
+    ref = O.scores(widen(lay["k"]), widen(lay["v"]), mu.astype(np.float64), sigma.astype(np.float64), 0.02)
+    P.check_scores(got, ref, 2.0 ** -22)
