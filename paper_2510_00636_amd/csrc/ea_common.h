@@ -34,8 +34,8 @@ struct ScorePlan {
   int passes;   // ceil(G / GH); K is streamed once per pass
   int NW;       // wavefronts per workgroup
   int nfrag;    // 1 KiB fragments per (unit, pass)
-  int span;     // keys per workgroup were the head split evenly (the kernel deals tiles by ticket)
-  int nchunk;   // workgroups per unit = ceil(n / span)
+  int nchunk;   // workgroups per (unit, pass)
+  int spare;    // 1: more workgroups than CUs; the ones dispatched late join heads that still have tiles
   int hw;       // 1: the register-fragment kernel (one wavefront per query head, d = 128, groups of four)
   int tpt;      // that kernel: tiles of 32 keys per ticket (1 or 4)
   int pg;       // keys per softmax partial (max, sum exp): partial j covers keys [j*pg, (j+1)*pg)

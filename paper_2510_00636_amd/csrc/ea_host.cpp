@@ -44,6 +44,7 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   ScorePlan s;
   s.hw = 0;
   s.tpt = 1;
+  s.spare = 0;
   s.lse_pass = 0;
   if (!paged && !d.kv_fp8 && d.D == 128 && d.dtype == EA_BF16 && d.G % 4 == 0 && n >= 2048 && (int64_t)d.units() * (d.G / 4) <= 8) {
     // groups of four query heads at d = 128, calls of up to 8 (KV head, group) units: fragments in
@@ -66,7 +67,6 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     const int64_t nblocks = (ntiles + s.tpt - 1) / s.tpt;
     if (wgs > nblocks) wgs = nblocks;
     s.nchunk = (int)wgs;
-    s.span = (int)((n + wgs - 1) / wgs);
     s.pg = 32 * s.tpt;
     s.npart = (int)nblocks;
     return s;
@@ -96,15 +96,27 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     s.nfrag = 2 * NF + 2 * NKS;
     s.lds_bytes = (size_t)2 * NF * 1024 + (size_t)s.NW * 4096;
   }
-  const int tile = s.NW * 32;
+  // A CU holds one workgroup.  Up to half as many units as CUs: every unit gets its share of the CUs,
+  // rounded down.  More (unit, pass) jobs than CUs that leave the last round of CUs to 85 % full or less:
+  // three spare workgroups per job are launched behind the first ones, and a CU whose head is done
+  // takes one of them and joins a head that still has tiles (tickets deal them).  query_stats + score in
+  // a row at d = 128, without and with: 304 units, G = 4, n = 4608 319 and 265 us; 384 units, G = 5,
+  // 421 and 382; 160 units in two passes 277 and 234.  With fewer jobs than CUs it does not pay at
+  // d <= 128: 192 CUs at the clock the chip then grants do what 256 do (192 units 203 and 200 us, the
+  // whole decode-time pass 415 and 420); at d = 256, one wavefront per SIMD, it does (192 units x 4000
+  // keys: 339 and 304 us).  Nor does it on heads of under 1024 keys.
+  const int64_t most = ((n + 31) / 32 + s.NW - 1) / s.NW;       // every wavefront with a tile at least
+  const int64_t jobs = (int64_t)d.units() * s.passes;
   int64_t wgs = num_cu / d.units();
-  if (wgs < 1) wgs = 1;
   if (wgs > 1024) wgs = 1024;
-  int64_t span = (n + wgs - 1) / wgs;
-  span = (span + tile - 1) / tile * tile;
-  if (span < tile) span = tile;
-  s.span = (int)span;
-  s.nchunk = (int)((n + span - 1) / span);
+  if (wgs < 2) {
+    const int64_t rounds = (jobs + num_cu - 1) / num_cu;
+    s.spare = rounds <= 8 && jobs * 20 < rounds * num_cu * 17 && n >= 1024 && (jobs > num_cu || d.D == 256);
+    wgs = !s.spare ? 1 : wgs == 1 ? 3 : 4;
+  }
+  if (wgs > most) wgs = most;
+  if (wgs < 2) s.spare = 0;
+  s.nchunk = (int)wgs;
   s.lse_pass = 1;
   s.pg = kLseBlock;
   s.npart = (int)((n + s.pg - 1) / s.pg);

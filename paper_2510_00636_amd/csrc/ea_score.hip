@@ -35,6 +35,7 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
   a.nchunk = sp.nchunk;
   a.npart = sp.npart;
   a.tpt = sp.tpt;
+  a.spare = sp.spare;
   a.units = d.units();
   a.nfrag = sp.nfrag;
   a.tickets = tickets;

@@ -39,6 +39,7 @@ struct ScoreArgs {
   PageMap pm;             // pm.table != nullptr: k and v are block pools (CLAMP instances only)
   const float* kscale;    // FP8 instances: real key = kscale[unit] * stored value (nullptr: 1)
   const float* vscale;    // likewise for the values
+  int spare;              // 1: more workgroups than CUs, see ScorePlan
   int skip_v;             // 1: the caller has its own per-pair weights; V is not read, vnorm not written
 };
 
@@ -232,10 +233,28 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   // lets the faster dies (clocks under matrix-core load differ by 15 % and more) take a larger
   // share of a head instead of idling while the slowest one finishes.
   int bid = blockIdx.x;
-  if ((gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);
-  const int unit = bid % a.units;
+  if (!a.spare && (gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);
+  int unit = bid % a.units;
   const int t2 = bid / a.units;
-  const int chunk = t2 % a.nchunk, pass = t2 / a.nchunk;
+  int chunk = t2 % a.nchunk, pass = t2 / a.nchunk;
+  if (a.spare) {
+    // spare workgroups: one of every (unit, pass) first, in dispatch order, then the second ones, .. (each
+    // three units on, so that they land on another die); one that comes when its head's tiles are all
+    // dealt out leaves before it loads the fragments
+    chunk = t2 / a.passes;
+    pass = t2 % a.passes;
+    unit = (unit + 3 * chunk) % a.units;
+    if (chunk > 0) {
+      uint32_t* left = reinterpret_cast<uint32_t*>(smem);
+      if (tid == 0)
+        *left = __hip_atomic_load(a.tickets + (size_t)unit * a.ticket_stride + pass * kTicketWays, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+      const bool none = *left >= (uint32_t)((a.n + 31) / 32);
+      __syncthreads();
+      if (none) return;
+    }
+  }
   const int g0 = pass * GH;
   const bool do_v = pass == 0 && !a.skip_v;
 
@@ -248,7 +267,7 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   // that a head scored by hundreds of workgroups (few KV heads per call) does not queue up on one
   // address: an atomic on one address takes about 13 ns.  A workgroup uses the counter of its
   // index modulo the number of counters in use.
-  const int ways = max(1, min(kTicketWays, a.nchunk / 8));    // at least 8 workgroups per counter
+  const int ways = a.spare ? 1 : max(1, min(kTicketWays, a.nchunk / 8));    // at least 8 workgroups per counter
   const int way = chunk % ways;
   uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + pass * kTicketWays + way;
   // The counter's value is only turned into a tile number where it is used, an iteration later:

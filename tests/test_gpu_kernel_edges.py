@@ -46,3 +46,21 @@ def test_fp32_scores_tile_edges(d, hq, hkv, n):
     got = P.run_score(cfg, lay, mu, sigma, 0.02, n_cap=n + 3)
     ref = O.scores(widen(lay["k"]), widen(lay["v"]), mu.astype(np.float64), sigma.astype(np.float64), 0.02)
     P.check_scores(got, ref, 2.0 ** -22)
+
+
+@pytest.mark.parametrize("d,hq,hkv,batch,n", [
+    (128, 5, 1, 260, 1030),      # a second round of four units
+    (128, 7, 1, 150, 1030),      # the same in two passes
+    (64, 2, 1, 300, 1500),       # more units than CUs
+    (256, 2, 1, 140, 1030),
+    (128, 4, 1, 150, 1000),      # too short for spare workgroups
+])
+def test_scores_with_spare_workgroups(d, hq, hkv, batch, n):
+    """Calls whose units do not fill the chip: workgroups dispatched late join heads in progress.
+    Against the oracle at the bf16 tolerance of the score path."""
+    cfg = CONFIGS["c2"].with_(head_dim=d, n_q_heads=hq, n_kv_heads=hkv, batch=batch)
+    lay = make_layer(cfg, n=n, window=64)
+    mu, sigma = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T)
+    mu, sigma = mu.astype(np.float32), sigma.astype(np.float32)
+    got = P.run_score(cfg, lay, mu, sigma, 0.02)
+    P.check_scores(got, O.scores(widen(lay["k"]), widen(lay["v"]), mu, sigma, 0.02), 2e-3)
