@@ -49,6 +49,21 @@ static ea_status run_stats(const Dims& d, const void* q_win, int64_t window, int
   return EA_OK;
 }
 
+// Statistics for a score pass that follows in the same call.  Returns through *frags_ready whether the score
+// kernel's operands stand in the workspace already (then mu and sigma were not written).
+static ea_status run_stats_for_score(const Dims& d, const void* q_win, int64_t window, int64_t q_pos0,
+                                     const double* inv_freq, int64_t t_next, int64_t n, bool paged, float* mu, float* sigma,
+                                     char* ws, const WsLayout& L, hipStream_t st, uint32_t* clear, size_t clear_words,
+                                     bool* frags_ready) {
+  *frags_ready = stats_makes_frags(d);
+  if (!*frags_ready) return run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, ws, L, st, clear, clear_words);
+  float2* tab = (float2*)(ws + L.tab);
+  EA_TRY(launch_rope_table(d, inv_freq, q_pos0, t_next, (int)window, tab, clear, clear_words, st));
+  const ScorePlan sp = make_score_plan(d, n, device_num_cu(), paged);
+  EA_TRY(launch_stats_frags(d, sp, q_win, (int)window, tab, (uint4*)(ws + L.frags), (float*)(ws + L.post), st));
+  return EA_OK;
+}
+
 // hist0 != nullptr: the finalize pass also fills the first radix-select histogram.
 // ev (nullable): ev[0] is recorded after the operand preparation, ev[1] after pass A.
 // The score kernel's tile counters live in words of the third histogram that the 1024-bin
@@ -58,7 +73,8 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
                            const float* mu, const float* sigma, float* scores, uint32_t* hist0,
                            bool hist_zeroed, char* ws, const WsLayout& L, hipStream_t st,
                            hipEvent_t* ev = nullptr, const float* wnorm = nullptr, float* wnorm_out = nullptr,
-                           const PageMap* pm = nullptr, const float* kscale = nullptr, const float* vscale = nullptr) {
+                           const PageMap* pm = nullptr, const float* kscale = nullptr, const float* vscale = nullptr,
+                           bool frags_ready = false) {
   // wnorm: Eq. 9 with per-query-head norms ||W_o v||.  wnorm_out: stop after pass A and turn its
   // quadratic forms into such norms (the caller passed the values as keys, mu = 0, Sigma = M_g).
   float* vnorm = (float*)(ws + L.vnorm);
@@ -68,7 +84,7 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
     ScorePlan sp = make_score_plan(d, n, device_num_cu(), pm != nullptr);
     uint4* frags = (uint4*)(ws + L.frags);
     float* post = (float*)(ws + L.post);
-    EA_TRY(launch_prep_frags(d, sp, mu, sigma, frags, post, st));
+    if (!frags_ready) EA_TRY(launch_prep_frags(d, sp, mu, sigma, frags, post, st));
     if (ev) EA_TRY(hipEventRecord(ev[0], st));
     EA_TRY(launch_score_mfma(d, sp, k, v, n, n_cap, frags, post, (float*)(ws + L.logits), vnorm,
                              (float2*)(ws + L.part), hist + 2 * kSelBins + kTicketSlot, 3 * kSelBins,
@@ -360,13 +376,14 @@ static ea_status compress_impl(const ea_params* p, const void* q_win, int64_t wi
   // hist .. flags are adjacent regions of ws: one clearing launch covers histograms (with the
   // status word and the tile counters in their free words), block counts and the compaction flags
   const size_t clear_words = (L.flags - L.hist) / 4 + flag_words(d, n_keep);
-  if ((s = run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, w, L, st, hist,
-                     clear_words)) != EA_OK)
+  bool frags_ready = false;
+  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, pm != nullptr, mu, sigma, w, L, st, hist,
+                               clear_words, &frags_ready)) != EA_OK)
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[1], st));
   if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores,
                      n_keep > 0 && !select_in_one_launch(n) ? hist : nullptr, true, w, L, st,
-                     ev ? ev + 2 : nullptr, nullptr, nullptr, pm, kscale, vscale)) != EA_OK)
+                     ev ? ev + 2 : nullptr, nullptr, nullptr, pm, kscale, vscale, frags_ready)) != EA_OK)
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[4], st));
   if (n_keep > 0)
@@ -458,8 +475,13 @@ ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int6
   float* mu = (float*)(w + L.mu);
   float* sigma = (float*)(w + L.sigma);
   float* scores = scores_out ? scores_out : (float*)(w + L.scores);
-  if ((s = run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, w, L, st)) != EA_OK) return s;
-  if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores, nullptr, false, w, L, st)) != EA_OK) return s;
+  bool frags_ready = false;
+  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, false, mu, sigma, w, L, st, nullptr, 0,
+                               &frags_ready)) != EA_OK)
+    return s;
+  if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores, nullptr, false, w, L, st, nullptr, nullptr, nullptr, nullptr,
+                     nullptr, nullptr, frags_ready)) != EA_OK)
+    return s;
   // after pass B the logit and value-norm scratch is free: the floor's lists and the lifted copy
   // of the scores go there
   if ((s = run_select_adaptive(d, scores, n, n_keep, floor, idx_out, lengths_out, (float*)(w + L.vnorm),

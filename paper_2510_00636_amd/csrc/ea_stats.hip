@@ -348,6 +348,129 @@ __global__ __launch_bounds__(256, (D <= 128 ? 3 : 2)) void k_stats(const void* _
 }
 
 // ---------------------------------------------------------------------------------------
+// Matrix-core operands for the score kernel, made by k_prep_frags from (mu, Sigma) in memory or by the
+// statistics kernel itself.
+//
+// The quadratic form k^T Sigma k is evaluated as sum_j (sum_c k_c M[c][j]) k_j where M folds
+// the symmetric pair (c, j) and (j, c) onto one side at the granularity of 16-channel
+// "folded blocks" fb(c) = (c mod d/2) / 16:  M[c][j] = Sigma[c][j] + Sigma[j][c] when
+// fb(c) < fb(j), Sigma[c][j] when fb(c) == fb(j), and 0 otherwise -- the zero blocks are
+// simply not stored, which removes 3/8 of the matrix-core work.  M is scaled by a power of
+// two into fp16 range and rounded to fp16; the rounding error of its diagonal (the dominant
+// error term, since k_c^2 never cancels) is kept as a residual row that multiplies k_c^2 in
+// an extra accumulator tile.  mu is split into an fp16 head and tail in the same tile.
+//
+// Fragment (1 KiB = 64 lanes x 8 halves) for (head g, output tile jt, k-step kt):
+//   lane l (rho = l % 32, hl = l / 32), element i:
+//     input channel   c_in  = hl * d/2 + kt * 8 + i
+//     output channel  c_out = ((rho / 4) % 2) * d/2 + jt * 16 + 4 * (rho / 8) + rho % 4
+// so that in the 32x32 accumulator layout a lane (hh = l / 32) holds exactly the output
+// channels hh * d/2 + x that it also feeds as inputs: the epilogue dot with k needs no
+// data movement.
+__device__ __forceinline__ float scale_for(float maxabs) {
+  if (!(maxabs > 0.f) || !isfinite(maxabs)) return 1.0f;
+  int e;
+  frexpf(maxabs, &e);                 // maxabs = f * 2^e, f in [0.5, 1)
+  int sh = 13 - e;                    // scaled max in [2^12, 2^13)
+  sh = max(-100, min(100, sh));
+  return ldexpf(1.0f, sh);
+}
+
+__device__ __forceinline__ uint4 pack_half8(const _Float16 (&h)[8]) {
+  uint4 pk;
+  pk.x = (uint32_t)__builtin_bit_cast(uint16_t, h[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[1]) << 16);
+  pk.y = (uint32_t)__builtin_bit_cast(uint16_t, h[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[3]) << 16);
+  pk.z = (uint32_t)__builtin_bit_cast(uint16_t, h[4]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[5]) << 16);
+  pk.w = (uint32_t)__builtin_bit_cast(uint16_t, h[6]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[7]) << 16);
+  return pk;
+}
+
+// Where FUSED instances write: the operands of the score kernel instead of mu and Sigma.
+struct FragsOut {
+  uint4* frags;
+  float* post;
+  int G, GH, passes, nfrag;
+};
+
+// an odd pitch: neither rows nor columns of Sigma in LDS pile up in a bank
+constexpr int stats_sigma_pitch(int D) { return D + 1; }
+
+// The fragments of one head (see above) out of its Sigma in LDS [D][pitch] and its mean shift + xbar, by the
+// 256 threads of a workgroup: the head's own fragments of the triangle, and its rows of the extra tile's.
+// The first head of a (unit, pass) also writes the rows and fragments that belong to no head.
+template <int D>
+__device__ __forceinline__ void stats_write_frags(const float* S, const float* s_shift, const float* s_xbar, int head,
+                                                  const FragsOut& fo) {
+  constexpr int HALF = D / 2, NKS = D / 16, NJT = D / 32, NF = NJT * (NJT + 1), SP = stats_sigma_pitch(D);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int unit = head / fo.G, gq = head - unit * fo.G, pass = gq / fo.GH, g = gq - pass * fo.GH;
+  const int nhere = min(fo.GH, fo.G - pass * fo.GH);          // heads of this (unit, pass)
+  float mxS = 0.f, mxM = 0.f;                                 // every wavefront for itself
+  for (int e = lane; e < D; e += 64) {
+    mxS = fmaxf(mxS, fabsf(S[e * SP + e]));
+    mxM = fmaxf(mxM, fabsf(s_shift[e] + s_xbar[e]));
+  }
+  for (int o = 32; o >= 1; o >>= 1) {
+    mxS = fmaxf(mxS, __shfl_xor(mxS, o));
+    mxM = fmaxf(mxM, __shfl_xor(mxM, o));
+  }
+  const float sM = scale_for(2.0f * mxS), smu = scale_for(mxM);
+  if (tid == 0) {
+    fo.post[(size_t)head * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
+    fo.post[(size_t)head * 2 + 1] = 1.0f / (sqrtf((float)D) * smu);
+  }
+  uint4* out = fo.frags + ((size_t)unit * fo.passes + pass) * fo.nfrag * 64;
+#pragma unroll
+  for (int it = 0; it < (NF * 64 + 255) / 256; ++it) {
+    const int item = it * 256 + tid, f = item >> 6, l = item & 63, rho = l & 31, hl = l >> 5;
+    if (NF * 64 % 256 != 0 && item >= NF * 64) break;
+    int rem = f, jt = 0;
+    while (rem >= 2 * jt + 2) { rem -= 2 * jt + 2; ++jt; }
+    const int c_out = ((rho >> 2) & 1) * HALF + jt * 16 + 4 * (rho >> 3) + (rho & 3), c_in0 = hl * HALF + rem * 8;
+    const bool folded = (rem >> 1) < jt;
+    _Float16 h[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float val = S[c_out * SP + c_in0 + i];
+      // (inside a 32 x 32 tile on the diagonal the two differ by rounding)
+      if (folded) val += S[(c_in0 + i) * SP + c_out];
+      h[i] = (_Float16)(val * sM);
+    }
+    out[g * NF * 64 + item] = pack_half8(h);
+  }
+  for (int item = tid; item < 2 * NKS * 64; item += 256) {
+    const int fe = item >> 6, l = item & 63, rho = l & 31, hl = l >> 5;
+    const bool is_res = fe >= NKS;
+    const int kt = is_res ? fe - NKS : fe;
+    int row = -1, kind = -1;                                  // whose row this is
+    if (!is_res && rho < 2 * fo.GH) { row = rho % fo.GH; kind = rho / fo.GH; }
+    if (is_res && rho >= 2 * fo.GH && rho < 3 * fo.GH) { row = rho - 2 * fo.GH; kind = 2; }
+    const bool mine = row == g, nobodys = g == 0 && (row < 0 || row >= nhere);
+    if (!mine && !nobodys) continue;
+    _Float16 h[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int c = hl * HALF + kt * 8 + i;
+      float val = 0.f;
+      if (mine && kind == 2) {
+        const float m = S[c * SP + c] * sM;
+        val = m - (float)(_Float16)m;
+      } else if (mine) {
+        const float m = (s_shift[c] + s_xbar[c]) * smu;
+        const float hi = (float)(_Float16)m;
+        val = kind == 0 ? hi : m - hi;
+      }
+      h[i] = (_Float16)val;
+    }
+    out[(fo.GH * NF) * 64 + item] = pack_half8(h);
+  }
+  if (g == 0) {                                               // heads that the last pass has room for but not
+    const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+    for (int item = nhere * NF * 64 + tid; item < fo.GH * NF * 64; item += 256) out[item] = z;
+  }
+}
+
+// ---------------------------------------------------------------------------------------
 // The same statistics for bf16 windows with the outer products on the fp16 matrix cores.
 //
 // fp32 matrix-core instructions run at the rate of the vector units (and do not overlap with
@@ -370,12 +493,35 @@ typedef _Float16 stats_half2 __attribute__((ext_vector_type(2)));
 // chunk's queries and table rows in flight during the matrix-core loop)
 constexpr int stats_split_chunk(int D) { return D >= 256 ? 32 : 64; }
 
-template <int D, int LAYOUT, int PARTS = 0>
+// u~ - shift: the 2x2 block of the table applied to one pair.  Which of the two products of a sum is rounded on
+// its own is spelled out (of the second: t.x qb, or t.y qa), and nothing else is contracted, so that the bits
+// of the statistics, and with them every score, do not hang on what the compiler makes of the code around it.
+__device__ __forceinline__ void stats_rotate(bool round_txqb, float2 t, float qa, float qb, float sha, float shb,
+                                             float& xa, float& xb) {
+#pragma clang fp contract(off)
+  const float pa = t.y * qb;
+  const float pb = round_txqb ? t.x * qb : t.y * qa;
+  const float ua = fmaf(t.x, qa, -pa), ub = round_txqb ? fmaf(t.y, qa, pb) : fmaf(t.x, qb, pb);
+  xa = ua - sha;
+  xb = ub - shb;
+}
+
+// What bounds it at the decode-time shape (960 heads, w = 512, two workgroups of four wavefronts per CU) is the
+// work between the barriers of a chunk, not memory: 101 us, and 84 with every load on one cached line.  Taking
+// the conditions out of the staging (a shift read under "inside the chunk" was a branch and an LDS round trip
+// per element) and out of the matrix loop (each tile's operands were waited for on the spot), and reading a
+// row operand once for two tiles, took 104 us to 94; keeping Sigma on the chip took the 64 MB it wrote, half of
+// them in 4-byte pieces, and the 27 us of k_prep_frags off (whole pass 422 -> 396 us).
+// FUSED (d <= 128, one workgroup per head): Sigma stays in LDS and leaves as the fragments that k_prep_frags
+// would have made of it, bit for bit.  SUMS says which two of a d = 128 head's ten tiles are added up
+// from four partial sums (the others are one sum): 0 the last of all, 1 the last of each half, as a
+// head split over two workgroups has them.
+template <int D, int LAYOUT, int PARTS = 0, bool FUSED = false, int SUMS = 0>
 __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2)) void k_stats_split(const void* __restrict__ q_win, int w,
                                                                          int ddof,
                                                                          const float2* __restrict__ tab,
                                                                          float* __restrict__ mu,
-                                                                         float* __restrict__ sigma) {
+                                                                         float* __restrict__ sigma, FragsOut fo) {
   constexpr int HALF = D / 2, G8 = HALF / 8, layout = LAYOUT;   // the channel pairing is a compile-time constant:
                                                                 // every LDS address below is a base plus an immediate
   constexpr int WC = stats_split_chunk(D);            // samples per chunk
@@ -397,7 +543,10 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
   extern __shared__ __align__(16) float s_dyn[];
   _Float16* s_hi = reinterpret_cast<_Float16*>(s_dyn);            // [D][P]
   _Float16* s_lo = s_hi + D * P;                                   // [D][P]
-  float* s_part = reinterpret_cast<float*>(s_lo + D * P);          // [4][D] column sums per wavefront
+  // FUSED: Sigma [D][pitch] takes the planes' place at the end (and more than that)
+  constexpr int SP = stats_sigma_pitch(D);
+  float* s_part = FUSED && D * SP * 4 > 2 * D * P * 2 ? s_dyn + D * SP
+                                                      : reinterpret_cast<float*>(s_lo + D * P);   // [4][D] column sums per wavefront
   float* s_shift = s_part + 4 * D;                                 // [D] u~_0
   float* s_xbar = s_shift + D;                                     // [D]
   float* s_max = s_xbar + D;                                       // [4]
@@ -409,11 +558,10 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 
   StatsRaw<true> raw[ITEMS];
   auto load_chunk = [&](int ch) __attribute__((always_inline)) {
-    const int s0 = ch * WC, ns = min(WC, w - s0);
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
-      const int sl = min(sl_t + it, ns - 1);            // no load under a condition: past the end, the last sample again
-      stats_fetch_item<D, true>(q_win, qbase + (size_t)(s0 + sl) * D, g, layout, tab + (size_t)(s0 + sl) * HALF, raw[it]);
+      const int sa = min(ch * WC + sl_t + it, w - 1);   // no load under a condition: past the end, the last sample again
+      stats_fetch_item<D, true>(q_win, qbase + (size_t)sa * D, g, layout, tab + (size_t)sa * HALF, raw[it]);
     }
   };
   load_chunk(0);
@@ -425,8 +573,10 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
     stats_unpack_item<true>(raw0, layout, qa, qb, tb);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      s_shift[stats_ja<D>(layout, g, e)] = tb[e].x * qa[e] - tb[e].y * qb[e];
-      s_shift[stats_jb<D>(layout, g, e)] = tb[e].y * qa[e] + tb[e].x * qb[e];
+      float ua, ub;
+      stats_rotate(D == 64 || (D == 128 && (PARTS == 0 || SUMS == 1)), tb[e], qa[e], qb[e], 0.f, 0.f, ua, ub);
+      s_shift[stats_ja<D>(layout, g, e)] = ua;
+      s_shift[stats_jb<D>(layout, g, e)] = ub;
     }
   }
   __syncthreads();
@@ -436,9 +586,13 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 
   const int r32 = lane & 31, kg = lane >> 5;
   int t_rb[TPW], t_ct[TPW];
+  // a whole head at d = 128: two tiles per wavefront, next to each other in the triangle's order (they mostly
+  // share their rows: the operand is read once), and the two shared ones
+  constexpr bool kPairs = D == 128 && PARTS == 1;
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
-    const int local = t < TL::WHOLE ? wave + 4 * t : 4 * TL::WHOLE + (t - TL::WHOLE);
+    int local = t < TL::WHOLE ? (kPairs ? 2 * wave + t : wave + 4 * t) : 4 * TL::WHOLE + (t - TL::WHOLE);
+    if constexpr (SUMS == 1) local = t < TL::WHOLE ? (local < 4 ? local : local + 1) : t == TL::WHOLE ? 4 : 9;
     int idx = part * TL::TP + local, rb = 0;
     const bool ok = local < TL::TP && idx < TL::NT;
     if (!ok) idx = 0;
@@ -453,18 +607,30 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
   for (int t = 0; t < TPW; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+  // Where a lane's operand of tile block b (channels 32 b + r32) and step ks starts: the swizzle of
+  // channel 32 b + r32 is U(b) ^ L(r32), L living in bits of its own, so the address is a part that is the
+  // same for all lanes plus one of two lane parts.
+  constexpr int LM = 1 | (LAYOUT ? 0 : D == 64 ? 4 : D == 128 ? 2 : 1);          // lane-dependent bits of the block number
+  const int lswz = kg ^ (LAYOUT ? 0 : swz_of_group(r32 / 8));
+  auto operand_at = [&](int blk, int ks) __attribute__((always_inline)) {
+    const int u = (2 * ks) ^ (swz_of_group(group_of_channel(blk * 32)));
+    return (blk * 32 * P + ((u & ~LM) << 3)) + (r32 * P + ((lswz ^ (u & LM)) << 3));
+  };
 
   // x = u~ - u~_0 of item `it` of the chunk in flight (zeros past the chunk's end): [0, 8) the first,
-  // [8, 16) the second channels of the group's pairs
-  auto item_x = [&](int it, int ns, float (&x)[16]) __attribute__((always_inline)) {
+  // [8, 16) the second channels of the group's pairs.  Nothing in it sits under a condition: a shift
+  // read inside "if (inside the chunk)" was a branch and an LDS round trip per element.
+  auto item_x = [&](int it, int ns, const float (&sh)[16], float (&x)[16]) __attribute__((always_inline)) {
     float qa[8], qb[8];
     float2 tb[8];
     stats_unpack_item<true>(raw[it], layout, qa, qb, tb);
     const bool ok = sl_t + it < ns;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      x[e] = ok ? tb[e].x * qa[e] - tb[e].y * qb[e] - s_shift[stats_ja<D>(layout, g, e)] : 0.f;
-      x[8 + e] = ok ? tb[e].y * qa[e] + tb[e].x * qb[e] - s_shift[stats_jb<D>(layout, g, e)] : 0.f;
+      float xa, xb;
+      stats_rotate(LAYOUT == 0 && D >= 128 && e == 0, tb[e], qa[e], qb[e], sh[e], sh[8 + e], xa, xb);
+      x[e] = ok ? xa : 0.f;
+      x[8 + e] = ok ? xb : 0.f;
     }
   };
 
@@ -474,9 +640,24 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
     // ---- this thread's samples of the chunk, then at once the requests for the next chunk: they
     //      travel during the conversion, the barriers and the matrix-core loop below
     float xs[ITEMS][16];
+    {
+      float sh[16];                                   // this thread's channels of u~_0, as four 16-byte reads
+      const float4* pa = reinterpret_cast<const float4*>(s_shift + (layout ? 16 * g : 8 * g));
+      const float4* pb = reinterpret_cast<const float4*>(s_shift + (layout ? 16 * g + 8 : HALF + 8 * g));
+      const float4 f[4] = {pa[0], pa[1], pb[0], pb[1]};
 #pragma unroll
-    for (int it = 0; it < ITEMS; ++it) item_x(it, ns, xs[it]);
-    if (ch + 1 < nchunks) load_chunk(ch + 1);
+      for (int c = 0; c < 4; ++c) {
+        const float y[4] = {f[c].x, f[c].y, f[c].z, f[c].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int m = 4 * c + i;                    // half-split: as they come; interleaved: pairs
+          sh[layout ? (m & 1) * 8 + (m >> 1) : m] = y[i];
+        }
+      }
+#pragma unroll
+      for (int it = 0; it < ITEMS; ++it) item_x(it, ns, sh, xs[it]);
+    }
+    load_chunk(ch + 1);                               // (behind the last chunk: its last sample)
     if (ch == 0) {
       // the head's scale: a power of two that puts the first chunk's largest |x| into [16, 32)
       float amax = 0.f;
@@ -524,24 +705,59 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
       }
     }
     __syncthreads();
-    // ---- three matrix-core instructions per tile and 16 samples
-    const int nks = (ns + 15) / 16;
-#pragma unroll 1
-    for (int ks = 0; ks < nks; ++ks) {
+    // ---- three matrix-core instructions per tile and 16 samples, one straight line (samples past the
+    //      window's end are zeros in the planes), so that the operand reads of the next step travel
+    //      under the matrix instructions of this one.  A tile that this wavefront does not have (d = 64)
+    //      is computed as tile 0 and not stored.
+    constexpr int KS = WC / 16;
+    auto step = [&](int t, int ks) __attribute__((always_inline)) {
+      const int oa = operand_at(max(t_rb[t], 0), ks), ob = operand_at(t_ct[t], ks);
+      const stats_half8 ah = *reinterpret_cast<const stats_half8*>(s_hi + oa);
+      const stats_half8 al = *reinterpret_cast<const stats_half8*>(s_lo + oa);
+      const stats_half8 bh = *reinterpret_cast<const stats_half8*>(s_hi + ob);
+      const stats_half8 bl = *reinterpret_cast<const stats_half8*>(s_lo + ob);
+      acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[t], 0, 0, 0);
+      acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[t], 0, 0, 0);
+      acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[t], 0, 0, 0);
+    };
+    if constexpr (kPairs) {
+      // (tiles 6 and 7 of the plain order, (1, 3) and (2, 2), are the one pair that shares no rows)
+      if (SUMS == 1 || wave != 3) {
 #pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-        if (t_rb[t] >= 0 && (t < TL::WHOLE || ((ch * (WC / 16) + ks) & 3) == wave)) {
-          const int ca = t_rb[t] * 32 + r32, cb = t_ct[t] * 32 + r32;
-          const int ra = ca * P + (((ks * 2 + kg) ^ swz_of_group(group_of_channel(ca))) << 3);
-          const int rbw = cb * P + (((ks * 2 + kg) ^ swz_of_group(group_of_channel(cb))) << 3);
-          const stats_half8 ah = *reinterpret_cast<const stats_half8*>(s_hi + ra);
-          const stats_half8 al = *reinterpret_cast<const stats_half8*>(s_lo + ra);
-          const stats_half8 bh = *reinterpret_cast<const stats_half8*>(s_hi + rbw);
-          const stats_half8 bl = *reinterpret_cast<const stats_half8*>(s_lo + rbw);
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[t], 0, 0, 0);
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[t], 0, 0, 0);
-          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[t], 0, 0, 0);
+        for (int ks = 0; ks < KS; ++ks) {
+          const int oa = operand_at(t_rb[0], ks), ob = operand_at(t_ct[0], ks), oc = operand_at(t_ct[1], ks);
+          const stats_half8 ah = *reinterpret_cast<const stats_half8*>(s_hi + oa);
+          const stats_half8 al = *reinterpret_cast<const stats_half8*>(s_lo + oa);
+          const stats_half8 bh = *reinterpret_cast<const stats_half8*>(s_hi + ob);
+          const stats_half8 bl = *reinterpret_cast<const stats_half8*>(s_lo + ob);
+          const stats_half8 ch2 = *reinterpret_cast<const stats_half8*>(s_hi + oc);
+          const stats_half8 cl2 = *reinterpret_cast<const stats_half8*>(s_lo + oc);
+          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, ch2, acc[1], 0, 0, 0);
+          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, cl2, acc[1], 0, 0, 0);
+          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, ch2, acc[1], 0, 0, 0);
         }
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int t = 0; t < TL::WHOLE; ++t) step(t, ks);
+      }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int t = 0; t < TL::WHOLE; ++t) step(t, ks);
+    }
+    // a shared tile's steps go round the wavefronts: step number ch * KS + ks modulo 4
+    if constexpr (TL::SHARED > 0) {
+      static_assert(4 % KS == 0, "at most one step of a shared tile per wavefront and chunk");
+      const int ks = (wave - ch * KS) & 3;
+      if (KS == 4 || ks < KS) {
+#pragma unroll
+        for (int t = TL::WHOLE; t < TPW; ++t) step(t, ks);
       }
     }
   }
@@ -586,12 +802,16 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
   for (int c = tid; c < D; c += 256) {
     const float xb = ((s_part[c] + s_part[D + c]) + (s_part[2 * D + c] + s_part[3 * D + c])) * invw;
     s_xbar[c] = xb;
-    if (part == 0) mu[(size_t)head * D + c] = s_shift[c] + xb;
+    if (!FUSED && part == 0) mu[(size_t)head * D + c] = s_shift[c] + xb;
   }
   __syncthreads();
   // In the matrix-core product a lane's B operand is column r32 and its A rows come back as
   // accumulator register v = row 8 (v / 4) + 4 kg + v % 4: the tile's entry (row, column r32).
   const float fw = (float)w, inv = 1.0f / (float)(w - ddof), unscale = 1.0f / (scale * scale);
+  auto sigma_entry = [&](float sum, float xi, float xj) {
+#pragma clang fp contract(off)
+    return fmaf(unscale, sum, -(xj * (fw * xi))) * inv;
+  };
   // A tile above the diagonal is also stored transposed.  Straight from the accumulators that is
   // 64 separate 4-byte writes per instruction (a lane holds one column).  At d = 256 (28 of 36 tiles
   // are mirrored, 64 MB of Sigma per launch of the four-sequence shape) the tile takes a trip
@@ -599,7 +819,8 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
   // d <= 128 that costs the registers that keep three workgroups on a CU without scratch memory,
   // and the direct stores are the faster ones (5.6 against 10.4 us per layer at the decode shape).
   constexpr bool kViaLds = D >= 256;
-  if constexpr (!kViaLds) {
+  if constexpr (FUSED) {
+    float* S = s_dyn;                                  // [D][SP]
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
       if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
@@ -609,7 +830,25 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int i = i0 + 8 * (v / 4) + 4 * kg + v % 4;
-          const float val = (acc[t][v] * unscale - fw * s_xbar[i] * xj) * inv;
+          const float val = sigma_entry(acc[t][v], s_xbar[i], xj);
+          S[i * SP + j] = val;
+          if (mirror) S[j * SP + i] = val;
+        }
+      }
+    }
+    __syncthreads();
+    stats_write_frags<D>(S, s_shift, s_xbar, head, fo);
+  } else if constexpr (!kViaLds) {
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
+        const int i0 = t_rb[t] * 32, j = t_ct[t] * 32 + r32;
+        const bool mirror = t_rb[t] != t_ct[t];
+        const float xj = s_xbar[j];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int i = i0 + 8 * (v / 4) + 4 * kg + v % 4;
+          const float val = sigma_entry(acc[t][v], s_xbar[i], xj);
           sigma[((size_t)head * D + i) * D + j] = val;
           if (mirror) sigma[((size_t)head * D + j) * D + i] = val;
         }
@@ -628,7 +867,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int il = 8 * (v / 4) + 4 * kg + v % 4;
-          const float val = (acc[t][v] * unscale - fw * s_xbar[i0 + il] * xj) * inv;
+          const float val = sigma_entry(acc[t][v], s_xbar[i0 + il], xj);
           sigma[((size_t)head * D + i0 + il) * D + j] = val;
           if (mirror) s_tr[r32 * 33 + il] = val;         // [column][row]
         }
@@ -649,33 +888,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 }
 
 // ---------------------------------------------------------------------------------------
-// Matrix-core operands for the score kernel, one workgroup per (unit, pass).
-//
-// The quadratic form k^T Sigma k is evaluated as sum_j (sum_c k_c M[c][j]) k_j where M folds
-// the symmetric pair (c, j) and (j, c) onto one side at the granularity of 16-channel
-// "folded blocks" fb(c) = (c mod d/2) / 16:  M[c][j] = Sigma[c][j] + Sigma[j][c] when
-// fb(c) < fb(j), Sigma[c][j] when fb(c) == fb(j), and 0 otherwise -- the zero blocks are
-// simply not stored, which removes 3/8 of the matrix-core work.  M is scaled by a power of
-// two into fp16 range and rounded to fp16; the rounding error of its diagonal (the dominant
-// error term, since k_c^2 never cancels) is kept as a residual row that multiplies k_c^2 in
-// an extra accumulator tile.  mu is split into an fp16 head and tail in the same tile.
-//
-// Fragment (1 KiB = 64 lanes x 8 halves) for (head g, output tile jt, k-step kt):
-//   lane l (rho = l % 32, hl = l / 32), element i:
-//     input channel   c_in  = hl * d/2 + kt * 8 + i
-//     output channel  c_out = ((rho / 4) % 2) * d/2 + jt * 16 + 4 * (rho / 8) + rho % 4
-// so that in the 32x32 accumulator layout a lane (hh = l / 32) holds exactly the output
-// channels hh * d/2 + x that it also feeds as inputs: the epilogue dot with k needs no
-// data movement.
-__device__ __forceinline__ float scale_for(float maxabs) {
-  if (!(maxabs > 0.f) || !isfinite(maxabs)) return 1.0f;
-  int e;
-  frexpf(maxabs, &e);                 // maxabs = f * 2^e, f in [0.5, 1)
-  int sh = 13 - e;                    // scaled max in [2^12, 2^13)
-  sh = max(-100, min(100, sh));
-  return ldexpf(1.0f, sh);
-}
-
+// The operands from (mu, Sigma) in memory, kPrepSplit workgroups per (unit, pass).
 constexpr int kPrepSplit = 16;   // workgroups per (unit, pass)
 
 template <int D>
@@ -777,12 +990,7 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
         h[i] = (_Float16)val;
       }
     }
-    uint4 pk;
-    pk.x = (uint32_t)__builtin_bit_cast(uint16_t, h[0]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[1]) << 16);
-    pk.y = (uint32_t)__builtin_bit_cast(uint16_t, h[2]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[3]) << 16);
-    pk.z = (uint32_t)__builtin_bit_cast(uint16_t, h[4]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[5]) << 16);
-    pk.w = (uint32_t)__builtin_bit_cast(uint16_t, h[6]) | ((uint32_t)__builtin_bit_cast(uint16_t, h[7]) << 16);
-    out[item] = pk;
+    out[item] = pack_half8(h);
   }
 }
 
@@ -817,7 +1025,7 @@ static hipError_t launch_stats_split_parts(const Dims& d, const void* q_win, int
   hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
   dim3 grid(d.qheads(), StatsTiling<D, PARTS>::PARTS);
-  kern<<<grid, 256, lds, st>>>(q_win, w, d.ddof, tab, mu, sigma);
+  kern<<<grid, 256, lds, st>>>(q_win, w, d.ddof, tab, mu, sigma, FragsOut{});
   return hipGetLastError();
 }
 // Every workgroup of a head stages all of the head's samples, so a head split over two workgroups
@@ -849,6 +1057,33 @@ hipError_t launch_stats(const Dims& d, const void* q_win, int w, const float2* t
   if (d.D == 64) return launch_stats_one<64, false>(d, q_win, w, tab, mu, sigma, st);
   if (d.D == 128) return launch_stats_one<128, false>(d, q_win, w, tab, mu, sigma, st);
   return launch_stats_one<256, false>(d, q_win, w, tab, mu, sigma, st);
+}
+
+template <int D, int LAYOUT, int PARTS, int SUMS>
+static hipError_t launch_stats_frags_one(const Dims& d, const void* q_win, int w, const float2* tab, const FragsOut& fo,
+                                         hipStream_t st) {
+  auto kern = k_stats_split<D, LAYOUT, PARTS, true, SUMS>;
+  const size_t planes = (size_t)2 * D * (stats_split_chunk(D) + 8) * sizeof(_Float16);
+  const size_t sig = (size_t)D * stats_sigma_pitch(D) * sizeof(float);
+  const size_t lds = (planes > sig ? planes : sig) + (size_t)(6 * D + 4) * sizeof(float);
+  static LdsOptIn opt;
+  hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);
+  if (e != hipSuccess) return e;
+  kern<<<d.qheads(), 256, lds, st>>>(q_win, w, d.ddof, tab, nullptr, nullptr, fo);
+  return hipGetLastError();
+}
+template <int LAYOUT>
+static hipError_t launch_stats_frags_layout(const Dims& d, const void* q_win, int w, const float2* tab, const FragsOut& fo,
+                                            hipStream_t st) {
+  if (d.D == 64) return launch_stats_frags_one<64, LAYOUT, 0, 0>(d, q_win, w, tab, fo, st);
+  return d.qheads() >= kStatsWholeHeadMin ? launch_stats_frags_one<128, LAYOUT, 1, 0>(d, q_win, w, tab, fo, st)
+                                          : launch_stats_frags_one<128, LAYOUT, 1, 1>(d, q_win, w, tab, fo, st);
+}
+hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_win, int w, const float2* tab,
+                              uint4* frags, float* post, hipStream_t st) {
+  const FragsOut fo{frags, post, d.G, sp.GH, sp.passes, sp.nfrag};
+  return d.rope_layout ? launch_stats_frags_layout<1>(d, q_win, w, tab, fo, st)
+                       : launch_stats_frags_layout<0>(d, q_win, w, tab, fo, st);
 }
 
 hipError_t launch_prep_frags(const Dims& d, const ScorePlan& sp, const float* mu,

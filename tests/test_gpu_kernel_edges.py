@@ -64,3 +64,30 @@ def test_scores_with_spare_workgroups(d, hq, hkv, batch, n):
     mu, sigma = mu.astype(np.float32), sigma.astype(np.float32)
     got = P.run_score(cfg, lay, mu, sigma, 0.02)
     P.check_scores(got, O.scores(widen(lay["k"]), widen(lay["v"]), mu, sigma, 0.02), 2e-3)
+
+
+@pytest.mark.parametrize("d,hq,hkv,batch", [
+    (64, 8, 1, 1), (64, 5, 1, 3),           # G = 5 in an eight-head instance: rows and fragments of no head
+    (128, 4, 1, 47), (128, 4, 1, 48),       # 188 and 192 heads: either side of the rule
+    (128, 7, 1, 40), (128, 5, 1, 77),       # two passes with room for an eighth head; 385 heads: the other order of sums
+])
+@pytest.mark.parametrize("w,layout", [(2, 0), (17, 1), (64, 0), (65, 1), (130, 0)])
+def test_fused_statistics_give_the_same_operands(d, hq, hkv, batch, w, layout):
+    """compress_layer's scores are those of query_stats followed by score, bit for bit: the statistics
+    kernel that writes the score kernel's operands itself makes the ones that the separate kernels
+    make of mu and sigma.  (Those are compared with the oracle elsewhere.)"""
+    import torch
+    n = 300
+    cfg = CONFIGS["c2"].with_(head_dim=d, n_q_heads=hq, n_kv_heads=hkv, batch=batch)
+    lay = make_layer(cfg, n=n, window=w, interleaved=bool(layout))
+    p = P.params_for(cfg, rope_layout=layout)
+    ws = P.workspace(p, n, w)
+    q, k, v, inv = (P.to_dev(lay[x]) for x in ("q_win", "k", "v", "inv_freq"))
+    mu = torch.empty(batch, hq, d, device="cuda")
+    sigma = torch.empty(batch, hq, d, d, device="cuda")
+    sc = [torch.empty(batch, hkv, n, device="cuda") for _ in range(2)]
+    ea.query_stats(p, q, w, lay["q_pos0"], inv, lay["t_next"], mu, sigma, ws)
+    ea.score(p, k, v, n, n, mu, sigma, sc[0], ws)
+    ea.compress_layer(p, q, w, lay["q_pos0"], inv, lay["t_next"], k, v, n, n, n // 2, sc[1], None, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(sc[0].cpu().numpy(), sc[1].cpu().numpy())
