@@ -60,7 +60,7 @@ hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D,
 // ea_select.hip
 // heads this short are selected by one workgroup per unit out of LDS, in one launch (no global
 // histograms: hist0 from the finalize pass is not needed then)
-constexpr int64_t kSelSmallMax = 16384;   // (32768-row heads: 12.4 us per layer in one launch, 9.8 in four)
+constexpr int64_t kSelSmallMax = 16384;   // (whole pass at 20000 keys per head, one launch and four: 117 us either way; 32768: 142 and 140)
 inline bool select_in_one_launch(int64_t n) { return n <= kSelSmallMax; }
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
                          uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st);

@@ -91,3 +91,18 @@ def test_fused_statistics_give_the_same_operands(d, hq, hkv, batch, w, layout):
     ea.compress_layer(p, q, w, lay["q_pos0"], inv, lay["t_next"], k, v, n, n, n // 2, sc[1], None, ws)
     torch.cuda.synchronize()
     assert np.array_equal(sc[0].cpu().numpy(), sc[1].cpu().numpy())
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 4095, 4096, 4097, 8192, 8193, 9217, 16383, 16384, 16385])
+@pytest.mark.parametrize("kind", ["spread", "ties", "equal"])
+def test_select_row_edges(n, kind):
+    """Heads around the row and register counts of the one-launch selection, few distinct values and one
+    single value among the inputs: the kept positions are exactly the stable top-k's."""
+    rng = np.random.default_rng(n)
+    shape = (1, 3, n)
+    sc = (np.exp(rng.standard_normal(shape)) if kind == "spread" else
+          rng.integers(0, 5, shape).astype(np.float64) if kind == "ties" else np.ones(shape)).astype(np.float32)
+    cfg = CONFIGS["c1"].with_(n_q_heads=3, n_kv_heads=3)
+    for n_keep in {1, n, max(1, n // 2), max(1, n - 1), min(n, 65)}:
+        idx = P.run_select(cfg, sc, n_keep)
+        assert np.array_equal(idx.astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
