@@ -38,6 +38,8 @@ static ea_status check_ws(const Dims& d, int64_t n, int64_t window, void* ws, si
   return EA_OK;
 }
 
+static size_t hist_words(const Dims& d) { return (size_t)d.units() * 3 * kSelBins; }
+
 // clear / clear_words: scratch words zeroed by the table kernel on its way (may be none)
 static ea_status run_stats(const Dims& d, const void* q_win, int64_t window, int64_t q_pos0,
                            const double* inv_freq, int64_t t_next, float* mu, float* sigma,
@@ -79,12 +81,13 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
   // quadratic forms into such norms (the caller passed the values as keys, mu = 0, Sigma = M_g).
   float* vnorm = (float*)(ws + L.vnorm);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
-  if (d.dtype == EA_BF16 && !hist_zeroed) EA_TRY(launch_zero(hist, (size_t)d.units() * 3 * kSelBins, st));
   if (d.dtype == EA_BF16) {
     ScorePlan sp = make_score_plan(d, n, device_num_cu(), pm != nullptr);
     uint4* frags = (uint4*)(ws + L.frags);
     float* post = (float*)(ws + L.post);
-    if (!frags_ready) EA_TRY(launch_prep_frags(d, sp, mu, sigma, frags, post, st));
+    // frags_ready comes with hist_zeroed: the caller's own first launch has cleared the words then
+    if (!frags_ready)
+      EA_TRY(launch_prep_frags(d, sp, mu, sigma, frags, post, st, hist, hist_zeroed ? 0 : hist_words(d), wnorm_out != nullptr));
     if (ev) EA_TRY(hipEventRecord(ev[0], st));
     EA_TRY(launch_score_mfma(d, sp, k, v, n, n_cap, frags, post, (float*)(ws + L.logits), vnorm,
                              (float2*)(ws + L.part), hist + 2 * kSelBins + kTicketSlot, 3 * kSelBins,
@@ -108,7 +111,6 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
   return EA_OK;
 }
 
-static size_t hist_words(const Dims& d) { return (size_t)d.units() * 3 * kSelBins; }
 static size_t flag_words(const Dims& d, int64_t n_keep) {
   return 2 * (size_t)d.units() * ((n_keep + kCompactRows - 1) / kCompactRows + kCompactTicketStride);
 }
@@ -223,6 +225,8 @@ ea_status ea_value_norms_wo(const ea_params* p, const void* v, int64_t n, int64_
   if ((s = check_ws(d, n, 1, ws, ws_bytes, &L)) != EA_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   // pass A over the value rows with mu = 0 and Sigma = M_g (the same M for every sequence)
+  if (d.dtype == EA_BF16)
+    return run_score(d, v, v, n, n_cap, nullptr, gram, nullptr, nullptr, false, (char*)ws, L, st, nullptr, nullptr, wnorm);
   float* mu0 = (float*)((char*)ws + L.mu);
   float* sg = (float*)((char*)ws + L.sigma);
   EA_TRY(launch_zero((uint32_t*)mu0, (size_t)d.qheads() * d.D, st));
@@ -407,29 +411,31 @@ ea_status ea_compress_layer(const ea_params* p, const void* q_win, int64_t windo
 }
 
 // Pooled selection of ea_select_adaptive on the caller's stream.  `lifted`: a buffer of units * n
-// floats that is not `scores` (only used with a floor); `top`: units * floor ints of scratch.
+// floats that is not `scores` (only used with a floor); `top`: units * floor ints of scratch.  The
+// histograms of the heads and of the pooled lists are zero on entry; hist0_done: the heads' first one
+// is filled.
 static ea_status run_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor,
                                      int32_t* idx, int32_t* lengths, float* lifted, int32_t* top, char* w,
-                                     const WsLayout& L, hipStream_t st) {
+                                     const WsLayout& L, bool hist0_done, hipStream_t st) {
   uint32_t* hist = (uint32_t*)(w + L.hist);
+  uint32_t* pool_hist = (uint32_t*)(w + L.pool_hist);
   uint32_t* blk = (uint32_t*)(w + L.blk);
   int32_t* flat = (int32_t*)(w + L.idx);                // [B][Hkv * n_keep], ascending in [0, Hkv * n)
-  const float* pooled = scores;
-  if (floor > 0 && n_keep > 0) {
-    // every head's own best `floor` pairs, then a copy of the scores with those lifted to +inf
-    EA_TRY(launch_zero(hist, hist_words(d), st));
-    EA_TRY(launch_select(d, scores, n, floor, top, hist, blk, false, st));
-    EA_TRY(hipMemcpyAsync(lifted, scores, (size_t)d.units() * n * sizeof(float), hipMemcpyDeviceToDevice, st));
-    EA_TRY(launch_mark_inf(lifted, top, d.units(), n, floor, st));
-    pooled = lifted;
-  }
   Dims layer = d;                                       // one pooled list per sequence
   layer.Hq = d.G;
   layer.Hkv = 1;
-  if (n_keep > 0) {
-    EA_TRY(launch_zero(hist, hist_words(d), st));
-    EA_TRY(launch_select(layer, pooled, (int64_t)d.Hkv * n, (int64_t)d.Hkv * n_keep, flat, hist, blk, false, st));
+  const float* pooled = scores;
+  bool pool_hist0 = false;
+  if (floor > 0 && n_keep > 0) {
+    // every head's own best `floor` pairs, then a copy of the scores with those lifted to +inf
+    EA_TRY(launch_select(d, scores, n, floor, top, hist, blk, hist0_done, st));
+    pool_hist0 = !select_in_one_launch((int64_t)d.Hkv * n);
+    EA_TRY(launch_lift(d, scores, top, n, floor, lifted, pool_hist0 ? pool_hist : nullptr, st));
+    pooled = lifted;
   }
+  if (n_keep > 0)
+    EA_TRY(launch_select(layer, pooled, (int64_t)d.Hkv * n, (int64_t)d.Hkv * n_keep, flat, pool_hist, blk, pool_hist0, st,
+                         hist));
   EA_TRY(launch_split_pooled(flat, d.B, d.Hkv, n, n_keep, idx, lengths, st));
   return EA_OK;
 }
@@ -446,8 +452,9 @@ ea_status ea_select_adaptive(const ea_params* p, const float* scores, int64_t n,
   WsLayout L;
   if ((s = check_ws(d, n, 1, ws, ws_bytes, &L)) != EA_OK) return s;
   char* w = (char*)ws;
+  EA_TRY(launch_zero((uint32_t*)(w + L.hist), (L.blk - L.hist) / 4, (hipStream_t)stream));
   return run_select_adaptive(d, scores, n, n_keep, floor, idx, lengths, (float*)(w + L.scores),
-                             (int32_t*)(w + L.logits), w, L, (hipStream_t)stream);
+                             (int32_t*)(w + L.logits), w, L, false, (hipStream_t)stream);
 }
 
 ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int64_t window, int64_t q_pos0,
@@ -476,20 +483,22 @@ ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int6
   float* sigma = (float*)(w + L.sigma);
   float* scores = scores_out ? scores_out : (float*)(w + L.scores);
   bool frags_ready = false;
-  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, false, mu, sigma, w, L, st, nullptr, 0,
-                               &frags_ready)) != EA_OK)
+  // one clearing launch for both sets of histograms, the block counts and the compaction flags
+  uint32_t* hist = (uint32_t*)(w + L.hist);
+  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, false, mu, sigma, w, L, st, hist,
+                               (L.flags - L.hist) / 4 + flag_words(d, n), &frags_ready)) != EA_OK)
     return s;
-  if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores, nullptr, false, w, L, st, nullptr, nullptr, nullptr, nullptr,
-                     nullptr, nullptr, frags_ready)) != EA_OK)
+  const bool hist0 = floor > 0 && n_keep > 0 && !select_in_one_launch(n);
+  if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores, hist0 ? hist : nullptr, true, w, L, st, nullptr, nullptr, nullptr,
+                     nullptr, nullptr, nullptr, frags_ready)) != EA_OK)
     return s;
   // after pass B the logit and value-norm scratch is free: the floor's lists and the lifted copy
   // of the scores go there
   if ((s = run_select_adaptive(d, scores, n, n_keep, floor, idx_out, lengths_out, (float*)(w + L.vnorm),
-                               (int32_t*)(w + L.logits), w, L, st)) != EA_OK)
+                               (int32_t*)(w + L.logits), w, L, hist0, st)) != EA_OK)
     return s;
   uint32_t* flags = (uint32_t*)(w + L.flags);
-  uint32_t* status = (uint32_t*)(w + L.hist) + 2 * kSelBins + kStatusSlot;
-  EA_TRY(launch_zero(flags, flag_words(d, n), st));
+  uint32_t* status = hist + 2 * kSelBins + kStatusSlot;
   EA_TRY(launch_compact(d, k, v, n, n_cap, idx_out, n, k, v, flags, status, st, lengths_out, n));
   return EA_OK;
 }

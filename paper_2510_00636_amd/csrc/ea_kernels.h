@@ -32,8 +32,11 @@ inline bool stats_makes_frags(const Dims& d) {
 }
 hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_win, int w, const float2* tab,
                               uint4* frags, float* post, hipStream_t st);
+// mu == nullptr: zero means; sigma_shared: sigma holds one set of Hq heads for all sequences; clear /
+// clear_words: words zeroed on the way (may be none)
 hipError_t launch_prep_frags(const Dims& d, const ScorePlan& sp, const float* mu,
-                             const float* sigma, uint4* frags, float* post, hipStream_t st);
+                             const float* sigma, uint4* frags, float* post, hipStream_t st, uint32_t* clear = nullptr,
+                             size_t clear_words = 0, bool sigma_shared = false);
 
 // ea_score.hip
 // tickets + unit * ticket_stride: 8 tile counters per pass of the unit (at most 64 passes), zero at launch
@@ -63,7 +66,8 @@ hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D,
 constexpr int64_t kSelSmallMax = 16384;   // (whole pass at 20000 keys per head, one launch and four: 117 us either way; 32768: 142 and 140)
 inline bool select_in_one_launch(int64_t n) { return n <= kSelSmallMax; }
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
-                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st);
+                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st, uint32_t* status_hist = nullptr);
+// status_hist: the histograms whose free words hold the status word, if not `hist`
 hipError_t launch_zero(uint32_t* p, size_t count, hipStream_t st, uint32_t* extra = nullptr);
 
 // ea_compact.hip
@@ -74,9 +78,11 @@ hipError_t launch_compact(const Dims& d, const void* k, const void* v, int64_t n
 // pm != nullptr: k and v are block pools (in place only; n_cap unused)
 // lengths != nullptr: unit u keeps lengths[u] <= n_keep rows, listed from idx + u * idx_stride
 
-// ea_select.hip, head-adaptive budgets: +inf into scores[unit][idx[unit][j]], j < n_mark; then the
+// ea_select.hip, head-adaptive budgets: lifted = scores with +inf at [unit][top[unit][j]], j < n_mark
+// (ascending lists); pool_hist (nullable, zero): first radix digit of each sequence's lifted scores.  Then the
 // split of a pooled, ascending list flat[b][0 .. H*n_keep) over [H][n] into per-head lists
-hipError_t launch_mark_inf(float* scores, const int32_t* idx, int units, int64_t n, int64_t n_mark, hipStream_t st);
+hipError_t launch_lift(const Dims& d, const float* scores, const int32_t* top, int64_t n, int64_t n_mark, float* lifted,
+                       uint32_t* pool_hist, hipStream_t st);
 hipError_t launch_split_pooled(const int32_t* flat, int B, int H, int64_t n, int64_t n_keep, int32_t* idx,
                                int32_t* lengths, hipStream_t st);
 

@@ -84,6 +84,7 @@ struct SelArgs {
   uint32_t* blk;     // [units][nblk][2] = (count > T, count == T)
   int32_t* idx;      // [units][n_keep]
   int nblk;
+  uint32_t* status;  // status word
 };
 
 // Digits fixed by the histogram passes before pass P: wavefront 0 re-derives them (a few
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_hist(SelArgs a) {
         atomicAdd(&s_hist[u >> 21], 1u);
         // outside the domain (negative or NaN): the order of bit patterns is not the order of
         // values there; the selection still completes, the status word records it
-        if (u > 0x7f800000u) atomicOr(a.hist + 2 * kSelBins + kStatusSlot, kStatusBadScore);
+        if (u > 0x7f800000u) atomicOr(a.status, kStatusBadScore);
       }
       if (P == 1 && (u >> 21) == prefix) atomicAdd(&s_hist[(u >> 10) & 2047u], 1u);
       if (P == 2 && (u >> 10) == prefix) atomicAdd(&s_hist[u & 1023u], 1u);
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
     prefix = s_res[0];
     rem = s_res[1];
   }
-  if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.hist + 2 * kSelBins + kStatusSlot, kStatusBadScore);
+  if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.status, kStatusBadScore);
   const uint32_t T = prefix, q = rem;             // threshold pattern, ties at T to keep
 
   // scores above T and at T per wavefront, then what lies in front of this wavefront
@@ -371,8 +372,9 @@ __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
 }
 
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
-                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st) {
+                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st, uint32_t* status_hist) {
   SelArgs a;
+  a.status = (status_hist ? status_hist : hist) + 2 * kSelBins + kStatusSlot;
   a.scores = scores;
   a.n = n;
   a.n_keep = (uint32_t)n_keep;
@@ -400,17 +402,68 @@ hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t 
 // Head-adaptive budgets (Sec. 2.2, "Head-Adaptive Compression"): the selection runs once over the
 // pooled scores of a layer's KV heads, [H][n] read as one list of H*n, after every head's own
 // `floor` best pairs have been lifted to +inf so that the pooled selection takes them first.
-__global__ void k_mark_inf(float* __restrict__ scores, const int32_t* __restrict__ idx, long long n,
-                           long long n_mark) {
-  const long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int unit = blockIdx.y;
-  if (j < n_mark) scores[(size_t)unit * n + idx[(size_t)unit * n_mark + j]] = INFINITY;
+//
+// One workgroup = kSelBlock scores of a head: copied into LDS, those on the head's list of its `n_mark` best
+// (the stretch of it that lies in the block: two 64-ary searches) set to +inf, written out, and the first
+// digit of the pooled list's radix select counted on the way: a copy, a marking and a histogram launch in one.
+// (With it, one clearing launch instead of four and the heads' first digit taken from the finalize pass, the
+// adaptive pass of 8 heads x 50001 keys went from 24 launches and 266 us to 18 and 253.)
+__global__ __launch_bounds__(kSelThreads) void k_lift(const float* __restrict__ scores, const int32_t* __restrict__ top,
+                                                      long long n, int n_mark, int Hkv, float* __restrict__ lifted,
+                                                      uint32_t* __restrict__ pool_hist) {
+  __shared__ float s_sc[kSelBlock];
+  __shared__ uint32_t s_hist[kSelBins];
+  __shared__ int s_j[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, unit = blockIdx.x;
+  const long long base = (long long)blockIdx.y * kSelBlock;
+  const int m = (int)min((long long)kSelBlock, n - base);
+  const int32_t* list = top + (size_t)unit * n_mark;
+  float x[kSelPer];
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) x[j] = scores[(size_t)unit * n + min(base + j * kSelThreads + tid, n - 1)];
+  for (int i = tid; i < kSelBins; i += kSelThreads) s_hist[i] = 0;
+  if (wave < 2) {                                        // first list entry at or past the block's start, and past its end
+    const long long key = wave == 0 ? base : base + m;
+    int lo = 0, hi = n_mark;                             // entries below lo are < key, from hi on >= key
+    while (lo < hi) {
+      const int stride = (hi - lo + 63) / 64, at = lo + lane * stride;
+      const unsigned long long ge = __ballot(at >= hi || list[min(at, n_mark - 1)] >= key);
+      const int first = ge ? __ffsll((long long)ge) - 1 : 64;
+      hi = first < 64 ? min(hi, lo + first * stride) : hi;
+      if (first > 0) lo = lo + (first - 1) * stride + 1;
+    }
+    if (lane == 0) s_j[wave] = hi;
+  }
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) s_sc[j * kSelThreads + tid] = x[j];
+  __syncthreads();
+  for (int j = s_j[0] + tid; j < s_j[1]; j += kSelThreads) {
+    const long long at = list[j] - base;
+    if (at >= 0 && at < m) s_sc[at] = INFINITY;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) {
+    const int i = j * kSelThreads + tid;
+    if (i < m) {
+      const float v = s_sc[i];
+      lifted[(size_t)unit * n + base + i] = v;
+      if (pool_hist) atomicAdd(&s_hist[__float_as_uint(v) >> 21], 1u);
+    }
+  }
+  if (!pool_hist) return;
+  __syncthreads();
+  uint32_t* out = pool_hist + (size_t)(unit / Hkv) * 3 * kSelBins;
+  for (int i = tid; i < kSelBins; i += kSelThreads) {
+    const uint32_t c = s_hist[i];
+    if (c) atomicAdd(&out[i], c);
+  }
 }
 
-hipError_t launch_mark_inf(float* scores, const int32_t* idx, int units, int64_t n, int64_t n_mark, hipStream_t st) {
-  if (n_mark == 0) return hipSuccess;
-  dim3 grid((unsigned)((n_mark + 255) / 256), units);
-  k_mark_inf<<<grid, 256, 0, st>>>(scores, idx, n, n_mark);
+hipError_t launch_lift(const Dims& d, const float* scores, const int32_t* top, int64_t n, int64_t n_mark, float* lifted,
+                       uint32_t* pool_hist, hipStream_t st) {
+  const dim3 grid(d.units(), (unsigned)((n + kSelBlock - 1) / kSelBlock));
+  k_lift<<<grid, kSelThreads, 0, st>>>(scores, top, n, (int)n_mark, d.Hkv, lifted, pool_hist);
   return hipGetLastError();
 }
 

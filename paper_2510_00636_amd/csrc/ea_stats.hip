@@ -894,9 +894,19 @@ constexpr int kPrepSplit = 16;   // workgroups per (unit, pass)
 template <int D>
 __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu,
                                                     const float* __restrict__ sigma, int G,
-                                                    int GH, int passes, int nfrag,
+                                                    int GH, int passes, int nfrag, int shared_heads,
                                                     uint4* __restrict__ frags,
-                                                    float* __restrict__ post) {
+                                                    float* __restrict__ post, uint32_t* __restrict__ clear,
+                                                    size_t clear_words) {
+  // mu == nullptr: zero means.  shared_heads > 0: one set of that many heads' Sigma for every sequence.
+  // clear: counters of the score kernel and what stands around them, zeroed on the way (one launch less)
+  for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < clear_words;
+       i += (size_t)gridDim.x * gridDim.y * 256)
+    clear[i] = 0u;
+  auto sigma_of = [&](int unit_, int gq_) {
+    const int head = unit_ * G + gq_;
+    return sigma + (size_t)(shared_heads ? head % shared_heads : head) * D * D;
+  };
   constexpr int HALF = D / 2, NKS = D / 16, NJT = D / 32, NF = NJT * (NJT + 1);
   __shared__ float s_scale[16];       // [2g] = sM, [2g+1] = smu   (GH <= 8)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -908,11 +918,10 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
     const int gq = g0 + g;
     float mxS = 0.f, mxM = 0.f;
     if (gq < G) {
-      const float* S = sigma + ((size_t)unit * G + gq) * D * D;
-      const float* m = mu + ((size_t)unit * G + gq) * D;
+      const float* S = sigma_of(unit, gq);
       for (int e = lane; e < D; e += 64) {
         mxS = fmaxf(mxS, fabsf(S[(size_t)e * D + e]));
-        mxM = fmaxf(mxM, fabsf(m[e]));
+        if (mu) mxM = fmaxf(mxM, fabsf(mu[((size_t)unit * G + gq) * D + e]));
       }
     }
     for (int o = 32; o >= 1; o >>= 1) {
@@ -945,11 +954,11 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
       const int c_out = ((rho >> 2) & 1) * HALF + jt * 16 + 4 * (rho >> 3) + (rho & 3);
       const int c_in0 = hl * HALF + kt * 8;
       const float sM = s_scale[2 * g];
-      const float* S = sigma + ((size_t)unit * G + gq) * D * D;
       float val[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) val[i] = 0.f;
       if (gq < G) {
+        const float* S = sigma_of(unit, gq);
         // the pair (c_in, c_out) and its mirror contribute the same product k_in * k_out, so the
         // contiguous row S[c_out][c_in0 .. c_in0+7] serves for the block on and above the
         // diagonal; blocks strictly above also take the mirrored entries S[c_in][c_out]
@@ -979,10 +988,10 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
         float val = 0.f;
         if (g >= 0 && gq < G) {
           if (kind == 2) {
-            float m = sigma[(((size_t)unit * G + gq) * D + c_in) * D + c_in] * s_scale[2 * g];
+            float m = sigma_of(unit, gq)[(size_t)c_in * D + c_in] * s_scale[2 * g];
             val = m - (float)(_Float16)m;
           } else {
-            float m = mu[((size_t)unit * G + gq) * D + c_in] * s_scale[2 * g + 1];
+            float m = mu ? mu[((size_t)unit * G + gq) * D + c_in] * s_scale[2 * g + 1] : 0.f;
             float hi = (float)(_Float16)m;
             val = kind == 0 ? hi : m - hi;
           }
@@ -1087,14 +1096,16 @@ hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_
 }
 
 hipError_t launch_prep_frags(const Dims& d, const ScorePlan& sp, const float* mu,
-                             const float* sigma, uint4* frags, float* post, hipStream_t st) {
+                             const float* sigma, uint4* frags, float* post, hipStream_t st, uint32_t* clear,
+                             size_t clear_words, bool sigma_shared) {
   dim3 grid(d.units() * sp.passes, kPrepSplit);
+  const int shared = sigma_shared ? d.Hq : 0;
   if (d.D == 64)
-    k_prep_frags<64><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, frags, post);
+    k_prep_frags<64><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, shared, frags, post, clear, clear_words);
   else if (d.D == 128)
-    k_prep_frags<128><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, frags, post);
+    k_prep_frags<128><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, shared, frags, post, clear, clear_words);
   else
-    k_prep_frags<256><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, frags, post);
+    k_prep_frags<256><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, shared, frags, post, clear, clear_words);
   return hipGetLastError();
 }
 

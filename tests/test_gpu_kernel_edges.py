@@ -106,3 +106,29 @@ def test_select_row_edges(n, kind):
     for n_keep in {1, n, max(1, n // 2), max(1, n - 1), min(n, 65)}:
         idx = P.run_select(cfg, sc, n_keep)
         assert np.array_equal(idx.astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
+
+
+@pytest.mark.parametrize("n,n_keep,floor", [(4095, 2000, 1), (4096, 4000, 4000), (4097, 1500, 700), (5500, 5500, 17),
+                                            (8193, 300, 300), (16385, 9000, 4097)])
+def test_adaptive_selection_block_edges(n, n_keep, floor):
+    """The copy that lifts every head's own best pairs, around its 4096-score blocks, with the pooled list in
+    one launch (3 n <= 16384) and in several: lists and lengths are exactly the oracle's.  The whole call is
+    made twice on one workspace: nothing of the first may be left in it."""
+    import torch
+    cfg = CONFIGS["c2"].with_(batch=2, n_kv_heads=3, n_q_heads=3)
+    p = P.params_for(cfg)
+    rng = np.random.default_rng(n + floor)
+    ws = P.workspace(p, n, 1)
+    for rep in range(2):
+        sc = np.exp(rng.standard_normal((2, 3, n))).astype(np.float32)
+        sc[:, 1] *= 3.0
+        sc[0, 0, ::3] = sc[0, 0, 0]
+        idx = torch.full((2, 3, n), -7, dtype=torch.int32, device="cuda")
+        lengths = torch.full((2, 3), -1, dtype=torch.int32, device="cuda")
+        ea.select_adaptive(p, P.to_dev(sc), n, n_keep, floor, idx, lengths, ws)
+        torch.cuda.synchronize()
+        rl, rk = X.select_adaptive(sc.astype(np.float64), n_keep, floor)
+        gl, gi = lengths.cpu().numpy(), idx.cpu().numpy()
+        assert np.array_equal(gl, rl)
+        assert all(np.array_equal(gi[b, h, :gl[b, h]], rk[b][h]) for b in range(2) for h in range(3))
+    assert ea.debug_status(p, n, 1, ws) == 0
