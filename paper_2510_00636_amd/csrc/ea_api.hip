@@ -265,8 +265,10 @@ ea_status ea_select(const ea_params* p, const float* scores, int64_t n, int64_t 
   if (n_keep == 0) return EA_OK;
   hipStream_t st = (hipStream_t)stream;
   uint32_t* hist = (uint32_t*)((char*)ws + L.hist);
-  EA_TRY(launch_zero(hist, hist_words(d), st));
-  EA_TRY(launch_select(d, scores, n, n_keep, idx, hist, (uint32_t*)((char*)ws + L.blk), false, st));
+  uint32_t* blk = (uint32_t*)((char*)ws + L.blk);
+  // one launch: the status word is in the histograms; several: they and the block counts start at zero
+  EA_TRY(launch_zero(hist, select_in_one_launch(n) ? hist_words(d) : (L.flags - L.hist) / 4, st));
+  EA_TRY(launch_select(d, scores, n, n_keep, idx, hist, blk, false, st));
   return EA_OK;
 }
 
@@ -282,10 +284,11 @@ ea_status ea_select_static(const ea_params* p, const float* scores, int64_t n, i
   uint32_t* hist = static_scratch_for_current_device();
   if (!hist) return EA_ERR_DEVICE;
   hipStream_t st = (hipStream_t)stream;
-  // the array keeps the previous call's contents: the histograms must start at zero (a fill
-  // kernel, so that the call can be captured in a graph); the block counts are overwritten
-  EA_TRY(launch_zero(hist, hist_words(d), st));
-  EA_TRY(launch_select(d, scores, n, n_keep, idx, hist, hist + kStaticHistWords, false, st));
+  // the array keeps the previous call's contents: the histograms and the block counts right behind them must
+  // start at zero (a fill kernel, so that the call can be captured in a graph)
+  const size_t blk_words = (size_t)d.units() * (size_t)((n + kSelBlock - 1) / kSelBlock);
+  EA_TRY(launch_zero(hist, hist_words(d) + blk_words, st));
+  EA_TRY(launch_select(d, scores, n, n_keep, idx, hist, hist + hist_words(d), false, st));
   return EA_OK;
 }
 
@@ -412,14 +415,16 @@ ea_status ea_compress_layer(const ea_params* p, const void* q_win, int64_t windo
 
 // Pooled selection of ea_select_adaptive on the caller's stream.  `lifted`: a buffer of units * n
 // floats that is not `scores` (only used with a floor); `top`: units * floor ints of scratch.  The
-// histograms of the heads and of the pooled lists are zero on entry; hist0_done: the heads' first one
+// histograms of the heads and of the pooled lists, and the block counts, are zero on entry; hist0_done: the heads' first one
 // is filled.
 static ea_status run_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor,
                                      int32_t* idx, int32_t* lengths, float* lifted, int32_t* top, char* w,
                                      const WsLayout& L, bool hist0_done, hipStream_t st) {
   uint32_t* hist = (uint32_t*)(w + L.hist);
   uint32_t* pool_hist = (uint32_t*)(w + L.pool_hist);
+  // block counts of the heads' selection, then of the pooled one (never more of them)
   uint32_t* blk = (uint32_t*)(w + L.blk);
+  uint32_t* pool_blk = blk + (size_t)d.units() * (size_t)((n + kSelBlock - 1) / kSelBlock);
   int32_t* flat = (int32_t*)(w + L.idx);                // [B][Hkv * n_keep], ascending in [0, Hkv * n)
   Dims layer = d;                                       // one pooled list per sequence
   layer.Hq = d.G;
@@ -434,7 +439,7 @@ static ea_status run_select_adaptive(const Dims& d, const float* scores, int64_t
     pooled = lifted;
   }
   if (n_keep > 0)
-    EA_TRY(launch_select(layer, pooled, (int64_t)d.Hkv * n, (int64_t)d.Hkv * n_keep, flat, pool_hist, blk, pool_hist0, st,
+    EA_TRY(launch_select(layer, pooled, (int64_t)d.Hkv * n, (int64_t)d.Hkv * n_keep, flat, pool_hist, pool_blk, pool_hist0, st,
                          hist));
   EA_TRY(launch_split_pooled(flat, d.B, d.Hkv, n, n_keep, idx, lengths, st));
   return EA_OK;
@@ -452,7 +457,7 @@ ea_status ea_select_adaptive(const ea_params* p, const float* scores, int64_t n,
   WsLayout L;
   if ((s = check_ws(d, n, 1, ws, ws_bytes, &L)) != EA_OK) return s;
   char* w = (char*)ws;
-  EA_TRY(launch_zero((uint32_t*)(w + L.hist), (L.blk - L.hist) / 4, (hipStream_t)stream));
+  EA_TRY(launch_zero((uint32_t*)(w + L.hist), (L.flags - L.hist) / 4, (hipStream_t)stream));
   return run_select_adaptive(d, scores, n, n_keep, floor, idx, lengths, (float*)(w + L.scores),
                              (int32_t*)(w + L.logits), w, L, false, (hipStream_t)stream);
 }

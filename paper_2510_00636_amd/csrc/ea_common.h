@@ -71,7 +71,7 @@ constexpr int kStatusSlot = 1030;
 constexpr int kTicketSlot = 1040;
 // Status bits (see ea_debug_status)
 constexpr uint32_t kStatusBadScore = 1u;      // ea_select met a negative or NaN score
-constexpr uint32_t kStatusCompactWait = 2u;   // in-place ea_compact gave up waiting: stores skipped
+constexpr uint32_t kStatusCompactWait = 2u;   // in-place ea_compact, or a block of ea_select, gave up waiting: stores skipped
 constexpr uint32_t kStatusBadIndex = 4u;      // ea_compact met an idx list that is not strictly ascending in [j, n)
 constexpr int kBaselineChunks = 256;          // most row chunks per head in the KeyDiff mean
 constexpr int kCompactTicketStride = 64;      // words per (unit, tensor) at the head of the flag region

@@ -132,3 +132,24 @@ def test_adaptive_selection_block_edges(n, n_keep, floor):
         assert np.array_equal(gl, rl)
         assert all(np.array_equal(gi[b, h, :gl[b, h]], rk[b][h]) for b in range(2) for h in range(3))
     assert ea.debug_status(p, n, 1, ws) == 0
+
+
+@pytest.mark.parametrize("n", [16385, 20480, 20481, 270000])
+@pytest.mark.parametrize("kind", ["spread", "ties", "equal"])
+def test_select_blocks(n, kind):
+    """Selections of several launches: last blocks of one score and of 4096, more than 64 blocks, ties that
+    run across blocks; twice on one workspace, where the second call must not see the first one's counts."""
+    import torch
+    rng = np.random.default_rng(n)
+    cfg = CONFIGS["c1"].with_(n_q_heads=3, n_kv_heads=3)
+    p = P.params_for(cfg)
+    ws = P.workspace(p, n, 1)
+    for n_keep in (n // 2, n - 1, 1, 5000):
+        shape = (1, 3, n)
+        sc = (np.exp(rng.standard_normal(shape)) if kind == "spread" else
+              rng.integers(0, 5, shape).astype(np.float64) if kind == "ties" else np.ones(shape)).astype(np.float32)
+        idx = torch.full((1, 3, n_keep), -1, dtype=torch.int32, device="cuda")
+        ea.select(p, P.to_dev(sc), n, n_keep, idx, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy().astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
+    assert ea.debug_status(p, n, 1, ws) == 0
