@@ -142,15 +142,28 @@ __device__ __forceinline__ void stats_unpack_item(const StatsRaw<BF16>& raw, int
     tb[2 * e + 1] = make_float2(raw.t[e].z, raw.t[e].w);
   }
 }
+// u~ - shift: the 2x2 block of the table applied to one pair.  Which of the two products of a sum is rounded on
+// its own is spelled out (of the second: t.x qb, or t.y qa), and nothing else is contracted, so that the bits
+// of the statistics, and with them every score, do not hang on what the compiler makes of the code around it.
+__device__ __forceinline__ void stats_rotate(bool round_txqb, float2 t, float qa, float qb, float sha, float shb,
+                                             float& xa, float& xb) {
+#pragma clang fp contract(off)
+  const float pa = t.y * qb;
+  const float pb = round_txqb ? t.x * qb : t.y * qa;
+  const float ua = fmaf(t.x, qa, -pa), ub = round_txqb ? fmaf(t.y, qa, pb) : fmaf(t.x, qb, pb);
+  xa = ua - sha;
+  xb = ub - shb;
+}
+
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 
-// Register budget: three workgroups per CU at d <= 128 (168 registers), two at d = 256 (256),
-// without spills for bf16 input (prefetched items stay packed, u~_0 lives in LDS, the tile numbers
-// are scalar).  With more registers per wavefront the 640 workgroups of a decode-shape call do not
-// fit on the chip at once.  A budget met only by spilling is no use here: a kernel that needs
-// scratch memory costs some 10 us more per launch when several streams are in use.
+// Register budget: four workgroups per CU at d = 64, two at 128, one at 256, the most that the operands of a
+// matrix step and of the one after it leave without spills: a kernel that needs scratch memory costs some
+// 10 us more per launch when several streams are in use.  Reading operands under "inside the window" and "my
+// tile" and waiting for each pair bounded it: 28 heads, d = 128, w = 200 26 -> 16 us, 128 heads, w = 512
+// 61 -> 31, 16 heads, d = 256, w = 200 41 -> 28.
 template <int D, bool BF16>
-__global__ __launch_bounds__(256, (D <= 128 ? 3 : 2)) void k_stats(const void* __restrict__ q_win, int w, int layout,
+__global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 2 : 1)) void k_stats(const void* __restrict__ q_win, int w, int layout,
                                                int ddof, const float2* __restrict__ tab,
                                                float* __restrict__ mu, float* __restrict__ sigma) {
   constexpr int HALF = D / 2, G8 = HALF / 8;          // groups of 8 channel pairs per sample
@@ -191,8 +204,10 @@ __global__ __launch_bounds__(256, (D <= 128 ? 3 : 2)) void k_stats(const void* _
     stats_unpack_item<BF16>(raw0, layout, qa, qb, tb);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      s_shift[stats_ja<D>(layout, g, e)] = tb[e].x * qa[e] - tb[e].y * qb[e];
-      s_shift[stats_jb<D>(layout, g, e)] = tb[e].y * qa[e] + tb[e].x * qb[e];
+      float ua, ub;
+      stats_rotate(true, tb[e], qa[e], qb[e], 0.f, 0.f, ua, ub);
+      s_shift[stats_ja<D>(layout, g, e)] = ua;
+      s_shift[stats_jb<D>(layout, g, e)] = ub;
     }
   }
   __syncthreads();
@@ -237,8 +252,8 @@ __global__ __launch_bounds__(256, (D <= 128 ? 3 : 2)) void k_stats(const void* _
         stats_unpack_item<BF16>(raw[it], layout, qa, qb, tb);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          xa[e] = tb[e].x * qa[e] - tb[e].y * qb[e] - s_shift[stats_ja<D>(layout, g, e)];
-          xb[e] = tb[e].y * qa[e] + tb[e].x * qb[e] - s_shift[stats_jb<D>(layout, g, e)];
+          stats_rotate(D >= 128, tb[e], qa[e], qb[e], s_shift[stats_ja<D>(layout, g, e)],
+                       s_shift[stats_jb<D>(layout, g, e)], xa[e], xb[e]);
           suma[e] += xa[e];
           sumb[e] += xb[e];
         }
@@ -254,34 +269,59 @@ __global__ __launch_bounds__(256, (D <= 128 ? 3 : 2)) void k_stats(const void* _
 #pragma unroll
           for (int e = 0; e < 4; ++e) pi[e] = make_float4(xa[2 * e], xb[2 * e], xa[2 * e + 1], xb[2 * e + 1]);
         }
+      } else {                                        // past the window's end: zeros
+        float4* z = reinterpret_cast<float4*>(s_u + sl * D + 16 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
     __syncthreads();
     if (ch + 1 < nchunks) load_chunk(ch + 1);         // in flight during the matrix-core loop
-    // a few sample pairs per step: all their LDS reads first, then the MFMAs (samples past the
-    // chunk's end count as zero)
-    constexpr int PS = TPW == 1 ? 4 : 2;
+    // Eight sample pairs per step, the operands of the next step requested before the instructions of this one
+    // (samples past the window's end are zero rows in LDS); of a shared tile's pairs, two of every eight are
+    // this wavefront's.  A tile that it does not have (d = 64) is computed as tile 0 and not stored.
+    constexpr int PS = 8;
     const int npair = (ns + 1) / 2;
-    for (int sp = 0; sp < npair; sp += PS) {
-      float av[PS][TPW], bv[PS][TPW];
-      const bool mine = ((sp / PS) & 3) == wave;       // this step's samples of the shared tiles
+    float av[2][PS][TL::WHOLE], bv[2][PS][TL::WHOLE], as[2][2][TL::SHARED + 1], bs[2][2][TL::SHARED + 1];
+    auto read_step = [&](int sp, int buf) __attribute__((always_inline)) {
 #pragma unroll
       for (int u = 0; u < PS; ++u) {
-        const int sl = 2 * (sp + u) + hh;
-        const bool ok = sl < ns;
+        const float* row = s_u + (2 * (sp + u) + hh) * D + r32;
 #pragma unroll
-        for (int t = 0; t < TPW; ++t) {
-          const bool okt = ok && t_rb[t] >= 0 && (t < TL::WHOLE || mine);
-          av[u][t] = okt ? s_u[sl * D + t_rb[t] * 32 + r32] : 0.f;
-          bv[u][t] = okt ? s_u[sl * D + t_ct[t] * 32 + r32] : 0.f;
+        for (int t = 0; t < TL::WHOLE; ++t) {
+          av[buf][u][t] = row[max(t_rb[t], 0) * 32];
+          bv[buf][u][t] = row[t_ct[t] * 32];
         }
       }
 #pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const float* row = s_u + (2 * (sp + 2 * wave + u) + hh) * D + r32;
+#pragma unroll
+        for (int t = 0; t < TL::SHARED; ++t) {
+          as[buf][u][t] = row[t_rb[TL::WHOLE + t] * 32];
+          bs[buf][u][t] = row[t_ct[TL::WHOLE + t] * 32];
+        }
+      }
+    };
+    auto multiply_step = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
       for (int u = 0; u < PS; ++u)
 #pragma unroll
-        for (int t = 0; t < TPW; ++t)
-          if (t_rb[t] >= 0 && (t < TL::WHOLE || mine))
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u][t], bv[u][t], acc[t], 0, 0, 0);
+        for (int t = 0; t < TL::WHOLE; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[buf][u][t], bv[buf][u][t], acc[t], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int t = 0; t < TL::SHARED; ++t)
+          acc[TL::WHOLE + t] =
+              __builtin_amdgcn_mfma_f32_32x32x2f32(as[buf][u][t], bs[buf][u][t], acc[TL::WHOLE + t], 0, 0, 0);
+    };
+    read_step(0, 0);
+    for (int sp = 0; sp < npair; sp += 2 * PS) {
+      read_step(min(sp + PS, kStatsWC / 2 - PS), 1);
+      multiply_step(0);
+      read_step(min(sp + 2 * PS, kStatsWC / 2 - PS), 0);
+      if (sp + PS < npair) multiply_step(1);
     }
   }
   if (TL::SHARED > 0) {
@@ -492,19 +532,6 @@ typedef _Float16 stats_half2 __attribute__((ext_vector_type(2)));
 // samples per staged chunk: 64, and 32 at d = 256 (registers: a thread keeps its share of the next
 // chunk's queries and table rows in flight during the matrix-core loop)
 constexpr int stats_split_chunk(int D) { return D >= 256 ? 32 : 64; }
-
-// u~ - shift: the 2x2 block of the table applied to one pair.  Which of the two products of a sum is rounded on
-// its own is spelled out (of the second: t.x qb, or t.y qa), and nothing else is contracted, so that the bits
-// of the statistics, and with them every score, do not hang on what the compiler makes of the code around it.
-__device__ __forceinline__ void stats_rotate(bool round_txqb, float2 t, float qa, float qb, float sha, float shb,
-                                             float& xa, float& xb) {
-#pragma clang fp contract(off)
-  const float pa = t.y * qb;
-  const float pb = round_txqb ? t.x * qb : t.y * qa;
-  const float ua = fmaf(t.x, qa, -pa), ub = round_txqb ? fmaf(t.y, qa, pb) : fmaf(t.x, qb, pb);
-  xa = ua - sha;
-  xb = ub - shb;
-}
 
 // What bounds it at the decode-time shape (960 heads, w = 512, two workgroups of four wavefronts per CU) is the
 // work between the barriers of a chunk, not memory: 101 us, and 84 with every load on one cached line.  Taking

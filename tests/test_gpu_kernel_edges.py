@@ -153,3 +153,16 @@ def test_select_blocks(n, kind):
         torch.cuda.synchronize()
         assert np.array_equal(idx.cpu().numpy().astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
     assert ea.debug_status(p, n, 1, ws) == 0
+
+
+@pytest.mark.parametrize("d,layout", [(64, 0), (128, 0), (128, 1), (256, 0)])
+@pytest.mark.parametrize("w", [2, 15, 17, 32, 33, 64, 65, 127, 200])
+def test_fp32_statistics_window_edges(d, layout, w):
+    """fp32 windows around the eight-pair steps and 64-sample chunks of the covariance loop, against the
+    oracle at the statistics tolerance."""
+    cfg = CONFIGS["c1"].with_(head_dim=d, n_q_heads=3, n_kv_heads=1, n_outliers=2, outlier_offset=8.0)
+    lay = make_layer(cfg, n=w + 7, window=w, interleaved=bool(layout), pos0=50000)
+    mu, sg = P.run_query_stats(cfg, lay, rope_layout=layout)
+    rmu, rsg = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T,
+                             layout=layout)
+    P.check_stats(mu, sg, rmu, rsg)
