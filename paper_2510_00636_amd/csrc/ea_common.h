@@ -64,8 +64,8 @@ ea_status check_params(const ea_params* p, Dims* d, bool rows_only = false);
 ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged = 0);
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window);
 
-// Free words of unit 0's third radix histogram (its last digit has 1024 bins): (T, q) of the
-// selection at 1024/1025, a status word at kStatusSlot, the score kernel's tile counters from
+// Free words of the third radix histogram (its last digit has 1024 bins): the emit pass's block counter of
+// every unit, unit 0's status word at kStatusSlot, the score kernel's tile counters of every unit from
 // kTicketSlot on.  The launch that clears the histograms clears them all.
 constexpr int kStatusSlot = 1030;
 constexpr int kTicketSlot = 1040;

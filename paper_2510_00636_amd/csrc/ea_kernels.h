@@ -61,7 +61,7 @@ hipError_t launch_finalize(const Dims& d, int64_t n, const void* logits, int log
 hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D, float* wnorm, hipStream_t st);
 
 // ea_select.hip
-// heads this short are selected by one workgroup per unit out of LDS, in one launch (no global
+// heads this short are selected by one workgroup per unit out of registers, in one launch (no global
 // histograms: hist0 from the finalize pass is not needed then)
 constexpr int64_t kSelSmallMax = 16384;   // (whole pass at 20000 keys per head, one launch and four: 117 us either way; 32768: 142 and 140)
 inline bool select_in_one_launch(int64_t n) { return n <= kSelSmallMax; }
