@@ -132,12 +132,22 @@ WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window) {
     return at;
   };
   const size_t qh = (size_t)d.qheads(), un = (size_t)d.units();
-  ScorePlan sp = make_score_plan(d, n, 256);
+  // The callers size one buffer for every cache layout: the fragments of whichever plan is larger, that of
+  // contiguous bf16 tensors (the register-fragment kernel where it serves them) or that of block pools and
+  // 8-bit caches.  At d = 128, n >= 2048 and one KV head they differ: 6 x 96 and 5 x 116 KiB for 24 query heads.
+  Dims contiguous = d;
+  contiguous.kv_fp8 = 0;
+  size_t frags_per_unit = 0;
+  for (int paged = 0; paged <= 1; ++paged) {
+    const ScorePlan sp = make_score_plan(contiguous, n, 256, paged);
+    const size_t need = (size_t)sp.passes * sp.nfrag * 1024;
+    if (need > frags_per_unit) frags_per_unit = need;
+  }
   w.tab = take((size_t)window * d.half * 2 * sizeof(float));
   w.qproj = take(qh * (size_t)window * d.D * sizeof(float));   // projected queries of ea_query_stats_hidden
   w.mu = take(qh * d.D * sizeof(float));
   w.sigma = take(qh * d.D * d.D * sizeof(float));
-  w.frags = take(un * sp.passes * sp.nfrag * 1024);
+  w.frags = take(un * frags_per_unit);
   w.post = take(qh * 2 * sizeof(float));
   w.logits = take(qh * (size_t)n * 8);          // fp32 logits (bf16 path) or fp64 (fp32 path)
   w.vnorm = take(un * (size_t)n * sizeof(float));

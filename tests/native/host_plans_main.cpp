@@ -1,0 +1,54 @@
+// Host-only driver: every score plan that a call on some cache layout can take (contiguous, paged, 8-bit)
+// fits the one workspace layout that callers size their buffers by.  Exits 0 when every check holds.
+#include <initializer_list>
+#include <stdio.h>
+#include <string.h>
+
+#include "../../paper_2510_00636_amd/csrc/ea_common.h"
+
+static int failures = 0;
+#define CHECK(cond, ...)                                                         \
+  do {                                                                           \
+    if (!(cond) && ++failures <= 20) {                                           \
+      fprintf(stderr, "%s:%d: check failed: %s: ", __FILE__, __LINE__, #cond);   \
+      fprintf(stderr, __VA_ARGS__);                                              \
+      fprintf(stderr, "\n");                                                     \
+    }                                                                            \
+  } while (0)
+
+int main() {
+  for (int d : {64, 128, 256})
+    for (int G = 1; G <= 64; ++G)
+      for (int units : {1, 2, 3, 4, 8, 9, 32, 200, 300})
+        for (int64_t n : {(int64_t)1, (int64_t)100, (int64_t)2047, (int64_t)2048, (int64_t)4096, (int64_t)131072}) {
+          ea_params p;
+          memset(&p, 0, sizeof p);
+          p.batch = 1; p.n_q_heads = G * units; p.n_kv_heads = units; p.head_dim = d; p.dtype = EA_BF16;
+          p.q_is_rotated = 1; p.horizon_T = 512; p.epsilon = 0.02f;
+          ea::Dims dims;
+          CHECK(ea::check_params(&p, &dims) == EA_OK, "d %d G %d", d, G);
+          const size_t bytes = ea_workspace_bytes(&p, n, 64);
+          for (int fp8 = 0; fp8 <= (d >= 128); ++fp8) {
+            ea::Dims dd = dims;
+            dd.kv_fp8 = fp8;
+            const ea::WsLayout L = ea::make_ws_layout(dd, n, 64), plain = ea::make_ws_layout(dims, n, 64);
+            // ea_workspace_bytes and ea_debug_status do not know how the cache is stored
+            CHECK(L.total == bytes && L.hist == plain.hist, "d %d G %d units %d n %ld fp8 %d: %zu bytes, %zu reserved", d, G,
+                  units, (long)n, fp8, L.total, bytes);
+            for (int paged = 0; paged <= !fp8; ++paged)
+              for (int cu : {64, 256, 304}) {
+                const ea::ScorePlan sp = ea::make_score_plan(dd, n, cu, paged);
+                const size_t need = (size_t)units * sp.passes * sp.nfrag * 1024;
+                CHECK(need <= L.post - L.frags, "d %d G %d units %d n %ld paged %d fp8 %d: fragments %zu, reserved %zu", d, G,
+                      units, (long)n, paged, fp8, need, L.post - L.frags);
+                CHECK((size_t)dd.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
+              }
+          }
+        }
+  if (failures) {
+    fprintf(stderr, "%d check(s) failed\n", failures);
+    return 1;
+  }
+  printf("host plans fit\n");
+  return 0;
+}

@@ -166,3 +166,47 @@ def test_fp32_statistics_window_edges(d, layout, w):
     rmu, rsg = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T,
                              layout=layout)
     P.check_stats(mu, sg, rmu, rsg)
+
+
+@pytest.mark.parametrize("hq,n", [(20, 2048), (24, 2048), (28, 4100), (32, 2100)])
+def test_one_kv_head_with_many_query_heads_on_every_cache_layout(hq, n):
+    """One KV head, five to eight passes at d = 128: paged and 8-bit caches take another plan than contiguous
+    tensors, with more fragments from 24 heads on and fewer at 20, in the one workspace that
+    workspace_bytes gives.  Scores against the oracle at the bf16 tolerance, the paged ones against the
+    contiguous call's to 2e-5 (other kernel, the same fp16 products), and a NaN value row of the 8-bit cache
+    shows in the status word."""
+    import torch
+    from ea_inputs import make_block_pools, quantize_fp8
+    cfg = CONFIGS["c2"].with_(n_q_heads=hq, n_kv_heads=1)
+    w = 64
+    lay = make_layer(cfg, n=n, window=w)
+    p = P.params_for(cfg, epsilon=0.02)
+    mu, sigma = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T)
+    mu, sigma = mu.astype(np.float32), sigma.astype(np.float32)
+    contiguous = P.run_score(cfg, lay, mu, sigma, 0.02)
+    P.check_scores(contiguous, O.scores(widen(lay["k"]), widen(lay["v"]), mu, sigma, 0.02), 2e-3)
+    kp, vp, tab, nb = make_block_pools(lay["k"], lay["v"], 64, 5)
+    tabd = torch.from_numpy(tab).cuda()
+    sc = torch.empty(1, 1, n, device="cuda")
+    ws = P.workspace(p, n, 1)
+    ws.fill_(255)
+    ea.score_paged(p, P.to_dev(kp), P.to_dev(vp), ea.make_paged(tabd, 64, nb), n, P.to_dev(mu), P.to_dev(sigma), sc, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(sc.cpu().numpy(), contiguous, rtol=2e-5, atol=0)
+
+    k8, ks = quantize_fp8(widen(lay["k"]))
+    v8, vs = quantize_fp8(widen(lay["v"]))
+    k8d, v8d, ksd, vsd = (torch.from_numpy(x).cuda() for x in (k8, v8, ks, vs))
+    ws.fill_(255)
+    ea.score_fp8(p, k8d, v8d, ksd, vsd, n, n, P.to_dev(mu), P.to_dev(sigma), sc, ws)
+    torch.cuda.synchronize()
+    real = [X.fp8_e4m3_decode(c) * s.astype(np.float64)[:, :, None, None] for c, s in ((k8, ks), (v8, vs))]
+    P.check_scores(sc.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), 0.02), 2e-3)
+
+    ws = P.workspace(p, n, w)
+    for bad in (False, True):
+        if bad:
+            v8d[0, 0, 5] = 0x7F
+        ea.compress_layer_fp8(p, P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"],
+                              k8d.clone(), v8d.clone(), ksd, vsd, n, n, n // 2, 0, None, None, None, ws)
+        assert ea.debug_status(p, n, w, ws) == (ea.STATUS_BAD_SCORE if bad else 0)
