@@ -149,32 +149,38 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_hist(SelArgs a) {
 // Counting and writing in one launch.  A workgroup takes the next block of its unit by ticket, counts what its
 // block keeps, publishes the two counts in one word and adds up those of the blocks in front of it: blocks
 // with lower tickets, so their workgroups are running already and publish before they wait for anybody;
-// every wait ends.  (The spin bound keeps even a corrupted workspace from hanging: the block then writes
-// nothing and the status word says so.)  Wavefront w holds 16 rows of 64 consecutive scores, so that loads and
-// stores run along the lanes and positions are ballots.  Against a counting launch and an emit launch in
-// which a thread read 16 consecutive scores (64 cache lines per load): 7.0 + 16.8 -> 16.8 us at 32 units x 131072,
-// 5.4 + 7.4 -> 10.7 at 8, and a launch less (whole pass of 8 units x 20011: 132.4 -> 128.6 us).
+// every wait ends.  (A thread's spin budget for the whole sum keeps even a corrupted workspace from hanging: the
+// block then writes nothing and the status word says so.)  Wavefront w holds 16 rows of 64 consecutive scores,
+// so that loads and stores run along the lanes and positions are ballots.  Against a counting launch and an emit
+// launch in which a thread read 16 consecutive scores (64 cache lines per load): 7.0 + 16.8 -> 16.8 us at 32 units x
+// 131072, 5.4 + 7.4 -> 10.7 at 8, and a launch less (whole pass of 8 units x 20011: 132.4 -> 128.6 us).
+// What lies in front of a block is (scores above T) + min(q, scores at T), whatever the order of the blocks, so a
+// lane just adds up words, two in flight.  Scanning them in order, 64 at a time, had made whole selections of one long
+// head slower than the two launches were: 2^22 scores 70.3 -> 76.2 us, 2^26 1489 -> 1815; now 70.6 and 915.  Four words
+// in flight per lane are 6 % faster at 2^26 and 2 % slower at 8 heads x 2^20 (69.7 us), all four wavefronts at it 18 %
+// slower there.
 constexpr uint32_t kEmitTicket = 1026;     // free word of a unit's third histogram
 constexpr uint32_t kEmitSeen = 1u << 31;
 constexpr int kEmitSpinLimit = 1 << 20;
 
 __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
-  constexpr int W = kSelThreads / 64;
+  constexpr int W = kSelThreads / 64, U = 2;
   __shared__ uint32_t s_tmp[258];
   __shared__ uint32_t s_w[2][W];
-  __shared__ uint32_t s_base[3];
+  __shared__ uint32_t s_front[3];
+  __shared__ uint32_t s_blk;
   const int tid = threadIdx.x, lane = tid & 63, unit = blockIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (tid == 0) s_base[0] = atomicAdd(a.hist + ((size_t)unit * 3 + 2) * kSelBins + kEmitTicket, 1u);
+  if (tid == 0) s_blk = atomicAdd(a.hist + ((size_t)unit * 3 + 2) * kSelBins + kEmitTicket, 1u);
   __syncthreads();
-  const int blk = (int)s_base[0];
+  const int blk = __builtin_amdgcn_readfirstlane((int)s_blk);
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
   const long long base = (long long)blk * kSelBlock + wave * (kSelBlock / W) + lane;    // of u[0]; u[j]: 64 j further
   uint32_t u[kSelPer];
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) u[j] = sc[min(base + 64 * j, a.n - 1)];
   uint32_t T, q;
-  resolve<3>(a, unit, s_tmp, &T, &q);       // (its barriers also order s_base)
+  resolve<3>(a, unit, s_tmp, &T, &q);
   uint32_t gt = 0, eq = 0;
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) {
@@ -183,56 +189,48 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
   }
   if (lane == 0) { s_w[0][wave] = gt; s_w[1][wave] = eq; }
   __syncthreads();
+  uint32_t* pub = a.blk + (size_t)unit * a.nblk;
+  const int front = min(blk, a.nblk);       // (a counter that did not start at zero never leads past the unit's words)
+  if (tid == 0 && blk < a.nblk) {
+    uint32_t g = 0, e = 0;
+    for (int w = 0; w < W; ++w) { g += s_w[0][w]; e += s_w[1][w]; }
+    __hip_atomic_store(&pub[blk], kEmitSeen | (e << 13) | g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // scores above T and at T in the blocks in front of this one
   if (wave == 0) {
-    uint32_t* pub = a.blk + (size_t)unit * a.nblk;
-    if (lane == 0) {
-      uint32_t g = 0, e = 0;
-      for (int w = 0; w < W; ++w) { g += s_w[0][w]; e += s_w[1][w]; }
-      __hip_atomic_store(&pub[blk], kEmitSeen | (e << 13) | g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // kept pairs and ==T pairs in the blocks before this one, 64 of them at a time, in order
-    uint32_t kept = 0, eqs = 0;
-    bool seen = true;
-    for (int j0 = 0; j0 < blk; j0 += 64) {
-      const int j = j0 + lane;
-      uint32_t word = 0;
-      if (j < blk) {
-        int spin = 0;
-        while (((word = __hip_atomic_load(&pub[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & kEmitSeen) == 0u) {
-          if (++spin >= kEmitSpinLimit) { seen = false; break; }
+    uint32_t gf = 0, ef = 0;
+    int spin = 0;
+    for (int j0 = lane; j0 < front && spin < kEmitSpinLimit; j0 += U * 64) {
+      uint32_t word[U];
+#pragma unroll
+      for (int x = 0; x < U; ++x)
+        word[x] = j0 + 64 * x < front ? __hip_atomic_load(&pub[j0 + 64 * x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kEmitSeen;
+#pragma unroll
+      for (int x = 0; x < U; ++x) {
+        while ((word[x] & kEmitSeen) == 0u && ++spin < kEmitSpinLimit) {
           __builtin_amdgcn_s_sleep(1);
+          word[x] = __hip_atomic_load(&pub[j0 + 64 * x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        gf += word[x] & 0x1fffu;
+        ef += (word[x] >> 13) & 0x1fffu;
       }
-      const uint32_t g = word & 0x1fffu, e = (word >> 13) & 0x1fffu;
-      uint32_t ei = e;                              // inclusive scan of e over the lanes
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t up = __shfl_up(ei, o);
-        if (lane >= o) ei += up;
-      }
-      const uint32_t eq_before = eqs + ei - e;      // ==T pairs before block j
-      const uint32_t room = q > eq_before ? q - eq_before : 0u;
-      uint32_t k = g + (e < room ? e : room);       // kept pairs of block j
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) k += __shfl_xor(k, o);
-      kept += k;
-      eqs += __shfl(ei, 63);
     }
-    const bool ok = __ballot(!seen) == 0ull;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) { gf += __shfl_xor(gf, o); ef += __shfl_xor(ef, o); }
+    const bool ok = __ballot(spin >= kEmitSpinLimit) == 0ull;
     if (lane == 0) {
-      s_base[0] = kept;
-      s_base[1] = eqs;
-      s_base[2] = ok;
+      s_front[0] = gf;
+      s_front[1] = ef;
+      s_front[2] = ok;
       if (!ok) atomicOr(a.status, kStatusCompactWait);
     }
   }
   __syncthreads();
-  if (!s_base[2]) return;
+  if (!s_front[2]) return;
   // what lies in front of this wavefront
-  uint32_t pos = s_base[0], eq_before = s_base[1];
-  const uint32_t first = eq_before < q ? eq_before : q;
+  uint32_t pos = s_front[0], eq_before = s_front[1];
   for (int w = 0; w < wave; ++w) { pos += s_w[0][w]; eq_before += s_w[1][w]; }
-  pos += (eq_before < q ? eq_before : q) - first;
+  pos += eq_before < q ? eq_before : q;
   int32_t* out = a.idx + (size_t)unit * a.n_keep;
   const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll

@@ -210,3 +210,18 @@ def test_one_kv_head_with_many_query_heads_on_every_cache_layout(hq, n):
         ea.compress_layer_fp8(p, P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"],
                               k8d.clone(), v8d.clone(), ksd, vsd, n, n, n // 2, 0, None, None, None, ws)
         assert ea.debug_status(p, n, w, ws) == (ea.STATUS_BAD_SCORE if bad else 0)
+
+
+@pytest.mark.parametrize("kind", ["spread", "ties"])
+@pytest.mark.parametrize("blocks", [1024, 1025, 2049])
+def test_select_more_blocks_than_one_sweep_of_the_counts(blocks, kind):
+    """Heads of so many 4096-score blocks that a workgroup adds up the counts in front of it in more than one
+    sweep (four words per thread), the last block a single score: exactly the stable top-k."""
+    n = (blocks - 1) * 4096 + 1
+    rng = np.random.default_rng(blocks)
+    sc = (np.exp(rng.standard_normal((1, 1, n))) if kind == "spread" else
+          rng.integers(0, 5, (1, 1, n)).astype(np.float64)).astype(np.float32)
+    cfg = CONFIGS["c1"].with_(n_q_heads=1, n_kv_heads=1)
+    for n_keep in (n // 3, n - 1):
+        idx = P.run_select(cfg, sc, n_keep)
+        assert np.array_equal(idx.astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
