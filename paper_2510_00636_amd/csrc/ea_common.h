@@ -76,6 +76,17 @@ constexpr uint32_t kStatusBadIndex = 4u;      // ea_compact met an idx list that
 constexpr int kBaselineChunks = 256;          // most row chunks per head in the KeyDiff mean
 constexpr int kCompactTicketStride = 64;      // words per (unit, tensor) at the head of the flag region
 
+// Workgroups of 256 threads of the table launch, which makes one entry per (sample, channel pair) and clears
+// the scratch words of the stages behind it: enough for the entries, and for at most kClearWords words each.
+// The entries alone leave all of the clearing to one workgroup at a window of two samples: 24 sequences x 8 heads x
+// 4608 pairs (5.7 MB to clear) took 442 us with head-adaptive budgets, 402 without, at windows of 2; now 283 and 242.
+// (1024, 4096 and 8192 words per workgroup measure the same.)
+constexpr size_t kClearWords = 2048;
+inline size_t table_blocks(int64_t w, int half, size_t clear_words) {
+  const size_t entries = ((size_t)w * half + 255) / 256, clearing = (clear_words + kClearWords - 1) / kClearWords;
+  return entries > clearing ? entries : clearing;
+}
+
 // fragments per head of the triangular Sigma tiling, and per pass
 inline int frags_per_head(int D) { int njt = D / 32; return njt * (njt + 1); }
 inline int ksteps(int D) { return D / 16; }

@@ -23,8 +23,8 @@ __global__ void k_rope_table(const double* __restrict__ inv_freq, long long q_po
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   // riding along: zero the counters / histograms / flags of the later stages (one launch less)
   for (size_t i = gid; i < clear_words; i += (size_t)gridDim.x * blockDim.x) clear[i] = 0u;
+  if (gid >= (size_t)w * half) return;
   int i = (int)gid;
-  if (i >= w * half) return;
   int s = i / half, c = i - s * half;
   double th = inv_freq[c];
   double sh = sin(0.5 * th);
@@ -1033,8 +1033,7 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
 // ---------------------------------------------------------------------------------------
 hipError_t launch_rope_table(const Dims& d, const double* inv_freq, int64_t q_pos0, int64_t t_next,
                              int w, float2* tab, uint32_t* clear, size_t clear_words, hipStream_t st) {
-  int total = w * d.half;
-  k_rope_table<<<(total + 255) / 256, 256, 0, st>>>(inv_freq, q_pos0, t_next, d.T, w, d.half,
+  k_rope_table<<<(unsigned)table_blocks(w, d.half, clear_words), 256, 0, st>>>(inv_freq, q_pos0, t_next, d.T, w, d.half,
                                                     d.q_is_rotated, tab, clear, clear_words);
   return hipGetLastError();
 }

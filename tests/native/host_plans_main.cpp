@@ -1,5 +1,5 @@
 // Host-only driver: every score plan that a call on some cache layout can take (contiguous, paged, 8-bit)
-// fits the one workspace layout that callers size their buffers by.  Exits 0 when every check holds.
+// fits the one workspace layout that callers size their buffers by, and the table launch covers what it clears.  Exits 0 when every check holds.
 #include <initializer_list>
 #include <stdio.h>
 #include <string.h>
@@ -45,6 +45,15 @@ int main() {
               }
           }
         }
+  // the launch that makes the table covers its entries, and no workgroup clears more than its share
+  for (int half : {32, 64, 128})
+    for (int64_t w : {1, 2, 3, 7, 64, 512, 4096})
+      for (size_t words : {(size_t)0, (size_t)1, (size_t)6144, (size_t)200000, (size_t)1200000, (size_t)40000000}) {
+        const size_t blocks = ea::table_blocks(w, half, words);
+        CHECK(blocks * 256 >= (size_t)w * half, "w %ld half %d", (long)w, half);
+        CHECK(blocks * ea::kClearWords >= words, "w %ld half %d: %zu words, %zu workgroups", (long)w, half, words, blocks);
+        CHECK(blocks <= ((size_t)w * half + 255) / 256 + words / ea::kClearWords + 1, "w %ld half %d words %zu", (long)w, half, words);
+      }
   if (failures) {
     fprintf(stderr, "%d check(s) failed\n", failures);
     return 1;
