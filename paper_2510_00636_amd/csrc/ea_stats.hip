@@ -46,8 +46,8 @@ __global__ void k_rope_table(const double* __restrict__ inv_freq, long long q_po
 // ---------------------------------------------------------------------------------------
 // Sigma is symmetric, so only its 32 x 32 tiles on and above the diagonal are computed (3 of 4 at
 // d = 64, 10 of 16 at d = 128, 36 of 64 at d = 256) and every tile above the diagonal is stored
-// twice, once transposed.  A head's tiles are dealt to kStatsParts<D> workgroups (1 / 2 / 4), each
-// of which reads the window ONCE, in chunks of up to 64 samples: every thread issues all its
+// twice, once transposed.  A head's tiles are dealt to StatsTiling<D>::PARTS workgroups (1 / 2 / 4), each
+// of which reads the window ONCE, in chunks of up to 64 or 32 samples: every thread issues all its
 // 16-byte query loads and table loads of a chunk together (one memory latency per chunk instead
 // of one per sample; the next chunk's loads go out before the current chunk's arithmetic), maps
 // them to u~, subtracts the head's first sample u~_0 and writes the result to LDS; the four
@@ -62,7 +62,10 @@ __global__ void k_rope_table(const double* __restrict__ inv_freq, long long q_po
 // items, all of one channel group) and combined in a fixed order, so results are reproducible.
 // The fp32 matrix-core work is what bounds the kernel for long windows (64 cycles per pair of
 // samples and tile): the triangle and the even deal over workgroups are what keep it short.
-constexpr int kStatsWC = 64;    // samples per LDS chunk
+
+// fp32 windows: samples per LDS chunk.  A thread keeps its share of the next chunk in registers, 32 of them per item of
+// 16 channels: with chunks of 64 samples that is 64 at d = 128 and 128 at d = 256, where a CU then holds one workgroup.
+constexpr int stats_f32_chunk(int D) { return D == 64 ? 64 : 32; }
 template <int D, int PARTS_ = 0> struct StatsTiling {
   static constexpr int NCT = D / 32;                       // 32-column tiles across Sigma
   static constexpr int NT = NCT * (NCT + 1) / 2;           // tiles on and above the diagonal
@@ -157,35 +160,37 @@ __device__ __forceinline__ void stats_rotate(bool round_txqb, float2 t, float qa
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 
-// Register budget: four workgroups per CU at d = 64, two at 128, one at 256, the most that the operands of a
-// matrix step and of the one after it leave without spills: a kernel that needs scratch memory costs some
-// 10 us more per launch when several streams are in use.  Reading operands under "inside the window" and "my
-// tile" and waiting for each pair bounded it: 28 heads, d = 128, w = 200 26 -> 16 us, 128 heads, w = 512
-// 61 -> 31, 16 heads, d = 256, w = 200 41 -> 28.
+// Register budget: four workgroups per CU at d = 64, two at d = 256, three at 128 (137 registers), without spills: a
+// kernel that needs scratch memory costs some 10 us more per launch when several streams are in use.  Reading
+// operands under "inside the window" and "my tile" and waiting for each pair bounded it (28 heads, d = 128,
+// w = 200 29 us).  With the operands requested a step ahead and chunks of 64 samples a long window of few heads
+// took 18, but at d = 256 one workgroup per CU was left (200 heads x 64 samples 54 -> 59 us, 800 x 16 112 -> 132) and
+// short windows of very many heads lost at d = 128 (2000 x 16: 64 -> 70).  Chunks of 32: 16.9, 42, 90 and 57.
 template <int D, bool BF16>
-__global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 2 : 1)) void k_stats(const void* __restrict__ q_win, int w, int layout,
+__global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __restrict__ q_win, int w, int layout,
                                                int ddof, const float2* __restrict__ tab,
                                                float* __restrict__ mu, float* __restrict__ sigma) {
   constexpr int HALF = D / 2, G8 = HALF / 8;          // groups of 8 channel pairs per sample
-  constexpr int ITEMS = kStatsWC * G8 / 256;          // (sample, group) items per thread and chunk
+  constexpr int WC = stats_f32_chunk(D);
+  constexpr int ITEMS = WC * G8 / 256;          // (sample, group) items per thread and chunk
   typedef StatsTiling<D> TL;
   constexpr int NCT = TL::NCT, TPW = TL::SLOTS;
   static_assert(256 % G8 == 0 && ITEMS >= 1, "one channel group per thread");
   extern __shared__ __align__(16) float s_dyn[];
-  float* s_u = s_dyn;                                 // [kStatsWC][D]   x = u~ - u~_0 of the chunk
-  float* s_part = s_dyn + kStatsWC * D;               // [4][D]          column sums per wavefront
+  float* s_u = s_dyn;                                 // [WC][D]   x = u~ - u~_0 of the chunk
+  float* s_part = s_dyn + WC * D;               // [4][D]          column sums per wavefront
   float* s_shift = s_part + 4 * D;                    // [D]             u~_0
   float* s_xbar = s_shift + D;                        // [D]             (1/w) sum_s x_s
   const int head = blockIdx.x, part = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);        // wave-uniform: tile numbers stay scalar
   const size_t qbase = (size_t)head * w * D;
-  const int nchunks = (w + kStatsWC - 1) / kStatsWC;
+  const int nchunks = (w + WC - 1) / WC;
   const int g = tid % G8;                             // the channel group of all this thread's items
 
   // the first chunk's loads go out before anything waits on memory
   StatsRaw<BF16> raw[ITEMS];
   auto load_chunk = [&](int ch) __attribute__((always_inline)) {
-    const int s0 = ch * kStatsWC, ns = min(kStatsWC, w - s0);
+    const int s0 = ch * WC, ns = min(WC, w - s0);
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
       const int sl = (tid + it * 256) / G8;
@@ -241,7 +246,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 2 : 1)) void k_stats
     for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
 
   for (int ch = 0; ch < nchunks; ++ch) {
-    const int s0 = ch * kStatsWC, ns = min(kStatsWC, w - s0);
+    const int s0 = ch * WC, ns = min(WC, w - s0);
     if (ch > 0) __syncthreads();                      // the previous chunk has been consumed
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
@@ -269,7 +274,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 2 : 1)) void k_stats
 #pragma unroll
           for (int e = 0; e < 4; ++e) pi[e] = make_float4(xa[2 * e], xb[2 * e], xa[2 * e + 1], xb[2 * e + 1]);
         }
-      } else {                                        // past the window's end: zeros
+      } else if (sl < ((ns + 15) & ~15)) {            // past the window's end, as far as a step of eight pairs goes: zeros
         float4* z = reinterpret_cast<float4*>(s_u + sl * D + 16 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) z[e] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -318,15 +323,15 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 2 : 1)) void k_stats
     };
     read_step(0, 0);
     for (int sp = 0; sp < npair; sp += 2 * PS) {
-      read_step(min(sp + PS, kStatsWC / 2 - PS), 1);
+      read_step(min(sp + PS, WC / 2 - PS), 1);
       multiply_step(0);
-      read_step(min(sp + 2 * PS, kStatsWC / 2 - PS), 0);
+      if (WC > 4 * PS) read_step(min(sp + 2 * PS, WC / 2 - PS), 0);
       if (sp + PS < npair) multiply_step(1);
     }
   }
   if (TL::SHARED > 0) {
     // the four partial tiles of every shared tile, added in wavefront order by wavefront 0
-    static_assert(TL::SHARED * 4 * 16 * 64 <= kStatsWC * D, "partial tiles fit in the chunk buffer");
+    static_assert(TL::SHARED * 4 * 16 * 64 <= WC * D, "partial tiles fit in the chunk buffer");
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < TL::SHARED; ++r)
@@ -1042,7 +1047,7 @@ template <int D, bool BF16>
 static hipError_t launch_stats_one(const Dims& d, const void* q_win, int w, const float2* tab,
                                    float* mu, float* sigma, hipStream_t st) {
   auto kern = k_stats<D, BF16>;
-  const size_t lds = (size_t)(kStatsWC * D + 6 * D) * sizeof(float);
+  const size_t lds = (size_t)(stats_f32_chunk(D) * D + 6 * D) * sizeof(float);
   static LdsOptIn opt;                    // one per kernel instance
   hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
