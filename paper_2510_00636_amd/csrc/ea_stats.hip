@@ -145,17 +145,15 @@ __device__ __forceinline__ void stats_unpack_item(const StatsRaw<BF16>& raw, int
     tb[2 * e + 1] = make_float2(raw.t[e].z, raw.t[e].w);
   }
 }
-// u~ - shift: the 2x2 block of the table applied to one pair.  Which of the two products of a sum is rounded on
-// its own is spelled out (of the second: t.x qb, or t.y qa), and nothing else is contracted, so that the bits
-// of the statistics, and with them every score, do not hang on what the compiler makes of the code around it.
-__device__ __forceinline__ void stats_rotate(bool round_txqb, float2 t, float qa, float qb, float sha, float shb,
-                                             float& xa, float& xb) {
+// u~ - shift: the 2x2 block of the table applied to one pair.  The products with t.y are rounded on their own, those
+// with t.x are not, and nothing else is contracted: written out, so that the bits of the statistics, and with them
+// every score, do not hang on what the compiler makes of the code around it, and one rule for every channel,
+// layout and instance, so that the first sample less the shift, which is the first sample, is zero.
+__device__ __forceinline__ void stats_rotate(float2 t, float qa, float qb, float sha, float shb, float& xa, float& xb) {
 #pragma clang fp contract(off)
-  const float pa = t.y * qb;
-  const float pb = round_txqb ? t.x * qb : t.y * qa;
-  const float ua = fmaf(t.x, qa, -pa), ub = round_txqb ? fmaf(t.y, qa, pb) : fmaf(t.x, qb, pb);
-  xa = ua - sha;
-  xb = ub - shb;
+  const float pa = t.y * qb, pb = t.y * qa;
+  xa = fmaf(t.x, qa, -pa) - sha;
+  xb = fmaf(t.x, qb, pb) - shb;
 }
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
@@ -210,7 +208,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float ua, ub;
-      stats_rotate(true, tb[e], qa[e], qb[e], 0.f, 0.f, ua, ub);
+      stats_rotate(tb[e], qa[e], qb[e], 0.f, 0.f, ua, ub);
       s_shift[stats_ja<D>(layout, g, e)] = ua;
       s_shift[stats_jb<D>(layout, g, e)] = ub;
     }
@@ -257,7 +255,7 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __
         stats_unpack_item<BF16>(raw[it], layout, qa, qb, tb);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          stats_rotate(D >= 128, tb[e], qa[e], qb[e], s_shift[stats_ja<D>(layout, g, e)],
+          stats_rotate(tb[e], qa[e], qb[e], s_shift[stats_ja<D>(layout, g, e)],
                        s_shift[stats_jb<D>(layout, g, e)], xa[e], xb[e]);
           suma[e] += xa[e];
           sumb[e] += xb[e];
@@ -606,7 +604,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float ua, ub;
-      stats_rotate(D == 64 || (D == 128 && (PARTS == 0 || SUMS == 1)), tb[e], qa[e], qb[e], 0.f, 0.f, ua, ub);
+      stats_rotate(tb[e], qa[e], qb[e], 0.f, 0.f, ua, ub);
       s_shift[stats_ja<D>(layout, g, e)] = ua;
       s_shift[stats_jb<D>(layout, g, e)] = ub;
     }
@@ -660,7 +658,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       float xa, xb;
-      stats_rotate(LAYOUT == 0 && D >= 128 && e == 0, tb[e], qa[e], qb[e], sh[e], sh[8 + e], xa, xb);
+      stats_rotate(tb[e], qa[e], qb[e], sh[e], sh[8 + e], xa, xb);
       x[e] = ok ? xa : 0.f;
       x[8 + e] = ok ? xb : 0.f;
     }

@@ -225,3 +225,31 @@ def test_select_more_blocks_than_one_sweep_of_the_counts(blocks, kind):
     for n_keep in (n // 3, n - 1):
         idx = P.run_select(cfg, sc, n_keep)
         assert np.array_equal(idx.astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
+
+
+@pytest.mark.parametrize("dtype,d,many", [("bf16", 64, 8), ("bf16", 128, 8), ("bf16", 128, 400), ("bf16", 256, 8),
+                                          ("f32", 64, 8), ("f32", 128, 8), ("f32", 256, 8)])
+def test_means_do_not_hang_on_layout_or_call_size(dtype, d, many):
+    """One rounding rule for the rotation of every channel, layout and instance: a head's mean has the same
+    bits in a call of 8 heads and of many, and when its channels come interleaved instead of half-split
+    (the same pairs in the same order, sums over the same samples)."""
+    import torch
+    rng = np.random.default_rng(d + many)
+    w, few = 70, 8
+    q = rng.standard_normal((1, many, w, d)) * 3.0 + rng.standard_normal((1, many, 1, d))
+    q = torch.from_numpy(q.astype(np.float32)).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    half_to_inter = np.arange(d).reshape(2, d // 2).T.reshape(-1)      # interleaved channel 2c + b = half-split b d/2 + c
+    inv = P.to_dev(1e4 ** (-np.arange(0, d, 2, dtype=np.float64) / d))
+
+    def means(x, layout):
+        heads = x.shape[1]
+        cfg = CONFIGS["c2"].with_(dtype=dtype, head_dim=d, n_q_heads=heads, n_kv_heads=heads)
+        p = P.params_for(cfg, rope_layout=layout)
+        mu = torch.empty(1, heads, d, device="cuda")
+        sigma = torch.empty(1, heads, d, d, device="cuda")
+        ea.query_stats(p, x.contiguous(), w, 4000, inv, 4000 + w, mu, sigma, P.workspace(p, 1, w))
+        torch.cuda.synchronize()
+        return mu.cpu().numpy()
+    plain = means(q[:, :few], 0)
+    assert np.array_equal(means(q, 0)[:, :few], plain)
+    assert np.array_equal(means(q[..., half_to_inter], 1)[:, :few], plain[..., half_to_inter])
