@@ -543,10 +543,8 @@ constexpr int stats_split_chunk(int D) { return D >= 256 ? 32 : 64; }
 // row operand once for two tiles, took 104 us to 94; keeping Sigma on the chip took the 64 MB it wrote, half of
 // them in 4-byte pieces, and the 27 us of k_prep_frags off (whole pass 422 -> 396 us).
 // FUSED (d <= 128, one workgroup per head): Sigma stays in LDS and leaves as the fragments that k_prep_frags
-// would have made of it, bit for bit.  SUMS says which two of a d = 128 head's ten tiles are added up
-// from four partial sums (the others are one sum): 0 the last of all, 1 the last of each half, as a
-// head split over two workgroups has them.
-template <int D, int LAYOUT, int PARTS = 0, bool FUSED = false, int SUMS = 0>
+// would have made of it, bit for bit.
+template <int D, int LAYOUT, int PARTS = 0, bool FUSED = false>
 __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2)) void k_stats_split(const void* __restrict__ q_win, int w,
                                                                          int ddof,
                                                                          const float2* __restrict__ tab,
@@ -616,13 +614,16 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 
   const int r32 = lane & 31, kg = lane >> 5;
   int t_rb[TPW], t_ct[TPW];
-  // a whole head at d = 128: two tiles per wavefront, next to each other in the triangle's order (they mostly
-  // share their rows: the operand is read once), and the two shared ones
+  // A whole head at d = 128: two tiles per wavefront, next to each other in the triangle's order and of one row of
+  // tiles (the row operand is read once for both), and as shared ones the tiles that are left, numbers 4 and 9:
+  // those that a head split over two workgroups adds up from partial sums as well, so that Sigma has the same
+  // bits either way.  (With the last two tiles shared, one pair of eight had two rows, and the second form of
+  // the loop that it needed took 8 to 10 registers more than there are.)
   constexpr bool kPairs = D == 128 && PARTS == 1;
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
     int local = t < TL::WHOLE ? (kPairs ? 2 * wave + t : wave + 4 * t) : 4 * TL::WHOLE + (t - TL::WHOLE);
-    if constexpr (SUMS == 1) local = t < TL::WHOLE ? (local < 4 ? local : local + 1) : t == TL::WHOLE ? 4 : 9;
+    if constexpr (kPairs) local = t < TL::WHOLE ? (local < 4 ? local : local + 1) : t == TL::WHOLE ? 4 : 9;
     int idx = part * TL::TP + local, rb = 0;
     const bool ok = local < TL::TP && idx < TL::NT;
     if (!ok) idx = 0;
@@ -751,29 +752,22 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
       acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[t], 0, 0, 0);
     };
     if constexpr (kPairs) {
-      // (tiles 6 and 7 of the plain order, (1, 3) and (2, 2), are the one pair that shares no rows)
-      if (SUMS == 1 || wave != 3) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const int oa = operand_at(t_rb[0], ks), ob = operand_at(t_ct[0], ks), oc = operand_at(t_ct[1], ks);
-          const stats_half8 ah = *reinterpret_cast<const stats_half8*>(s_hi + oa);
-          const stats_half8 al = *reinterpret_cast<const stats_half8*>(s_lo + oa);
-          const stats_half8 bh = *reinterpret_cast<const stats_half8*>(s_hi + ob);
-          const stats_half8 bl = *reinterpret_cast<const stats_half8*>(s_lo + ob);
-          const stats_half8 ch2 = *reinterpret_cast<const stats_half8*>(s_hi + oc);
-          const stats_half8 cl2 = *reinterpret_cast<const stats_half8*>(s_lo + oc);
-          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, ch2, acc[1], 0, 0, 0);
-          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, cl2, acc[1], 0, 0, 0);
-          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, ch2, acc[1], 0, 0, 0);
-        }
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-          for (int t = 0; t < TL::WHOLE; ++t) step(t, ks);
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks > 0 && ks * 16 >= ns) break;           // a window's last samples fill no chunk
+        const int oa = operand_at(t_rb[0], ks), ob = operand_at(t_ct[0], ks), oc = operand_at(t_ct[1], ks);
+        const stats_half8 ah = *reinterpret_cast<const stats_half8*>(s_hi + oa);
+        const stats_half8 al = *reinterpret_cast<const stats_half8*>(s_lo + oa);
+        const stats_half8 bh = *reinterpret_cast<const stats_half8*>(s_hi + ob);
+        const stats_half8 bl = *reinterpret_cast<const stats_half8*>(s_lo + ob);
+        const stats_half8 ch2 = *reinterpret_cast<const stats_half8*>(s_hi + oc);
+        const stats_half8 cl2 = *reinterpret_cast<const stats_half8*>(s_lo + oc);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, ch2, acc[1], 0, 0, 0);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, cl2, acc[1], 0, 0, 0);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, ch2, acc[1], 0, 0, 0);
       }
     } else {
 #pragma unroll
@@ -1097,10 +1091,10 @@ hipError_t launch_stats(const Dims& d, const void* q_win, int w, const float2* t
   return launch_stats_one<256, false>(d, q_win, w, tab, mu, sigma, st);
 }
 
-template <int D, int LAYOUT, int PARTS, int SUMS>
+template <int D, int LAYOUT, int PARTS>
 static hipError_t launch_stats_frags_one(const Dims& d, const void* q_win, int w, const float2* tab, const FragsOut& fo,
                                          hipStream_t st) {
-  auto kern = k_stats_split<D, LAYOUT, PARTS, true, SUMS>;
+  auto kern = k_stats_split<D, LAYOUT, PARTS, true>;
   const size_t planes = (size_t)2 * D * (stats_split_chunk(D) + 8) * sizeof(_Float16);
   const size_t sig = (size_t)D * stats_sigma_pitch(D) * sizeof(float);
   const size_t lds = (planes > sig ? planes : sig) + (size_t)(6 * D + 4) * sizeof(float);
@@ -1113,9 +1107,8 @@ static hipError_t launch_stats_frags_one(const Dims& d, const void* q_win, int w
 template <int LAYOUT>
 static hipError_t launch_stats_frags_layout(const Dims& d, const void* q_win, int w, const float2* tab, const FragsOut& fo,
                                             hipStream_t st) {
-  if (d.D == 64) return launch_stats_frags_one<64, LAYOUT, 0, 0>(d, q_win, w, tab, fo, st);
-  return d.qheads() >= kStatsWholeHeadMin ? launch_stats_frags_one<128, LAYOUT, 1, 0>(d, q_win, w, tab, fo, st)
-                                          : launch_stats_frags_one<128, LAYOUT, 1, 1>(d, q_win, w, tab, fo, st);
+  return d.D == 64 ? launch_stats_frags_one<64, LAYOUT, 0>(d, q_win, w, tab, fo, st)
+                   : launch_stats_frags_one<128, LAYOUT, 1>(d, q_win, w, tab, fo, st);
 }
 hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_win, int w, const float2* tab,
                               uint4* frags, float* post, hipStream_t st) {

@@ -229,10 +229,10 @@ def test_select_more_blocks_than_one_sweep_of_the_counts(blocks, kind):
 
 @pytest.mark.parametrize("dtype,d,many", [("bf16", 64, 8), ("bf16", 128, 8), ("bf16", 128, 400), ("bf16", 256, 8),
                                           ("f32", 64, 8), ("f32", 128, 8), ("f32", 256, 8)])
-def test_means_do_not_hang_on_layout_or_call_size(dtype, d, many):
-    """One rounding rule for the rotation of every channel, layout and instance: a head's mean has the same
-    bits in a call of 8 heads and of many, and when its channels come interleaved instead of half-split
-    (the same pairs in the same order, sums over the same samples)."""
+def test_statistics_do_not_hang_on_layout_or_call_size(dtype, d, many):
+    """A head's statistics have the same bits in a call of 8 heads (at d = 128 two workgroups a head) and of
+    many (one), and its mean also when the channels come interleaved instead of half-split: one rounding
+    rule for the rotation, and the same sums in the same order."""
     import torch
     rng = np.random.default_rng(d + many)
     w, few = 70, 8
@@ -241,7 +241,7 @@ def test_means_do_not_hang_on_layout_or_call_size(dtype, d, many):
     half_to_inter = np.arange(d).reshape(2, d // 2).T.reshape(-1)      # interleaved channel 2c + b = half-split b d/2 + c
     inv = P.to_dev(1e4 ** (-np.arange(0, d, 2, dtype=np.float64) / d))
 
-    def means(x, layout):
+    def stats(x, layout):
         heads = x.shape[1]
         cfg = CONFIGS["c2"].with_(dtype=dtype, head_dim=d, n_q_heads=heads, n_kv_heads=heads)
         p = P.params_for(cfg, rope_layout=layout)
@@ -249,7 +249,8 @@ def test_means_do_not_hang_on_layout_or_call_size(dtype, d, many):
         sigma = torch.empty(1, heads, d, d, device="cuda")
         ea.query_stats(p, x.contiguous(), w, 4000, inv, 4000 + w, mu, sigma, P.workspace(p, 1, w))
         torch.cuda.synchronize()
-        return mu.cpu().numpy()
-    plain = means(q[:, :few], 0)
-    assert np.array_equal(means(q, 0)[:, :few], plain)
-    assert np.array_equal(means(q[..., half_to_inter], 1)[:, :few], plain[..., half_to_inter])
+        return mu.cpu().numpy()[:, :few], sigma.cpu().numpy()[:, :few]
+    plain, sigma = stats(q[:, :few], 0)
+    mu_many, sigma_many = stats(q, 0)
+    assert np.array_equal(mu_many, plain) and np.array_equal(sigma_many, sigma)
+    assert np.array_equal(stats(q[..., half_to_inter], 1)[0], plain[..., half_to_inter])
