@@ -97,21 +97,26 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     s.lds_bytes = (size_t)2 * NF * 1024 + (size_t)s.NW * 4096;
   }
   // A CU holds one workgroup.  Up to half as many units as CUs: every unit gets its share of the CUs,
-  // rounded down.  More (unit, pass) jobs than CUs that leave the last round of CUs to 85 % full or less:
-  // three spare workgroups per job are launched behind the first ones, and a CU whose head is done
-  // takes one of them and joins a head that still has tiles (tickets deal them).  query_stats + score in
-  // a row at d = 128, without and with: 304 units, G = 4, n = 4608 319 and 265 us; 384 units, G = 5,
-  // 421 and 382; 160 units in two passes 277 and 234.  With fewer jobs than CUs it does not pay at
-  // d <= 128: 192 CUs at the clock the chip then grants do what 256 do (192 units 203 and 200 us, the
-  // whole decode-time pass 415 and 420); at d = 256, one wavefront per SIMD, it does (192 units x 4000
-  // keys: 339 and 304 us).  Nor does it on heads of under 1024 keys.
+  // rounded down.  Beyond that one workgroup per (unit, pass) job, and where these leave the last round of
+  // CUs to 85 % full or less, spare ones behind them, three per job (two while the units do not exceed the CUs:
+  // fewer CUs are idle then): a CU whose head is done takes one of them and joins a head that still has
+  // tiles (tickets deal them).  query_stats + score in a row at d = 128, without and with: 304 units, G = 4,
+  // n = 4608 319 and 265 us; 384 units, G = 5, 421 and 382; 160 units in two passes 277 and 234.  Not on heads of
+  // under 1024 keys.  (From seven rounds on the last one is always more than 85 % of the whole.)
+  // With fewer jobs than CUs it does not pay at d <= 128: 192 CUs at the clock the chip then grants do what 256
+  // do (192 units 203 and 200 us, the whole decode-time pass 415 and 420).  At d = 256, one wavefront per SIMD, it
+  // does once the head is long enough for the fragments that a spare workgroup loads first, 72 KiB per query
+  // head, the longer the fewer CUs are idle.  score, two query heads per pass, without and with: 160 units x
+  // 1024 keys 94.4 and 98.5 us, x 1500 119 and 118, x 4000 242 and 211; 200 units x 1500 133 and 144, x 4000 261 and
+  // 260, x 9000 512 and 493; one query head, 200 units x 1024 72.2 and 74.1, x 2000 118 and 113.
   const int64_t most = ((n + 31) / 32 + s.NW - 1) / s.NW;       // every wavefront with a tile at least
   const int64_t jobs = (int64_t)d.units() * s.passes;
   int64_t wgs = num_cu / d.units();
   if (wgs > 1024) wgs = 1024;
   if (wgs < 2) {
     const int64_t rounds = (jobs + num_cu - 1) / num_cu;
-    s.spare = rounds <= 8 && jobs * 20 < rounds * num_cu * 17 && n >= 1024 && (jobs > num_cu || d.D == 256);
+    const int64_t least = jobs > num_cu ? 1024 : s.GH * (jobs * 4 > (int64_t)num_cu * 3 ? 2000 : 640);
+    s.spare = jobs * 20 < rounds * num_cu * 17 && n >= 1024 && n >= least && (jobs > num_cu || d.D == 256);
     wgs = !s.spare ? 1 : wgs == 1 ? 3 : 4;
   }
   if (wgs > most) wgs = most;

@@ -45,6 +45,25 @@ int main() {
               }
           }
         }
+  // spare workgroups: where the last round of CUs is short, and at d = 256 with fewer jobs than CUs only on
+  // heads long enough for the fragments that a spare workgroup loads
+  struct { int d, G, units; int64_t n; int spare, nchunk; } plan[] = {
+      {128, 4, 300, 1024, 1, 4}, {128, 4, 300, 1000, 0, 1}, {128, 4, 436, 2000, 0, 1}, {128, 7, 140, 2000, 1, 3},
+      {128, 4, 200, 8000, 0, 1}, {128, 4, 128, 8000, 0, 2}, {128, 4, 1800, 2000, 0, 1},
+      {256, 2, 160, 1024, 0, 1}, {256, 2, 160, 1500, 1, 3}, {256, 2, 200, 1500, 0, 1}, {256, 2, 200, 3999, 0, 1},
+      {256, 2, 200, 4000, 1, 3}, {256, 1, 200, 1999, 0, 1}, {256, 1, 200, 2000, 1, 3}, {256, 1, 160, 1024, 1, 3},
+      {256, 2, 260, 1024, 1, 4}, {256, 4, 140, 1024, 1, 3}, {256, 2, 240, 9000, 0, 1}};
+  for (const auto& c : plan) {
+    ea_params p;
+    memset(&p, 0, sizeof p);
+    p.batch = 1; p.n_q_heads = c.G * c.units; p.n_kv_heads = c.units; p.head_dim = c.d; p.dtype = EA_BF16;
+    p.q_is_rotated = 1; p.horizon_T = 512;
+    ea::Dims dims;
+    CHECK(ea::check_params(&p, &dims) == EA_OK, "d %d G %d", c.d, c.G);
+    const ea::ScorePlan sp = ea::make_score_plan(dims, c.n, 256);
+    CHECK(sp.spare == c.spare && sp.nchunk == c.nchunk, "d %d G %d units %d n %ld: spare %d, %d workgroups", c.d, c.G, c.units,
+          (long)c.n, sp.spare, sp.nchunk);
+  }
   // the launch that makes the table covers its entries, and no workgroup clears more than its share
   for (int half : {32, 64, 128})
     for (int64_t w : {1, 2, 3, 7, 64, 512, 4096})

@@ -52,7 +52,9 @@ def test_fp32_scores_tile_edges(d, hq, hkv, n):
     (128, 5, 1, 260, 1030),      # a second round of four units
     (128, 7, 1, 150, 1030),      # the same in two passes
     (64, 2, 1, 300, 1500),       # more units than CUs
-    (256, 2, 1, 140, 1030),
+    (256, 2, 1, 140, 1030),      # too short for what a spare workgroup loads at d = 256
+    (256, 2, 1, 140, 1290),      # fewer jobs than CUs
+    (256, 4, 1, 130, 1030),
     (128, 4, 1, 150, 1000),      # too short for spare workgroups
 ])
 def test_scores_with_spare_workgroups(d, hq, hkv, batch, n):
