@@ -58,10 +58,6 @@ __device__ __forceinline__ float row_sum16(float x) {
 }
 
 constexpr int kBaseRowsPerWg = 128;     // 16 rows at a time, 8 rounds
-// KeyDiff: how many workgroups its passes are cut into, as far as the heads are long enough.  The
-// first pass is bound by the loads a CU keeps in flight: 8 heads x 65536 rows at d = 128 took 121 us in
-// both passes with 4096 rows per workgroup of the first (128 workgroups, 1.6 TB/s), 56 us with 512.
-constexpr int kKeydiffWgs = 1024;
 constexpr int kKeydiffMaxRows = 1024;   // second pass: every workgroup adds up the head's partial sums, 512
                                         // bytes per chunk at d = 128, which this many rows pay for
 
@@ -136,7 +132,8 @@ __global__ __launch_bounds__(256) void k_keydiff_partial(const void* __restrict_
   }
 }
 
-// KeyDiff pass 2: the anchor a (partials added in chunk order), then 1 - cos(k_i, a) per row
+// KeyDiff pass 2: the anchor a (every (1024 / D)-th chunk's partial sums by one lane, then the lanes', each in
+// increasing order), then 1 - cos(k_i, a) per row
 template <int D, bool BF16>
 __global__ __launch_bounds__(256) void k_keydiff_score(const void* __restrict__ k, long long n,
                                                        long long n_cap, int units, int nchunk, int rows_per_wg,
@@ -157,13 +154,17 @@ __global__ __launch_bounds__(256) void k_keydiff_score(const void* __restrict__ 
     const int cg = tid % CG, sh = tid / CG;
     const float4* pp = reinterpret_cast<const float4*>(partial + (size_t)unit * nchunk * D) + cg;
     float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int q0 = sh; q0 < nchunk; q0 += 8 * SH) {
-      float4 x[8];
+    if (nchunk <= SH) {                     // one chunk per lane, or none
+      if (sh < nchunk) t = pp[(size_t)sh * CG];
+    } else {
+      for (int q0 = sh; q0 < nchunk; q0 += 8 * SH) {
+        float4 x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = pp[(size_t)min(q0 + u * SH, nchunk - 1) * CG];
+        for (int u = 0; u < 8; ++u) x[u] = pp[(size_t)min(q0 + u * SH, nchunk - 1) * CG];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (q0 + u * SH < nchunk) { t.x += x[u].x; t.y += x[u].y; t.z += x[u].z; t.w += x[u].w; }
+        for (int u = 0; u < 8; ++u)
+          if (q0 + u * SH < nchunk) { t.x += x[u].x; t.y += x[u].y; t.z += x[u].z; t.w += x[u].w; }
+      }
     }
     s_sum[sh][cg] = t;
   }
@@ -224,15 +225,11 @@ static hipError_t launch_baseline_t(const Dims& d, int kind, const void* k, int6
   if (kind == EA_SCORER_KNORM) {
     k_knorm<D, BF16><<<nblk * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), scores);
   } else {
-    // both passes: rows per workgroup in multiples of 128 (16 rows at a time, eight loads in flight)
-    const int64_t spread = (n * d.units() / kKeydiffWgs + 127) / 128 * 128;
-    int64_t rows = spread < 128 ? 128 : spread;
-    const int64_t least = ((n + kBaselineChunks - 1) / kBaselineChunks + 127) / 128 * 128;   // the scratch holds that many chunks
-    if (rows < least) rows = least;
-    if (rows > n + 127) rows = n + 127;                     // (one chunk; keeps the count an int)
+    const int rows = keydiff_rows(n, d.units());
     const int nchunk = (int)((n + rows - 1) / rows);
-    k_keydiff_partial<D, BF16><<<nchunk * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), (int)rows, scratch);
-    const int rows2 = spread < 128 ? 128 : spread > kKeydiffMaxRows ? kKeydiffMaxRows : (int)spread;
+    k_keydiff_partial<D, BF16><<<nchunk * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), rows, scratch);
+    const int64_t spread = keydiff_spread(n, d.units());
+    const int rows2 = (int)(spread < kKeydiffMaxRows ? spread : kKeydiffMaxRows);
     const unsigned nblk2 = (unsigned)((n + rows2 - 1) / rows2);
     k_keydiff_score<D, BF16><<<nblk2 * d.units(), 256, 0, st>>>(k, n, n_cap, d.units(), nchunk, rows2, scratch, scores);
   }

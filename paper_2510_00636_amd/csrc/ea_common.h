@@ -87,6 +87,28 @@ inline size_t table_blocks(int64_t w, int half, size_t clear_words) {
   return entries > clearing ? entries : clearing;
 }
 
+// KeyDiff, rows per workgroup in multiples of 128 (16 rows at a time, eight loads in flight).  Its passes are cut
+// into about 1024 workgroups, as far as the heads are long enough: the first one is bound by the loads a CU
+// keeps in flight (8 heads x 65536 rows at d = 128: 121 us in both passes with 4096 rows per workgroup of the
+// first, 1.6 TB/s, 56 with 512).
+constexpr int64_t kKeydiffWgs = 1024;
+inline int64_t keydiff_spread(int64_t n, int64_t units) {
+  const int64_t rows = (n * units / kKeydiffWgs + 127) / 128 * 128;
+  return rows < 128 ? 128 : rows;
+}
+// The first pass: stretches of up to 4096 rows where they are 600 workgroups or more already (300 heads x 5000 rows,
+// two of 2500 each or four of 1280: 134 and 141 us for fp32 keys at d = 64; 700 x 4000, one or two of 2048: 280 and 289;
+// 256 x 32768, eight of 4096 or four of 8192: 819 and 834; but 500 x 2500, one or two of 1280: 116 and 110, 192 x 4608,
+// two or five: 88 and 81).  No more chunks than the scratch holds, and a head's chunks of one size but for what
+// rounding to 128 rows leaves.
+inline int keydiff_rows(int64_t n, int64_t units) {
+  int64_t rows = units * ((n + 4095) / 4096) >= 600 ? 4096 : keydiff_spread(n, units);
+  const int64_t least = ((n + kBaselineChunks - 1) / kBaselineChunks + 127) / 128 * 128;
+  if (rows < least) rows = least;
+  const int64_t nchunk = (n + rows - 1) / rows;
+  return (int)(((n + nchunk - 1) / nchunk + 127) / 128 * 128);
+}
+
 // fragments per head of the triangular Sigma tiling, and per pass
 inline int frags_per_head(int D) { int njt = D / 32; return njt * (njt + 1); }
 inline int ksteps(int D) { return D / 16; }

@@ -64,6 +64,16 @@ int main() {
     CHECK(sp.spare == c.spare && sp.nchunk == c.nchunk, "d %d G %d units %d n %ld: spare %d, %d workgroups", c.d, c.G, c.units,
           (long)c.n, sp.spare, sp.nchunk);
   }
+  // KeyDiff's first pass: chunks that the scratch holds, of one size but for what 128 rows round
+  for (int64_t units : {1, 2, 8, 40, 300, 960, 5000, 1 << 20})
+    for (int64_t n : {(int64_t)1, (int64_t)127, (int64_t)128, (int64_t)129, (int64_t)600, (int64_t)4608, (int64_t)5000, (int64_t)9000,
+                      (int64_t)32768, (int64_t)131072, ((int64_t)1 << 20) + 1, (int64_t)1 << 26}) {
+      const int64_t rows = ea::keydiff_rows(n, units), nchunk = (n + rows - 1) / rows;
+      CHECK(rows >= 128 && rows % 128 == 0 && nchunk <= ea::kBaselineChunks, "units %ld n %ld: %ld rows", (long)units, (long)n, (long)rows);
+      CHECK(rows <= 4096 || n > 4096 * (ea::kBaselineChunks - 1), "units %ld n %ld: %ld rows", (long)units, (long)n, (long)rows);
+      CHECK(rows <= (n + nchunk - 1) / nchunk + 127, "units %ld n %ld: %ld rows in the first chunk, %ld in the last", (long)units,
+            (long)n, (long)rows, (long)(n - (nchunk - 1) * rows));
+    }
   // the launch that makes the table covers its entries, and no workgroup clears more than its share
   for (int half : {32, 64, 128})
     for (int64_t w : {1, 2, 3, 7, 64, 512, 4096})
