@@ -256,3 +256,91 @@ def test_statistics_do_not_hang_on_layout_or_call_size(dtype, d, many):
     mu_many, sigma_many = stats(q, 0)
     assert np.array_equal(mu_many, plain) and np.array_equal(sigma_many, sigma)
     assert np.array_equal(stats(q[..., half_to_inter], 1)[0], plain[..., half_to_inter])
+
+
+@pytest.mark.parametrize("form,d,hq,hkv,batch,w", [
+    (form, *shape) for form in ("unordered", "paged", "fp8", "adaptive")
+    for shape in ((64, 5, 1, 3, 17), (128, 4, 1, 47, 64), (128, 4, 1, 48, 65), (128, 5, 1, 77, 2))
+    if not (form == "fp8" and shape[0] == 64)])                    # (8-bit rows have 128 channels or more)
+def test_fused_statistics_behind_every_compress_call(form, d, hq, hkv, batch, w):
+    """The other compress calls, on either side of the number of heads from which the statistics kernel writes
+    the score kernel's operands: their scores are those of query_stats followed by the score call of the
+    same cache layout, bit for bit."""
+    import torch
+    from ea_inputs import make_block_pools, quantize_fp8
+    n, n_keep = 300, 120
+    cfg = CONFIGS["c2"].with_(head_dim=d, n_q_heads=hq, n_kv_heads=hkv, batch=batch)
+    lay = make_layer(cfg, n=n, window=w)
+    p = P.params_for(cfg)
+    ws = P.workspace(p, n, w)
+    q, k, v, inv = (P.to_dev(lay[x]) for x in ("q_win", "k", "v", "inv_freq"))
+    win = (q, w, lay["q_pos0"], inv, lay["t_next"])
+    mu = torch.empty(batch, hq, d, device="cuda")
+    sigma = torch.empty(batch, hq, d, d, device="cuda")
+    want, got = (torch.empty(batch, hkv, n, device="cuda") for _ in range(2))
+    idx = torch.empty(batch, hkv, n, dtype=torch.int32, device="cuda")
+    lengths = torch.empty(batch, hkv, dtype=torch.int32, device="cuda")
+    ea.query_stats(p, *win, mu, sigma, ws)
+    if form == "paged":
+        kp, vp, tab, nb = make_block_pools(lay["k"], lay["v"], 32, 3)
+        k, v, tabd = P.to_dev(kp), P.to_dev(vp), torch.from_numpy(tab).cuda()
+        pg = ea.make_paged(tabd, 32, nb)
+        ea.score_paged(p, k, v, pg, n, mu, sigma, want, ws)
+        ea.compress_layer_paged(p, *win, k, v, pg, n, n_keep, 0, got, None, None, ws)
+    elif form == "fp8":
+        k8, ks = quantize_fp8(widen(lay["k"]))
+        v8, vs = quantize_fp8(widen(lay["v"]))
+        k, v, ks, vs = (torch.from_numpy(x).cuda() for x in (k8, v8, ks, vs))
+        ea.score_fp8(p, k, v, ks, vs, n, n, mu, sigma, want, ws)
+        ea.compress_layer_fp8(p, *win, k, v, ks, vs, n, n, n_keep, 1, got, None, None, ws)
+    else:
+        ea.score(p, k, v, n, n, mu, sigma, want, ws)
+        if form == "unordered":
+            ea.compress_layer_unordered(p, *win, k, v, n, n, n_keep, got, None, None, ws)
+        else:
+            ea.compress_layer_adaptive(p, *win, k, v, n, n, n_keep, 30, got, idx, lengths, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), want.cpu().numpy())
+
+
+@pytest.mark.parametrize("n,w,floor", [(16385, 64, 300), (20481, 2, 300), (20481, 64, 0), (16385, 3, 6000)])
+def test_adaptive_pass_over_long_heads(n, w, floor):
+    """The whole adaptive call where the heads' selection takes several launches: the first digit of the heads'
+    and of the pooled lists counted on the way, everything cleared at the start of the call, also under
+    windows of a few samples (one or two workgroups for the table).  Two passes over different caches on one
+    workspace that starts with rubbish; lists, lengths and moved rows are exactly the oracle's for the
+    call's own scores, and a NaN value row shows in the status word."""
+    import torch
+    cfg = CONFIGS["c2"].with_(batch=2, n_q_heads=4, n_kv_heads=2)
+    n_keep = int(0.4 * n)
+    p = P.params_for(cfg)
+    ws = P.workspace(p, n, w)
+    ws.fill_(255)
+    for rep in range(2):
+        lay = make_layer(cfg, layer=rep, n=n, window=w)
+        k, v = P.to_dev(lay["k"]), P.to_dev(lay["v"])
+        sc = torch.empty(2, 2, n, device="cuda")
+        idx = torch.full((2, 2, n), -7, dtype=torch.int32, device="cuda")
+        lengths = torch.full((2, 2), -1, dtype=torch.int32, device="cuda")
+        ea.compress_layer_adaptive(p, P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"],
+                                   k, v, n, n, n_keep, floor, sc, idx, lengths, ws)
+        assert ea.debug_status(p, n, w, ws) == 0
+        own = sc.cpu().numpy().astype(np.float64)
+        rl, rk = X.select_adaptive(own, n_keep, floor)
+        gl, gi, ko, vo = lengths.cpu().numpy(), idx.cpu().numpy(), P.to_host(k), P.to_host(v)
+        moved = X.compact_ragged(lay["k"], lay["v"], rk)
+        assert np.array_equal(gl, rl)
+        for b in range(2):
+            for h in range(2):
+                m = gl[b, h]
+                assert np.array_equal(gi[b, h, :m], rk[b][h])
+                assert np.array_equal(ko[b, h, :m], moved[b][h][0]) and np.array_equal(vo[b, h, :m], moved[b][h][1])
+                assert np.array_equal(ko[b, h, m:], lay["k"][b, h, m:])
+    if w >= 16:                                            # (near-rank-one covariances: see the accuracy of ea_score)
+        rmu, rsg = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T)
+        P.check_scores(own, O.scores(widen(lay["k"]), widen(lay["v"]), rmu, rsg, cfg.epsilon), 2e-3)
+    v = P.to_dev(lay["v"])
+    v[1, 1, n // 2] = float("nan")
+    ea.compress_layer_adaptive(p, P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"],
+                               P.to_dev(lay["k"]), v, n, n, n_keep, floor, None, idx, lengths, ws)
+    assert ea.debug_status(p, n, w, ws) & ea.STATUS_BAD_SCORE
