@@ -1,4 +1,4 @@
-"""Workload shapes.  Names c1..c5 follow the five configurations of the build's baseline file;
+"""Workload shapes c1..c5, from a tiny correctness case to full caches of 8 to 14 billion parameter models;
 the *_mini variants keep the structure (GQA ratio, head_dim, outliers, dtype) at sizes a CPU
 oracle finishes in seconds while still spanning several kernel tiles and a ragged tail."""
 from dataclasses import dataclass, replace
@@ -42,8 +42,7 @@ CONFIGS = {
     "c2": CacheConfig("c2", "bf16", 1, 1, 32, 8, 128, 16384, 128, 5e5, 4, 8.0, 0.5, 2),
     # 3: Llama-3.1-8B-shaped full cache, 128k tokens x 32 layers (seed 3000 + layer)
     "c3": CacheConfig("c3", "bf16", 1, 32, 32, 8, 128, 131072, 128, 5e5, 4, 8.0, 0.5, 3000),
-    # 4: Gemma3-12B-shaped, d=256, batch 4 (seed 4000 + 48*b + layer); base and window are
-    #    not fixed by the baseline file: 1e6 and 128 are this build's choice
+    # 4: Gemma3-12B-shaped, d=256, batch 4 (seed 4000 + 48*b + layer), rotary base 1e6, window 128
     "c4": CacheConfig("c4", "bf16", 4, 48, 16, 8, 256, 32768, 128, 1e6, 4, 8.0, 0.5, 4000),
     # 5: decode pass, Qwen-14B-shaped: 4608 cached tokens compressed back to 4096, window 512
     "c5": CacheConfig("c5", "bf16", 1, 48, 40, 8, 128, 4608, 512, 1e6, 4, 8.0, 4096 / 4608, 5000),

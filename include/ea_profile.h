@@ -16,7 +16,9 @@ extern "C" {
  * HIP event recorded on `stream` between stages.  It creates and destroys the events, WAITS for
  * the layer to finish, and writes the milliseconds of each stage to stage_ms (HOST pointer,
  * EA_N_STAGES floats):
- *   0 clear + rotary table + statistics   1 matrix-core operand preparation
+ *   0 clear + rotary table + statistics   1 matrix-core operand preparation (empty, next to 0, where the
+ *     statistics kernel writes the operands itself: bf16 windows at d = 64, and at d = 128 from 192
+ *     query heads per call on)
  *   2 score pass A (K/V streaming kernel)  3 score pass B (normalise, weight by ||v||)
  *   4 selection                            5 compaction */
 #define EA_N_STAGES 6

@@ -1,6 +1,6 @@
 """GPU parity: every C-ABI entry point against the fp64 oracle on the same seeded inputs.
 
-Tolerances (from the benchmark spec): scores within 2e-3 relative for bf16 caches (fp32
+Tolerances: scores within 2e-3 relative for bf16 caches (fp32
 accumulation), 1e-5 for fp32 caches; kept-index sets equal to the oracle's except where oracle
 scores lie within that tolerance of the threshold, and bit-exact top-k of the kernel's own
 scores; compacted bytes bit-exact given the indices."""
