@@ -96,20 +96,29 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     s.nfrag = 2 * NF + 2 * NKS;
     s.lds_bytes = (size_t)2 * NF * 1024 + (size_t)s.NW * 4096;
   }
-  // A CU holds one workgroup.  Up to half as many units as CUs: every unit gets its share of the CUs,
-  // rounded down.  Beyond that one workgroup per (unit, pass) job, and where these leave the last round of
-  // CUs to 85 % full or less, spare ones behind them, three per job (two while the units do not exceed the CUs:
-  // fewer CUs are idle then): a CU whose head is done takes one of them and joins a head that still has
-  // tiles (tickets deal them).  query_stats + score in a row at d = 128, without and with: 304 units, G = 4,
-  // n = 4608 319 and 265 us; 384 units, G = 5, 421 and 382; 160 units in two passes 277 and 234.  Not on heads of
-  // under 1024 keys.  (From seven rounds on the last one is always more than 85 % of the whole.)
-  // With fewer jobs than CUs it does not pay at d <= 128: 192 CUs at the clock the chip then grants do what 256
-  // do (192 units 203 and 200 us, the whole decode-time pass 415 and 420).  At d = 256, one wavefront per SIMD, it
-  // does once the head is long enough for the fragments that a spare workgroup loads first, 72 KiB per query
-  // head, the longer the fewer CUs are idle.  score, two query heads per pass, without and with: 160 units x
-  // 1024 keys 94.4 and 98.5 us, x 1500 119 and 118, x 4000 242 and 211; 200 units x 1500 133 and 144, x 4000 261 and
-  // 260, x 9000 512 and 493; one query head, 200 units x 1024 72.2 and 74.1, x 2000 118 and 113.
-  const int64_t most = ((n + 31) / 32 + s.NW - 1) / s.NW;       // every wavefront with a tile at least
+  // A CU holds one workgroup.  Up to half as many units as CUs: every unit gets its share of the CUs, rounded down.
+  // Where that leaves a wavefront few tiles, only as many workgroups as finish in the same number of tiles per
+  // wavefront: more of them draw more tickets for nothing.  score, with the share and with fewer: d = 128, G = 3,
+  // one head x 100000 keys (256 and 196 workgroups) 99.3 and 89.2 us, x 200000 138 and 126; 8 heads x 9999 34.2 and 31.4;
+  // 32 x 4608 39.9 and 38.8; d = 256, G = 2, one head x 100000 87 and 80, 32 x 1500 45.2 and 42.9, G = 4, 24 x 4608 93.5
+  // and 82.8.  Few means three, and seven where the share is eight workgroups or more: five of them cut to four
+  // cost what they save (d = 128, G = 6, 50 heads x 4000 69.0 and 70.7), and with more tiles the last one does not
+  // show (d = 256, G = 2, 8 x 50000 126 and 130).  Two to four heads in one or two passes at d = 256 keep their
+  // share (4 x 25000, G = 1, 43.4 and 48.6; 2 x 30000, G = 2, 50.8 and 54.5; 2 x 40000, G = 4, 85.2 and 87.6).
+  //
+  // More units: one workgroup per (unit, pass) job, and where these leave the last round of CUs to 85 % full
+  // or less, spare ones behind them, three per job (two while the units do not exceed the CUs: fewer CUs are
+  // idle then): a CU whose head is done takes one of them and joins a head that still has tiles (tickets deal
+  // them).  query_stats + score in a row at d = 128, without and with: 304 units, G = 4, n = 4608 319 and 265 us;
+  // 384 units, G = 5, 421 and 382; 160 units in two passes 277 and 234.  Not on heads of under 1024 keys.  (From
+  // seven rounds on the last one is always more than 85 % of the whole.)  With fewer jobs than CUs it does not
+  // pay at d <= 128: 192 CUs at the clock the chip then grants do what 256 do (192 units 203 and 200 us, the whole
+  // decode-time pass 415 and 420).  At d = 256, one wavefront per SIMD, it does once the head is long enough for
+  // the fragments that a spare workgroup loads first, 72 KiB per query head, the longer the fewer CUs are idle.
+  // score, two query heads per pass, without and with: 160 units x 1024 keys 94.4 and 98.5 us, x 1500 119 and 118,
+  // x 4000 242 and 211; 200 units x 1500 133 and 144, x 4000 261 and 260, x 9000 512 and 493; one query head, 200 units
+  // x 1024 72.2 and 74.1, x 2000 118 and 113.
+  const int64_t ntiles = (n + 31) / 32, most = (ntiles + s.NW - 1) / s.NW;       // every wavefront with a tile at least
   const int64_t jobs = (int64_t)d.units() * s.passes;
   int64_t wgs = num_cu / d.units();
   if (wgs > 1024) wgs = 1024;
@@ -118,6 +127,9 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     const int64_t least = jobs > num_cu ? 1024 : s.GH * (jobs * 4 > (int64_t)num_cu * 3 ? 2000 : 640);
     s.spare = jobs * 20 < rounds * num_cu * 17 && n >= 1024 && n >= least && (jobs > num_cu || d.D == 256);
     wgs = !s.spare ? 1 : wgs == 1 ? 3 : 4;
+  } else if (!(d.D == 256 && s.passes <= 2 && d.units() >= 2 && d.units() <= 4)) {
+    const int64_t per_wave = (ntiles + wgs * s.NW - 1) / (wgs * s.NW);
+    if (per_wave <= 3 || (per_wave < 8 && wgs >= 8)) wgs = (ntiles + per_wave * s.NW - 1) / (per_wave * s.NW);
   }
   if (wgs > most) wgs = most;
   if (wgs < 2) s.spare = 0;
