@@ -145,15 +145,16 @@ __device__ __forceinline__ void stats_unpack_item(const StatsRaw<BF16>& raw, int
     tb[2 * e + 1] = make_float2(raw.t[e].z, raw.t[e].w);
   }
 }
-// u~ - shift: the 2x2 block of the table applied to one pair.  The products with t.y are rounded on their own, those
-// with t.x are not, and nothing else is contracted: written out, so that the bits of the statistics, and with them
-// every score, do not hang on what the compiler makes of the code around it, and one rule for every channel,
-// layout and instance, so that the first sample less the shift, which is the first sample, is zero.
+// u~ - shift: the 2x2 block of the table applied to one pair.  The products with the pair's second channel are
+// rounded on their own, those with its first are not, and nothing else is contracted: written out, so that the
+// bits of the statistics, and with them every score, do not hang on what the compiler makes of the code around
+// it, and one rule for every channel, layout and instance, so that the first sample less the shift, which is
+// the first sample, is zero.
 __device__ __forceinline__ void stats_rotate(float2 t, float qa, float qb, float sha, float shb, float& xa, float& xb) {
 #pragma clang fp contract(off)
-  const float pa = t.y * qb, pb = t.y * qa;
+  const float pa = t.y * qb, pb = t.x * qb;
   xa = fmaf(t.x, qa, -pa) - sha;
-  xb = fmaf(t.x, qb, pb) - shb;
+  xb = fmaf(t.y, qa, pb) - shb;
 }
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
