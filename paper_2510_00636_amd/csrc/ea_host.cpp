@@ -40,6 +40,17 @@ ea_status check_params(const ea_params* p, Dims* d, bool rows_only) {
 
 // Largest number of query heads whose fragments fit the 160 KiB LDS next to the per-wave
 // staging buffers, and the template instance (GH) that covers ceil(G / passes) heads.
+// Of the workgroups that k_score_mfma's launch starts with, one per CU, how many the head with the fewest has (its
+// order: transposed over the eight dies where the grid is a multiple of eight, units innermost).
+static int least_served(int units, int64_t grid, int num_cu) {
+  int count[512] = {};
+  if (units > 512) return 0;
+  for (int64_t b = 0; b < num_cu && b < grid; ++b) ++count[(grid % 8 == 0 ? (b % 8) * (grid / 8) + b / 8 : b) % units];
+  int least = count[0];
+  for (int u = 1; u < units; ++u) least = count[u] < least ? count[u] : least;
+  return least;
+}
+
 ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   ScorePlan s;
   s.hw = 0;
@@ -97,14 +108,20 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     s.lds_bytes = (size_t)2 * NF * 1024 + (size_t)s.NW * 4096;
   }
   // A CU holds one workgroup.  Up to half as many units as CUs: every unit gets its share of the CUs, rounded down.
-  // Where that leaves a wavefront few tiles, only as many workgroups as finish in the same number of tiles per
-  // wavefront: more of them draw more tickets for nothing.  score, with the share and with fewer: d = 128, G = 3,
-  // one head x 100000 keys (256 and 196 workgroups) 99.3 and 89.2 us, x 200000 138 and 126; 8 heads x 9999 34.2 and 31.4;
-  // 32 x 4608 39.9 and 38.8; d = 256, G = 2, one head x 100000 87 and 80, 32 x 1500 45.2 and 42.9, G = 4, 24 x 4608 93.5
-  // and 82.8.  Few means three, and seven where the share is eight workgroups or more: five of them cut to four
-  // cost what they save (d = 128, G = 6, 50 heads x 4000 69.0 and 70.7), and with more tiles the last one does not
-  // show (d = 256, G = 2, 8 x 50000 126 and 130).  Two to four heads in one or two passes at d = 256 keep their
-  // share (4 x 25000, G = 1, 43.4 and 48.6; 2 x 30000, G = 2, 50.8 and 54.5; 2 x 40000, G = 4, 85.2 and 87.6).
+  // Where that leaves a wavefront at most three tiles, only as many workgroups as finish in the same number of tiles
+  // per wavefront: more of them draw more tickets for nothing.  score, with the share and with fewer: d = 128, G = 3,
+  // one head x 100000 keys (256 and 196 workgroups) 99.3 and 89.2 us; 8 heads x 9999 34.2 and 31.4; 32 x 4608 39.9
+  // and 38.8; d = 256, G = 2, one head x 100000 87 and 80, 32 x 1500 45.2 and 42.9.  With four to seven tiles it
+  // gives 1 % or costs 5 (G = 8, 8 heads x 30698 79 and 85), but for heads of 40 workgroups and more (G = 3, one head
+  // x 200000 138 and 126; G = 7, 5 x 44385 88.5 and 84.3; G = 16, 3 x 91387 232 and 157) that lose more than a few of
+  // them (G = 7, 4 x 95757, 63 and not 64: 126 and 131).
+  // In several passes not all workgroups are on the chip at once, and a head that the first ones leave out starts late:
+  // there the smaller launch has to serve every head as the share does (G = 7, 48 x 2043, four workgroups each and
+  // not five, leave 16 heads out: 54.5 and 59.2; 20 x 4915, ten and not twelve, leave none behind: 62.8 and 57.7), and
+  // keep a grid of a multiple of eight (G = 7, 6 x 27931, 37 and not 42: 69 and 71; d = 256, G = 8, one x 180219,
+  // 235 and not 256: 229 and 373).  Few long heads at d = 256 keep their share (4 x 25000, G = 1, 43.4 and 48.6;
+  // 2 x 30000, G = 2, 50.8 and 54.5; 6 x 12091, G = 4, 71.1 and 73.8) unless nearly half of the workgroups go
+  // (3 x 11963, G = 4, 63.8 and 52.2).
   //
   // More units: one workgroup per (unit, pass) job, and where these leave the last round of CUs to 85 % full
   // or less, spare ones behind them, three per job (two while the units do not exceed the CUs: fewer CUs are
@@ -127,9 +144,14 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     const int64_t least = jobs > num_cu ? 1024 : s.GH * (jobs * 4 > (int64_t)num_cu * 3 ? 2000 : 640);
     s.spare = jobs * 20 < rounds * num_cu * 17 && n >= 1024 && n >= least && (jobs > num_cu || d.D == 256);
     wgs = !s.spare ? 1 : wgs == 1 ? 3 : 4;
-  } else if (!(d.D == 256 && s.passes <= 2 && d.units() >= 2 && d.units() <= 4)) {
-    const int64_t per_wave = (ntiles + wgs * s.NW - 1) / (wgs * s.NW);
-    if (per_wave <= 3 || (per_wave < 8 && wgs >= 8)) wgs = (ntiles + per_wave * s.NW - 1) / (per_wave * s.NW);
+  } else {
+    const int64_t per_wave = (ntiles + wgs * s.NW - 1) / (wgs * s.NW), fewer = (ntiles + per_wave * s.NW - 1) / (per_wave * s.NW);
+    bool take = per_wave <= 3 || (per_wave < 8 && wgs >= 40 && fewer * 20 <= wgs * 19);
+    if (d.D == 256 && s.passes <= 2 && d.units() >= 2 && d.units() <= 6) take = take && fewer * 5 < wgs * 3;
+    if (take && fewer < wgs && s.passes > 1)
+      take = least_served(d.units(), jobs * fewer, num_cu) * 10 >= least_served(d.units(), jobs * wgs, num_cu) * 9 &&
+             ((jobs * wgs) % 8 != 0 || (jobs * fewer) % 8 == 0);
+    if (take) wgs = fewer;
   }
   if (wgs > most) wgs = most;
   if (wgs < 2) s.spare = 0;

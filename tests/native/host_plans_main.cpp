@@ -45,14 +45,17 @@ int main() {
               }
           }
         }
-  // workgroups per head: no more than finish in the same number of tiles per wavefront, while these are few.
+  // workgroups per head: no more than finish in the same number of tiles per wavefront, while these are few and, in
+  // several passes, no head is left out of the workgroups that start first.
   // Spare workgroups: where the last round of CUs is short, and at d = 256 with fewer jobs than CUs only on
   // heads long enough for the fragments that a spare workgroup loads
   struct { int d, G, units; int64_t n; int spare, nchunk; } plan[] = {
       {128, 3, 1, 100000, 0, 196}, {128, 3, 8, 9999, 0, 20}, {128, 3, 1, 131072, 0, 256}, {128, 3, 1, 700000, 0, 256},
       {64, 8, 1, 100000, 0, 196}, {64, 4, 8, 300, 0, 2}, {256, 2, 32, 1500, 0, 6}, {256, 2, 2, 30000, 0, 128},
       {256, 1, 4, 25000, 0, 64}, {256, 8, 1, 100000, 0, 196}, {256, 4, 8, 9999, 0, 27}, {256, 2, 8, 50000, 0, 32},
-      {128, 6, 50, 4000, 0, 5}, {128, 6, 12, 30000, 0, 20}, {128, 16, 5, 40000, 0, 40}, {256, 4, 2, 40000, 0, 128},
+      {128, 6, 50, 4000, 0, 5}, {128, 6, 12, 30000, 0, 21}, {128, 16, 5, 40000, 0, 40}, {256, 4, 2, 40000, 0, 128},
+      {128, 7, 48, 2043, 0, 5}, {128, 7, 20, 4915, 0, 10}, {128, 7, 6, 27931, 0, 42}, {256, 8, 1, 180219, 0, 256},
+      {256, 4, 3, 11963, 0, 47}, {256, 4, 6, 12091, 0, 42}, {128, 8, 8, 30698, 0, 32}, {128, 16, 3, 91387, 0, 72},
       {128, 4, 300, 1024, 1, 4}, {128, 4, 300, 1000, 0, 1}, {128, 4, 436, 2000, 0, 1}, {128, 7, 140, 2000, 1, 3},
       {128, 4, 200, 8000, 0, 1}, {128, 4, 128, 8000, 0, 2}, {128, 4, 1800, 2000, 0, 1},
       {256, 2, 160, 1024, 0, 1}, {256, 2, 160, 1500, 1, 3}, {256, 2, 200, 1500, 0, 1}, {256, 2, 200, 3999, 0, 1},
