@@ -542,7 +542,8 @@ constexpr int stats_split_chunk(int D) { return D >= 256 ? 32 : 64; }
 // the conditions out of the staging (a shift read under "inside the chunk" was a branch and an LDS round trip
 // per element) and out of the matrix loop (each tile's operands were waited for on the spot), and reading a
 // row operand once for two tiles, took 104 us to 94; keeping Sigma on the chip took the 64 MB it wrote, half of
-// them in 4-byte pieces, and the 27 us of k_prep_frags off (whole pass 422 -> 396 us).
+// them in 4-byte pieces, and the 27 us of k_prep_frags off (whole pass 422 -> 396 us; with the order of tiles that
+// needs no scratch memory 390 -> 381).
 // FUSED (d <= 128, one workgroup per head): Sigma stays in LDS and leaves as the fragments that k_prep_frags
 // would have made of it, bit for bit.
 template <int D, int LAYOUT, int PARTS = 0, bool FUSED = false>
