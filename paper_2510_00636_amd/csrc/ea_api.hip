@@ -61,7 +61,7 @@ static ea_status run_stats_for_score(const Dims& d, const void* q_win, int64_t w
   if (!*frags_ready) return run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, ws, L, st, clear, clear_words);
   float2* tab = (float2*)(ws + L.tab);
   EA_TRY(launch_rope_table(d, inv_freq, q_pos0, t_next, (int)window, tab, clear, clear_words, st));
-  const ScorePlan sp = make_score_plan(d, n, device_num_cu(), paged);
+  const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), paged);
   EA_TRY(launch_stats_frags(d, sp, q_win, (int)window, tab, (uint4*)(ws + L.frags), (float*)(ws + L.post), st));
   return EA_OK;
 }
@@ -82,7 +82,7 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
   float* vnorm = (float*)(ws + L.vnorm);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
   if (d.dtype == EA_BF16) {
-    ScorePlan sp = make_score_plan(d, n, device_num_cu(), pm != nullptr);
+    ScorePlan sp = choose_score_plan(d, n, device_num_cu(), pm != nullptr);
     uint4* frags = (uint4*)(ws + L.frags);
     float* post = (float*)(ws + L.post);
     // frags_ready comes with hist_zeroed: the caller's own first launch has cleared the words then

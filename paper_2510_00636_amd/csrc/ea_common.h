@@ -7,6 +7,7 @@
 
 namespace ea {
 
+constexpr int kHwTile = 64;          // keys per iteration of the register-fragment score kernel
 constexpr int kNW128 = 8;            // wavefronts per workgroup of the d = 128 score kernel
 constexpr int kMaxWindow = 4096;
 constexpr int64_t kMaxN = (int64_t)1 << 26;   // cached rows per head the launch grids cover
@@ -33,11 +34,11 @@ struct ScorePlan {
   int GH;       // query heads whose Sigma fragments are LDS-resident in one pass
   int passes;   // ceil(G / GH); K is streamed once per pass
   int NW;       // wavefronts per workgroup
-  int nfrag;    // 1 KiB fragments per (unit, pass)
+  int nfrag;    // 1 KiB fragments per (unit, pass) (LDS-fragment kernels)
+  int unit_frags;   // 1 KiB fragments per unit
   int nchunk;   // workgroups per (unit, pass)
   int spare;    // 1: more workgroups than CUs; the ones dispatched late join heads that still have tiles
-  int hw;       // 1: the register-fragment kernel (one wavefront per query head, d = 128, groups of four)
-  int tpt;      // that kernel: tiles of 32 keys per ticket (1 or 4)
+  int hw;       // 1: the register-fragment kernel (one wavefront per query head, d = 128, four heads per pass)
   int pg;       // keys per softmax partial (max, sum exp): partial j covers keys [j*pg, (j+1)*pg)
   int npart;    // partials per query head = ceil(n / pg)
   int lse_pass; // 1: pass A leaves only logits; the partials are taken from them by a pass of their own
@@ -60,8 +61,9 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // rows_only: the call only moves cache rows, so p->dtype may also be EA_FP8_E4M3
 ea_status check_params(const ea_params* p, Dims* d, bool rows_only = false);
-// paged: the caches are block pools (the register-fragment kernel does not read those)
+// the LDS-fragment kernels' plan, and the plan of the kernel that serves the call; paged: the caches are block pools
 ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged = 0);
+ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged = 0);
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window);
 
 // Free words of the third radix histogram (its last digit has 1024 bins): the emit pass's block counter of
@@ -107,6 +109,25 @@ inline int keydiff_rows(int64_t n, int64_t units) {
   if (rows < least) rows = least;
   const int64_t nchunk = (n + rows - 1) / rows;
   return (int)(((n + nchunk - 1) / nchunk + 127) / 128 * 128);
+}
+
+// The tiles of a (unit, pass) of the register-fragment kernel: `ways` counters deal those of a residue class each.  Which
+// class a workgroup takes part in, its number among those that do, and how many do.
+// Of the two workgroups on a CU the one that came first gets the issue slots that both want and is up to a third faster,
+// so a counter has to serve first and second ones alike (and every die): the residue goes round by one from each group of
+// `ways` workgroups to the next.  With the residue chunk % ways the first ones of a CU were done after 69 us and the
+// second ones after 95 (8-bit cache, 8 units x 131072 keys); now all within 6 us of each other.
+struct HwDeal { int way, nth, peers; };
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline HwDeal hw_deal(int chunk, int nchunk, int ways) {
+  HwDeal x;
+  x.nth = chunk / ways;
+  x.way = (chunk + x.nth) % ways;
+  const int groups = nchunk / ways;
+  x.peers = groups + ((x.way + ways - groups % ways) % ways < nchunk % ways ? 1 : 0);
+  return x;
 }
 
 // fragments per head of the triangular Sigma tiling, and per pass

@@ -53,35 +53,10 @@ static int least_served(int units, int64_t grid, int num_cu) {
 
 ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   ScorePlan s;
+  (void)paged;                               // (a tile lies inside one block, or two of 16 rows: nothing to plan)
   s.hw = 0;
-  s.tpt = 1;
   s.spare = 0;
   s.lse_pass = 0;
-  if (!paged && !d.kv_fp8 && d.D == 128 && d.dtype == EA_BF16 && d.G % 4 == 0 && n >= 2048 && (int64_t)d.units() * (d.G / 4) <= 8) {
-    // groups of four query heads at d = 128, calls of up to 8 (KV head, group) units: fragments in
-    // registers, one wavefront per head, two workgroups of four wavefronts per CU.  Measured per
-    // layer of 8 KV heads x 131072 keys: 128 us against 129 us for the LDS-fragment kernel and a
-    // cheaper finalize pass (coarser partials) when a call holds one layer; with two or more
-    // layers per call the LDS-fragment kernel is the faster one (115 against 121 us).
-    s.hw = 1;
-    s.GH = 4;
-    s.passes = d.G / 4;
-    s.NW = 4;
-    s.nfrag = 4 * frags_per_head(128) + 2 * ksteps(128);
-    s.lds_bytes = 0;
-    const int64_t ntiles = (n + 31) / 32;
-    int64_t wgs = 2 * (int64_t)num_cu / ((int64_t)d.units() * s.passes);
-    if (wgs < 1) wgs = 1;
-    if (wgs > 1024) wgs = 1024;
-    // a ticket is four tiles where that still leaves every workgroup several tickets
-    s.tpt = (ntiles + 3) / 4 >= 4 * wgs ? 4 : 1;
-    const int64_t nblocks = (ntiles + s.tpt - 1) / s.tpt;
-    if (wgs > nblocks) wgs = nblocks;
-    s.nchunk = (int)wgs;
-    s.pg = 32 * s.tpt;
-    s.npart = (int)nblocks;
-    return s;
-  }
   const int NF = frags_per_head(d.D), NKS = ksteps(d.D);
   const size_t lds_max = 160 * 1024, slack = 1024;
   const int inst64[] = {1, 2, 4, 8}, inst128[] = {1, 2, 3, 4, 5}, inst256[] = {1};
@@ -98,6 +73,7 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   for (int i = ninst - 1; i >= 0; --i)
     if (inst[i] >= need) s.GH = inst[i];
   s.nfrag = s.GH * NF + 2 * NKS;
+  s.unit_frags = s.passes * s.nfrag;
   s.lds_bytes = (size_t)s.nfrag * 1024 + stage + slack;
   if (d.D == 256 && d.G >= 2) {
     // two query heads per pass: their triangular fragments in LDS (144 KiB), the extra tile's in
@@ -105,6 +81,7 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     s.GH = 2;
     s.passes = (d.G + 1) / 2;
     s.nfrag = 2 * NF + 2 * NKS;
+    s.unit_frags = s.passes * s.nfrag;
     s.lds_bytes = (size_t)2 * NF * 1024 + (size_t)s.NW * 4096;
   }
   // A CU holds one workgroup.  Up to half as many units as CUs: every unit gets its share of the CUs, rounded down.
@@ -162,6 +139,52 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   return s;
 }
 
+// The register-fragment kernel (d = 128): four query heads per pass, one wavefront each, two workgroups of four
+// wavefronts on a CU, whatever the cache layout.  Operands + score, LDS-fragment kernel and this one, us:
+//   as many passes, and every wavefront (or all but the last pass's fourth) with a head: always.  G = 4, 8 heads x 16384
+//     38 and 31, x 131072 155 and 130, 32 x 131072 515 and 479, 192 x 4608 144 and 132, one head x 100000 84 and 46,
+//     320 x 700 91 and 76; G = 7, 4 x 30000 67 and 41, 192 x 4608 238 and 230
+//   as many passes with more idle wavefronts: its cheaper start (20 KiB of fragments per wavefront, not 36 and more per
+//     query head through LDS) has to pay for them, so only calls of few tiles.  G = 1, 8 x 30000 42 and 38, x 131072 110
+//     and 109; G = 3, 8 x 60000 70 and 65, 192 x 4608 125 and 125; G = 6, 4 x 131072 154 and 113, 192 x 4608 206 and 227
+//   more passes (G = 5 in two instead of one, 9 in three instead of two): fewer still.  G = 5, 8 x 12000 40 and 36,
+//     x 30000 59 and 61; G = 9, 4 x 30000 72 and 55, x 131072 161 and 172; G = 13, 4 x 20000 67 and 49
+ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
+  ScorePlan s = make_score_plan(d, n, num_cu, paged);
+  if (d.D != 128 || d.dtype != EA_BF16 || n < kHwTile) return s;
+  const int64_t ntiles = (n + kHwTile - 1) / kHwTile, tiles = ntiles * d.units();
+  const int passes = (d.G + 3) / 4;
+  if (passes > s.passes ? tiles * passes > 6000 : passes * 4 - d.G > (passes > 1) && tiles > 10000) return s;
+  s.hw = 1;
+  s.GH = 4;
+  s.passes = passes;
+  s.NW = 4;
+  s.spare = 0;
+  s.lse_pass = 0;
+  s.lds_bytes = 0;
+  // the fragments of the unit's heads, then those of the extra rows of every pass: no more than the other kernel's
+  s.nfrag = 0;
+  s.unit_frags = d.G * frags_per_head(128) + s.passes * ksteps(128);
+  // Two workgroups per CU.  Where whole ones for every (unit, pass) leave more than a twentieth of them out, one more for
+  // each, as in make_score_plan: 192 units x 4608, G = 4, two and three per unit 138 and 132 us; G = 7 251 and 230;
+  // 384 jobs (G = 6) 248 and 227, 576 (G = 9) 375 and 337.
+  const int64_t jobs = (int64_t)d.units() * s.passes, slots = 2 * (int64_t)num_cu;
+  int64_t wgs = slots / jobs;
+  if (wgs < 8) {
+    const int64_t rounds = (jobs + slots - 1) / slots, used = wgs ? wgs * jobs : jobs;
+    s.spare = n >= 1024 && used * 20 < rounds * slots * 19;
+    wgs = s.spare ? (wgs ? wgs + 1 : 2) : wgs;
+  }
+  if (wgs > 1024) wgs = 1024;
+  if (wgs > ntiles) wgs = ntiles;
+  if (wgs < 1) wgs = 1;
+  if (wgs < 2) s.spare = 0;
+  s.nchunk = (int)wgs;
+  s.pg = kHwTile;
+  s.npart = (int)ntiles;
+  return s;
+}
+
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window) {
   WsLayout w;
   size_t o = 0;
@@ -171,17 +194,11 @@ WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window) {
     return at;
   };
   const size_t qh = (size_t)d.qheads(), un = (size_t)d.units();
-  // The callers size one buffer for every cache layout: the fragments of whichever plan is larger, that of
-  // contiguous bf16 tensors (the register-fragment kernel where it serves them) or that of block pools and
-  // 8-bit caches.  At d = 128, n >= 2048 and one KV head they differ: 6 x 96 and 5 x 116 KiB for 24 query heads.
+  // the fragments: the register-fragment kernel's are never more than the LDS-fragment kernel's, and these do not
+  // depend on the cache layout
   Dims contiguous = d;
   contiguous.kv_fp8 = 0;
-  size_t frags_per_unit = 0;
-  for (int paged = 0; paged <= 1; ++paged) {
-    const ScorePlan sp = make_score_plan(contiguous, n, 256, paged);
-    const size_t need = (size_t)sp.passes * sp.nfrag * 1024;
-    if (need > frags_per_unit) frags_per_unit = need;
-  }
+  const size_t frags_per_unit = (size_t)make_score_plan(contiguous, n, 256, 0).unit_frags * 1024;
   w.tab = take((size_t)window * d.half * 2 * sizeof(float));
   w.qproj = take(qh * (size_t)window * d.D * sizeof(float));   // projected queries of ea_query_stats_hidden
   w.mu = take(qh * d.D * sizeof(float));

@@ -34,14 +34,13 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
   a.passes = sp.passes;
   a.nchunk = sp.nchunk;
   a.npart = sp.npart;
-  a.tpt = sp.tpt;
   a.spare = sp.spare;
   a.units = d.units();
-  a.nfrag = sp.nfrag;
+  a.unit_frags = sp.unit_frags;
   a.tickets = tickets;
   a.ticket_stride = ticket_stride;
+  if (sp.hw) return launch_score_hw(a, sp, d.kv_fp8 != 0, st);
   if (d.kv_fp8) return launch_score_mfma_fp8(d.D, a, sp, st);
-  if (sp.hw) return launch_score_hw(a, sp, st);
   switch (d.D) {
     case 64: return launch_score_mfma_d64(a, sp, st);
     case 128: return sp.GH <= 3 ? launch_score_mfma_d128(a, sp, st) : launch_score_mfma_d128b(a, sp, st);

@@ -1,363 +1,451 @@
-// Score pass A for a group of four query heads at d = 128 with the Sigma fragments held in
-// REGISTERS (Eq. 7 of the paper: l_g = mu_g.k/sqrt(d) + k^T Sigma_g k/(2d) for every cached key).
+// Score pass A at d = 128 with the Sigma fragments held in REGISTERS, four query heads per pass (Eq. 7 of the paper:
+// l_g = mu_g.k/sqrt(d) + k^T Sigma_g k/(2d) for every cached key).
 //
-// The LDS-fragment kernel (ea_score_mfma.h) reads one 1 KiB fragment from LDS per matrix-core
-// instruction; with four SIMDs that is the whole LDS bandwidth of a CU at the matrix cores'
-// peak.  Here a workgroup is four wavefronts, one per query head of the GQA group: each keeps 16
-// of its own head's 20 triangular fragments in registers for the whole kernel (the other four,
-// and its share of the extra tile, are re-read from LDS per tile), and the four of them share
-// ONE tile of 32 keys per iteration, converted to fp16 once and laid out in LDS as matrix-core
-// B operands.  Per tile a wavefront reads 18 KiB from LDS for 24 matrix-core instructions
-// instead of 24 KiB, two such workgroups fit a CU, and the softmax partials belong to fixed
-// blocks of 128 keys (a quarter of the partials the per-tile scheme leaves to the finalize pass).
+// The LDS-fragment kernel (ea_score_mfma.h) reads one 1 KiB fragment from LDS per matrix-core instruction; with four SIMDs
+// that is the whole LDS bandwidth of a CU at the matrix cores' peak, and a workgroup starts with 96 KiB of them.  Here a
+// workgroup is four wavefronts, one per query head: each keeps its head's 20 triangular fragments and the 8 of the extra
+// rows in registers, and the four share ONE tile of 64 keys per iteration, converted to fp16 once.  Two workgroups fit a CU.
 //
-//   * K tile: each wavefront loads a quarter of the next tiles' rows (coalesced 16-byte loads,
-//     held in registers two to three iterations ahead), converts them bf16 -> fp16 and writes
-//     them to the LDS tile  [16-byte chunk j of the row][key r]  with a chunk stride of 33 slots
-//     (conflict-free both ways, and every address a lane needs is one base plus a constant);
-//     lane (r, hh) reads chunk hh*8 + kt of key r as its B operand of k-step kt.
-//   * V rows: same quarter split; squared norms straight from the coalesced registers.
-//   * extra tile (rows: fp16 head / tail of mu_g, rounding residual of diag(Sigma_g) times k^2):
-//     its 16 k-steps are split over the four wavefronts, four each; the partial row sums go
-//     through LDS and every wavefront picks up its own head's three rows one iteration later.
-//   * softmax partials: a ticket is a block of `tpt` consecutive tiles; a wavefront keeps the
-//     running (max, sum exp) of its head over the block and stores it to the block's slot, so
-//     the finalize pass combines the same numbers in the same order on every run.
+//   * K tile: each wavefront loads 16 rows of the tile after next (coalesced 16-byte loads, in flight for a whole
+//     iteration), converts those that arrived bf16 / e4m3 -> fp16 and writes them to LDS as 16-byte chunks; lane
+//     (c, q) = (l % 16, l / 16) reads chunk 4 b + q of key 16 m + c as its B operand of k-step b for key group m.
+//   * V rows: same split; squared norms straight from the coalesced registers.
+//   * quadratic form: v_mfma_f32_16x16x32_f16, A = 16 output channels x 32 input channels of M, every fragment used for
+//     two key groups in a row; a lane gets back channels it holds of the same keys, so k.(M k) is 4 FMAs per tile.
+//   * extra rows (fp16 head / tail of mu_g on k, rounding residual of diag(Sigma_g) on k^2): wavefront w computes those of
+//     all four heads for key group w; they go through LDS and every wavefront picks up its own head's an iteration later.
+//   * softmax partials: (max, sum exp) per tile of 64 keys, so that the finalize pass combines the same numbers in the
+//     same order on every run, whichever workgroup scored the tile.
 //
-// Fragment layout, scales and the meaning of `post` are those of k_prep_frags (ea_stats.hip).
+// What bounds it: instruction issue (88 matrix and about 320 vector instructions per wavefront and tile, 2100 cycles of the
+// issue port; two wavefronts per SIMD take 4900 for one each) and, in long runs, the power the chip may draw: it then clocks at 1.5 to
+// 1.8 GHz, and the energy per key is what counts.  Of the 16-bit forms the 16x16x32 one draws least (sustained with random
+// data 1850 TFLOP/s, 32x32x16 1650, bf16 1400), and every zero in the operands helps, which is why the fragments on the
+// diagonal are folded onto their triangle too (8-bit cache, 8 x 131072 keys: 115 -> 112.5 us).  Against the kernel it
+// replaces (32x32x16, tiles of 32 keys, four fragments re-read from LDS; contiguous bf16 only) and, for 8-bit caches and
+// block pools, the LDS-fragment one: operands + score, 8 heads of 4 x 131072 keys 155 -> 130 us, 8-bit 120 -> 113, x 16384
+// 38 -> 31, keys only x 32768 46 -> 43, pools of 16-row blocks x 20011 44 -> 39.
+//
+// Scales and the meaning of `post` are those of k_prep_frags (ea_stats.hip).
 #include "ea_score_mfma.h"
 
 namespace ea {
 
-constexpr int kHwLookahead = 3;      // the load cursor runs this many tiles ahead of the tile being scored
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-template <int D>
+// The 40 steps of an iteration, two 16x16x32 instructions with the same fragment each: the output tiles 0 .. 7 of the
+// quadratic form of keys 0-15 and 16-31, then of keys 32-47 and 48-63.  Tile j takes the k-steps 0 .. j / 2.
+
+// Sums over the four groups of 16 lanes of four values per lane: value m, complete, in the lanes of group m.
+__device__ __forceinline__ float sum_groups(const float (&p)[4]) {
+  auto merge32 = [](float x, float y) {      // lower half: x of both halves, upper half: y of both
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  };
+  const float e = merge32(p[0], p[2]), o = merge32(p[1], p[3]);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(e), __float_as_uint(o), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+
+// Maxima of lane l and lane l ^ 16, l ^ 32, or another lane of the row of 16; the median of x, y and infinity is one
+// instruction where fmaxf, which first quiets a signalling operand, makes three.
+__device__ __forceinline__ float max_of(float x, float y) {
+  float inf = INFINITY;
+  asm("" : "+s"(inf));                    // (or the compiler makes the longer form of it)
+  return __builtin_amdgcn_fmed3f(x, y, inf);
+}
+__device__ __forceinline__ float max_xor16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max_of(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float max_xor32(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max_of(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_xor16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float max_dpp(float x) {
+  const int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true);
+  return max_of(x, __int_as_float(y));
+}
+
+struct HwStep { int sub, tile, kt, frag, set; };
+constexpr int hw_end(int u) {              // last step of tile u of the iteration (u = 0 .. 15)
+  int e = -1;
+  for (int i = 0; i <= u; ++i) e += (i % 8) / 2 + 1;
+  return e;
+}
+constexpr HwStep hw_step(int f) {
+  int u = 0;
+  while (hw_end(u) < f) ++u;
+  const int first = u == 0 ? 0 : hw_end(u - 1) + 1, j = u % 8;
+  return HwStep{u / 8, j, f - first, j / 2 * (j / 2 + 1) + j % 2 * (j / 2 + 1) + f - first, u % 4};
+}
+
+template <bool FP8, bool PAGED>
 __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
-  static_assert(D == 128, "instance for head dimension 128");
-  constexpr int NKS = 8, NF = 20, GH = 4, CPR = 16, NFRAG = GH * NF + 2 * NKS;
-  constexpr int LA = kHwLookahead;
-  __shared__ u32x4 s_k[2][16 * 33];          // fp16 K tile [16-byte chunk j of the row][key r], chunk stride 33: double buffered
-  __shared__ float s_p[2][4][GH][64];        // extra-tile partial rows: [buffer][source wave][head][lane]
-  __shared__ int s_tk[8];                    // ring of drawn blocks, by draw ordinal
-  __shared__ u32x4 s_x[2 * NKS * 64];        // the extra tile's 16 fragments (read back four per wave and tile)
-  __shared__ u32x4 s_f0[GH * 4 * 64];        // each head's first four fragments (tile 0, half of tile 1): registers are short by about that much
+  constexpr int NKS = 4, NF = 20, GH = 4;
+  constexpr int RB = FP8 ? 128 : 256;        // bytes of a row
+  constexpr int NL = FP8 ? 2 : 4;            // wave-wide loads of a wavefront's 16 rows
+  constexpr int S = kHwTile;                 // slots between the 16-byte chunks of a row in LDS
+  // fp16 K tile [16-byte chunk of the row][key ^ chunk]: double buffered.  The swizzle keeps both the staging writes (16
+  // chunks of a row) and the operand reads (16 keys of four chunks) free of bank conflicts.
+  __shared__ u32x4 s_k[2][16 * S];
+  constexpr int SP = 68;                     // pitch of the extra rows: the four rows a wavefront touches at once in different banks
+  __shared__ float s_p[2][16 * SP];          // extra rows: [buffer][row][key]
+  __shared__ int s_tk[8];                    // ring of tiles, by ordinal
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 31, hh = lane >> 5;
-  const int lrow = lane >> 4, lch = lane & 15;
+  const int c16 = lane & 15, q = lane >> 4;  // matrix-core column (key of a group of 16) and group of rows / channels
+  const int lrow = FP8 ? lane >> 3 : lane >> 4, lch = FP8 ? lane & 7 : lane & 15;
 
   int bid = blockIdx.x;
-  if ((gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);   // every unit on all dies
-  const int unit = bid % a.units;
+  if (!a.spare && (gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);   // every unit on all dies
+  int unit = bid % a.units;
   const int t2 = bid / a.units;
-  const int chunk = t2 % a.nchunk, pass = t2 / a.nchunk;
+  int chunk = t2 % a.nchunk, pass = t2 / a.nchunk;
+  if (a.spare) {                             // more workgroups than the chip holds: see k_score_mfma
+    chunk = t2 / a.passes;
+    pass = t2 % a.passes;
+    unit = (unit + 3 * chunk) % a.units;
+  }
   const int g0 = pass * GH;
   const bool do_v = pass == 0 && !a.skip_v;
-  const int tpt = a.tpt, tsh = tpt == 4 ? 2 : 0;
-  const int ntiles = (int)((a.n + 31) / 32);
-  const int nblocks = (ntiles + tpt - 1) >> tsh;
-  const int ways = max(1, min(kTicketWays, a.nchunk / 8));
-  const int way = chunk % ways;
-  uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + pass * kTicketWays + way;
-
-  // ---- prologue: first draws, fragments, first three tiles
-  constexpr int NPRE = LA + 2;               // at most this many ordinals are needed before the loop's own draws arrive
-  const int npre = ((LA + 1) >> tsh) + 1;
-  if (tid == 0) {
-    uint32_t raw[NPRE];
-#pragma unroll
-    for (int i = 0; i < NPRE; ++i) raw[i] = i < npre ? atomicAdd(tk, 1u) : 0u;
-#pragma unroll
-    for (int i = 0; i < NPRE; ++i)
-      if (i < npre) s_tk[i] = nblocks - 1 - ((int)raw[i] * ways + way);
-  }
-  half8 F[NF];
-  {
-    const u32x4* src = a.frags + ((size_t)unit * a.passes + pass) * NFRAG * 64;
-#pragma unroll
-    for (int i = 4; i < NF; ++i) F[i] = __builtin_bit_cast(half8, src[(w * NF + i) * 64 + lane]);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s_f0[(w * 4 + i) * 64 + lane] = src[(w * NF + i) * 64 + lane];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s_x[tid + 256 * i] = src[GH * NF * 64 + tid + 256 * i];
-  }
-  // post[2g] = 1 / (2 d sM_g), post[2g+1] = 1 / (sqrt(d) smu_g)
-  float pm[GH], cq[GH];
-  float pq_mine = 0.f;
-#pragma unroll
-  for (int g = 0; g < GH; ++g) {
-    const float pq = a.post[((size_t)unit * a.G + g0 + g) * 2 + 0];
-    pm[g] = a.post[((size_t)unit * a.G + g0 + g) * 2 + 1];
-    cq[g] = 256.0f * pq;
-    pq_mine = w == g ? pq : pq_mine;
-  }
-  __syncthreads();
-
-  // All row arithmetic is 32-bit (n <= 2^26); a tile's global address is a per-tile scalar base
-  // plus a per-lane offset that never changes.  The loop body is ONE basic block (the instruction
-  // scheduler interleaves matrix-core and vector work only inside a block), so nothing in it is
-  // conditional: stores that must not happen go to a dump area instead (the upper half of the
-  // logit scratch, which only the fp32 path uses), loads without a tile read the head's first rows.
   const int n = (int)a.n;
-  const char* kbase = (const char*)(a.k + (size_t)unit * a.n_cap * CPR);
-  const char* vbase = (const char*)(a.v + (size_t)unit * a.n_cap * CPR);
-  const uint32_t ld_off = (uint32_t)((2 * w) * 1024 + lane * 16);
-  const uint32_t ld_off_v = do_v ? ld_off : 0u;           // later passes: every lane on the same 16 bytes
-  float* lg_out = a.logits + ((size_t)unit * a.G + g0 + w) * a.n;
-  float* vn_out = a.vnorm + (size_t)unit * a.n;
-  float2* part_out = a.part + ((size_t)unit * a.G + g0 + w) * a.npart;
-  float* dump = a.logits + (size_t)a.units * a.G * a.n;   // at least n floats; indexed like a head's rows; contents never read
-  float* vn_eff = do_v ? vn_out : dump;       // later passes hold no V rows: their "norms" go to the dump
+  const int ntiles = (n + kHwTile - 1) / kHwTile;
 
-  // A tile is one int: its index (rows [32 t, 32 t + 32)), -1 = no more work; an index >= ntiles is
-  // padding of the head's last, ragged, block (scored on dummy data, nothing stored).
-  int lc_ord = 0, lc_left = tpt;
-  int lc_tile;
-  {
-    const int blk = s_tk[0];
-    lc_tile = blk < 0 ? -1 : blk << tsh;
+  // Tiles of a (unit, pass): the first two of a workgroup by its number, the others as they are drawn from its counter,
+  // the last tile of the head first (see k_score_mfma).
+  const int ways = max(1, min(kTicketWays, a.nchunk / 8));
+  const HwDeal deal = hw_deal(chunk, a.nchunk, ways);
+  const int way = deal.way, nth = deal.nth, peers = deal.peers;
+  uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + pass * kTicketWays + way;
+  auto tile_of = [&](int raw) { return max(ntiles - 1 - (raw * ways + way), -1); };
+  int t_cur = tile_of(nth), t_n1 = tile_of(peers + nth);
+  const int dealt = a.spare ? 0 : 2 * peers; // tiles of the class that are dealt by number
+  uint32_t draw2 = 0, draw3 = 0;
+  if (a.spare) {                             // all tiles are drawn: a workgroup may come when there are none left
+    if (tid == 0) {
+      const uint32_t d0 = atomicAdd(tk, 1u), d1 = atomicAdd(tk, 1u);
+      draw2 = atomicAdd(tk, 1u);
+      draw3 = atomicAdd(tk, 1u);
+      s_tk[0] = tile_of((int)d0);
+      s_tk[1] = tile_of((int)d1);
+    }
+    __syncthreads();
+    t_cur = __builtin_amdgcn_readfirstlane(s_tk[0]);
+    t_n1 = __builtin_amdgcn_readfirstlane(s_tk[1]);
+    if (t_cur < 0) return;
+  } else if (tid == 0) {
+    draw2 = atomicAdd(tk, 1u);
+    draw3 = atomicAdd(tk, 1u);
   }
-  // cand: the ring entry of the next ordinal, read at the top of every iteration whether it is
-  // needed or not (it is only looked at when the current block is used up, and by then published)
-  auto next_tile = [&](int cand) -> int {
-    const bool fresh = lc_left == 0;
-    int blk = cand >= nblocks ? -1 : cand;   // never leave the head, whatever the ring holds
-    const int first = blk < 0 ? -1 : blk << tsh;
-    lc_ord += fresh ? 1 : 0;
-    lc_tile = fresh ? first : lc_tile;
-    lc_left = fresh ? tpt : lc_left;
-    const int t = lc_tile;
-    lc_tile += lc_tile >= 0 ? 1 : 0;
-    --lc_left;
-    return t;
-  };
-  auto ring_next = [&]() -> int { return __builtin_amdgcn_readfirstlane(s_tk[(lc_ord + 1) & 7]); };
-  auto is_real = [&](int t) -> bool { return (unsigned)t < (unsigned)ntiles; };
-  // first row actually loaded: the head's last tile is moved back to end at row n
-  auto base_row = [&](int t) -> int { return is_real(t) ? min(t * 32, n - 32) : 0; };
 
-  u32x4 rawK[2][2], rawV[2][2];              // [tile parity][load]: this wave's quarter of a tile
-  auto issue_loads = [&](auto slot_, int t) {
-    constexpr int SL = decltype(slot_)::value;
-    const size_t off = (size_t)base_row(t) * (CPR * 16);
-    const char* kp = kbase + off;
-    const char* vp = vbase + (do_v ? off : (size_t)0);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      rawK[SL][j] = __builtin_nontemporal_load((const u32x4*)(kp + (ld_off + j * 1024)));
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      rawV[SL][j] = __builtin_nontemporal_load((const u32x4*)(vp + (ld_off_v + (do_v ? j * 1024 : 0))));
+  const char* kbase = (const char*)a.k + (PAGED ? (size_t)0 : (size_t)unit * a.n_cap * RB);
+  const char* vbase = (const char*)a.v + (PAGED ? (size_t)0 : (size_t)unit * a.n_cap * RB);
+  // byte offset of this lane's 16 bytes in load j, from the first of the wavefront's 16 rows
+  const uint32_t row_off = (uint32_t)lrow * RB, ch_off = (uint32_t)lch * 16;
+  // first row of tile t (contiguous: the last one is moved back to end at row n)
+  auto base_row = [&](int t) -> int { return t < 0 ? 0 : PAGED ? t * kHwTile : min(t * kHwTile, n - kHwTile); };
+  // where the wavefront's 16 rows of tile t start, in bytes
+  auto rows_at = [&](int t) -> size_t {
+    const int row = base_row(t) + 16 * w;
+    if constexpr (!PAGED) return (size_t)row * RB;
+    // (a wavefront's rows lie inside one block; past the end of the head: its last 16 rows)
+    else return paged_row(a.pm, unit, min(row, (n - 1) & ~15)) * RB;
   };
-  // raw quarter -> fp16 rows of the LDS tile `buf`; value norms of the quarter's rows
-  const int st_idx0 = lch * 33 + 8 * w + lrow, st_idx1 = st_idx0 + 4;
-  const int vn_row = 8 * w + 4 * (lch & 1) + lrow;   // even / odd lanes of a row group store the norm of load 0 / 1
-  auto stage_tile = [&](auto slot_, int buf, int t) {
-    constexpr int SL = decltype(slot_)::value;
-    s_k[buf][st_idx0] = __builtin_bit_cast(u32x4, bf16x8_to_half8(rawK[SL][0]));
-    s_k[buf][st_idx1] = __builtin_bit_cast(u32x4, bf16x8_to_half8(rawK[SL][1]));
-    const float s0 = group_sum<16>(sumsq_bf16x8(rawV[SL][0]));
-    const float s1 = group_sum<16>(sumsq_bf16x8(rawV[SL][1]));
-    // Stored without a condition: the eight lanes that share a row write the same value, rows that
-    // a moved-back last tile shares with its predecessor get the same bits again (same data, same
-    // arithmetic), and so do rows 0..31 when there is no tile (the loads then read those rows).
-    vn_eff[base_row(t) + vn_row] = __builtin_amdgcn_sqrtf((lch & 1) ? s1 : s0);
+  // PAGED: rows past the end of the head become its last row again: of the 16 rows, those that are loaded
+  struct Lim { int lo, hi; };
+  auto rows_left = [&](int t) -> Lim {
+    const int row = base_row(t) + 16 * w, last = (n - 1) & ~15, hi = min(n - 1 - min(row, last), 15);
+    return Lim{row > last ? hi : 0, hi};
   };
 
-  int t_cur = next_tile(ring_next()), t_n1 = next_tile(ring_next()), t_n2 = next_tile(ring_next());
-  issue_loads(std::integral_constant<int, 0>{}, t_cur);
-  issue_loads(std::integral_constant<int, 1>{}, t_n1);
-  stage_tile(std::integral_constant<int, 0>{}, 0, t_cur);
-  issue_loads(std::integral_constant<int, 0>{}, t_n2);
+  u32x4 rawK[NL], rawV[NL];
+  auto lane_off = [&](int j, const Lim& lim) -> uint32_t {
+    if constexpr (!PAGED) return row_off + ch_off;          // + j KiB as an immediate
+    else return (uint32_t)max(lim.lo, min(j * (16 / NL) + lrow, lim.hi)) * RB + ch_off;
+  };
+  auto load_k = [&](int j, size_t at, const Lim& lim) __attribute__((always_inline)) {
+    rawK[j] = __builtin_nontemporal_load((const u32x4*)(kbase + at + (PAGED ? 0 : j * 1024) + lane_off(j, lim)));
+  };
+  auto load_v = [&](int j, size_t at, const Lim& lim) __attribute__((always_inline)) {   // later passes: the same 16 rows of the head
+    rawV[j] = __builtin_nontemporal_load((const u32x4*)(vbase + (do_v ? at : 0) + (PAGED ? 0 : j * 1024) + lane_off(j, lim)));
+  };
+  {
+    const size_t at = rows_at(t_cur);
+    const Lim lim = rows_left(t_cur);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) load_k(j, at, lim);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) load_v(j, at, lim);
+  }
+
+  half8 F[NF], X[2 * NKS];                   // this head's fragments, and those of the extra rows
+  {
+    const u32x4* src = a.frags + (size_t)unit * a.unit_frags * 64;
+    const bool mine = g0 + w < a.G;          // a wavefront without a head multiplies zeros, which draw little power
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+      F[i] = mine ? __builtin_bit_cast(half8, src[((g0 + w) * NF + i) * 64 + lane]) : (half8)(_Float16)0.f;
+#pragma unroll
+    for (int i = 0; i < 2 * NKS; ++i)
+      X[i] = __builtin_bit_cast(half8, src[(a.G * NF + pass * 2 * NKS + i) * 64 + lane]);
+  }
+  const float ks = (FP8 && a.kscale) ? a.kscale[unit] : 1.0f;
+  const float vs2 = (FP8 && a.vscale) ? a.vscale[unit] * a.vscale[unit] : 1.0f;
+  // post[2g] = 1 / (2 d sM_g), post[2g+1] = 1 / (sqrt(d) smu_g)
+  float pq_mine = 0.f, sc_mine = 0.f;        // sc: of the extra rows that this lane adds up (4 q + w: head, tail, residual, nothing)
+  if (g0 + w < a.G) {
+    pq_mine = a.post[((size_t)unit * a.G + g0 + w) * 2 + 0] * (ks * ks);
+    sc_mine = a.post[((size_t)unit * a.G + g0 + w) * 2 + 1] * ks;
+    sc_mine = q < 2 ? sc_mine : q == 2 ? 256.0f * pq_mine : 0.f;
+  }
+
+  float* dump = a.logits + (size_t)a.units * a.G * a.n;     // at least n floats; contents never read
+  const bool mine = g0 + w < a.G;                           // this wavefront has a head
+  float* lg_out = mine ? a.logits + ((size_t)unit * a.G + g0 + w) * a.n : dump;
+  float* vn_eff = do_v ? a.vnorm + (size_t)unit * a.n : dump;
+  float2* part_out = a.part + ((size_t)unit * a.G + g0 + (mine ? w : 0)) * a.npart;
+
+  // K chunk j of the raw rows -> fp16 -> LDS
+  const int row0 = 16 * w + lrow, chunk0 = FP8 ? 2 * lch : lch;
+  auto stage_k = [&](int j, int buf) __attribute__((always_inline)) {
+    const int row = row0 + j * (16 / NL);
+    if constexpr (FP8) {
+      half8 lo, hi;
+      fp8x16_to_half8x2(rawK[j], lo, hi);
+      s_k[buf][chunk0 * S + (row ^ chunk0)] = __builtin_bit_cast(u32x4, lo);
+      s_k[buf][(chunk0 + 1) * S + (row ^ (chunk0 + 1))] = __builtin_bit_cast(u32x4, hi);
+    } else {
+      s_k[buf][chunk0 * S + (row ^ chunk0)] = __builtin_bit_cast(u32x4, bf16x8_to_half8(rawK[j]));
+    }
+  };
+  auto square_v = [&](int j) __attribute__((always_inline)) -> float {
+    return FP8 ? sumsq_fp8x16(rawV[j]) : sumsq_bf16x8(rawV[j]);
+  };
+  // The sums over the lanes of a row; this lane ends up with load lch & 3 (FP8: lch / 4): the first steps of the
+  // butterfly hand half of the loads to each side.
+  auto reduce_v = [&](const float (&s)[NL]) __attribute__((always_inline)) -> float {
+    float x;
+    if constexpr (FP8) {
+      const bool o4 = lane & 4;
+      x = dpp_add_of<0x141>(o4 ? s[1] : s[0], o4 ? s[0] : s[1]);
+      x = dpp_add<0xB1>(x);
+      x = dpp_add<0x4E>(x);
+    } else {
+      const bool o1 = lane & 1, o2 = lane & 2;
+      const float a0 = dpp_add_of<0xB1>(o1 ? s[1] : s[0], o1 ? s[0] : s[1]);
+      const float a1 = dpp_add_of<0xB1>(o1 ? s[3] : s[2], o1 ? s[2] : s[3]);
+      x = dpp_add_of<0x4E>(o2 ? a1 : a0, o2 ? a0 : a1);
+      // 4 lanes of a quad hold 4 loads; the quads of a row of 16 hold parts of the same sums: rotations by 4 and 8
+      x = dpp_add<0x124>(x);
+      x = dpp_add<0x128>(x);
+    }
+    return x;
+  };
+  const int vn_row = 16 * w + (FP8 ? lch >> 2 : lch & 3) * (16 / NL) + lrow;
+  // keys past the end (PAGED) hold the last key again: same value, same place
+  auto out_row = [&](int row) -> int { return PAGED ? min(row, n - 1) : row; };
+
+  {
+    float sv[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) stage_k(j, 0);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) sv[j] = square_v(j);
+    const float x = reduce_v(sv);
+    vn_eff[out_row(base_row(t_cur) + vn_row)] = __builtin_amdgcn_sqrtf(FP8 ? x * vs2 : x);
+    const size_t at = rows_at(t_n1);
+    const Lim lim = rows_left(t_n1);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) load_k(j, at, lim);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) load_v(j, at, lim);
+  }
+  if (tid == 0) {
+    s_tk[2] = tile_of(dealt + (int)draw2);
+    s_tk[3] = tile_of(dealt + (int)draw3);
+  }
   __syncthreads();
 
-  float m_run = -INFINITY, s_run = 0.f;      // this head's softmax state over the current block
-  float quad_prev = 0.f;
+  float quad[4] = {0.f, 0.f, 0.f, 0.f};      // of the previous tile, by group of 16 keys
   int t_prev = -1;
-  uint32_t pend = 0;                         // wave 0, lane 0: the draw waiting to be published
+  uint32_t pend = 0;                         // wavefront 0, lane 0: the draw waiting to be published
   int s = 0;
-
-  const int kh_idx = (hh * 8) * 33 + r;        // lane's B operand of k-step kt: s_k[.][kh_idx + kt * 33]
-  auto body = [&](auto pb_) {
-    constexpr int PB = decltype(pb_)::value;
-    constexpr floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // ---- LDS reads of the iteration: ring entry, B operands, and the previous tile's extra-tile
-    //      rows from all four wavefronts
-    const int cand = ring_next();
-    half8 Kh[NKS], Kx[2], XL[2], XS[2], sq[2];
+  // lane's B operand of k-step b for key group m: s_k[.][kh_idx[b] + 16 m]
+  int kh_idx[NKS];
 #pragma unroll
-    for (int kt = 0; kt < NKS; ++kt)
-      Kh[kt] = __builtin_bit_cast(half8, s_k[PB][kh_idx + kt * 33]);
-    const float lin = (s_p[PB ^ 1][0][w][lane] + s_p[PB ^ 1][1][w][lane]) +
-                      (s_p[PB ^ 1][2][w][lane] + s_p[PB ^ 1][3][w][lane]);
+  for (int b = 0; b < NKS; ++b) kh_idx[b] = (4 * b + q) * S + (c16 ^ (4 * b + q));
+  const int p_out = 4 * q * SP + 16 * w + c16, p_in = (4 * q + w) * SP + c16;
+
+  // One body, the buffers by a number that the compiler does not know: unrolled for the two of them, the loop gets two
+  // exits, and the paths that then join in front of it make every wavefront wait there for all the loads in flight.
+  do {
+    const int PB = s & 1;
+    constexpr floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    half8 K[2][2][NKS], Kx[NKS];
+    auto read_k = [&](int m, int kt) __attribute__((always_inline)) {
+      return __builtin_bit_cast(half8, s_k[PB][kh_idx[kt] + 16 * m]);
+    };
+    auto read_pair = [&](auto sub_, auto kt_) __attribute__((always_inline)) {
+      constexpr int sub = decltype(sub_)::value, kt = decltype(kt_)::value;
+      K[sub][0][kt] = read_k(2 * sub, kt);
+      K[sub][1][kt] = read_k(2 * sub + 1, kt);
+    };
+    read_pair(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+    read_pair(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int b = 0; b < NKS; ++b) Kx[b] = read_k(w, b);
+    float lp[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) lp[m] = s_p[PB ^ 1][p_in + 16 * m];
+    const int t_n2 = __builtin_amdgcn_readfirstlane(s_tk[(s + 2) & 7]);
+    const size_t at_n2 = rows_at(t_n2);
+    const Lim lim_n2 = rows_left(t_n2);
     __builtin_amdgcn_sched_barrier(0);
 
-    // ---- 24 steps, one matrix-core instruction each, in this order:
-    //   0..7   output tile 3 of the head's quadratic form (k-steps 0..7: on or below the diagonal)
-    //   8..13  tile 2     14..17  tile 1     18..19  tile 0
-    //   20..23 this wave's four steps of the extra tile (two on k, two on k^2 / 256)
-    // and the vector / memory work placed in the shadow of each (nothing moves across a step):
-    //   0..1   the previous tile's logit, its store and the running softmax
-    //   2..6   staging of tile s+1 (bf16 -> fp16 into the other LDS buffer, value norms)
-    //   7      request of tile s+3 into the registers just staged
-    //   the dot product of a finished tile with k two and three steps after its last instruction
-    //   16     fetch of the extra tile's operands; 18, 21 their squares
-    floatx16 acc3, acc2, acc1, acc0, ex;
-    float partial = 0.f, vs0 = 0.f, vs1 = 0.f, lg = 0.f;
-    int t_n3 = -1;
-    auto dot8 = [&](auto jt_, auto h_, const floatx16& acc) {
-      constexpr int jt = decltype(jt_)::value, h = decltype(h_)::value;
-      static_for<8>([&](auto v_) {
-        constexpr int v = 8 * h + decltype(v_)::value;
-        constexpr int x = jt * 16 + v;
-        partial = fmaf(acc[v], (float)Kh[x / 8][x % 8], partial);
+    floatx4 acc[4][2], ex;
+    half8 sq;
+    float dot[4] = {0.f, 0.f, 0.f, 0.f};
+    float sv[NL], lg = 0.f, lm = 0.f, le = 0.f, vn = 0.f;
+    const int row_prev = base_row(t_prev) + lane;
+    auto dots = [&](auto u_, auto h_) __attribute__((always_inline)) {     // rows 2 h, 2 h + 1 of the tile, both groups
+      constexpr int u = decltype(u_)::value, h = decltype(h_)::value, sub = u / 8, j = u % 8;
+      static_for<2>([&](auto v_) {
+        constexpr int v = 2 * h + decltype(v_)::value;
+        dot[2 * sub] = fmaf(acc[u % 4][0][v], (float)K[sub][0][j / 2][4 * (j % 2) + v], dot[2 * sub]);
+        dot[2 * sub + 1] = fmaf(acc[u % 4][1][v], (float)K[sub][1][j / 2][4 * (j % 2) + v], dot[2 * sub + 1]);
       });
-      asm volatile("" : "+v"(partial));      // pin: left alone, the dot products sink to the end of the block
+      asm volatile("" : "+v"(dot[2 * sub]), "+v"(dot[2 * sub + 1]));
     };
-    using C0 = std::integral_constant<int, 0>;
-    using C1 = std::integral_constant<int, 1>;
-    using C2 = std::integral_constant<int, 2>;
-    using C3 = std::integral_constant<int, 3>;
-    static_for<24>([&](auto f_) {
+    __builtin_amdgcn_s_setprio(1);
+    static_for<43>([&](auto f_) {
       constexpr int f = decltype(f_)::value;
-      // -- the step's matrix-core instruction
-      if constexpr (f < 8) acc3 = __builtin_amdgcn_mfma_f32_32x32x16_f16(F[12 + f], Kh[f], f == 0 ? zero : acc3, 0, 0, 0);
-      else if constexpr (f < 14) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(F[6 + f - 8], Kh[f - 8], f == 8 ? zero : acc2, 0, 0, 0);
-      else if constexpr (f < 18) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(F[2 + f - 14], Kh[f - 14], f == 14 ? zero : acc1, 0, 0, 0);
-      else if constexpr (f < 20) acc0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(F[f - 18], Kh[f - 18], f == 18 ? zero : acc0, 0, 0, 0);
-      else if constexpr (f < 22) ex = __builtin_amdgcn_mfma_f32_32x32x16_f16(XL[f - 20], Kx[f - 20], f == 20 ? zero : ex, 0, 0, 0);
-      else ex = __builtin_amdgcn_mfma_f32_32x32x16_f16(XS[f - 22], sq[f - 22], ex, 0, 0, 0);
-      // -- vector and memory work of the step
-      if constexpr (f == 0) {
-        // the previous tile's logit: its quadratic part was formed last iteration, the extra-tile
-        // rows of all four wavefronts are in LDS since the barrier
-        lg = sum_halves(fmaf(quad_prev, pq_mine, lin));
-        // stored without a per-lane condition (see the value norms); only the very first iteration,
-        // which has no previous tile, must not reach the logits
-        float* dst = t_prev >= 0 ? lg_out : dump;
-        dst[base_row(t_prev) + r] = lg;
-      }
-      if constexpr (f == 1) {
-        const int key = base_row(t_prev) + r;
-        const bool valid = is_real(t_prev) && key >= t_prev * 32;      // key < n by construction
-        const float mn = valid ? fmaxf(m_run, lg) : m_run;
-        const float e1 = __expf(m_run - mn), e2 = valid ? __expf(lg - mn) : 0.f;
-        s_run = fmaf(s_run, mn == -INFINITY ? 0.f : e1, e2);
-        m_run = mn;
-      }
-      if constexpr (f == 2) s_k[PB ^ 1][st_idx0] = __builtin_bit_cast(u32x4, bf16x8_to_half8(rawK[PB ^ 1][0]));
-      if constexpr (f == 3) s_k[PB ^ 1][st_idx1] = __builtin_bit_cast(u32x4, bf16x8_to_half8(rawK[PB ^ 1][1]));
-      if constexpr (f == 4) vs0 = group_sum<16>(sumsq_bf16x8(rawV[PB ^ 1][0]));
-      if constexpr (f == 5) vs1 = group_sum<16>(sumsq_bf16x8(rawV[PB ^ 1][1]));
-      if constexpr (f == 6) {
-        // Stored without a condition: the eight lanes that share a row write the same value, rows
-        // that a moved-back last tile shares with its predecessor get the same bits again (same
-        // data, same arithmetic), and so do rows 0..31 when there is no tile (the loads then read
-        // those rows).
-        vn_eff[base_row(t_n1) + vn_row] = __builtin_amdgcn_sqrtf((lch & 1) ? vs1 : vs0);
-      }
-      if constexpr (f == 7) {
-        t_n3 = next_tile(cand);
-        issue_loads(std::integral_constant<int, PB ^ 1>{}, t_n3);
-      }
-      if constexpr (f == 11) {
+      if constexpr (f < 40) {
+        constexpr HwStep st = hw_step(f);
 #pragma unroll
-        for (int jx = 2; jx < 4; ++jx) F[jx] = __builtin_bit_cast(half8, s_f0[(w * 4 + jx) * 64 + lane]);
+        for (int m = 0; m < 2; ++m)
+          acc[st.set][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F[st.frag], K[st.sub][m][st.kt], st.kt == 0 ? zero4 : acc[st.set][m], 0, 0, 0);
       }
-      if constexpr (f == 9) dot8(C3{}, C0{}, acc3);
-      if constexpr (f == 10) dot8(C3{}, C1{}, acc3);
-      if constexpr (f == 15) dot8(C2{}, C0{}, acc2);
-      if constexpr (f == 16) {
-        dot8(C2{}, C1{}, acc2);
-#pragma unroll
-        for (int jx = 0; jx < 2; ++jx) {
-          Kx[jx] = __builtin_bit_cast(half8, s_k[PB][kh_idx + (2 * w + jx) * 33]);
-          XL[jx] = __builtin_bit_cast(half8, s_x[(2 * w + jx) * 64 + lane]);
-          XS[jx] = __builtin_bit_cast(half8, s_x[(NKS + 2 * w + jx) * 64 + lane]);
-          F[jx] = __builtin_bit_cast(half8, s_f0[(w * 4 + jx) * 64 + lane]);
+      // -- extra rows of key group w
+      if constexpr (f >= 2 && f < 2 + 2 * NKS) {
+        constexpr int b = (f - 2) / 2;
+        if constexpr (f % 2 == 0) {
+          const half8 t = Kx[b] * (_Float16)0.0625f;
+          // saturate instead of overflowing for |k| > 4096: infinity times a zero residual is NaN
+          sq = __builtin_elementwise_min(t * t, (half8)(_Float16)65504.0f);
+          ex = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[b], Kx[b], b == 0 ? zero4 : ex, 0, 0, 0);
+        } else {
+          ex = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[NKS + b], sq, ex, 0, 0, 0);
         }
       }
-      if constexpr (f == 18 || f == 21) {
-        constexpr int jx = f == 18 ? 0 : 1;
-        const half8 t = Kx[jx] * (_Float16)0.0625f;
-        // saturate instead of overflowing for |k| > 4096: infinity times a zero residual is NaN
-        sq[jx] = __builtin_elementwise_min(t * t, (half8)(_Float16)65504.0f);
-      }
-      if constexpr (f == 19) dot8(C1{}, C0{}, acc1);
-      if constexpr (f == 20) dot8(C1{}, C1{}, acc1);
-      if constexpr (f == 22) dot8(C0{}, C0{}, acc0);
-      if constexpr (f == 23) dot8(C0{}, C1{}, acc0);
-    });
-    // the order asked of the scheduler: one matrix-core instruction, then the vector and memory
-    // work that fits in its shadow
-    static_for<24>([&](auto) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);     // VALU
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // LDS read
-      __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);     // LDS write
-      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);     // global load
-      __builtin_amdgcn_sched_group_barrier(0x040, 1, 0);     // global store
-    });
-    __builtin_amdgcn_sched_barrier(0);
-    // lower half-wave: rows g (head of mu_g) and 8 + g (diagonal residual); upper half-wave:
-    // rows 4 + g (tail of mu_g) and 12 + g (empty fragment rows: exact zeros); the halves are
-    // added when the logit is formed
+      if constexpr (f == 12) {
 #pragma unroll
-    for (int g = 0; g < GH; ++g) s_p[PB][w][g][lane] = fmaf(ex[4 + g], cq[g], ex[g] * pm[g]);
-
+        for (int v = 0; v < 4; ++v) s_p[PB][p_out + v * SP] = ex[v];
+      }
+      // -- operands, a few steps ahead of their first use
+      if constexpr (f == 2) read_pair(std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
+      if constexpr (f == 6) read_pair(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
+      if constexpr (f == 16) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
+      if constexpr (f == 18) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+      if constexpr (f == 22) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+      if constexpr (f == 26) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{});
+      // -- the previous tile's logits, key `lane` of 64
+      if constexpr (f == 0) {
+        float p[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) p[m] = fmaf(quad[m], pq_mine, lp[m] * sc_mine);
+        lg = sum_groups(p);
+      }
+      if constexpr (f == 2) {
+        char* dst = (char*)(t_prev >= 0 ? lg_out : dump);
+        *(float*)(dst + (uint32_t)(4 * out_row(row_prev))) = lg;
+        const bool valid = PAGED ? row_prev < n : row_prev >= t_prev * kHwTile;
+        lg = valid ? lg : -INFINITY;
+        lm = lg;
+      }
+      // -- its softmax partial: max and sum over the 64 lanes, one step of the butterflies at a time
+      if constexpr (f == 5) lm = max_xor16(lm);
+      if constexpr (f == 6) lm = max_xor32(lm);
+      if constexpr (f == 7) lm = max_dpp<0xB1>(lm);
+      if constexpr (f == 9) lm = max_dpp<0x4E>(lm);
+      if constexpr (f == 11) lm = max_dpp<0x141>(lm);
+      if constexpr (f == 13) lm = max_dpp<0x140>(lm);
+      if constexpr (f == 15) le = __expf(lg - lm);
+      if constexpr (f == 18) le = dpp_add<0xB1>(le);
+      if constexpr (f == 19) le = dpp_add<0x4E>(le);
+      if constexpr (f == 21) le = dpp_add<0x141>(le);
+      if constexpr (f == 23) le = dpp_add<0x140>(le);
+      if constexpr (f == 25) le = sum_xor16(le);
+      if constexpr (f == 27) le = sum_halves(le);
+      // -- staging of the next tile, each chunk requested again for the one after it
+      if constexpr (f >= 30 && f < 30 + 2 * NL && (f & 1) == 0) {
+        constexpr int j = (f - 30) / 2;
+        stage_k(j, PB ^ 1);
+        load_k(j, at_n2, lim_n2);
+      }
+      if constexpr (f >= 31 && f < 31 + 2 * NL && (f & 1) == 1) {
+        constexpr int j = (f - 31) / 2;
+        sv[j] = square_v(j);
+        load_v(j, at_n2, lim_n2);
+      }
+      if constexpr (f == 39) vn = reduce_v(sv);
+      if constexpr (f == 40) *(float*)((char*)vn_eff + (uint32_t)(4 * out_row(base_row(t_n1) + vn_row))) = __builtin_amdgcn_sqrtf(FP8 ? vn * vs2 : vn);
+      // -- dot products of finished output tiles with k
+      static_for<16>([&](auto u_) {
+        constexpr int u = decltype(u_)::value, e = hw_end(u);
+        if constexpr (f == e + 2) dots(u_, std::integral_constant<int, 0>{});
+        if constexpr (f == e + 3) dots(u_, std::integral_constant<int, 1>{});
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    __builtin_amdgcn_s_setprio(0);
     // ---- tail: the parts that need a branch
-    const int t_done = t_prev;               // the tile whose logit was just formed
-    if (t_done >= 0 && (t_done & (tpt - 1)) == tpt - 1) {     // it was the last of its block (uniform)
-      const float m = max_lanes32(m_run);
-      const float sm = sum_lanes32(m_run == -INFINITY ? 0.f : s_run * __expf(m_run - m));
-      if (lane == 0) part_out[t_done >> tsh] = make_float2(m, sm);
-      m_run = -INFINITY;
-      s_run = 0.f;
+    if (t_prev >= 0 && mine && lane == 0) part_out[t_prev] = make_float2(lm, le);
+    if (tid == 0) {
+      if (s >= 1) s_tk[(s + 3) & 7] = tile_of(dealt + (int)pend);
+      pend = atomicAdd(tk, 1u);
     }
-    // tickets (wavefront 0): publish the draw of the previous iteration, then draw again
-    if (s >= 1 && ((s + LA + 1) & (tpt - 1)) == 0 && tid == 0)
-      s_tk[((s + LA + 1) >> tsh) & 7] = nblocks - 1 - ((int)pend * ways + way);
-    if (((s + LA + 2) & (tpt - 1)) == 0 && tid == 0) pend = atomicAdd(tk, 1u);
-
-    quad_prev = partial;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) quad[m] = dot[m];
     t_prev = t_cur;
     t_cur = t_n1;
     t_n1 = t_n2;
-    t_n2 = t_n3;
     ++s;
-    __syncthreads();
-  };
-
-  for (;;) {
-    if (t_cur < 0) break;
-    body(std::integral_constant<int, 0>{});
-    if (t_cur < 0) break;
-    body(std::integral_constant<int, 1>{});
-  }
-  // the last tile's logit: one more half-iteration without matrix work
-  {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  } while (t_cur >= 0);
+  // the last tile's logits
+  if (t_prev >= 0) {
     const int pb = (s - 1) & 1;
-    const float lin = (s_p[pb][0][w][lane] + s_p[pb][1][w][lane]) + (s_p[pb][2][w][lane] + s_p[pb][3][w][lane]);
-    const float lg = sum_halves(fmaf(quad_prev, pq_mine, lin));
-    const int key = base_row(t_prev) + r;
-    const bool valid = is_real(t_prev) && key >= t_prev * 32;
-    if (valid && hh == 0) lg_out[key] = lg;
-    if (valid) {
-      const float mn = fmaxf(m_run, lg);
-      s_run = s_run * __expf(m_run - mn) + __expf(lg - mn);
-      m_run = mn;
+    float p[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      p[m] = fmaf(quad[m], pq_mine, s_p[pb][p_in + 16 * m] * sc_mine);
     }
-    if (t_prev >= 0 && (t_prev & (tpt - 1)) == tpt - 1) {
-      const float m = max_lanes32(m_run);
-      const float sm = sum_lanes32(m_run == -INFINITY ? 0.f : s_run * __expf(m_run - m));
-      if (lane == 0) part_out[t_prev >> tsh] = make_float2(m, sm);
-    }
+    const float lg = sum_groups(p);
+    const int row = base_row(t_prev) + lane;
+    lg_out[out_row(row)] = lg;
+    const bool valid = PAGED ? row < n : row >= t_prev * kHwTile;
+    float m = valid ? lg : -INFINITY;
+    m = max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(max_xor32(max_xor16(m))))));
+    float e = __expf((valid ? lg : -INFINITY) - m);
+    e = sum_halves(sum_xor16(dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(e))))));
+    if (mine && lane == 0) part_out[t_prev] = make_float2(m, e);
   }
 }
 
-hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, hipStream_t st) {
+hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, bool fp8, hipStream_t st) {
   const int grid = a.units * a.nchunk * a.passes;
-  k_score_hw<128><<<grid, 256, 0, st>>>(a);
+  if (a.pm.table) k_score_hw<false, true><<<grid, 256, 0, st>>>(a);
+  else if (fp8) k_score_hw<true, false><<<grid, 256, 0, st>>>(a);
+  else k_score_hw<false, false><<<grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -31,9 +31,8 @@ struct ScoreArgs {
   float* logits;
   float* vnorm;
   float2* part;           // register-fragment kernel only: its (max, sum exp) partials
-  int G, passes, nchunk, units, nfrag;     // nchunk: workgroups per (unit, pass)
+  int G, passes, nchunk, units, unit_frags;     // nchunk: workgroups per (unit, pass)
   int npart;              // that kernel: partials per query head, partial j covers keys [pg*j, pg*j + pg)
-  int tpt;                // register-fragment kernel: tiles per ticket (pg = 32 * tpt); else unused
   uint32_t* tickets;      // tickets + unit * ticket_stride + pass * kTicketWays + way: tile counters, zero at launch
   int ticket_stride;
   PageMap pm;             // pm.table != nullptr: k and v are block pools (CLAMP instances only)
@@ -115,6 +114,13 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_add(float x) {
   int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true);
   return x + __int_as_float(y);
+}
+
+// x + (y of another lane of the same 16-lane row)
+template <int CTRL>
+__device__ __forceinline__ float dpp_add_of(float x, float y) {
+  const int z = __builtin_amdgcn_update_dpp(0, __float_as_int(y), CTRL, 0xf, 0xf, true);
+  return x + __int_as_float(z);
 }
 
 // Sum over aligned groups of N consecutive lanes (N = 8, 16 or 32); every lane gets the total.
@@ -613,6 +619,6 @@ hipError_t launch_score_mfma_d256(const ScoreArgs& a, const ScorePlan& sp, hipSt
 hipError_t launch_score_mfma_fp8(int D, const ScoreArgs& a, const ScorePlan& sp, hipStream_t st);
 hipError_t launch_score_mfma_fp8b(int D, const ScoreArgs& a, const ScorePlan& sp, hipStream_t st);
 // ea_score_hw.hip: fragments in registers, one wavefront per query head (d = 128, groups of four)
-hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, hipStream_t st);
+hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, bool fp8, hipStream_t st);
 
 }  // namespace ea

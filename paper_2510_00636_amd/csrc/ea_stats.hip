@@ -433,8 +433,65 @@ __device__ __forceinline__ uint4 pack_half8(const _Float16 (&h)[8]) {
 struct FragsOut {
   uint4* frags;
   float* post;
-  int G, GH, passes, nfrag;
+  int G, GH, passes, nfrag, unit_frags, hw;
 };
+// First fragment of query head gq of a unit, and of the extra rows of a pass: passes of `nfrag` fragments each, or (hw)
+// all of a unit's heads, then the extra rows of every pass.
+__device__ __forceinline__ size_t head_frags(const FragsOut& fo, int unit, int gq, int NF) {
+  const int pass = gq / fo.GH;
+  return (size_t)unit * fo.unit_frags + (fo.hw ? gq * NF : pass * fo.nfrag + (gq - pass * fo.GH) * NF);
+}
+__device__ __forceinline__ size_t extra_frags(const FragsOut& fo, int unit, int pass, int NF, int nks) {
+  return (size_t)unit * fo.unit_frags + (fo.hw ? fo.G * NF + pass * 2 * nks : pass * fo.nfrag + fo.GH * NF);
+}
+
+// What lane l of fragment f of a head holds: eight entries of M, output channel `out`, input channels from `in0` on,
+// `folded` where the mirrored entries are added.  The LDS-fragment kernels' are 32 x 16 operands as above.  The
+// register-fragment kernel's (hw) are 16 x 32 operands: k-step b is the channels 32 b .. 32 b + 31, lane l's key operand
+// the eight from 32 b + 8 (l / 16) on, output tile j has the rows 4 q + v for channel 32 (j / 2) + 8 q + 4 (j % 2) + v, so
+// that a lane gets back channels it holds here too, and takes the k-steps 0 .. j / 2.
+struct FragItem { int out, in0; bool folded; };
+template <int D>
+__device__ __forceinline__ FragItem frag_item(bool hw, int f, int l) {
+  FragItem x;
+  if (hw) {
+    int j = 0;
+    while (f >= j / 2 + 1) { f -= j / 2 + 1; ++j; }
+    const int m = l & 15;
+    x.out = j / 2 * 32 + 8 * (m >> 2) + 4 * (j & 1) + (m & 3);
+    x.in0 = 32 * f + 8 * (l >> 4);
+    x.folded = f < j / 2;
+  } else {
+    int jt = 0;
+    while (f >= 2 * jt + 2) { f -= 2 * jt + 2; ++jt; }
+    const int rho = l & 31;
+    x.out = ((rho >> 2) & 1) * (D / 2) + jt * 16 + 4 * (rho >> 3) + (rho & 3);
+    x.in0 = (l >> 5) * (D / 2) + f * 8;
+    x.folded = (f >> 1) < jt;
+  }
+  return x;
+}
+// What lane l of an extra fragment of k-step kt holds: eight channels from `c0` on of kind 0 (fp16 head of mu), 1 (its
+// tail) or 2 (rounding residual of the diagonal) of head g of the pass, or nothing (g < 0).  Rows of the 32 x 16
+// operands: [0, GH) heads, [GH, 2 GH) tails, [2 GH, 3 GH) residuals; of the 16 x 32 ones: 4 kind + g.
+struct ExtraItem { int g, kind, c0; };
+template <int D>
+__device__ __forceinline__ ExtraItem extra_item(bool hw, int GH, bool is_res, int kt, int l) {
+  ExtraItem x = {-1, -1, 0};
+  if (hw) {
+    const int m = l & 15;
+    x.c0 = 32 * kt + 8 * (l >> 4);
+    if (is_res == (m >> 2 == 2) && m < 12) { x.g = m & 3; x.kind = m >> 2; }
+  } else {
+    const int rho = l & 31;
+    x.c0 = (l >> 5) * (D / 2) + kt * 8;
+    if (!is_res && rho < 2 * GH) { x.g = rho % GH; x.kind = rho / GH; }
+    if (is_res && rho >= 2 * GH && rho < 3 * GH) { x.g = rho - 2 * GH; x.kind = 2; }
+  }
+  return x;
+}
+// k-steps of the extra rows
+constexpr int extra_ksteps(int D, bool hw) { return hw ? D / 32 : D / 16; }
 
 // an odd pitch: neither rows nor columns of Sigma in LDS pile up in a bank
 constexpr int stats_sigma_pitch(int D) { return D + 1; }
@@ -442,10 +499,10 @@ constexpr int stats_sigma_pitch(int D) { return D + 1; }
 // The fragments of one head (see above) out of its Sigma in LDS [D][pitch] and its mean shift + xbar, by the
 // 256 threads of a workgroup: the head's own fragments of the triangle, and its rows of the extra tile's.
 // The first head of a (unit, pass) also writes the rows and fragments that belong to no head.
-template <int D>
+template <int D, bool HW>
 __device__ __forceinline__ void stats_write_frags(const float* S, const float* s_shift, const float* s_xbar, int head,
                                                   const FragsOut& fo) {
-  constexpr int HALF = D / 2, NKS = D / 16, NJT = D / 32, NF = NJT * (NJT + 1), SP = stats_sigma_pitch(D);
+  constexpr int NJT = D / 32, NF = NJT * (NJT + 1), SP = stats_sigma_pitch(D);
   const int tid = threadIdx.x, lane = tid & 63;
   const int unit = head / fo.G, gq = head - unit * fo.G, pass = gq / fo.GH, g = gq - pass * fo.GH;
   const int nhere = min(fo.GH, fo.G - pass * fo.GH);          // heads of this (unit, pass)
@@ -463,53 +520,51 @@ __device__ __forceinline__ void stats_write_frags(const float* S, const float* s
     fo.post[(size_t)head * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
     fo.post[(size_t)head * 2 + 1] = 1.0f / (sqrtf((float)D) * smu);
   }
-  uint4* out = fo.frags + ((size_t)unit * fo.passes + pass) * fo.nfrag * 64;
+  uint4* out = fo.frags + head_frags(fo, unit, gq, NF) * 64;
 #pragma unroll
   for (int it = 0; it < (NF * 64 + 255) / 256; ++it) {
-    const int item = it * 256 + tid, f = item >> 6, l = item & 63, rho = l & 31, hl = l >> 5;
+    const int item = it * 256 + tid;
     if (NF * 64 % 256 != 0 && item >= NF * 64) break;
-    int rem = f, jt = 0;
-    while (rem >= 2 * jt + 2) { rem -= 2 * jt + 2; ++jt; }
-    const int c_out = ((rho >> 2) & 1) * HALF + jt * 16 + 4 * (rho >> 3) + (rho & 3), c_in0 = hl * HALF + rem * 8;
-    const bool folded = (rem >> 1) < jt;
+    const FragItem x = frag_item<D>(HW, item >> 6, item & 63);
     _Float16 h[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      float val = S[c_out * SP + c_in0 + i];
+      float val = S[x.out * SP + x.in0 + i];
       // (inside a 32 x 32 tile on the diagonal the two differ by rounding)
-      if (folded) val += S[(c_in0 + i) * SP + c_out];
+      if (x.folded) val += S[(x.in0 + i) * SP + x.out];
+      else if (HW) val = x.in0 + i < x.out ? 2.f * val : x.in0 + i == x.out ? val : 0.f;
       h[i] = (_Float16)(val * sM);
     }
-    out[g * NF * 64 + item] = pack_half8(h);
+    out[item] = pack_half8(h);
   }
-  for (int item = tid; item < 2 * NKS * 64; item += 256) {
-    const int fe = item >> 6, l = item & 63, rho = l & 31, hl = l >> 5;
-    const bool is_res = fe >= NKS;
-    const int kt = is_res ? fe - NKS : fe;
-    int row = -1, kind = -1;                                  // whose row this is
-    if (!is_res && rho < 2 * fo.GH) { row = rho % fo.GH; kind = rho / fo.GH; }
-    if (is_res && rho >= 2 * fo.GH && rho < 3 * fo.GH) { row = rho - 2 * fo.GH; kind = 2; }
-    const bool mine = row == g, nobodys = g == 0 && (row < 0 || row >= nhere);
+  constexpr int nks = extra_ksteps(D, HW);
+  out = fo.frags + extra_frags(fo, unit, pass, NF, nks) * 64;
+  for (int item = tid; item < 2 * nks * 64; item += 256) {
+    const int fe = item >> 6, l = item & 63;
+    const bool is_res = fe >= nks;
+    const ExtraItem x = extra_item<D>(HW, fo.GH, is_res, is_res ? fe - nks : fe, l);
+    const bool mine = x.g == g, nobodys = g == 0 && (x.g < 0 || x.g >= nhere);
     if (!mine && !nobodys) continue;
     _Float16 h[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int c = hl * HALF + kt * 8 + i;
+      const int c = x.c0 + i;
       float val = 0.f;
-      if (mine && kind == 2) {
+      if (mine && x.kind == 2) {
         const float m = S[c * SP + c] * sM;
         val = m - (float)(_Float16)m;
-      } else if (mine) {
+      } else if (mine && x.kind >= 0) {
         const float m = (s_shift[c] + s_xbar[c]) * smu;
         const float hi = (float)(_Float16)m;
-        val = kind == 0 ? hi : m - hi;
+        val = x.kind == 0 ? hi : m - hi;
       }
       h[i] = (_Float16)val;
     }
-    out[(fo.GH * NF) * 64 + item] = pack_half8(h);
+    out[item] = pack_half8(h);
   }
-  if (g == 0) {                                               // heads that the last pass has room for but not
+  if (g == 0 && !HW) {                                     // heads that the last pass has room for but not
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
+    out = fo.frags + head_frags(fo, unit, gq, NF) * 64;
     for (int item = nhere * NF * 64 + tid; item < fo.GH * NF * 64; item += 256) out[item] = z;
   }
 }
@@ -863,7 +918,8 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
       }
     }
     __syncthreads();
-    stats_write_frags<D>(S, s_shift, s_xbar, head, fo);
+    if (D == 128 && fo.hw) stats_write_frags<D, D == 128>(S, s_shift, s_xbar, head, fo);
+    else stats_write_frags<D, false>(S, s_shift, s_xbar, head, fo);
   } else if constexpr (!kViaLds) {
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -918,11 +974,8 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
 constexpr int kPrepSplit = 16;   // workgroups per (unit, pass)
 
 template <int D>
-__global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu,
-                                                    const float* __restrict__ sigma, int G,
-                                                    int GH, int passes, int nfrag, int shared_heads,
-                                                    uint4* __restrict__ frags,
-                                                    float* __restrict__ post, uint32_t* __restrict__ clear,
+__global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu, const float* __restrict__ sigma,
+                                                    FragsOut fo, int shared_heads, uint32_t* __restrict__ clear,
                                                     size_t clear_words) {
   // mu == nullptr: zero means.  shared_heads > 0: one set of that many heads' Sigma for every sequence.
   // clear: counters of the score kernel and what stands around them, zeroed on the way (one launch less)
@@ -930,10 +983,11 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
        i += (size_t)gridDim.x * gridDim.y * 256)
     clear[i] = 0u;
   auto sigma_of = [&](int unit_, int gq_) {
-    const int head = unit_ * G + gq_;
+    const int head = unit_ * fo.G + gq_;
     return sigma + (size_t)(shared_heads ? head % shared_heads : head) * D * D;
   };
-  constexpr int HALF = D / 2, NKS = D / 16, NJT = D / 32, NF = NJT * (NJT + 1);
+  constexpr int NJT = D / 32, NF = NJT * (NJT + 1);
+  const int G = fo.G, GH = fo.GH, passes = fo.passes, nks = extra_ksteps(D, fo.hw);
   __shared__ float s_scale[16];       // [2g] = sM, [2g+1] = smu   (GH <= 8)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int unit = blockIdx.x / passes, pass = blockIdx.x % passes;
@@ -959,26 +1013,23 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
       s_scale[2 * g] = sM;
       s_scale[2 * g + 1] = sm;
       if (gq < G && blockIdx.y == 0) {
-        post[((size_t)unit * G + gq) * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
-        post[((size_t)unit * G + gq) * 2 + 1] = 1.0f / (sqrtf((float)D) * sm);
+        fo.post[((size_t)unit * G + gq) * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
+        fo.post[((size_t)unit * G + gq) * 2 + 1] = 1.0f / (sqrtf((float)D) * sm);
       }
     }
   }
   __syncthreads();
 
-  uint4* out = frags + ((size_t)unit * passes + pass) * nfrag * 64;
-  for (int item = blockIdx.y * 256 + tid; item < nfrag * 64; item += kPrepSplit * 256) {
+  for (int item = blockIdx.y * 256 + tid; item < (GH * NF + 2 * nks) * 64; item += kPrepSplit * 256) {
     const int f = item >> 6, l = item & 63;
-    const int rho = l & 31, hl = l >> 5;
+    uint4* out;
     _Float16 h[8];
     if (f < GH * NF) {
-      const int g = f / NF;
-      int rem = f - g * NF, jt = 0;
-      while (rem >= 2 * jt + 2) { rem -= 2 * jt + 2; ++jt; }
-      const int kt = rem;
-      const int gq = g0 + g;
-      const int c_out = ((rho >> 2) & 1) * HALF + jt * 16 + 4 * (rho >> 3) + (rho & 3);
-      const int c_in0 = hl * HALF + kt * 8;
+      const int g = f / NF, gq = g0 + g;
+      if (fo.hw && gq >= G) continue;
+      out = fo.frags + (head_frags(fo, unit, gq, NF) + (f - g * NF)) * 64 + l;
+      const FragItem x = frag_item<D>(fo.hw, f - g * NF, l);
+      const int c_out = x.out, c_in0 = x.in0;
       const float sM = s_scale[2 * g];
       float val[8];
 #pragma unroll
@@ -992,40 +1043,40 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
         const float4 hi = *reinterpret_cast<const float4*>(S + (size_t)c_out * D + c_in0 + 4);
         val[0] = lo.x; val[1] = lo.y; val[2] = lo.z; val[3] = lo.w;
         val[4] = hi.x; val[5] = hi.y; val[6] = hi.z; val[7] = hi.w;
-        if ((kt >> 1) < jt) {
+        if (x.folded) {
 #pragma unroll
           for (int i = 0; i < 8; ++i) val[i] += S[(size_t)(c_in0 + i) * D + c_out];
+        } else if (fo.hw) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) val[i] = c_in0 + i < c_out ? 2.f * val[i] : c_in0 + i == c_out ? val[i] : 0.f;
         }
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) h[i] = (_Float16)(val[i] * sM);
     } else {
       const int fe = f - GH * NF;
-      const bool is_res = fe >= NKS;
-      const int kt = is_res ? fe - NKS : fe;
-      // rows: [0, GH) mu head, [GH, 2GH) mu tail, [2GH, 3GH) diagonal residual of M
-      int g = -1, kind = -1;
-      if (!is_res && rho < 2 * GH) { g = rho % GH; kind = rho / GH; }
-      if (is_res && rho >= 2 * GH && rho < 3 * GH) { g = rho - 2 * GH; kind = 2; }
-      const int gq = g0 + g;
+      const bool is_res = fe >= nks;
+      out = fo.frags + (extra_frags(fo, unit, pass, NF, nks) + fe) * 64 + l;
+      const ExtraItem x = extra_item<D>(fo.hw, GH, is_res, is_res ? fe - nks : fe, l);
+      const int gq = g0 + x.g;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int c_in = hl * HALF + kt * 8 + i;
+        const int c_in = x.c0 + i;
         float val = 0.f;
-        if (g >= 0 && gq < G) {
-          if (kind == 2) {
-            float m = sigma_of(unit, gq)[(size_t)c_in * D + c_in] * s_scale[2 * g];
+        if (x.kind >= 0 && gq < G) {
+          if (x.kind == 2) {
+            float m = sigma_of(unit, gq)[(size_t)c_in * D + c_in] * s_scale[2 * x.g];
             val = m - (float)(_Float16)m;
           } else {
-            float m = mu ? mu[((size_t)unit * G + gq) * D + c_in] * s_scale[2 * g + 1] : 0.f;
+            float m = mu ? mu[((size_t)unit * G + gq) * D + c_in] * s_scale[2 * x.g + 1] : 0.f;
             float hi = (float)(_Float16)m;
-            val = kind == 0 ? hi : m - hi;
+            val = x.kind == 0 ? hi : m - hi;
           }
         }
         h[i] = (_Float16)val;
       }
     }
-    out[item] = pack_half8(h);
+    *out = pack_half8(h);
   }
 }
 
@@ -1114,7 +1165,7 @@ static hipError_t launch_stats_frags_layout(const Dims& d, const void* q_win, in
 }
 hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_win, int w, const float2* tab,
                               uint4* frags, float* post, hipStream_t st) {
-  const FragsOut fo{frags, post, d.G, sp.GH, sp.passes, sp.nfrag};
+  const FragsOut fo{frags, post, d.G, sp.GH, sp.passes, sp.nfrag, sp.unit_frags, sp.hw};
   return d.rope_layout ? launch_stats_frags_layout<1>(d, q_win, w, tab, fo, st)
                        : launch_stats_frags_layout<0>(d, q_win, w, tab, fo, st);
 }
@@ -1124,12 +1175,10 @@ hipError_t launch_prep_frags(const Dims& d, const ScorePlan& sp, const float* mu
                              size_t clear_words, bool sigma_shared) {
   dim3 grid(d.units() * sp.passes, kPrepSplit);
   const int shared = sigma_shared ? d.Hq : 0;
-  if (d.D == 64)
-    k_prep_frags<64><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, shared, frags, post, clear, clear_words);
-  else if (d.D == 128)
-    k_prep_frags<128><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, shared, frags, post, clear, clear_words);
-  else
-    k_prep_frags<256><<<grid, 256, 0, st>>>(mu, sigma, d.G, sp.GH, sp.passes, sp.nfrag, shared, frags, post, clear, clear_words);
+  const FragsOut fo{frags, post, d.G, sp.GH, sp.passes, sp.nfrag, sp.unit_frags, sp.hw};
+  if (d.D == 64) k_prep_frags<64><<<grid, 256, 0, st>>>(mu, sigma, fo, shared, clear, clear_words);
+  else if (d.D == 128) k_prep_frags<128><<<grid, 256, 0, st>>>(mu, sigma, fo, shared, clear, clear_words);
+  else k_prep_frags<256><<<grid, 256, 0, st>>>(mu, sigma, fo, shared, clear, clear_words);
   return hipGetLastError();
 }
 

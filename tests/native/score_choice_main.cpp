@@ -1,0 +1,63 @@
+// Host-only driver: whatever kernel a call's score plan names, its fragments and partials fit the workspace, no
+// workgroup is without a tile at the start, and the tiles that the register-fragment kernel deals out (two to every
+// workgroup by its number, the rest by counters, one per residue class) are every tile of a head once.
+#include <initializer_list>
+#include <stdio.h>
+#include <string.h>
+
+#include <vector>
+
+#include "../../paper_2510_00636_amd/csrc/ea_common.h"
+
+static int failures = 0;
+#define CHECK(cond, ...)                                                         \
+  do {                                                                           \
+    if (!(cond) && ++failures <= 20) {                                           \
+      fprintf(stderr, "%s:%d: check failed: %s: ", __FILE__, __LINE__, #cond);   \
+      fprintf(stderr, __VA_ARGS__);                                              \
+      fprintf(stderr, "\n");                                                     \
+    }                                                                            \
+  } while (0)
+
+int main() {
+  int registers = 0;
+  for (int d : {64, 128, 256})
+    for (int G = 1; G <= 64; ++G)
+      for (int units : {1, 2, 3, 8, 33, 192, 600})
+        for (int64_t n : {(int64_t)1, (int64_t)63, (int64_t)64, (int64_t)65, (int64_t)4608, (int64_t)131072})
+          for (int fp8 = 0; fp8 <= (d >= 128); ++fp8)
+            for (int paged = 0; paged <= !fp8; ++paged)
+              for (int cu : {64, 256, 304}) {
+                ea_params p;
+                memset(&p, 0, sizeof p);
+                p.batch = 1; p.n_q_heads = G * units; p.n_kv_heads = units; p.head_dim = d; p.dtype = EA_BF16;
+                p.q_is_rotated = 1; p.horizon_T = 512;
+                ea::Dims dims;
+                CHECK(ea::check_params(&p, &dims) == EA_OK, "d %d G %d", d, G);
+                dims.kv_fp8 = fp8;
+                const ea::WsLayout L = ea::make_ws_layout(dims, n, 64);
+                const ea::ScorePlan sp = ea::choose_score_plan(dims, n, cu, paged);
+                CHECK((size_t)units * sp.unit_frags * 1024 <= L.post - L.frags, "d %d G %d units %d n %ld fragments", d, G, units, (long)n);
+                CHECK((size_t)dims.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
+                if (!sp.hw) continue;
+                ++registers;
+                const int64_t ntiles = (n + ea::kHwTile - 1) / ea::kHwTile;
+                CHECK(n >= ea::kHwTile && d == 128 && sp.nchunk >= 1 && sp.nchunk <= ntiles, "n %ld: %d workgroups", (long)n, sp.nchunk);
+                CHECK(sp.passes * 4 >= G && sp.passes * 4 < G + 4, "G %d: %d passes", G, sp.passes);
+              }
+  CHECK(registers > 1000, "%d plans", registers);
+  for (int nchunk = 1; nchunk <= 600; ++nchunk) {
+    const int ways = nchunk / 8 < 1 ? 1 : nchunk / 8 > 8 ? 8 : nchunk / 8;
+    std::vector<std::vector<int>> members(ways);
+    for (int chunk = 0; chunk < nchunk; ++chunk) {
+      const ea::HwDeal x = ea::hw_deal(chunk, nchunk, ways);
+      CHECK(x.way >= 0 && x.way < ways && x.nth == (int)members[x.way].size(), "workgroup %d of %d", chunk, nchunk);
+      members[x.way].push_back(x.peers);
+    }
+    for (const auto& m : members)
+      for (int peers : m) CHECK(peers == (int)m.size(), "%d workgroups: %d peers of %zu", nchunk, peers, m.size());
+  }
+  if (failures) return 1;
+  printf("score plans fit\n");
+  return 0;
+}

@@ -344,3 +344,35 @@ def test_adaptive_pass_over_long_heads(n, w, floor):
     ea.compress_layer_adaptive(p, P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"],
                                P.to_dev(lay["k"]), v, n, n, n_keep, floor, None, idx, lengths, ws)
     assert ea.debug_status(p, n, w, ws) & ea.STATUS_BAD_SCORE
+
+
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (6, 2), (4, 1), (5, 1), (6, 1), (14, 2), (9, 1)])
+@pytest.mark.parametrize("n", [63, 64, 65, 128, 1000, 1040])
+def test_register_fragment_scores_at_tile_edges(hq, hkv, n):
+    """d = 128, passes of four query heads with one to four wavefronts at work, tiles of 64 keys: heads around one
+    tile, the ragged last one inside a group of 16 keys and at its edge, on contiguous tensors (rows beyond n hold
+    NaN), block pools and 8-bit caches, all in the workspace that workspace_bytes gives.  Against the oracle at the
+    bf16 tolerance; the pools' scores against the contiguous ones to 2e-5 (the same fp16 products)."""
+    import torch
+    from ea_inputs import make_block_pools, quantize_fp8
+    cfg = CONFIGS["c2"].with_(n_q_heads=hq, n_kv_heads=hkv)
+    lay = make_layer(cfg, n=n, window=32)
+    p = P.params_for(cfg, epsilon=0.02)
+    mu, sigma = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T)
+    mu, sigma = mu.astype(np.float32), sigma.astype(np.float32)
+    contiguous = P.run_score(cfg, lay, mu, sigma, 0.02, n_cap=n + 5)
+    P.check_scores(contiguous, O.scores(widen(lay["k"]), widen(lay["v"]), mu, sigma, 0.02), 2e-3)
+    kp, vp, tab, nb = make_block_pools(lay["k"], lay["v"], 16, 3)
+    tabd = torch.from_numpy(tab).cuda()
+    sc = torch.empty(1, hkv, n, device="cuda")
+    ws = P.workspace(p, n, 1)
+    ea.score_paged(p, P.to_dev(kp), P.to_dev(vp), ea.make_paged(tabd, 16, nb), n, P.to_dev(mu), P.to_dev(sigma), sc, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(sc.cpu().numpy(), contiguous, rtol=2e-5, atol=0)
+    k8, ks = quantize_fp8(widen(lay["k"]))
+    v8, vs = quantize_fp8(widen(lay["v"]))
+    k8d, v8d, ksd, vsd = (torch.from_numpy(x).cuda() for x in (k8, v8, ks, vs))
+    ea.score_fp8(p, k8d, v8d, ksd, vsd, n, n, P.to_dev(mu), P.to_dev(sigma), sc, ws)
+    torch.cuda.synchronize()
+    real = [X.fp8_e4m3_decode(c) * s.astype(np.float64)[:, :, None, None] for c, s in ((k8, ks), (v8, vs))]
+    P.check_scores(sc.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), 0.02), 2e-3)

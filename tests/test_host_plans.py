@@ -19,3 +19,15 @@ def test_every_plan_fits_the_workspace(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "host plans fit" in r.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_chosen_score_plans_fit_the_workspace(tmp_path):
+    exe = str(tmp_path / "score_choice")
+    cmd = ["g++", "-std=c++17", "-O1", "-o", exe, os.path.join(ROOT, "tests", "native", "score_choice_main.cpp"),
+           os.path.join(ROOT, "paper_2510_00636_amd", "csrc", "ea_host.cpp")]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert "score plans fit" in r.stdout
