@@ -63,20 +63,21 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
 // to d/16 KiB x 2, are put together in LDS from Sigma by the four wavefronts and then used by each
 // for its KT x 16 keys, which stay in registers as fp32.
 //
-// What bounds it is the matrix cores' fp64 rate (64 cycles per instruction, 33 us of the first shape
-// below) and, at two wavefronts per SIMD, the latency around the slabs.  The vector units' fp64 rate
-// is the same, but the kernel on them that this replaces did the dense product and converted both
-// operands of every multiplication: 28 query heads x 5003 keys at d = 128 338 -> 82 us, 32 x 16000 at
-// d = 64 303 -> 83 us, 16 x 2000 at d = 256 446 -> 72 us, 4 x 1024 at d = 64 27 -> 10 us.
+// What bounds it is the matrix cores' fp64 rate (64 cycles per instruction, 37 us of the 63 that the first shape below
+// takes) and the latency around it.  Slabs of M per step, in turn with their use, left the matrix cores idle 60 % of the
+// time; at d = 64 and 128 all of M fits in LDS (k_score_f32_whole).  score, 28 query heads x 5003 keys at d = 128 83 -> 73
+// us, x 12000 157 -> 136; 8 x 9000 59 -> 51; 32 x 16000 at d = 64 84 -> 68, 4 x 1024 13.3 -> 12.5.  (The next tiles' rows
+// requested ahead: 1 to 2 us slower; three tiles at a time: no registers for it.)  At d = 256 M takes 272 KiB and comes in
+// slabs (16 x 2000 72 us).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-template <int D, int KT>
-__global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 5 - KT : 2)) void k_score_f32(const float* __restrict__ k, const float* __restrict__ v, long long n,
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_score_f32(const float* __restrict__ k, const float* __restrict__ v, long long n,
                                                    long long n_cap, const float* __restrict__ mu,
                                                    const float* __restrict__ sigma, int G, int units, int span,
                                                    int nchunk, double* __restrict__ logits, float* __restrict__ vnorm,
                                                    double2* __restrict__ part) {
-  constexpr int QW = D / 4, NT = D / 16;
+  constexpr int QW = D / 4, NT = D / 16, KT = 1;
   __shared__ double s_a[NT * 4 * 64];       // fragments of a slab, [k-step][lane]
   __shared__ double s_mu[D];
   __shared__ double s_ms[4][2];
@@ -227,32 +228,218 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : D == 128 ? 5 - KT : 2)) void k_
   }
 }
 
+// d = 64 and 128: all of the folded M, 20 or 72 KiB of it, stands in LDS from the start (one memory latency and one barrier
+// per workgroup instead of one of each per slab and 64 or 128 keys), and the wavefronts then go their own ways through
+// every fourth tile of 16 keys of the workgroup's span, two at a time.  Two workgroups fit a CU at d = 128.  Same
+// arithmetic per key as above.
+template <int D>
+__global__ __launch_bounds__(256, D == 64 ? 4 : 2) void k_score_f32_whole(const float* __restrict__ k, const float* __restrict__ v, long long n,
+                                                   long long n_cap, const float* __restrict__ mu,
+                                                   const float* __restrict__ sigma, int G, int units, int span,
+                                                   int nchunk, double* __restrict__ logits, float* __restrict__ vnorm,
+                                                   double2* __restrict__ part) {
+  constexpr int QW = D / 4, NT = D / 16, NB = NT * (NT + 1) / 2;
+  extern __shared__ __align__(16) double s_m[];    // blocks (jt, b), b <= jt, of 4 fragments [lane] each, then mu
+  double* s_mu = s_m + NB * 256;
+  __shared__ double s_ms[4][2];
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int unit = blockIdx.x % units;
+  const int t2 = blockIdx.x / units;
+  const int gq = t2 % G, chunk = t2 / G;
+  const float* S = sigma + ((size_t)unit * G + gq) * D * D;
+  const float* kb = k + (size_t)unit * n_cap * D;
+  const float* vb = v + (size_t)unit * n_cap * D;
+  const long long key_lo = (long long)chunk * span, key_hi = min(key_lo + (long long)span, n);
+  {
+    // block `at` of the triangle, jt rows down and b along: M's own side and, for b < jt, the mirrored entries
+    constexpr int PER = (NB + 3) / 4;
+    const int ms = (lane >> 2) & 3, mq = lane & 3;
+    float4 own[PER], mir[PER];
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int at = min(wave + 4 * x, NB - 1);
+      int jt = 0, b = at;
+      while (b > jt) { b -= jt + 1; ++jt; }
+      own[x] = *reinterpret_cast<const float4*>(S + (size_t)((r & 3) * QW + 4 * jt + (r >> 2)) * D + q * QW + 4 * b);
+      mir[x] = *reinterpret_cast<const float4*>(S + (size_t)(q * QW + 4 * b + ms) * D + mq * QW + 4 * jt);
+    }
+    if (tid < D) s_mu[tid] = (double)mu[((size_t)unit * G + gq) * D + tid];
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int at = wave + 4 * x;
+      if (at < NB) {
+        double* to = s_m + at * 256;
+        to[lane] = own[x].x;
+        to[64 + lane] = own[x].y;
+        to[128 + lane] = own[x].z;
+        to[192 + lane] = own[x].w;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+      const int at = wave + 4 * x;
+      int jt = 0, b = at;
+      while (b > jt) { b -= jt + 1; ++jt; }
+      if (at < NB && b < jt) {
+        double* am = s_m + at * 256 + ms * 64 + q * 16 + mq;
+        am[0] += (double)mir[x].x;
+        am[4] += (double)mir[x].y;
+        am[8] += (double)mir[x].z;
+        am[12] += (double)mir[x].w;
+      }
+    }
+  }
+  __syncthreads();
+  double m_run = -INFINITY, s_run = 0.0;    // of the keys in this lane's slots r
+  auto tiles = [&](auto kt_, long long key0) __attribute__((always_inline)) {      // tiles at key0 and key0 + 64
+    constexpr int KT = decltype(kt_)::value;
+    float kf[KT][QW];
+    long long key[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      key[t] = key0 + t * 64 + r;
+      const float4* kp = reinterpret_cast<const float4*>(kb + min(key[t], n - 1) * D + q * QW);
+#pragma unroll
+      for (int x = 0; x < QW / 4; ++x) {
+        const float4 f = kp[x];
+        kf[t][4 * x] = f.x; kf[t][4 * x + 1] = f.y; kf[t][4 * x + 2] = f.z; kf[t][4 * x + 3] = f.w;
+      }
+    }
+    double lin[KT], quad[KT];
+#pragma unroll
+    for (int t = 0; t < KT; ++t) { lin[t] = 0.0; quad[t] = 0.0; }
+#pragma unroll
+    for (int x = 0; x < QW; ++x) {
+      const double m = s_mu[q * QW + x];
+#pragma unroll
+      for (int t = 0; t < KT; ++t) lin[t] = fma(m, (double)kf[t][x], lin[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(lin[t]));
+    static_for<NT>([&](auto jt_) {
+      constexpr int jt = decltype(jt_)::value, at = jt * (jt + 1) / 2;
+      // (keeps the compiler from holding the keys widened to 64 bits across the tiles)
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int x = 0; x < QW; ++x) asm volatile("" : "+v"(kf[t][x]));
+      doublex4 acc[KT];
+#pragma unroll
+      for (int t = 0; t < KT; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+      double f[2][4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[0][e] = s_m[(at * 4 + e) * 64 + lane];
+      static_for<jt + 1>([&](auto b_) {
+        constexpr int b = decltype(b_)::value;
+        if constexpr (b < jt) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) f[(b + 1) & 1][e] = s_m[((at + b + 1) * 4 + e) * 64 + lane];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < KT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[b & 1][e], (double)kf[t][4 * b + e], acc[t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) quad[t] = fma(acc[t][x], (double)kf[t][4 * jt + x], quad[t]);
+#pragma unroll
+      for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(quad[t]));
+    });
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      double lg = lin[t] / sqrt((double)D) + quad[t] / (2.0 * D);
+      lg += __shfl_xor(lg, 16);
+      lg += __shfl_xor(lg, 32);
+      if (key[t] < n) {
+        if (q == 0) logits[((size_t)unit * G + gq) * n + key[t]] = lg;
+        const double mn = fmax(m_run, lg);
+        s_run = s_run * exp(m_run - mn) + exp(lg - mn);
+        m_run = mn;
+      }
+      if (((key0 + t * 64) >> 4) % G == gq) {        // the value norms: dealt to the group's heads tile by tile
+        const float4* vp = reinterpret_cast<const float4*>(vb + min(key[t], n - 1) * D + q * QW);
+        double ss = 0.0;
+#pragma unroll
+        for (int x = 0; x < QW / 4; ++x) {
+          const float4 f = vp[x];
+          ss = fma((double)f.x, (double)f.x, ss);
+          ss = fma((double)f.y, (double)f.y, ss);
+          ss = fma((double)f.z, (double)f.z, ss);
+          ss = fma((double)f.w, (double)f.w, ss);
+        }
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        if (q == 0 && key[t] < n) vnorm[(size_t)unit * n + key[t]] = (float)sqrt(ss);
+      }
+    }
+  };
+  long long key0 = key_lo + wave * 16;
+  for (; key0 + 64 < key_hi; key0 += 128) tiles(std::integral_constant<int, 2>{}, key0);
+  if (key0 < key_hi) tiles(std::integral_constant<int, 1>{}, key0);
+  // (max, sum exp) of the span: the 16 key slots of each wavefront, then the four wavefronts
+  double m = m_run, s = s_run;
+  auto merge = [&](double m2, double s2) {
+    const double mn = fmax(m, m2);
+    if (mn == -INFINITY) s = 0.0;
+    else s = s * exp(m - mn) + s2 * exp(m2 - mn);
+    m = mn;
+  };
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1) merge(__shfl_xor(m, o), __shfl_xor(s, o));
+  if (lane == 0) { s_ms[wave][0] = m; s_ms[wave][1] = s; }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 4; ++w) merge(s_ms[w][0], s_ms[w][1]);
+    part[((size_t)unit * G + gq) * nchunk + chunk] = make_double2(m, s);
+  }
+}
+
+template <int D>
+static hipError_t launch_f32_whole(const Dims& d, const float* k, const float* v, int64_t n, int64_t n_cap, const float* mu,
+                                   const float* sigma, double* logits, float* vnorm, double2* part, int* nchunk_out,
+                                   hipStream_t st) {
+  constexpr int NT = D / 16;
+  const size_t lds = (size_t)(NT * (NT + 1) / 2 * 256 + D) * sizeof(double);
+  auto kern = k_score_f32_whole<D>;
+  static LdsOptIn opt;
+  hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);
+  if (e != hipSuccess) return e;
+  // Spans of whole 64 keys.  The workgroups that fit the chip at once do the same amount each, so what counts is rounds of
+  // them x (tiles per wavefront + what a workgroup pays at its start).
+  const int64_t heads = d.qheads(), steps = (n + 63) / 64, slots = (int64_t)device_num_cu() * (D == 64 ? 4 : 2);
+  int64_t best = 0, best_cost = 0;
+  for (int64_t c = 1; c <= steps && c <= 1024; ++c) {
+    const int64_t per = (steps + c - 1) / c, rounds = (heads * c + slots - 1) / slots, cost = rounds * (2 * per + 1);
+    if (best == 0 || cost < best_cost) { best = c; best_cost = cost; }
+  }
+  const int64_t span = (steps + best - 1) / best * 64;
+  const int nchunk = (int)((n + span - 1) / span);
+  *nchunk_out = nchunk;
+  kern<<<(unsigned)(heads * nchunk), 256, lds, st>>>(k, v, n, n_cap, mu, sigma, d.G, d.units(), (int)span, nchunk, logits, vnorm, part);
+  return hipGetLastError();
+}
+
 hipError_t launch_score_f32(const Dims& d, const void* k, const void* v, int64_t n, int64_t n_cap,
                             const float* mu, const float* sigma, double* logits, float* vnorm,
                             double2* part, int* nchunk_out, hipStream_t st) {
-  // 64 KT keys per workgroup and step: two key tiles per wavefront halve the reads and the building of
-  // the slabs per key, once that still leaves two workgroups per CU (at d = 256 one tile's keys fill the
-  // registers); spans so that a head has at most 1024 partials
-  const int64_t heads = d.qheads();
-  const int kt = d.D <= 128 && heads * ((n + 127) / 128) >= 2 * (int64_t)device_num_cu() ? 2 : 1;
+  if (d.D == 64) return launch_f32_whole<64>(d, (const float*)k, (const float*)v, n, n_cap, mu, sigma, logits, vnorm, part, nchunk_out, st);
+  if (d.D == 128) return launch_f32_whole<128>(d, (const float*)k, (const float*)v, n, n_cap, mu, sigma, logits, vnorm, part, nchunk_out, st);
+  // 64 keys per workgroup and step, spans so that a head has at most 1024 partials
   int64_t span = (n + 1023) / 1024;
-  span = (span + 64 * kt - 1) / (64 * kt) * (64 * kt);
-  int nchunk = (int)((n + span - 1) / span);
+  span = (span + 63) / 64 * 64;
+  const int nchunk = (int)((n + span - 1) / span);
   *nchunk_out = nchunk;
-  const int64_t grid = heads * nchunk;
-#define EA_F32(DD, KK)                                                                             \
-  if (d.D == DD && kt == KK) {                                                                     \
-    k_score_f32<DD, KK><<<(unsigned)grid, 256, 0, st>>>((const float*)k, (const float*)v, n, n_cap, mu, sigma, d.G, \
-                                                        d.units(), (int)span, nchunk, logits, vnorm, part); \
-    return hipGetLastError();                                                                      \
-  }
-  EA_F32(64, 1)
-  EA_F32(64, 2)
-  EA_F32(128, 1)
-  EA_F32(128, 2)
-  EA_F32(256, 1)
-#undef EA_F32
-  return hipErrorInvalidValue;
+  if (d.D != 256) return hipErrorInvalidValue;
+  k_score_f32<256><<<(unsigned)((int64_t)d.qheads() * nchunk), 256, 0, st>>>((const float*)k, (const float*)v, n, n_cap, mu, sigma, d.G,
+                                                                   d.units(), (int)span, nchunk, logits, vnorm, part);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------
