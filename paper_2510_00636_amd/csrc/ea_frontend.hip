@@ -53,72 +53,105 @@ __global__ __launch_bounds__(256) void k_project(const void* __restrict__ hidden
   }
 }
 
-// The same projection on the matrix cores, for bf16 inputs whose rows are 16-byte aligned
-// (d_model a multiple of 8): one workgroup = a 32 (samples) x 32 (channels) tile, its operands
-// read straight from global memory in the layout v_mfma_f32_32x32x16_bf16 takes them -- lane
-// (r, hh) = (lane % 32, lane / 32) holds 8 consecutive d_model entries of row r, of the hidden
-// states as A operand and of W_Q as B operand; the instruction does not care which 16 of the
-// d_model entries it is given as long as both operands agree, so per block of 64 entries half hh
-// takes the 32 contiguous ones at 32 hh (64 contiguous bytes per lane, 128 per row) and the block
-// is four instructions.  The four wavefronts split the d_model axis into four contiguous quarters
-// (a short dependent chain each, 2048 wavefronts in flight at the Llama-8B shape); the four partial
-// tiles meet in LDS and are added in wavefront order, so the result does not depend on timing.
-// bf16 products are exact in fp32.
+// The same projection on the matrix cores, for bf16 inputs whose rows are 16-byte aligned (d_model a
+// multiple of 8): one workgroup = 16 MT samples x 32 channels, its operands read straight from global memory in
+// the layout v_mfma_f32_16x16x32_bf16 takes them: lane (c, q) = (lane % 16, lane / 16) holds 8 consecutive d_model
+// entries of row c, so that four lanes read 64 contiguous bytes of a row and the two k-steps of a block of 64
+// entries its whole 128-byte line.  The NW wavefronts split the d_model axis into as many contiguous parts; the
+// partial tiles meet in LDS and are added in wavefront order, so the result does not depend on timing.  bf16
+// products are exact in fp32.
+//
+// What bounds it is the way of the hidden states from L2 into the workgroups of every 32 channels.  With the 32x32x16
+// form a lane read 64 contiguous bytes in four instructions, each of which touched 64 lines for 16 bytes of them, and
+// every 32 samples read W_Q again: 128 x 4096 hidden states, 32 heads of 128 channels 36.5 -> 27.6 us (the matrix W_Q
+// alone takes 5.4 at the rate of a large read).
 typedef __bf16 pj_bf16x8 __attribute__((ext_vector_type(8)));
-typedef float pj_floatx16 __attribute__((ext_vector_type(16)));
+typedef float pj_floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t pj_u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_project_mfma(const uint16_t* __restrict__ hidden,
+template <int MT, int NW>
+__global__ __launch_bounds__(64 * NW) void k_project_mfma(const uint16_t* __restrict__ hidden,
                                                       const uint16_t* __restrict__ wq, int w, int dm, int D, int Hq,
-                                                      float* __restrict__ q) {
-  __shared__ float s_acc[4][16][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane & 31, hh = lane >> 5;
-  const int t0 = blockIdx.x * 32, b = blockIdx.z;
+                                                      float* __restrict__ q_out) {
+  __shared__ float s_acc[NW][16 * MT][32];
+  const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t0 = blockIdx.x * 16 * MT, b = blockIdx.z;
   const int g = (blockIdx.y * 32) / D, c0 = (blockIdx.y * 32) % D;
-  const int kq = ((dm + 255) / 256) * 64;               // entries per wavefront, a multiple of the block
-  const int kbeg = wave * kq, kend = min(dm, kbeg + kq);
-  const uint16_t* arow = hidden + ((size_t)b * w + min(t0 + r, w - 1)) * dm + hh * 32;
-  const uint16_t* brow = wq + ((size_t)g * D + c0 + r) * dm + hh * 32;
-  pj_floatx16 acc;
+  const int kq = (dm + 64 * NW - 1) / (64 * NW) * 64;     // entries per wavefront, a multiple of the block
+  const int kbeg = min(dm, wave * kq), kend = min(dm, kbeg + kq);
+  const uint16_t* arow[MT];
+  const uint16_t* brow[2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  const pj_u32x4 zero4 = {0u, 0u, 0u, 0u};
-  auto fetch = [&](int k0, pj_u32x4 (&a)[4], pj_u32x4 (&bq)[4]) {
+  for (int m = 0; m < MT; ++m) arow[m] = hidden + ((size_t)b * w + min(t0 + 16 * m + c, w - 1)) * dm + q * 8;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int kk = k0 + hh * 32 + j * 8;              // d_model % 8 == 0: a chunk lies inside the row or outside
-      const bool ok = kk < kend;                        // (kend - kbeg is a multiple of 8 as well)
-      a[j] = ok ? *reinterpret_cast<const pj_u32x4*>(arow + k0 + j * 8) : zero4;
-      bq[j] = ok ? *reinterpret_cast<const pj_u32x4*>(brow + k0 + j * 8) : zero4;
+  for (int x = 0; x < 2; ++x) brow[x] = wq + ((size_t)g * D + c0 + 16 * x + c) * dm + q * 8;
+  pj_floatx4 acc[MT][2];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[m][x] = pj_floatx4{0.f, 0.f, 0.f, 0.f};
+  struct Block { pj_u32x4 a[2][MT], w[2][2]; };
+  auto fetch = [&](int k0, Block& f) __attribute__((always_inline)) {      // 64 entries, all inside the row
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) f.a[s][m] = *reinterpret_cast<const pj_u32x4*>(arow[m] + k0 + 32 * s);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) f.w[s][x] = *reinterpret_cast<const pj_u32x4*>(brow[x] + k0 + 32 * s);
     }
   };
-  pj_u32x4 a0[4], b0[4], a1[4], b1[4];
-  fetch(kbeg, a0, b0);
-  for (int k0 = kbeg; k0 < kend; k0 += 128) {
-    fetch(k0 + 64, a1, b1);                             // (past the end: all chunks are zeros, nothing is read)
+  auto multiply = [&](const Block& f) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(pj_bf16x8, a0[j]),
-                                                    __builtin_bit_cast(pj_bf16x8, b0[j]), acc, 0, 0, 0);
-    fetch(k0 + 128, a0, b0);
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(pj_bf16x8, a1[j]),
-                                                    __builtin_bit_cast(pj_bf16x8, b1[j]), acc, 0, 0, 0);
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+          acc[m][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(pj_bf16x8, f.a[s][m]),
+                                                             __builtin_bit_cast(pj_bf16x8, f.w[s][x]), acc[m][x], 0, 0, 0);
+  };
+  const int full = (kend - kbeg) / 64;
+  if (full > 0) {
+    Block f0, f1;
+    fetch(kbeg, f0);
+    for (int i = 0; i < full; i += 2) {                    // (past the last block: it once more, not used)
+      fetch(kbeg + 64 * min(i + 1, full - 1), f1);
+      multiply(f0);
+      fetch(kbeg + 64 * min(i + 2, full - 1), f0);
+      if (i + 1 < full) multiply(f1);
+    }
   }
+  const int k0 = kbeg + 64 * full;
+  if (k0 < kend) {                                         // d_model % 64 entries: a lane's eight lie inside the row or outside
+    Block f;
+    const pj_u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int v = 0; v < 16; ++v) s_acc[wave][v][lane] = acc[v];
+    for (int s = 0; s < 2; ++s) {
+      const bool in = k0 + 32 * s + 8 * q < kend;
+#pragma unroll
+      for (int m = 0; m < MT; ++m) f.a[s][m] = in ? *reinterpret_cast<const pj_u32x4*>(arow[m] + k0 + 32 * s) : zero4;
+#pragma unroll
+      for (int x = 0; x < 2; ++x) f.w[s][x] = in ? *reinterpret_cast<const pj_u32x4*>(brow[x] + k0 + 32 * s) : zero4;
+    }
+    multiply(f);
+  }
+  // accumulator register v of lane (c, q) is the tile's entry (row 4 q + v, column c)
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s_acc[wave][16 * m + 4 * q + v][16 * x + c] = acc[m][x][v];
   __syncthreads();
-  // accumulator register v of lane (r, hh) is the tile's entry (row 8 (v / 4) + 4 hh + v % 4, column r);
-  // wavefront i adds and stores registers 4 i .. 4 i + 3
-  float* out = q + (((size_t)b * Hq + g) * w) * D + c0 + r;
+  float* out = q_out + (((size_t)b * Hq + g) * w) * D + c0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = 4 * wave + i;
-    const float sum = ((s_acc[0][v][lane] + s_acc[1][v][lane]) + s_acc[2][v][lane]) + s_acc[3][v][lane];
-    const int t = t0 + 8 * wave + 4 * hh + i;
-    if (t < w) out[(size_t)t * D] = sum;
+  for (int i = 0; i < 8 * MT / NW; ++i) {
+    const int e = tid + 64 * NW * i, t = e >> 5, ch = e & 31;
+    float sum = s_acc[0][t][ch];
+#pragma unroll
+    for (int p = 1; p < NW; ++p) sum += s_acc[p][t][ch];
+    if (t0 + t < w) out[(size_t)(t0 + t) * D + ch] = sum;
   }
 }
 
@@ -166,8 +199,27 @@ hipError_t launch_gram(const Dims& d, const void* w_o, int dm, float* gram, hipS
 hipError_t launch_project(const Dims& d, const void* hidden, const void* wq, int w, int dm, float* q,
                           hipStream_t st) {
   if (d.dtype == EA_BF16 && dm % 8 == 0 && ((uintptr_t)hidden % 16) == 0 && ((uintptr_t)wq % 16) == 0) {
-    dim3 gm((w + 31) / 32, d.Hq * d.D / 32, d.B);
-    k_project_mfma<<<gm, 256, 0, st>>>((const uint16_t*)hidden, (const uint16_t*)wq, w, dm, d.D, d.Hq, q);
+    // The more samples a workgroup takes, the less often W_Q is read: as many as leave workgroups for three quarters of the
+    // CUs (with the statistics, us: 64 x 4096 and 32 heads of 128 channels, 64 samples 37.8, 32 29.7; 100 x 4104 and 24
+    // heads 35.1 and 44.3).
+    auto blocks = [&](int mt) { return (int64_t)((w + 16 * mt - 1) / (16 * mt)) * (d.Hq * d.D / 32) * d.B; };
+    int mt = w > 32 ? 4 : w > 16 ? 2 : 1;
+    while (mt > 1 && blocks(mt) * 4 < 3 * (int64_t)device_num_cu()) mt /= 2;
+    const dim3 gm((unsigned)((w + 16 * mt - 1) / (16 * mt)), (unsigned)(d.Hq * d.D / 32), (unsigned)d.B);
+    const uint16_t* h = (const uint16_t*)hidden;
+    const uint16_t* m = (const uint16_t*)wq;
+#define EA_PROJECT(MM, NN) \
+  if (mt == MM && nw == NN) k_project_mfma<MM, NN><<<gm, 64 * NN, 0, st>>>(h, m, w, dm, d.D, d.Hq, q)
+    // four wavefronts over d_model where there are more workgroups than CUs or little to split (320 workgroups x 5120 entries 76
+    // and 72.5 us with the statistics, 256 x 4096 40.5 and 43.7)
+    const int nw = blocks(mt) > device_num_cu() || dm <= 2048 ? 4 : 8;
+    EA_PROJECT(4, 8);
+    EA_PROJECT(2, 8);
+    EA_PROJECT(1, 8);
+    EA_PROJECT(4, 4);
+    EA_PROJECT(2, 4);
+    EA_PROJECT(1, 4);
+#undef EA_PROJECT
     return hipGetLastError();
   }
   dim3 grid((w + 31) / 32, d.D / 32, d.qheads());

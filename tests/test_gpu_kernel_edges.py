@@ -376,3 +376,23 @@ def test_register_fragment_scores_at_tile_edges(hq, hkv, n):
     torch.cuda.synchronize()
     real = [X.fp8_e4m3_decode(c) * s.astype(np.float64)[:, :, None, None] for c, s in ((k8, ks), (v8, vs))]
     P.check_scores(sc.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), 0.02), 2e-3)
+
+
+@pytest.mark.parametrize("w,dm,hq", [(16, 64, 2), (17, 512, 2), (33, 520, 2), (65, 2056, 2), (100, 4104, 24)])
+def test_projection_tile_edges(w, dm, hq):
+    """bf16 projections around the edges of their tiles of 16, 32 and 64 samples, four and eight parts of the d_model
+    axis, parts that are empty and parts that end inside a block of 64 entries.  Against Eq. 5 in fp64 at the tolerance
+    of the statistics: products of bf16 numbers are exact, their fp32 sums carry about sqrt(d_model) 2^-24."""
+    import torch
+    from ea_inputs import bf16_bits_from_f64, inv_freq_table
+    cfg = CONFIGS["c2"].with_(n_q_heads=hq, n_kv_heads=2)
+    r = np.random.default_rng(w + dm)
+    hb = bf16_bits_from_f64(r.standard_normal((1, w, dm)) * 1.5 + r.standard_normal(dm))
+    wb = bf16_bits_from_f64(r.standard_normal((hq, 128, dm)) / np.sqrt(dm))
+    inv = inv_freq_table(128, cfg.rope_base)
+    p = P.params_for(cfg)
+    mu, sg = torch.empty(1, hq, 128, device="cuda"), torch.empty(1, hq, 128, 128, device="cuda")
+    ea.query_stats_hidden(p, P.to_dev(hb), P.to_dev(wb), dm, w, P.to_dev(inv), 70000, mu, sg, P.workspace(p, 8, w))
+    torch.cuda.synchronize()
+    rmu, rsg = X.query_stats_hidden(widen(hb), widen(wb), inv, 70000, T=cfg.horizon_T)
+    P.check_stats(mu.cpu().numpy(), sg.cpu().numpy(), rmu, rsg)
