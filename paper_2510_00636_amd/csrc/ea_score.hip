@@ -15,7 +15,7 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
                              int64_t n, int64_t n_cap, const uint4* frags, const float* post,
                              float* logits, float* vnorm, float2* part, uint32_t* tickets,
                              int ticket_stride, hipStream_t st, const PageMap* pm, const float* kscale,
-                             const float* vscale, bool skip_v) {
+                             const float* vscale, bool skip_v, float* norms_out) {
   ScoreArgs a;
   a.skip_v = skip_v ? 1 : 0;
   a.pm = pm ? *pm : PageMap{nullptr, 0, 0, 1, 0};
@@ -27,7 +27,10 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
   a.n_cap = n_cap;
   a.frags = (const u32x4*)frags;
   a.post = post;
-  a.logits = logits;
+  // (the upper half of the logit scratch serves only fp32 caches)
+  a.dump = norms_out ? logits : logits + (size_t)d.qheads() * n;
+  a.norms_out = norms_out ? 1 : 0;
+  a.logits = norms_out ? norms_out : logits;
   a.vnorm = vnorm;
   a.part = part;
   a.G = d.G;

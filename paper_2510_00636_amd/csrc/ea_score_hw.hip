@@ -86,7 +86,11 @@ constexpr HwStep hw_step(int f) {
   return HwStep{u / 8, j, f - first, j / 2 * (j / 2 + 1) + j % 2 * (j / 2 + 1) + f - first, u % 4};
 }
 
-template <bool FP8, bool PAGED>
+// MODE kHwNoV: the caller has weights of its own, V is not read.  kHwNorms: neither, nor a softmax; the quadratic forms
+// leave as norms sqrt(k^T M k) (the rows are values then, M = W_o^T W_o, mu = 0).
+constexpr int kHwScores = 0, kHwNoV = 1, kHwNorms = 2;
+
+template <bool FP8, bool PAGED, int MODE>
 __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
   constexpr int NKS = 4, NF = 20, GH = 4;
   constexpr int RB = FP8 ? 128 : 256;        // bytes of a row
@@ -114,7 +118,8 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     unit = (unit + 3 * chunk) % a.units;
   }
   const int g0 = pass * GH;
-  const bool do_v = pass == 0 && !a.skip_v;
+  constexpr bool kV = MODE == kHwScores;
+  const bool do_v = pass == 0;
   const int n = (int)a.n;
   const int ntiles = (n + kHwTile - 1) / kHwTile;
 
@@ -181,8 +186,10 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     const Lim lim = rows_left(t_cur);
 #pragma unroll
     for (int j = 0; j < NL; ++j) load_k(j, at, lim);
+    if constexpr (kV) {
 #pragma unroll
-    for (int j = 0; j < NL; ++j) load_v(j, at, lim);
+      for (int j = 0; j < NL; ++j) load_v(j, at, lim);
+    }
   }
 
   half8 F[NF], X[2 * NKS];                   // this head's fragments, and those of the extra rows
@@ -206,7 +213,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     sc_mine = q < 2 ? sc_mine : q == 2 ? 256.0f * pq_mine : 0.f;
   }
 
-  float* dump = a.logits + (size_t)a.units * a.G * a.n;     // at least n floats; contents never read
+  float* dump = a.dump;                                     // at least n floats; contents never read
   const bool mine = g0 + w < a.G;                           // this wavefront has a head
   float* lg_out = mine ? a.logits + ((size_t)unit * a.G + g0 + w) * a.n : dump;
   float* vn_eff = do_v ? a.vnorm + (size_t)unit * a.n : dump;
@@ -249,23 +256,32 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     return x;
   };
   const int vn_row = 16 * w + (FP8 ? lch >> 2 : lch & 3) * (16 / NL) + lrow;
+  auto out_value = [&](float lg) __attribute__((always_inline)) -> float {
+    if constexpr (MODE != kHwNorms) return lg;
+    const float x = lg * 256.f;              // 2 d
+    return x > 0.f ? sqrtf(x) : 0.f;
+  };
   // keys past the end (PAGED) hold the last key again: same value, same place
   auto out_row = [&](int row) -> int { return PAGED ? min(row, n - 1) : row; };
 
   {
-    float sv[NL];
 #pragma unroll
     for (int j = 0; j < NL; ++j) stage_k(j, 0);
+    if constexpr (kV) {
+      float sv[NL];
 #pragma unroll
-    for (int j = 0; j < NL; ++j) sv[j] = square_v(j);
-    const float x = reduce_v(sv);
-    vn_eff[out_row(base_row(t_cur) + vn_row)] = __builtin_amdgcn_sqrtf(FP8 ? x * vs2 : x);
+      for (int j = 0; j < NL; ++j) sv[j] = square_v(j);
+      const float x = reduce_v(sv);
+      vn_eff[out_row(base_row(t_cur) + vn_row)] = __builtin_amdgcn_sqrtf(FP8 ? x * vs2 : x);
+    }
     const size_t at = rows_at(t_n1);
     const Lim lim = rows_left(t_n1);
 #pragma unroll
     for (int j = 0; j < NL; ++j) load_k(j, at, lim);
+    if constexpr (kV) {
 #pragma unroll
-    for (int j = 0; j < NL; ++j) load_v(j, at, lim);
+      for (int j = 0; j < NL; ++j) load_v(j, at, lim);
+    }
   }
   if (tid == 0) {
     s_tk[2] = tile_of(dealt + (int)draw2);
@@ -364,38 +380,40 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
       }
       if constexpr (f == 2) {
         char* dst = (char*)(t_prev >= 0 ? lg_out : dump);
-        *(float*)(dst + (uint32_t)(4 * out_row(row_prev))) = lg;
+        *(float*)(dst + (uint32_t)(4 * out_row(row_prev))) = out_value(lg);
         const bool valid = PAGED ? row_prev < n : row_prev >= t_prev * kHwTile;
         lg = valid ? lg : -INFINITY;
         lm = lg;
       }
       // -- its softmax partial: max and sum over the 64 lanes, one step of the butterflies at a time
-      if constexpr (f == 5) lm = max_xor16(lm);
-      if constexpr (f == 6) lm = max_xor32(lm);
-      if constexpr (f == 7) lm = max_dpp<0xB1>(lm);
-      if constexpr (f == 9) lm = max_dpp<0x4E>(lm);
-      if constexpr (f == 11) lm = max_dpp<0x141>(lm);
-      if constexpr (f == 13) lm = max_dpp<0x140>(lm);
-      if constexpr (f == 15) le = __expf(lg - lm);
-      if constexpr (f == 18) le = dpp_add<0xB1>(le);
-      if constexpr (f == 19) le = dpp_add<0x4E>(le);
-      if constexpr (f == 21) le = dpp_add<0x141>(le);
-      if constexpr (f == 23) le = dpp_add<0x140>(le);
-      if constexpr (f == 25) le = sum_xor16(le);
-      if constexpr (f == 27) le = sum_halves(le);
+      if constexpr (MODE != kHwNorms) {
+        if constexpr (f == 5) lm = max_xor16(lm);
+        if constexpr (f == 6) lm = max_xor32(lm);
+        if constexpr (f == 7) lm = max_dpp<0xB1>(lm);
+        if constexpr (f == 9) lm = max_dpp<0x4E>(lm);
+        if constexpr (f == 11) lm = max_dpp<0x141>(lm);
+        if constexpr (f == 13) lm = max_dpp<0x140>(lm);
+        if constexpr (f == 15) le = __expf(lg - lm);
+        if constexpr (f == 18) le = dpp_add<0xB1>(le);
+        if constexpr (f == 19) le = dpp_add<0x4E>(le);
+        if constexpr (f == 21) le = dpp_add<0x141>(le);
+        if constexpr (f == 23) le = dpp_add<0x140>(le);
+        if constexpr (f == 25) le = sum_xor16(le);
+        if constexpr (f == 27) le = sum_halves(le);
+      }
       // -- staging of the next tile, each chunk requested again for the one after it
       if constexpr (f >= 30 && f < 30 + 2 * NL && (f & 1) == 0) {
         constexpr int j = (f - 30) / 2;
         stage_k(j, PB ^ 1);
         load_k(j, at_n2, lim_n2);
       }
-      if constexpr (f >= 31 && f < 31 + 2 * NL && (f & 1) == 1) {
+      if constexpr (kV && f >= 31 && f < 31 + 2 * NL && (f & 1) == 1) {
         constexpr int j = (f - 31) / 2;
         sv[j] = square_v(j);
         load_v(j, at_n2, lim_n2);
       }
-      if constexpr (f == 39) vn = reduce_v(sv);
-      if constexpr (f == 40) *(float*)((char*)vn_eff + (uint32_t)(4 * out_row(base_row(t_n1) + vn_row))) = __builtin_amdgcn_sqrtf(FP8 ? vn * vs2 : vn);
+      if constexpr (kV && f == 39) vn = reduce_v(sv);
+      if constexpr (kV && f == 40) *(float*)((char*)vn_eff + (uint32_t)(4 * out_row(base_row(t_n1) + vn_row))) = __builtin_amdgcn_sqrtf(FP8 ? vn * vs2 : vn);
       // -- dot products of finished output tiles with k
       static_for<16>([&](auto u_) {
         constexpr int u = decltype(u_)::value, e = hw_end(u);
@@ -406,7 +424,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     });
     __builtin_amdgcn_s_setprio(0);
     // ---- tail: the parts that need a branch
-    if (t_prev >= 0 && mine && lane == 0) part_out[t_prev] = make_float2(lm, le);
+    if (MODE != kHwNorms && t_prev >= 0 && mine && lane == 0) part_out[t_prev] = make_float2(lm, le);
     if (tid == 0) {
       if (s >= 1) s_tk[(s + 3) & 7] = tile_of(dealt + (int)pend);
       pend = atomicAdd(tk, 1u);
@@ -431,21 +449,25 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     }
     const float lg = sum_groups(p);
     const int row = base_row(t_prev) + lane;
-    lg_out[out_row(row)] = lg;
-    const bool valid = PAGED ? row < n : row >= t_prev * kHwTile;
-    float m = valid ? lg : -INFINITY;
-    m = max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(max_xor32(max_xor16(m))))));
-    float e = __expf((valid ? lg : -INFINITY) - m);
-    e = sum_halves(sum_xor16(dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(e))))));
-    if (mine && lane == 0) part_out[t_prev] = make_float2(m, e);
+    lg_out[out_row(row)] = out_value(lg);
+    if constexpr (MODE != kHwNorms) {
+      const bool valid = PAGED ? row < n : row >= t_prev * kHwTile;
+      float m = valid ? lg : -INFINITY;
+      m = max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(max_xor32(max_xor16(m))))));
+      float e = __expf((valid ? lg : -INFINITY) - m);
+      e = sum_halves(sum_xor16(dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(e))))));
+      if (mine && lane == 0) part_out[t_prev] = make_float2(m, e);
+    }
   }
 }
 
 hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, bool fp8, hipStream_t st) {
   const int grid = a.units * a.nchunk * a.passes;
-  if (a.pm.table) k_score_hw<false, true><<<grid, 256, 0, st>>>(a);
-  else if (fp8) k_score_hw<true, false><<<grid, 256, 0, st>>>(a);
-  else k_score_hw<false, false><<<grid, 256, 0, st>>>(a);
+  if (a.pm.table) k_score_hw<false, true, kHwScores><<<grid, 256, 0, st>>>(a);
+  else if (fp8) k_score_hw<true, false, kHwScores><<<grid, 256, 0, st>>>(a);
+  else if (a.norms_out) k_score_hw<false, false, kHwNorms><<<grid, 256, 0, st>>>(a);
+  else if (a.skip_v) k_score_hw<false, false, kHwNoV><<<grid, 256, 0, st>>>(a);
+  else k_score_hw<false, false, kHwScores><<<grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 

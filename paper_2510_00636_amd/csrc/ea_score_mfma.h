@@ -39,6 +39,8 @@ struct ScoreArgs {
   const float* kscale;    // FP8 instances: real key = kscale[unit] * stored value (nullptr: 1)
   const float* vscale;    // likewise for the values
   int spare;              // 1: more workgroups than CUs, see ScorePlan
+  float* dump;            // register-fragment kernel: n floats for stores that must not be seen
+  int norms_out;          // that kernel: norms instead of logits (skip_v is then 1)
   int skip_v;             // 1: the caller has its own per-pair weights; V is not read, vnorm not written
 };
 
