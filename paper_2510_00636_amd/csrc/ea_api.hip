@@ -57,11 +57,11 @@ static ea_status run_stats_for_score(const Dims& d, const void* q_win, int64_t w
                                      const double* inv_freq, int64_t t_next, int64_t n, bool paged, float* mu, float* sigma,
                                      char* ws, const WsLayout& L, hipStream_t st, uint32_t* clear, size_t clear_words,
                                      bool* frags_ready) {
-  *frags_ready = stats_makes_frags(d);
+  const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), paged);
+  *frags_ready = stats_makes_frags(d, sp);
   if (!*frags_ready) return run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, ws, L, st, clear, clear_words);
   float2* tab = (float2*)(ws + L.tab);
   EA_TRY(launch_rope_table(d, inv_freq, q_pos0, t_next, (int)window, tab, clear, clear_words, st));
-  const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), paged);
   EA_TRY(launch_stats_frags(d, sp, q_win, (int)window, tab, (uint4*)(ws + L.frags), (float*)(ws + L.post), st));
   return EA_OK;
 }
@@ -390,7 +390,7 @@ static ea_status compress_impl(const ea_params* p, const void* q_win, int64_t wi
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[1], st));
   if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores,
-                     n_keep > 0 && !select_in_one_launch(n) ? hist : nullptr, true, w, L, st,
+                     n_keep > 0 ? hist : nullptr, true, w, L, st,
                      ev ? ev + 2 : nullptr, nullptr, nullptr, pm, kscale, vscale, frags_ready)) != EA_OK)
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[4], st));

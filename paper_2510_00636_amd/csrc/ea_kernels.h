@@ -22,13 +22,15 @@ hipError_t launch_stats(const Dims& d, const void* q_win, int w, const float2* t
                         float* sigma, hipStream_t st);
 // the two of them in one for bf16 windows: mu and Sigma stay on the chip, the operands are those
 // launch_prep_frags makes of what launch_stats writes, bit for bit.  At d = 64 a head is one workgroup's either
-// way and the one launch wins at every size; at d = 128 the two launches spread a head over two and sixteen
-// workgroups, which is faster while the heads leave the chip idle (whole pass, n = 3000, w = 128, two launches
-// against one: 32 heads 60 and 63 us, 128 85 and 86, 192 105 and 102, 352 152 and 144; decode-time shape,
-// 960 heads, w = 512: 422 and 396).  At d = 256 Sigma does not fit in LDS.
+// way and the one launch wins at every size.  At d = 128 two workgroups that share a head can each make the register-fragment
+// kernel's fragments of their own tiles of Sigma (whole pass, 8 heads x 16384, 94.5 -> 91.2 us with the histogram of the finalize pass, x 3000 57.3 -> 53.7; 32 x 9000 138 ->
+// 132); from 192 heads on, and for the other kernel's fragments,
+// which mix rows of several tiles, a head is one workgroup's, and that is slower while the heads leave the chip idle (whole
+// pass, n = 3000, w = 128, LDS-fragment kernel, two launches against one: 32 heads 60 and 63 us, 128 85 and 86, 192 105 and
+// 102, 352 152 and 144; decode-time shape, 960 heads, w = 512: 422 and 396).  At d = 256 Sigma does not fit in LDS.
 constexpr int kStatsFragsMin = 192;
-inline bool stats_makes_frags(const Dims& d) {
-  return d.dtype == EA_BF16 && (d.D == 64 || (d.D == 128 && d.qheads() >= kStatsFragsMin));
+inline bool stats_makes_frags(const Dims& d, const ScorePlan& sp) {
+  return d.dtype == EA_BF16 && (d.D == 64 || (d.D == 128 && (sp.hw || d.qheads() >= kStatsFragsMin)));
 }
 hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_win, int w, const float2* tab,
                               uint4* frags, float* post, hipStream_t st);

@@ -260,7 +260,7 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
 constexpr int kSelSmallThreads = 1024;
 constexpr int kSelCopies = 4;
 
-template <int PER>
+template <int PER, bool HIST0>
 __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
   __shared__ uint32_t s_hist[kSelBins * kSelCopies];
   __shared__ uint32_t s_w[2][kSelSmallThreads / 64];
@@ -282,8 +282,22 @@ __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
   bool bad = false;
 #pragma unroll
   for (int P = 0; P < 3; ++P) {
-    for (int i = tid; i < (P == 0 ? kSelBins * kSelCopies : kSelBins); i += kSelSmallThreads) s_hist[i] = 0;
-    __syncthreads();
+    if (HIST0 && P == 0) {                          // the caller's first histogram
+      if (wave == 0) {
+        uint32_t r;
+        const int b = find_bin_wave(a.hist + (size_t)unit * 3 * kSelBins, 2048, rem, &r, lane);
+        if (lane == 0) { s_res[0] = (uint32_t)b; s_res[1] = r; }
+      }
+      for (int i = tid; i < kSelBins; i += kSelSmallThreads) s_hist[i] = 0;
+      __syncthreads();
+      prefix = s_res[0];
+      rem = s_res[1];
+      continue;
+    }
+    if (!(HIST0 && P == 1)) {
+      for (int i = tid; i < (P == 0 ? kSelBins * kSelCopies : kSelBins); i += kSelSmallThreads) s_hist[i] = 0;
+      __syncthreads();
+    }
     asm volatile("" : "+v"(lim));
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
@@ -361,9 +375,13 @@ hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t 
   a.nblk = (int)((n + kSelBlock - 1) / kSelBlock);
   static_assert(kSelSmallMax <= 16 * kSelSmallThreads, "scores per thread");
   if (select_in_one_launch(n)) {
-    if (n <= 4 * kSelSmallThreads) k_sel_small<4><<<d.units(), kSelSmallThreads, 0, st>>>(a);
-    else if (n <= 8 * kSelSmallThreads) k_sel_small<8><<<d.units(), kSelSmallThreads, 0, st>>>(a);
-    else k_sel_small<16><<<d.units(), kSelSmallThreads, 0, st>>>(a);
+#define EA_SMALL(PP)                                                                                  \
+  if (hist0_done) k_sel_small<PP, true><<<d.units(), kSelSmallThreads, 0, st>>>(a);                   \
+  else k_sel_small<PP, false><<<d.units(), kSelSmallThreads, 0, st>>>(a)
+    if (n <= 4 * kSelSmallThreads) { EA_SMALL(4); }
+    else if (n <= 8 * kSelSmallThreads) { EA_SMALL(8); }
+    else { EA_SMALL(16); }
+#undef EA_SMALL
     return hipGetLastError();
   }
   dim3 grid(d.units(), a.nblk);

@@ -602,7 +602,7 @@ constexpr int stats_split_chunk(int D) { return D >= 256 ? 32 : 64; }
 // FUSED (d <= 128, one workgroup per head): Sigma stays in LDS and leaves as the fragments that k_prep_frags
 // would have made of it, bit for bit.
 template <int D, int LAYOUT, int PARTS = 0, bool FUSED = false>
-__global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2)) void k_stats_split(const void* __restrict__ q_win, int w,
+__global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSED)) ? 3 : 2)) void k_stats_split(const void* __restrict__ q_win, int w,
                                                                          int ddof,
                                                                          const float2* __restrict__ tab,
                                                                          float* __restrict__ mu,
@@ -630,7 +630,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
   _Float16* s_lo = s_hi + D * P;                                   // [D][P]
   // FUSED: Sigma [D][pitch] takes the planes' place at the end (and more than that)
   constexpr int SP = stats_sigma_pitch(D);
-  float* s_part = FUSED && D * SP * 4 > 2 * D * P * 2 ? s_dyn + D * SP
+  float* s_part = FUSED && StatsTiling<D, PARTS>::PARTS == 1 && D * SP * 4 > 2 * D * P * 2 ? s_dyn + D * SP
                                                       : reinterpret_cast<float*>(s_lo + D * P);   // [4][D] column sums per wavefront
   float* s_shift = s_part + 4 * D;                                 // [D] u~_0
   float* s_xbar = s_shift + D;                                     // [D]
@@ -665,9 +665,12 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
     }
   }
   __syncthreads();
-  float suma[8], sumb[8];
+  // OWN: two workgroups of a head, each making the fragments of its own tiles; the scale of the head's fragments comes from
+  // sums of squares, which both take of all channels
+  constexpr bool OWN = FUSED && TL::PARTS == 2;
+  float suma[8], sumb[8], sqa[8], sqb[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) { suma[e] = 0.f; sumb[e] = 0.f; }
+  for (int e = 0; e < 8; ++e) { suma[e] = sumb[e] = sqa[e] = sqb[e] = 0.f; }
 
   const int r32 = lane & 31, kg = lane >> 5;
   int t_rb[TPW], t_ct[TPW];
@@ -778,6 +781,9 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
         if constexpr (ITEMS >= 2) {
           const float x1 = xs[it + 1][c16];
           if (c16 < 8) suma[e] += x0 + x1; else sumb[e] += x0 + x1;
+          if constexpr (OWN) {
+            if (c16 < 8) sqa[e] = fmaf(x0, x0, fmaf(x1, x1, sqa[e])); else sqb[e] = fmaf(x0, x0, fmaf(x1, x1, sqb[e]));
+          }
           const float y1 = x1 * scale;
           const stats_half2 h = __builtin_bit_cast(stats_half2, __builtin_amdgcn_cvt_pkrtz(y0, y1));
           const stats_half2 l = {(_Float16)(y0 - (float)h[0]), (_Float16)(y1 - (float)h[1])};
@@ -886,6 +892,24 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
     if (!FUSED && part == 0) mu[(size_t)head * D + c] = s_shift[c] + xb;
   }
   __syncthreads();
+  if constexpr (OWN) {                                 // largest diagonal entry, from the sums of squares
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+      for (int o = G8; o < 64; o <<= 1) {
+        sqa[e] += __shfl_xor(sqa[e], o);
+        sqb[e] += __shfl_xor(sqb[e], o);
+      }
+    }
+    if (lane < G8) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        s_part[wave * D + stats_ja<D>(layout, g, e)] = sqa[e];
+        s_part[wave * D + stats_jb<D>(layout, g, e)] = sqb[e];
+      }
+    }
+    __syncthreads();
+  }
   // In the matrix-core product a lane's B operand is column r32 and its A rows come back as
   // accumulator register v = row 8 (v / 4) + 4 kg + v % 4: the tile's entry (row, column r32).
   const float fw = (float)w, inv = 1.0f / (float)(w - ddof), unscale = 1.0f / (scale * scale);
@@ -900,7 +924,92 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && PARTS == 1) ? 3 : 2
   // d <= 128 that costs the registers that keep three workgroups on a CU without scratch memory,
   // and the direct stores are the faster ones (5.6 against 10.4 us per layer at the decode shape).
   constexpr bool kViaLds = D >= 256;
-  if constexpr (FUSED) {
+  if constexpr (OWN) {
+    float mxS = 0.f, mxM = 0.f;                          // every wavefront for itself
+    for (int c = lane; c < D; c += 64) {
+      const float sq = (s_part[c] + s_part[D + c]) + (s_part[2 * D + c] + s_part[3 * D + c]);
+      mxS = fmaxf(mxS, fabsf((sq - fw * s_xbar[c] * s_xbar[c]) * inv));
+      mxM = fmaxf(mxM, fabsf(s_shift[c] + s_xbar[c]));
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      mxS = fmaxf(mxS, __shfl_xor(mxS, o));
+      mxM = fmaxf(mxM, __shfl_xor(mxM, o));
+    }
+    const float sM = scale_for(2.0f * mxS), smu = scale_for(mxM);
+    constexpr int NF = NCT * (NCT + 1), nks = NCT;
+    const int unit = head / fo.G, gq = head - unit * fo.G, pass = gq / fo.GH, gp = gq - pass * fo.GH;
+    uint4* out = fo.frags + head_frags(fo, unit, gq, NF) * 64;
+    uint4* extra = fo.frags + extra_frags(fo, unit, pass, NF, nks) * 64;
+    float* patch = s_dyn + wave * (32 * 33);
+    // The tile (rows of block rb, columns of block ct) is fragments (2 ct, rb) and (2 ct + 1, rb), see frag_item: through
+    // the wavefront's own patch of LDS.  On the diagonal also the residuals of the extra rows.
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
+        const int rb = t_rb[t], ct = t_ct[t];
+        const float xj = s_xbar[ct * 32 + r32];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int il = 8 * (v / 4) + 4 * kg + v % 4;
+          patch[il * 33 + r32] = sigma_entry(acc[t][v], s_xbar[rb * 32 + il], xj);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int m = lane & 15, grp = lane >> 4;
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {
+          const int ol = 8 * (m >> 2) + 4 * jj + (m & 3);
+          _Float16 h[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const int il = 8 * grp + i;
+            float val = 2.f * patch[rb < ct ? il * 33 + ol : ol * 33 + il];
+            if (rb == ct && il >= ol) val = il == ol ? 0.5f * val : 0.f;
+            h[i] = (_Float16)(val * sM);
+          }
+          out[(ct * (ct + 1) + jj * (ct + 1) + rb) * 64 + lane] = pack_half8(h);
+        }
+        if (rb == ct && lane < 4) {
+          _Float16 h[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float x = patch[(8 * lane + i) * 34] * sM;
+            h[i] = (_Float16)(x - (float)(_Float16)x);
+          }
+          extra[(nks + rb) * 64 + lane * 16 + 8 + gp] = pack_half8(h);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    if (part == 0) {
+      if (tid == 0) {
+        fo.post[(size_t)head * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
+        fo.post[(size_t)head * 2 + 1] = 1.0f / (sqrtf((float)D) * smu);
+      }
+      if (tid < 8 * nks) {                               // head and tail of mu
+        const int kind = tid / (4 * nks), b = tid / 4 % nks, grp = tid & 3;
+        _Float16 h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int c = 32 * b + 8 * grp + i;
+          const float x = (s_shift[c] + s_xbar[c]) * smu;
+          const float hi = (float)(_Float16)x;
+          h[i] = (_Float16)(kind == 0 ? hi : x - hi);
+        }
+        extra[b * 64 + grp * 16 + 4 * kind + gp] = pack_half8(h);
+      }
+      if (gp == 0) {                                     // rows that belong to no head
+        const int nhere = min(fo.GH, fo.G - pass * fo.GH);
+        for (int item = tid; item < 2 * nks * 64; item += 256) {
+          const int fe = item >> 6;
+          const ExtraItem x = extra_item<D>(true, fo.GH, fe >= nks, fe % nks, item & 63);
+          if (x.g < 0 || x.g >= nhere) extra[item] = make_uint4(0u, 0u, 0u, 0u);
+        }
+      }
+    }
+  } else if constexpr (FUSED) {
     float* S = s_dyn;                                  // [D][SP]
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -1149,19 +1258,22 @@ static hipError_t launch_stats_frags_one(const Dims& d, const void* q_win, int w
                                          hipStream_t st) {
   auto kern = k_stats_split<D, LAYOUT, PARTS, true>;
   const size_t planes = (size_t)2 * D * (stats_split_chunk(D) + 8) * sizeof(_Float16);
-  const size_t sig = (size_t)D * stats_sigma_pitch(D) * sizeof(float);
+  // one workgroup per head: Sigma takes the planes' place
+  const size_t sig = StatsTiling<D, PARTS>::PARTS == 1 ? (size_t)D * stats_sigma_pitch(D) * sizeof(float) : 0;
   const size_t lds = (planes > sig ? planes : sig) + (size_t)(6 * D + 4) * sizeof(float);
   static LdsOptIn opt;
   hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
-  kern<<<d.qheads(), 256, lds, st>>>(q_win, w, d.ddof, tab, nullptr, nullptr, fo);
+  const dim3 grid(d.qheads(), StatsTiling<D, PARTS>::PARTS);
+  kern<<<grid, 256, lds, st>>>(q_win, w, d.ddof, tab, nullptr, nullptr, fo);
   return hipGetLastError();
 }
 template <int LAYOUT>
 static hipError_t launch_stats_frags_layout(const Dims& d, const void* q_win, int w, const float2* tab, const FragsOut& fo,
                                             hipStream_t st) {
-  return d.D == 64 ? launch_stats_frags_one<64, LAYOUT, 0>(d, q_win, w, tab, fo, st)
-                   : launch_stats_frags_one<128, LAYOUT, 1>(d, q_win, w, tab, fo, st);
+  if (d.D == 64) return launch_stats_frags_one<64, LAYOUT, 0>(d, q_win, w, tab, fo, st);
+  if (d.qheads() < kStatsFragsMin) return launch_stats_frags_one<128, LAYOUT, 0>(d, q_win, w, tab, fo, st);
+  return launch_stats_frags_one<128, LAYOUT, 1>(d, q_win, w, tab, fo, st);
 }
 hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_win, int w, const float2* tab,
                               uint4* frags, float* post, hipStream_t st) {
