@@ -26,21 +26,13 @@ __global__ void k_rope_table(const double* __restrict__ inv_freq, long long q_po
   if (gid >= (size_t)w * half) return;
   int i = (int)gid;
   int s = i / half, c = i - s * half;
-  double th = inv_freq[c];
-  double sh = sin(0.5 * th);
-  double cb, sb;
-  if (T == 1 || fabs(sh) < 1e-300) {
-    sincos(th * (double)t_next, &sb, &cb);
-  } else {
-    double amp = sin(0.5 * th * (double)T) / ((double)T * sh);
-    double ph = th * ((double)t_next + 0.5 * (double)(T - 1));
-    sincos(ph, &sb, &cb);
-    cb *= amp;
-    sb *= amp;
-  }
-  double ca = 1.0, sa = 0.0;
-  if (q_is_rotated) sincos(th * (double)(q_pos0 + s), &sa, &ca);
-  tab[i] = make_float2((float)(cb * ca + sb * sa), (float)(sb * ca - cb * sa));
+  // R-bar and the way back to position 0 in one angle: one sine and cosine instead of two, and of a smaller number
+  const double th = inv_freq[c], sh = sin(0.5 * th), back = q_is_rotated ? (double)(q_pos0 + s) : 0.0;
+  const bool flat = T == 1 || fabs(sh) < 1e-300;
+  const double amp = flat ? 1.0 : sin(0.5 * th * (double)T) / ((double)T * sh);
+  double co, si;
+  sincos(th * ((double)t_next + (flat ? 0.0 : 0.5 * (double)(T - 1)) - back), &si, &co);
+  tab[i] = make_float2((float)(amp * co), (float)(amp * si));
 }
 
 // ---------------------------------------------------------------------------------------
