@@ -473,12 +473,41 @@ __device__ __forceinline__ void merge_lt(LT& m, LT& s, LT m2, LT s2) {
   else { s = s * ea_exp(m - mn) + s2 * ea_exp(m2 - mn); m = mn; }
 }
 
+// (max, sum exp) of partials c0, c0 + step, .. of a head: four at a time, requested together, the largest maximum first
+// and one exponential per partial then (merged one by one they cost two exponentials and a memory latency each).
+template <typename LT>
+__device__ __forceinline__ void gather_lt(const typename LT2<LT>::type* __restrict__ p, int npart, int c0, int step, LT& m, LT& s) {
+  constexpr int U = 4;
+  m = -INFINITY;
+  s = 0;
+  if (npart <= step) {                      // one, or none
+    if (c0 < npart) { m = p[c0].x; s = p[c0].y; }
+    return;
+  }
+  for (int c = c0; c < npart; c += U * step) {
+    typename LT2<LT>::type x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      x[u] = p[min(c + u * step, npart - 1)];
+      if (c + u * step >= npart) x[u].x = -INFINITY;
+    }
+    LT mn = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) mn = mn > x[u].x ? mn : x[u].x;
+    if (mn == -INFINITY) continue;
+    s *= ea_exp(m - mn);
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += c + u * step < npart ? x[u].y * ea_exp(x[u].x - mn) : (LT)0;
+    m = mn;
+  }
+}
+
 // log-sum-exp of one head from its npart partials, by one wavefront: lane l takes partials
 // l, l + 64, ... in increasing order, then a fixed butterfly over the lanes.
 template <typename LT>
 __device__ __forceinline__ LT wave_lse(const typename LT2<LT>::type* __restrict__ p, int npart, int lane) {
-  LT m = -INFINITY, s = 0;
-  for (int c = lane; c < npart; c += 64) merge_lt<LT>(m, s, p[c].x, p[c].y);
+  LT m, s;
+  gather_lt<LT>(p, npart, lane, 64, m, s);
   for (int o = 32; o >= 1; o >>= 1) {
     LT m2 = __shfl_xor(m, o), s2 = __shfl_xor(s, o);
     merge_lt<LT>(m, s, m2, s2);
@@ -530,8 +559,8 @@ __global__ __launch_bounds__(256) void k_lse(const typename LT2<LT>::type* __res
   __shared__ LT s_m[4], s_s[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const typename LT2<LT>::type* p = part + (size_t)blockIdx.x * npart;
-  LT m = -INFINITY, s = 0;
-  for (int c = tid; c < npart; c += 256) merge_lt<LT>(m, s, p[c].x, p[c].y);
+  LT m, s;
+  gather_lt<LT>(p, npart, tid, 256, m, s);
   for (int o = 32; o >= 1; o >>= 1) {
     LT m2 = __shfl_xor(m, o), s2 = __shfl_xor(s, o);
     merge_lt<LT>(m, s, m2, s2);
@@ -651,10 +680,10 @@ hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D,
   return hipGetLastError();
 }
 
-constexpr int kLseInlineMax = 256;    // more partials per head than this: reduce them in k_lse first
-                                      // (one short launch; every finalize workgroup then reads G numbers
-                                      // instead of re-reducing the list: at 1024 partials per head, one
-                                      // 131072-key layer per call, pass B takes 14.8 instead of 18.1 us)
+constexpr int kLseInlineMax = 1024;   // more partials per head than this: reduce them in k_lse first (one short launch; every
+                                      // finalize workgroup then reads G numbers instead of the list).  Operands + score, with
+                                      // and without that launch: G = 3, 8 heads x 30000 keys (469 partials) 41.4 and 39.4 us,
+                                      // whole pass of 8 x 20000 105.2 and 102.7; 8 x 131072 (2048) 127 and 132
 
 hipError_t launch_finalize(const Dims& d, int64_t n, const void* logits, int logits_f64,
                            const float* vnorm, const void* part, int npart, void* lse, float* scores,
