@@ -15,7 +15,7 @@ constexpr int kFragPrefetch = 4;  // LDS fragments in flight ahead of the MFMA t
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4m __attribute__((ext_vector_type(4)));
 // native 16-byte vector: plain loads/stores the optimiser can keep in registers (HIP's uint4 is
 // a struct whose copies go through memcpy)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -75,6 +75,16 @@ __device__ __forceinline__ void fp8x16_to_half8x2(u32x4 r, half8& lo, half8& hi)
   hi[0] = e[0]; hi[1] = e[1]; hi[2] = f[0]; hi[3] = f[1]; hi[4] = g[0]; hi[5] = g[1]; hi[6] = h[0]; hi[7] = h[1];
 }
 
+// 8 of them -> one half8
+__device__ __forceinline__ half8 fp8x8_to_half8(uint32_t w0, uint32_t w1) {
+  auto two = [](auto f) { return __builtin_amdgcn_cvt_pkrtz(f[0], f[1]); };
+  const auto a = two(__builtin_amdgcn_cvt_pk_f32_fp8((int)w0, false)), b = two(__builtin_amdgcn_cvt_pk_f32_fp8((int)w0, true));
+  const auto c = two(__builtin_amdgcn_cvt_pk_f32_fp8((int)w1, false)), d = two(__builtin_amdgcn_cvt_pk_f32_fp8((int)w1, true));
+  half8 o;
+  o[0] = a[0]; o[1] = a[1]; o[2] = b[0]; o[3] = b[1]; o[4] = c[0]; o[5] = c[1]; o[6] = d[0]; o[7] = d[1];
+  return o;
+}
+
 __device__ __forceinline__ float sumsq_fp8x16(u32x4 r) {
   float s = 0.f;
   const uint32_t w[4] = {r[0], r[1], r[2], r[3]};
@@ -108,6 +118,12 @@ __device__ __forceinline__ float sumsq_bf16x8(u32x4 r) {
 // halves of the wavefront the other half's registers) instead of a trip through LDS.
 __device__ __forceinline__ float sum_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// x of lane l plus x of lane l ^ 16
+__device__ __forceinline__ float sum_xor16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
@@ -171,30 +187,31 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// output tile index jt of the rem-th fragment of a head (tile jt owns fragments
-// jt*(jt+1) .. jt*(jt+1) + 2jt + 1 of the triangular tiling)
-constexpr int tri_jt(int rem) {
-  int jt = 0;
-  while (rem >= (jt + 1) * (jt + 2)) ++jt;
-  return jt;
+// output tile j (16 channels) of the rem-th fragment of a head; tile j owns the fragments tile_frag(j) ..
+// tile_frag(j) + j / 2, one per k-step of 32 channels on or below the diagonal
+constexpr int tile_frag(int j) { return (j / 2) * (j / 2 + 1) + (j % 2) * (j / 2 + 1); }
+constexpr int frag_tile(int rem) {
+  int j = 0;
+  while (rem >= tile_frag(j + 1)) ++j;
+  return j;
 }
-// LDS fragment index used by matrix-core step f (the extra tile's fragments are stored last)
-template <int GH, int NF, int NX>
-constexpr int step_frag(int f) { return f < NX ? GH * NF + f : f - NX; }
+// The steps of the extra rows: those on k first, tile by tile, then those on k^2 with the tiles side by side, so that
+// the squares are formed once.  Fragments: [tile][k | k^2][k-step].
+struct ExtraStep { int x, res, b; };
+template <int XT, int NK>
+constexpr ExtraStep extra_step(int f) {
+  return f < XT * NK ? ExtraStep{f / NK, 0, f % NK} : ExtraStep{(f - XT * NK) % XT, 1, (f - XT * NK) / XT};
+}
 
 // The 2*NL global loads of the next tile are spread evenly over the steps [NX, NS).
 template <int NX, int NS, int NL>
 constexpr int load_slot(int i) { return NX + (i * (NS - NX)) / (2 * NL); }
-// accumulator row rho of a 32x32 tile lives in register ROW_V(rho) of the lanes with
-// lane / 32 == ROW_HH(rho)  (column = lane % 32)
-#define ROW_V(rho) (4 * ((rho) / 8) + (rho) % 4)
-#define ROW_HH(rho) (((rho) / 4) % 2)
-
 // ---------------------------------------------------------------------------------------
-// One wavefront scores 32 keys per iteration.  Lane l = (r = l % 32, hh = l / 32) owns the
-// channels hh*d/2 .. hh*d/2 + d/2 - 1 of key r as fp16 (B operand of the 32x32x16 MFMA), the
-// fragments of M (A operand) come from LDS, and the accumulator layout hands the lane the
-// same channels back, so  sum_j acc_j k_j  is 16 mixed-precision FMAs per output tile.
+// One wavefront scores 32 keys per iteration, two groups of 16.  Lane l = (c, q) = (l % 16, l / 16) owns the channels
+// 32 b + 8 q .. + 7 (b = 0 .. d/32 - 1) of key c of both groups as fp16 (B operands of the 16x16x32 MFMA, the 16-bit form
+// that draws least power; these passes run at the power limit), the fragments of M (A operand, used for both groups in a
+// row) come from LDS, and the accumulator layout hands the lane channels back that it holds, so  sum_j acc_j k_j  is 4
+// mixed-precision FMAs per output tile of 16 channels.
 // K rows reach that layout through a per-wave LDS staging buffer (coalesced 16-byte global
 // loads in, conflict-free 16-byte LDS reads out); V rows are squared and summed straight
 // from the coalesced layout.  The next tile's K and V loads are issued before the matrix
@@ -213,8 +230,9 @@ constexpr int load_slot(int i) { return NX + (i * (NS - NX)) / (2 * NL); }
 // the linear term, its square on the quadratic one) and onto the value norm.
 template <int D, int GH, int NW, bool CLAMP, bool FP8 = false>
 __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
-  constexpr int NKS = D / 16, NJT = D / 32, NF = NJT * (NJT + 1);
-  constexpr int NFRAG = GH * NF + 2 * NKS;
+  constexpr int NK = D / 32, NT16 = D / 16, NF = NK * (NK + 1);
+  constexpr int XT = GH > 5 ? 2 : 1;    // tiles of extra rows: 4 kind + head for four heads each; a fifth in rows 12, 13, 14
+  constexpr int NFRAG = GH * NF + XT * 2 * NK;
   constexpr int EPC = FP8 ? 16 : 8;     // channels per 16-byte chunk
   constexpr int CPR = D / EPC;          // 16-byte chunks per row
   constexpr int RPL = 64 / CPR;         // rows per wave-wide load
@@ -226,8 +244,6 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   constexpr bool XR = D == 256 && GH == 2;
   constexpr int NPH = (XR ? 4 : 2) / (FP8 ? 2 : 1);   // staging phases per tile
   constexpr int NLF = XR ? GH * NF : NFRAG;   // fragments held in LDS
-  constexpr int CH = CPR / 2;           // chunks per half row (the half a lane holds as B operands)
-  constexpr int CPP = CH / NPH;         // of those, staged per phase
   constexpr int RP = CPR / NPH;         // staged chunks per row and phase
   constexpr int RPS = 16 / RP;          // staged rows per 256 bytes (one sweep of the LDS banks)
   extern __shared__ u32x4 smem[];
@@ -291,8 +307,8 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   int t_nxt_raw = grab();
   constexpr int NFIT = XR ? 1 : (NFRAG + NW - 1) / NW;
   u32x4 ftmp[NFIT];
-  half8 xf[XR ? 2 * NKS : 1];            // XR: the extra tile's fragments
-  const u32x4* fsrc = a.frags + ((size_t)unit * a.passes + pass) * NFRAG * 64;
+  half8 xf[XR ? XT * 2 * NK : 1];        // XR: the extra rows' fragments
+  const u32x4* fsrc = a.frags + ((size_t)unit * a.unit_frags + pass * (a.unit_frags / a.passes)) * 64;
   if constexpr (!XR) {
 #pragma unroll
     for (int it = 0; it < NFIT; ++it) {
@@ -301,19 +317,21 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < 2 * NKS; ++i) xf[i] = __builtin_bit_cast(half8, fsrc[(GH * NF + i) * 64 + lane]);
+    for (int i = 0; i < XT * 2 * NK; ++i) xf[i] = __builtin_bit_cast(half8, fsrc[(GH * NF + i) * 64 + lane]);
   }
-  float pq[GH], pm[GH];
+  const int c16 = lane & 15, q = lane >> 4;
+  float pq[GH], sc[GH];                  // sc: of the extra row of head g that this lane holds (head, tail, residual, nothing)
   const float ks = (FP8 && a.kscale) ? a.kscale[unit] : 1.0f;
   const float vs2 = (FP8 && a.vscale) ? a.vscale[unit] * a.vscale[unit] : 1.0f;
 #pragma unroll
   for (int g = 0; g < GH; ++g) {
     const bool ok = g0 + g < a.G;
     pq[g] = ok ? a.post[((size_t)unit * a.G + g0 + g) * 2 + 0] * (ks * ks) : 0.f;
-    pm[g] = ok ? a.post[((size_t)unit * a.G + g0 + g) * 2 + 1] * ks : 0.f;
+    const float pm = ok ? a.post[((size_t)unit * a.G + g0 + g) * 2 + 1] * ks : 0.f;
+    if (GH == 5 && g == 4) sc[g] = q == 3 ? pm : 0.f;        // (the residual's factor is put together where it is used)
+    else sc[g] = q < 2 ? pm : q == 2 ? 256.0f * pq[g] : 0.f;
   }
 
-  const int r = lane & 31, hh = lane >> 5;
   const int lrow = lane / CPR, lch = lane % CPR;
   // Tiles of 32 keys are handed out by a ticket counter per (unit, pass), last tile of the head
   // first: at any moment the waves of a unit stream one contiguous region (which spreads the
@@ -409,8 +427,8 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   bool have_prev = false;
   auto store_prev = [&]() {
     const long long b0 = tile_base(key_prev);
-    const long long key = b0 + r;
-    if (hh == 0 && key >= key_prev && key < a.n) {
+    const long long key = b0 + 16 * (lane >> 5) + c16;
+    if ((lane & 16) == 0 && key >= key_prev && key < a.n) {
 #pragma unroll
       for (int g = 0; g < GH; ++g)
         if (g0 + g < a.G) a.logits[((size_t)unit * a.G + g0 + g) * a.n + key] = lg_prev[g];
@@ -423,28 +441,33 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   };
 
   for (; t_cur < ntiles; key0 = tile_key(t_cur)) {
-    // ---- K: coalesced registers -> LDS -> MFMA B layout.  Two phases, each staging one half
-    //      of every lane's k-steps for all 32 rows (half-size buffer, all lanes busy).
-    half8 Kh[NKS];
+    // ---- K: coalesced registers -> LDS -> MFMA B layout, in phases of RP chunks of every row
+    half8 Kh[2][NK];
 #pragma unroll
     for (int hf = 0; hf < NPH; ++hf) {
-      if (((lch % CH) / CPP) == hf) {
-        const int sc = (lch / CH) * CPP + (lch % CPP);
+      if (lch / RP == hf) {
+        const int at = lch % RP;
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
           const int rho = j * RPL + lrow;
-          stg[rho * RP + (sc ^ ((rho / RPS) & (RP - 1)))] = kraw[j];
+          stg[rho * RP + (at ^ ((rho / RPS) & (RP - 1)))] = kraw[j];
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
+      constexpr int KP = NK / NPH;         // k-steps per phase
 #pragma unroll
-      for (int q = 0; q < CPP; ++q) {
-        const int sc = hh * CPP + q;
-        const u32x4 piece = stg[r * RP + (sc ^ ((r / RPS) & (RP - 1)))];
-        if constexpr (FP8) fp8x16_to_half8x2(piece, Kh[2 * (hf * CPP + q)], Kh[2 * (hf * CPP + q) + 1]);
-        else Kh[hf * CPP + q] = bf16x8_to_half8(piece);
-      }
+      for (int x = 0; x < KP; ++x)
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int row = 16 * m + c16, sw = (row / RPS) & (RP - 1);
+          if constexpr (FP8) {             // half a piece: 8 of its 16 channels
+            const uint2 piece = reinterpret_cast<const uint2*>(stg)[2 * (row * RP + ((2 * x + (q >> 1)) ^ sw)) + (q & 1)];
+            Kh[m][hf * KP + x] = fp8x8_to_half8(piece.x, piece.y);
+          } else {
+            Kh[m][hf * KP + x] = bf16x8_to_half8(stg[row * RP + ((4 * x + q) ^ sw)]);
+          }
+        }
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       __builtin_amdgcn_wave_barrier();
     }
@@ -470,15 +493,14 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
       for (int j = 0; j < NL; ++j) noff[j] = has_next ? lane_piece(nkey0, j, r0, r1) : (size_t)0;
     }
 
-    // ---- matrix-core phase: NS = 2*NKS + GH*NF steps, one LDS fragment and one MFMA each.
-    //   steps [0, NKS)       extra tile, rows g / GH+g = fp16 head / tail of mu, times k
-    //   steps [NKS, 2NKS)    extra tile, rows 2GH+g = rounding residual of diag(M), times k^2/256
-    //   then per output tile t = (head g, 32 output channels jt): 2jt+2 steps over the k-steps on
-    //   or below the diagonal; its accumulator is then dotted with k (16 FMAs).
+    // ---- matrix-core phase: NS = NX + GH*NF steps, one LDS fragment and two MFMAs (one per key group) each.
+    //   steps [0, NX)        extra rows: fp16 head and tail of mu times k, rounding residual of diag(M) times k^2/256
+    //   then per output tile t = (head g, 16 output channels j): j/2 + 1 steps over the k-steps on
+    //   or below the diagonal; its accumulators are then dotted with k (4 FMAs per group).
     // Everything else of the iteration rides in the shadow of the MFMAs:
     //   * fragments are fetched PD steps ahead into a register ring;
-    //   * the 16 FMAs of tile t are issued four per step during steps end(t)+2 .. end(t)+5
-    //     (three accumulators rotate, so a tile is not rewritten before it has been read);
+    //   * the 8 FMAs of tile t are issued four per step during steps end(t)+2 and end(t)+3
+    //     (four accumulator pairs rotate, so a tile is not rewritten before it has been read);
     //   * the squared norm of V chunk j is formed at step j;
     //   * the 2*NL global loads of the next tile are spread over the steps after the extra
     //     tile, one at a time, so they never queue up in front of the memory pipeline.
@@ -486,57 +508,73 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
     // its staging or store phase, this wave's instructions are issued first and the matrix pipeline
     // stays fed (4 % on the kernel; the level, 1 to 3, makes no difference).
     __builtin_amdgcn_s_setprio(1);
-    float lin[GH], partial[GH], vsq = 0.f;
-    static_for<GH>([&](auto g_) { partial[decltype(g_)::value] = 0.f; lin[decltype(g_)::value] = 0.f; });
+    float partial[GH][2], vsq = 0.f;
+    static_for<GH>([&](auto g_) { partial[decltype(g_)::value][0] = partial[decltype(g_)::value][1] = 0.f; });
+    floatx4m ex[XT][2];
     {
       // (the five-head instance prefetches one fragment less: with four it spills, and a kernel that
       // needs scratch memory pays for it at every launch)
-      constexpr int NX = 2 * NKS, NS = NX + GH * NF, NT = GH * NJT, PD = GH >= 5 ? 3 : kFragPrefetch;
+      constexpr int NX = XT * 2 * NK, NS = NX + GH * NF, NT = GH * NT16, PD = GH >= 5 ? 3 : kFragPrefetch;
       half8 fb[PD + 1];
-      floatx16 ex, accb[3];
+      floatx4m accb[4][2];
+      half8 sq[2];
       // step f reads LDS fragment lfrag(f) into ring slot f % (PD + 1); with the extra tile in
       // registers the LDS stream starts at step NX
       constexpr int F0 = XR ? NX : 0;
-      auto lfrag = [](int f) constexpr { return XR ? f - NX : step_frag<GH, NF, NX>(f); };
+      auto xfrag = [](int f) constexpr {
+        const ExtraStep e = extra_step<XT, NK>(f);
+        return (e.x * 2 + e.res) * NK + e.b;
+      };
+      auto lfrag = [&](int f) constexpr { return f >= NX ? f - NX : GH * NF + xfrag(f); };
       static_for<PD>([&](auto i_) {
         constexpr int i = decltype(i_)::value;
         fb[(F0 + i) % (PD + 1)] = fr[lfrag(F0 + i) * 64 + lane];
       });
       __builtin_amdgcn_sched_barrier(0);
-      // FMAs 4q .. 4q+3 of the dot product of tile tt
-      auto dot4 = [&](auto tt_, auto q_) {
-        constexpr int tt = decltype(tt_)::value, q = decltype(q_)::value;
-        constexpr int g = tt / NJT, jt = tt % NJT;
+      // rows 2 h, 2 h + 1 of tile tt, both groups
+      auto dot4 = [&](auto tt_, auto h_) {
+        constexpr int tt = decltype(tt_)::value, h = decltype(h_)::value;
+        constexpr int g = tt / NT16, j = tt % NT16;
         static_for<4>([&](auto v_) {
-          constexpr int v = 4 * q + decltype(v_)::value;
-          constexpr int x = jt * 16 + v;
-          partial[g] = fmaf(accb[tt % 3][v], (float)Kh[x / 8][x % 8], partial[g]);
+          constexpr int v = 2 * h + decltype(v_)::value / 2, m = decltype(v_)::value % 2;
+          partial[g][m] = fmaf(accb[tt % 4][m][v], (float)Kh[m][j / 2][4 * (j % 2) + v], partial[g][m]);
         });
         // pin: otherwise the optimiser sinks the dot products to the end of the phase and keeps
         // every accumulator tile alive
-        if constexpr (q == 3) asm volatile("" : "+v"(partial[g]));
+        if constexpr (h == 1) asm volatile("" : "+v"(partial[g][0]), "+v"(partial[g][1]));
       };
-      static_for<NS + 6>([&](auto f_) {
+      static_for<NS + 4>([&](auto f_) {
         constexpr int f = decltype(f_)::value;
         if constexpr (f < NS) {
           if constexpr (f + PD < NS && f >= F0)
             fb[(f + PD) % (PD + 1)] = fr[lfrag(f + PD) * 64 + lane];
           half8 A;
-          if constexpr (XR && f < NX) A = xf[f];
+          if constexpr (XR && f < NX) A = xf[xfrag(f)];
           else A = fb[f % (PD + 1)];
-          constexpr floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          if constexpr (f < NKS) {
-            ex = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, Kh[f], f == 0 ? zero : ex, 0, 0, 0);
-          } else if constexpr (f < NX) {
-            half8 t = Kh[f - NKS] * (_Float16)0.0625f;
-            // |k| > 4096 would square to infinity (and infinity times a zero residual is NaN): the
-            // correction saturates there instead, an error far below the rounding it corrects
-            t = __builtin_elementwise_min(t * t, (half8)(_Float16)65504.0f);
-            ex = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, t, ex, 0, 0, 0);
+          constexpr floatx4m zero = {0.f, 0.f, 0.f, 0.f};
+          if constexpr (f < NX) {
+            constexpr ExtraStep e = extra_step<XT, NK>(f);
+            static_for<2>([&](auto m_) {
+              constexpr int m = decltype(m_)::value;
+              if constexpr (!e.res) {
+                ex[e.x][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, Kh[m][e.b], e.b == 0 ? zero : ex[e.x][m], 0, 0, 0);
+              } else {
+                if constexpr (e.x == 0) {
+                  const half8 t = Kh[m][e.b] * (_Float16)0.0625f;
+                  // |k| > 4096 would square to infinity (and infinity times a zero residual is NaN): the
+                  // correction saturates there instead, an error far below the rounding it corrects
+                  sq[m] = __builtin_elementwise_min(t * t, (half8)(_Float16)65504.0f);
+                }
+                ex[e.x][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, sq[m], ex[e.x][m], 0, 0, 0);
+              }
+            });
           } else {
-            constexpr int m = f - NX, g = m / NF, rem = m % NF;
-            constexpr int jt = tri_jt(rem), kt = rem - jt * (jt + 1), t = g * NJT + jt;
-            accb[t % 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, Kh[kt], kt == 0 ? zero : accb[t % 3], 0, 0, 0);
+            constexpr int mm = f - NX, g = mm / NF, rem = mm % NF;
+            constexpr int j = frag_tile(rem), kt = rem - tile_frag(j), t = g * NT16 + j;
+            static_for<2>([&](auto m_) {
+              constexpr int m = decltype(m_)::value;
+              accb[t % 4][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, Kh[m][kt], kt == 0 ? zero : accb[t % 4][m], 0, 0, 0);
+            });
           }
         }
         // ---- vector work placed in this step
@@ -549,20 +587,11 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
           const float ss = group_sum<CPR>(FP8 ? sumsq_fp8x16(vraw[f]) : sumsq_bf16x8(vraw[f]));
           vsq = lch == f ? ss : vsq;
         }
-        if constexpr (f == NX + 1) {              // rows of the extra tile, two steps after its end
-          static_for<GH>([&](auto g_) {
-            constexpr int g = decltype(g_)::value;
-            float e = 0.f;
-            if (hh == ROW_HH(g)) e += ex[ROW_V(g)] * pm[g];
-            if (hh == ROW_HH(GH + g)) e += ex[ROW_V(GH + g)] * pm[g];
-            if (hh == ROW_HH(2 * GH + g)) e += ex[ROW_V(2 * GH + g)] * (256.0f * pq[g]);
-            lin[g] = e;
-          });
-        }
         static_for<NT>([&](auto tt_) {
           constexpr int tt = decltype(tt_)::value;
-          constexpr int e = NX + (tt / NJT) * NF + (tt % NJT + 1) * (tt % NJT + 2) - 1;   // last step of tile tt
-          if constexpr (f >= e + 2 && f < e + 6) dot4(tt_, std::integral_constant<int, f - e - 2>{});
+          constexpr int e = NX + (tt / NT16) * NF + tile_frag(tt % NT16 + 1) - 1;         // last step of tile tt
+          if constexpr (f == e + 2) dot4(tt_, std::integral_constant<int, 0>{});
+          if constexpr (f == e + 3) dot4(tt_, std::integral_constant<int, 1>{});
         });
         // ---- loads of the next tile that belong to this step (K first, then V)
         static_for<2 * NL>([&](auto i_) {
@@ -587,8 +616,22 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
     // The softmax over keys (Eq. 8) is not this kernel's business: the (max, sum exp) partials are
     // taken from the stored logits per fixed block of keys by a pass of their own (k_lse_part), so
     // they do not depend on which wave scored which tile.
-#pragma unroll
-    for (int g = 0; g < GH; ++g) lg_prev[g] = sum_halves(partial[g] * pq[g] + lin[g]);
+    // The four lanes of a key's channels are added up: group 0 ends up in the lower, group 1 in the upper half-wave.
+    static_for<GH>([&](auto g_) {
+      constexpr int g = decltype(g_)::value;
+      float x[2];
+      static_for<2>([&](auto m_) {
+        constexpr int m = decltype(m_)::value;
+        if constexpr (GH == 5 && g == 4) {               // rows 12, 13, 14: the lanes of q = 3
+          const float cq = q == 3 ? 256.0f * pq[g] : 0.f;
+          x[m] = fmaf(partial[g][m], pq[g], fmaf(ex[0][m][2], cq, (ex[0][m][0] + ex[0][m][1]) * sc[g]));
+        } else {
+          x[m] = fmaf(partial[g][m], pq[g], ex[g / 4][m][g % 4] * sc[g]);
+        }
+      });
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[0]), __float_as_uint(x[1]), false, false);
+      lg_prev[g] = sum_xor16(__uint_as_float(sw[0]) + __uint_as_float(sw[1]));
+    });
     vsq_prev = vsq;
     key_prev = key0;
     have_prev = true;

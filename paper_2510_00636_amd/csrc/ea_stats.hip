@@ -438,52 +438,38 @@ __device__ __forceinline__ size_t extra_frags(const FragsOut& fo, int unit, int 
 }
 
 // What lane l of fragment f of a head holds: eight entries of M, output channel `out`, input channels from `in0` on,
-// `folded` where the mirrored entries are added.  The LDS-fragment kernels' are 32 x 16 operands as above.  The
-// register-fragment kernel's (hw) are 16 x 32 operands: k-step b is the channels 32 b .. 32 b + 31, lane l's key operand
-// the eight from 32 b + 8 (l / 16) on, output tile j has the rows 4 q + v for channel 32 (j / 2) + 8 q + 4 (j % 2) + v, so
-// that a lane gets back channels it holds here too, and takes the k-steps 0 .. j / 2.
+// `folded` where the mirrored entries are added.  Fragments are 16 x 32 operands: k-step b is the channels 32 b .. 32 b + 31,
+// lane l's key operand the eight from 32 b + 8 (l / 16) on, output tile j has the rows 4 q + v for channel 32 (j / 2) + 8 q +
+// 4 (j % 2) + v, so that a lane gets back channels it holds, and takes the k-steps 0 .. j / 2.  In the block on the diagonal
+// the entries with the smaller input channel are doubled and those with the larger one left out: the products are the same,
+// and zeros draw less power.
 struct FragItem { int out, in0; bool folded; };
-template <int D>
-__device__ __forceinline__ FragItem frag_item(bool hw, int f, int l) {
+__device__ __forceinline__ FragItem frag_item(int f, int l) {
   FragItem x;
-  if (hw) {
-    int j = 0;
-    while (f >= j / 2 + 1) { f -= j / 2 + 1; ++j; }
-    const int m = l & 15;
-    x.out = j / 2 * 32 + 8 * (m >> 2) + 4 * (j & 1) + (m & 3);
-    x.in0 = 32 * f + 8 * (l >> 4);
-    x.folded = f < j / 2;
-  } else {
-    int jt = 0;
-    while (f >= 2 * jt + 2) { f -= 2 * jt + 2; ++jt; }
-    const int rho = l & 31;
-    x.out = ((rho >> 2) & 1) * (D / 2) + jt * 16 + 4 * (rho >> 3) + (rho & 3);
-    x.in0 = (l >> 5) * (D / 2) + f * 8;
-    x.folded = (f >> 1) < jt;
-  }
+  int j = 0;
+  while (f >= j / 2 + 1) { f -= j / 2 + 1; ++j; }
+  const int m = l & 15;
+  x.out = j / 2 * 32 + 8 * (m >> 2) + 4 * (j & 1) + (m & 3);
+  x.in0 = 32 * f + 8 * (l >> 4);
+  x.folded = f < j / 2;
   return x;
 }
-// What lane l of an extra fragment of k-step kt holds: eight channels from `c0` on of kind 0 (fp16 head of mu), 1 (its
-// tail) or 2 (rounding residual of the diagonal) of head g of the pass, or nothing (g < 0).  Rows of the 32 x 16
-// operands: [0, GH) heads, [GH, 2 GH) tails, [2 GH, 3 GH) residuals; of the 16 x 32 ones: 4 kind + g.
+// What lane l of extra fragment fe (tile, then on k or on k^2, then k-step) holds: eight channels from `c0` on of kind 0
+// (fp16 head of mu), 1 (its tail) or 2 (rounding residual of the diagonal) of head g of the pass, or nothing (g < 0).
+// Rows 4 kind + g for four heads per tile; a fifth head of five in rows 12, 13 and 14.
 struct ExtraItem { int g, kind, c0; };
+constexpr int extra_tiles(int GH) { return GH > 5 ? 2 : 1; }
 template <int D>
-__device__ __forceinline__ ExtraItem extra_item(bool hw, int GH, bool is_res, int kt, int l) {
-  ExtraItem x = {-1, -1, 0};
-  if (hw) {
-    const int m = l & 15;
-    x.c0 = 32 * kt + 8 * (l >> 4);
-    if (is_res == (m >> 2 == 2) && m < 12) { x.g = m & 3; x.kind = m >> 2; }
-  } else {
-    const int rho = l & 31;
-    x.c0 = (l >> 5) * (D / 2) + kt * 8;
-    if (!is_res && rho < 2 * GH) { x.g = rho % GH; x.kind = rho / GH; }
-    if (is_res && rho >= 2 * GH && rho < 3 * GH) { x.g = rho - 2 * GH; x.kind = 2; }
-  }
-  return x;
+__device__ __forceinline__ ExtraItem extra_item(int GH, int fe, int l) {
+  constexpr int NK = D / 32;
+  const int m = l & 15, tile = fe / (2 * NK);
+  const bool is_res = fe / NK % 2 != 0;
+  int g = -1, kind = -1;
+  if (m < 12) { g = 4 * tile + (m & 3); kind = m >> 2; }
+  else if (GH == 5 && m < 15) { g = 4; kind = m - 12; }
+  if (g >= GH || (kind == 2) != is_res) g = -1;
+  return ExtraItem{g, kind, 32 * (fe % NK) + 8 * (l >> 4)};
 }
-// k-steps of the extra rows
-constexpr int extra_ksteps(int D, bool hw) { return hw ? D / 32 : D / 16; }
 
 // an odd pitch: neither rows nor columns of Sigma in LDS pile up in a bank
 constexpr int stats_sigma_pitch(int D) { return D + 1; }
@@ -491,7 +477,7 @@ constexpr int stats_sigma_pitch(int D) { return D + 1; }
 // The fragments of one head (see above) out of its Sigma in LDS [D][pitch] and its mean shift + xbar, by the
 // 256 threads of a workgroup: the head's own fragments of the triangle, and its rows of the extra tile's.
 // The first head of a (unit, pass) also writes the rows and fragments that belong to no head.
-template <int D, bool HW>
+template <int D>
 __device__ __forceinline__ void stats_write_frags(const float* S, const float* s_shift, const float* s_xbar, int head,
                                                   const FragsOut& fo) {
   constexpr int NJT = D / 32, NF = NJT * (NJT + 1), SP = stats_sigma_pitch(D);
@@ -517,24 +503,22 @@ __device__ __forceinline__ void stats_write_frags(const float* S, const float* s
   for (int it = 0; it < (NF * 64 + 255) / 256; ++it) {
     const int item = it * 256 + tid;
     if (NF * 64 % 256 != 0 && item >= NF * 64) break;
-    const FragItem x = frag_item<D>(HW, item >> 6, item & 63);
+    const FragItem x = frag_item(item >> 6, item & 63);
     _Float16 h[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       float val = S[x.out * SP + x.in0 + i];
       // (inside a 32 x 32 tile on the diagonal the two differ by rounding)
       if (x.folded) val += S[(x.in0 + i) * SP + x.out];
-      else if (HW) val = x.in0 + i < x.out ? 2.f * val : x.in0 + i == x.out ? val : 0.f;
+      else val = x.in0 + i < x.out ? 2.f * val : x.in0 + i == x.out ? val : 0.f;
       h[i] = (_Float16)(val * sM);
     }
     out[item] = pack_half8(h);
   }
-  constexpr int nks = extra_ksteps(D, HW);
-  out = fo.frags + extra_frags(fo, unit, pass, NF, nks) * 64;
-  for (int item = tid; item < 2 * nks * 64; item += 256) {
-    const int fe = item >> 6, l = item & 63;
-    const bool is_res = fe >= nks;
-    const ExtraItem x = extra_item<D>(HW, fo.GH, is_res, is_res ? fe - nks : fe, l);
+  constexpr int NK = D / 32;
+  out = fo.frags + extra_frags(fo, unit, pass, NF, NK) * 64;
+  for (int item = tid; item < extra_tiles(fo.GH) * 2 * NK * 64; item += 256) {
+    const ExtraItem x = extra_item<D>(fo.GH, item >> 6, item & 63);
     const bool mine = x.g == g, nobodys = g == 0 && (x.g < 0 || x.g >= nhere);
     if (!mine && !nobodys) continue;
     _Float16 h[8];
@@ -554,7 +538,7 @@ __device__ __forceinline__ void stats_write_frags(const float* S, const float* s
     }
     out[item] = pack_half8(h);
   }
-  if (g == 0 && !HW) {                                     // heads that the last pass has room for but not
+  if (g == 0 && !fo.hw) {                                     // heads that the last pass has room for but not
     const uint4 z = make_uint4(0u, 0u, 0u, 0u);
     out = fo.frags + head_frags(fo, unit, gq, NF) * 64;
     for (int item = nhere * NF * 64 + tid; item < fo.GH * NF * 64; item += 256) out[item] = z;
@@ -995,8 +979,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
       if (gp == 0) {                                     // rows that belong to no head
         const int nhere = min(fo.GH, fo.G - pass * fo.GH);
         for (int item = tid; item < 2 * nks * 64; item += 256) {
-          const int fe = item >> 6;
-          const ExtraItem x = extra_item<D>(true, fo.GH, fe >= nks, fe % nks, item & 63);
+          const ExtraItem x = extra_item<D>(fo.GH, item >> 6, item & 63);
           if (x.g < 0 || x.g >= nhere) extra[item] = make_uint4(0u, 0u, 0u, 0u);
         }
       }
@@ -1019,8 +1002,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
       }
     }
     __syncthreads();
-    if (D == 128 && fo.hw) stats_write_frags<D, D == 128>(S, s_shift, s_xbar, head, fo);
-    else stats_write_frags<D, false>(S, s_shift, s_xbar, head, fo);
+    stats_write_frags<D>(S, s_shift, s_xbar, head, fo);
   } else if constexpr (!kViaLds) {
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
@@ -1088,7 +1070,8 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
     return sigma + (size_t)(shared_heads ? head % shared_heads : head) * D * D;
   };
   constexpr int NJT = D / 32, NF = NJT * (NJT + 1);
-  const int G = fo.G, GH = fo.GH, passes = fo.passes, nks = extra_ksteps(D, fo.hw);
+  constexpr int NK = D / 32;
+  const int G = fo.G, GH = fo.GH, passes = fo.passes, nextra = extra_tiles(GH) * 2 * NK;
   __shared__ float s_scale[16];       // [2g] = sM, [2g+1] = smu   (GH <= 8)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int unit = blockIdx.x / passes, pass = blockIdx.x % passes;
@@ -1121,7 +1104,7 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
   }
   __syncthreads();
 
-  for (int item = blockIdx.y * 256 + tid; item < (GH * NF + 2 * nks) * 64; item += kPrepSplit * 256) {
+  for (int item = blockIdx.y * 256 + tid; item < (GH * NF + nextra) * 64; item += kPrepSplit * 256) {
     const int f = item >> 6, l = item & 63;
     uint4* out;
     _Float16 h[8];
@@ -1129,7 +1112,7 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
       const int g = f / NF, gq = g0 + g;
       if (fo.hw && gq >= G) continue;
       out = fo.frags + (head_frags(fo, unit, gq, NF) + (f - g * NF)) * 64 + l;
-      const FragItem x = frag_item<D>(fo.hw, f - g * NF, l);
+      const FragItem x = frag_item(f - g * NF, l);
       const int c_out = x.out, c_in0 = x.in0;
       const float sM = s_scale[2 * g];
       float val[8];
@@ -1147,7 +1130,7 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
         if (x.folded) {
 #pragma unroll
           for (int i = 0; i < 8; ++i) val[i] += S[(size_t)(c_in0 + i) * D + c_out];
-        } else if (fo.hw) {
+        } else {
 #pragma unroll
           for (int i = 0; i < 8; ++i) val[i] = c_in0 + i < c_out ? 2.f * val[i] : c_in0 + i == c_out ? val[i] : 0.f;
         }
@@ -1156,15 +1139,14 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
       for (int i = 0; i < 8; ++i) h[i] = (_Float16)(val[i] * sM);
     } else {
       const int fe = f - GH * NF;
-      const bool is_res = fe >= nks;
-      out = fo.frags + (extra_frags(fo, unit, pass, NF, nks) + fe) * 64 + l;
-      const ExtraItem x = extra_item<D>(fo.hw, GH, is_res, is_res ? fe - nks : fe, l);
+      out = fo.frags + (extra_frags(fo, unit, pass, NF, NK) + fe) * 64 + l;
+      const ExtraItem x = extra_item<D>(GH, fe, l);
       const int gq = g0 + x.g;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int c_in = x.c0 + i;
         float val = 0.f;
-        if (x.kind >= 0 && gq < G) {
+        if (x.g >= 0 && gq < G) {
           if (x.kind == 2) {
             float m = sigma_of(unit, gq)[(size_t)c_in * D + c_in] * s_scale[2 * x.g];
             val = m - (float)(_Float16)m;
