@@ -471,8 +471,9 @@ __device__ __forceinline__ ExtraItem extra_item(int GH, int fe, int l) {
   return ExtraItem{g, kind, 32 * (fe % NK) + 8 * (l >> 4)};
 }
 
-// an odd pitch: neither rows nor columns of Sigma in LDS pile up in a bank
-constexpr int stats_sigma_pitch(int D) { return D + 1; }
+// an odd pitch: neither rows nor columns of Sigma in LDS pile up in a bank; three more than D rather than one, because a
+// fragment's 16 rows times four runs of eight columns then meet three deep in a bank instead of four
+constexpr int stats_sigma_pitch(int D) { return D + 3; }
 
 // The fragments of one head (see above) out of its Sigma in LDS [D][pitch] and its mean shift + xbar, by the
 // 256 threads of a workgroup: the head's own fragments of the triangle, and its rows of the extra tile's.
@@ -482,6 +483,7 @@ __device__ __forceinline__ void stats_write_frags(const float* S, const float* s
                                                   const FragsOut& fo) {
   constexpr int NJT = D / 32, NF = NJT * (NJT + 1), SP = stats_sigma_pitch(D);
   const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a fragment is one wavefront's: its numbers stay scalar)
   const int unit = head / fo.G, gq = head - unit * fo.G, pass = gq / fo.GH, g = gq - pass * fo.GH;
   const int nhere = min(fo.GH, fo.G - pass * fo.GH);          // heads of this (unit, pass)
   float mxS = 0.f, mxM = 0.f;                                 // every wavefront for itself
@@ -503,7 +505,7 @@ __device__ __forceinline__ void stats_write_frags(const float* S, const float* s
   for (int it = 0; it < (NF * 64 + 255) / 256; ++it) {
     const int item = it * 256 + tid;
     if (NF * 64 % 256 != 0 && item >= NF * 64) break;
-    const FragItem x = frag_item(item >> 6, item & 63);
+    const FragItem x = frag_item(it * 4 + wave, lane);
     _Float16 h[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -517,8 +519,9 @@ __device__ __forceinline__ void stats_write_frags(const float* S, const float* s
   }
   constexpr int NK = D / 32;
   out = fo.frags + extra_frags(fo, unit, pass, NF, NK) * 64;
-  for (int item = tid; item < extra_tiles(fo.GH) * 2 * NK * 64; item += 256) {
-    const ExtraItem x = extra_item<D>(fo.GH, item >> 6, item & 63);
+  for (int fe = wave; fe < extra_tiles(fo.GH) * 2 * NK; fe += 4) {
+    const int item = fe * 64 + lane;
+    const ExtraItem x = extra_item<D>(fo.GH, fe, lane);
     const bool mine = x.g == g, nobodys = g == 0 && (x.g < 0 || x.g >= nhere);
     if (!mine && !nobodys) continue;
     _Float16 h[8];
