@@ -149,14 +149,14 @@ def timed(step, restore, steps, warmup, torch):
 
 
 def score_flops(ea, p_one, n, d, G):
-    """(executed, dense) matrix-core flops per key of the score pass: the kernels run nfrag 32x32x16
-    steps per tile of 32 keys and pass (triangular Sigma tiling plus the extra tile); the dense count
-    is G (2 d^2 + 2 d) of Eq. 7."""
+    """(executed, dense) matrix-core flops per key of the score pass: per key and query head the triangular
+    tiling of Sigma, (d/32)(d/32 + 1) fragments of 16 x 32 products, and per pass the extra rows' d/16 (twice that for
+    more than five heads); the dense count is G (2 d^2 + 2 d) of Eq. 7."""
     NF = (d // 32) * (d // 32 + 1)
-    gh = {64: min(G, 8), 128: 4 if G % 4 == 0 else min(G, 5), 256: min(G, 2)}[d]
+    gh = {64: min(G, 8), 128: 5 if G == 5 else 4, 256: min(G, 2)}[d]
     passes = -(-G // gh)
-    nfrag = gh * NF + 2 * (d // 16)
-    return passes * nfrag * 1024.0, G * (2.0 * d * d + 2 * d)
+    nfrag = G * NF + passes * (d // 16) * (2 if gh > 5 else 1)
+    return nfrag * 1024.0, G * (2.0 * d * d + 2 * d)
 
 
 def oracle_sample(cfg, q, k0, v0, inv, q_pos0, t_next, n_keep, eps, L, B, Hkv, n, budget_s=12.0):

@@ -663,7 +663,7 @@ hipError_t launch_score_mfma_d256(const ScoreArgs& a, const ScorePlan& sp, hipSt
 // ea_score_fp8.hip: the instances for caches stored as e4m3 bytes (d = 128 and 256)
 hipError_t launch_score_mfma_fp8(int D, const ScoreArgs& a, const ScorePlan& sp, hipStream_t st);
 hipError_t launch_score_mfma_fp8b(int D, const ScoreArgs& a, const ScorePlan& sp, hipStream_t st);
-// ea_score_hw.hip: fragments in registers, one wavefront per query head (d = 128, groups of four)
+// ea_score_hw.hip: fragments in registers, one wavefront per query head (d = 128, four heads per pass)
 hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, bool fp8, hipStream_t st);
 
 }  // namespace ea

@@ -388,21 +388,13 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __
 // statistics kernel itself.
 //
 // The quadratic form k^T Sigma k is evaluated as sum_j (sum_c k_c M[c][j]) k_j where M folds
-// the symmetric pair (c, j) and (j, c) onto one side at the granularity of 16-channel
-// "folded blocks" fb(c) = (c mod d/2) / 16:  M[c][j] = Sigma[c][j] + Sigma[j][c] when
-// fb(c) < fb(j), Sigma[c][j] when fb(c) == fb(j), and 0 otherwise -- the zero blocks are
-// simply not stored, which removes 3/8 of the matrix-core work.  M is scaled by a power of
+// the symmetric pair (c, j) and (j, c) onto one side at the granularity of blocks of 32 channels:
+// M[c][j] = Sigma[c][j] + Sigma[j][c] when c / 32 < j / 32, and 0 the other way round -- these blocks are
+// simply not stored, which removes 3/8 of the matrix-core work at d = 128.  M is scaled by a power of
 // two into fp16 range and rounded to fp16; the rounding error of its diagonal (the dominant
 // error term, since k_c^2 never cancels) is kept as a residual row that multiplies k_c^2 in
 // an extra accumulator tile.  mu is split into an fp16 head and tail in the same tile.
-//
-// Fragment (1 KiB = 64 lanes x 8 halves) for (head g, output tile jt, k-step kt):
-//   lane l (rho = l % 32, hl = l / 32), element i:
-//     input channel   c_in  = hl * d/2 + kt * 8 + i
-//     output channel  c_out = ((rho / 4) % 2) * d/2 + jt * 16 + 4 * (rho / 8) + rho % 4
-// so that in the 32x32 accumulator layout a lane (hh = l / 32) holds exactly the output
-// channels hh * d/2 + x that it also feeds as inputs: the epilogue dot with k needs no
-// data movement.
+// A fragment is 1 KiB, 64 lanes x 8 halves; what a lane holds say frag_item and extra_item below.
 __device__ __forceinline__ float scale_for(float maxabs) {
   if (!(maxabs > 0.f) || !isfinite(maxabs)) return 1.0f;
   int e;
