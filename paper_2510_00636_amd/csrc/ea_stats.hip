@@ -388,8 +388,8 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __
 // statistics kernel itself.
 //
 // The quadratic form k^T Sigma k is evaluated as sum_j (sum_c k_c M[c][j]) k_j where M folds
-// the symmetric pair (c, j) and (j, c) onto one side at the granularity of blocks of 32 channels:
-// M[c][j] = Sigma[c][j] + Sigma[j][c] when c / 32 < j / 32, and 0 the other way round -- these blocks are
+// the pair (c, j) and (j, c) onto one side: M[c][j] = Sigma[c][j] + Sigma[j][c] when c < j, and 0 the other way
+// round, so the form is that of any Sigma, symmetric or not.  Blocks of 32 x 32 channels that are all zeros are
 // simply not stored, which removes 3/8 of the matrix-core work at d = 128.  M is scaled by a power of
 // two into fp16 range and rounded to fp16; the rounding error of its diagonal (the dominant
 // error term, since k_c^2 never cancels) is kept as a residual row that multiplies k_c^2 in
@@ -429,13 +429,12 @@ __device__ __forceinline__ size_t extra_frags(const FragsOut& fo, int unit, int 
   return (size_t)unit * fo.unit_frags + (fo.hw ? fo.G * NF + pass * 2 * nks : pass * fo.nfrag + fo.GH * NF);
 }
 
-// What lane l of fragment f of a head holds: eight entries of M, output channel `out`, input channels from `in0` on,
-// `folded` where the mirrored entries are added.  Fragments are 16 x 32 operands: k-step b is the channels 32 b .. 32 b + 31,
-// lane l's key operand the eight from 32 b + 8 (l / 16) on, output tile j has the rows 4 q + v for channel 32 (j / 2) + 8 q +
-// 4 (j % 2) + v, so that a lane gets back channels it holds, and takes the k-steps 0 .. j / 2.  In the block on the diagonal
-// the entries with the smaller input channel are doubled and those with the larger one left out: the products are the same,
-// and zeros draw less power.
-struct FragItem { int out, in0; bool folded; };
+// What lane l of fragment f of a head holds: eight entries of M, output channel `out`, input channels from `in0` on.
+// Fragments are 16 x 32 operands: k-step b is the channels 32 b .. 32 b + 31, lane l's key operand the eight from
+// 32 b + 8 (l / 16) on, output tile j has the rows 4 q + v for channel 32 (j / 2) + 8 q + 4 (j % 2) + v, so that a lane gets
+// back channels it holds, and takes the k-steps 0 .. j / 2.  The zeros of the block on the diagonal draw less power than
+// the same form spread over all of it.
+struct FragItem { int out, in0; };
 __device__ __forceinline__ FragItem frag_item(int f, int l) {
   FragItem x;
   int j = 0;
@@ -443,8 +442,13 @@ __device__ __forceinline__ FragItem frag_item(int f, int l) {
   const int m = l & 15;
   x.out = j / 2 * 32 + 8 * (m >> 2) + 4 * (j & 1) + (m & 3);
   x.in0 = 32 * f + 8 * (l >> 4);
-  x.folded = f < j / 2;
   return x;
+}
+// M's entry for input channel `in` and output channel `out` out of Sigma[out][in] and Sigma[in][out].  Both are
+// taken: a caller's Sigma need not be symmetric, and inside a 32 x 32 tile on the diagonal the statistics kernels'
+// two differ by rounding.
+__device__ __forceinline__ float folded_entry(int in, int out, float val, float mirrored) {
+  return in < out ? val + mirrored : in == out ? val : 0.f;
 }
 // What lane l of extra fragment fe (tile, then on k or on k^2, then k-step) holds: eight channels from `c0` on of kind 0
 // (fp16 head of mu), 1 (its tail) or 2 (rounding residual of the diagonal) of head g of the pass, or nothing (g < 0).
@@ -501,11 +505,7 @@ __device__ __forceinline__ void stats_write_frags(const float* S, const float* s
     _Float16 h[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      float val = S[x.out * SP + x.in0 + i];
-      // (inside a 32 x 32 tile on the diagonal the two differ by rounding)
-      if (x.folded) val += S[(x.in0 + i) * SP + x.out];
-      else val = x.in0 + i < x.out ? 2.f * val : x.in0 + i == x.out ? val : 0.f;
-      h[i] = (_Float16)(val * sM);
+      h[i] = (_Float16)(folded_entry(x.in0 + i, x.out, S[x.out * SP + x.in0 + i], S[(x.in0 + i) * SP + x.out]) * sM);
     }
     out[item] = pack_half8(h);
   }
@@ -935,9 +935,8 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             const int il = 8 * grp + i;
-            float val = 2.f * patch[rb < ct ? il * 33 + ol : ol * 33 + il];
-            if (rb == ct && il >= ol) val = il == ol ? 0.5f * val : 0.f;
-            h[i] = (_Float16)(val * sM);
+            const float mirrored = patch[il * 33 + ol];        // (Sigma[in][out]; off the diagonal Sigma[out][in] too)
+            h[i] = (_Float16)((rb < ct ? mirrored + mirrored : folded_entry(il, ol, patch[ol * 33 + il], mirrored)) * sM);
           }
           out[(ct * (ct + 1) + jj * (ct + 1) + rb) * 64 + lane] = pack_half8(h);
         }
@@ -1122,13 +1121,8 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
         const float4 hi = *reinterpret_cast<const float4*>(S + (size_t)c_out * D + c_in0 + 4);
         val[0] = lo.x; val[1] = lo.y; val[2] = lo.z; val[3] = lo.w;
         val[4] = hi.x; val[5] = hi.y; val[6] = hi.z; val[7] = hi.w;
-        if (x.folded) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) val[i] += S[(size_t)(c_in0 + i) * D + c_out];
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) val[i] = c_in0 + i < c_out ? 2.f * val[i] : c_in0 + i == c_out ? val[i] : 0.f;
-        }
+        for (int i = 0; i < 8; ++i) val[i] = folded_entry(c_in0 + i, c_out, val[i], S[(size_t)(c_in0 + i) * D + c_out]);
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) h[i] = (_Float16)(val[i] * sM);

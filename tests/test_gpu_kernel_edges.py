@@ -396,3 +396,43 @@ def test_projection_tile_edges(w, dm, hq):
     torch.cuda.synchronize()
     rmu, rsg = X.query_stats_hidden(widen(hb), widen(wb), inv, 70000, T=cfg.horizon_T)
     P.check_stats(mu.cpu().numpy(), sg.cpu().numpy(), rmu, rsg)
+
+
+@pytest.mark.parametrize("d,hq,hkv,n", [(64, 4, 2, 200), (64, 5, 1, 33), (128, 4, 2, 40), (128, 5, 1, 63), (128, 8, 2, 300),
+                                        (256, 1, 1, 200), (256, 4, 2, 300)])
+def test_bf16_scores_with_a_sigma_that_is_not_symmetric(d, hq, hkv, n):
+    """k^T Sigma k takes both entries of every pair of channels, also inside the blocks on the diagonal, on every cache
+    layout.  Sigma is a covariance of unit scale plus noise of 5 %, against the oracle at the bf16 tolerance of the
+    score path; an entry of either side that is not a number has to show in the head's scores."""
+    import torch
+    from ea_inputs import make_block_pools, quantize_fp8
+    rng = np.random.default_rng(11 * n + d)
+    cfg = CONFIGS["c2"].with_(head_dim=d, n_q_heads=hq, n_kv_heads=hkv)
+    lay = make_layer(cfg, n=n, window=2)
+    p = P.params_for(cfg, epsilon=0.02)
+    a = rng.standard_normal((1, hq, d, d)) / np.sqrt(d)
+    sigma = (a @ a.transpose(0, 1, 3, 2) + 0.05 * rng.standard_normal((1, hq, d, d))).astype(np.float32)
+    mu = rng.standard_normal((1, hq, d)).astype(np.float32)
+    ref = O.scores(widen(lay["k"]), widen(lay["v"]), mu.astype(np.float64), sigma.astype(np.float64), 0.02)
+    P.check_scores(P.run_score(cfg, lay, mu, sigma, 0.02), ref, 2e-3)
+    kp, vp, tab, nb = make_block_pools(lay["k"], lay["v"], 16, 3)
+    tabd = torch.from_numpy(tab).cuda()
+    sc = torch.empty(1, hkv, n, device="cuda")
+    ws = P.workspace(p, n, 1)
+    ea.score_paged(p, P.to_dev(kp), P.to_dev(vp), ea.make_paged(tabd, 16, nb), n, P.to_dev(mu), P.to_dev(sigma), sc, ws)
+    torch.cuda.synchronize()
+    P.check_scores(sc.cpu().numpy(), ref, 2e-3)
+    if d >= 128:
+        (k8, ks), (v8, vs) = quantize_fp8(widen(lay["k"])), quantize_fp8(widen(lay["v"]))
+        k8d, v8d, ksd, vsd = (torch.from_numpy(x).cuda() for x in (k8, v8, ks, vs))
+        ea.score_fp8(p, k8d, v8d, ksd, vsd, n, n, P.to_dev(mu), P.to_dev(sigma), sc, ws)
+        torch.cuda.synchronize()
+        real = [X.fp8_e4m3_decode(c) * s.astype(np.float64)[:, :, None, None] for c, s in ((k8, ks), (v8, vs))]
+        P.check_scores(sc.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), 0.02), 2e-3)
+    for i, j in ((3, 9), (9, 3), (0, d - 1), (d - 1, 0)):
+        bad = sigma.copy()
+        bad[0, 0, i, j] = np.nan
+        got = torch.empty(1, hkv, n, device="cuda")
+        ea.score(p, P.to_dev(lay["k"]), P.to_dev(lay["v"]), n, n, P.to_dev(mu), P.to_dev(bad), got, ws)
+        torch.cuda.synchronize()
+        assert torch.isnan(got[0, 0]).all() and torch.isfinite(got[0, 1:]).all(), (i, j)
