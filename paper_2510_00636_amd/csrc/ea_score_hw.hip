@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
         if constexpr (f == 9) lm = max_dpp<0x4E>(lm);
         if constexpr (f == 11) lm = max_dpp<0x141>(lm);
         if constexpr (f == 13) lm = max_dpp<0x140>(lm);
-        if constexpr (f == 15) le = __expf(lg - lm);
+        if constexpr (f == 15) le = expf(lg - lm);
         if constexpr (f == 18) le = dpp_add<0xB1>(le);
         if constexpr (f == 19) le = dpp_add<0x4E>(le);
         if constexpr (f == 21) le = dpp_add<0x141>(le);
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
       const bool valid = PAGED ? row < n : row >= t_prev * kHwTile;
       float m = valid ? lg : -INFINITY;
       m = max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(max_xor32(max_xor16(m))))));
-      float e = __expf((valid ? lg : -INFINITY) - m);
+      float e = expf((valid ? lg : -INFINITY) - m);
       e = sum_halves(sum_xor16(dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(e))))));
       if (mine && lane == 0) part_out[t_prev] = make_float2(m, e);
     }

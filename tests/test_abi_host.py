@@ -140,3 +140,13 @@ def test_paged_arguments_are_checked_on_the_host(lib):
     assert call(EaPaged(0, 64, 100, 100)) == 1                # no table
     assert call(EaPaged(0x20000, 64, 100, 0)) == 1            # empty pool
     assert call(EaPaged(0x20000, 64, 100, 100), params=make_params(1, 4, 2, 128, EA_F32)) == 2
+
+
+def test_kernels_take_no_fast_exponentials_or_logarithms():
+    """Every exponential of the softmax is expf or exp: a fast one (its argument times log2 e rounded once to fp32) is off
+    by up to |x| 2^-24 relative, several units in the last place of the terms that carry a block's sum."""
+    csrc = os.path.join(ROOT, "paper_2510_00636_amd", "csrc")
+    fast = re.compile(r"\b(__expf|__exp2f|__exp10f|__logf|__log2f|__powf|__builtin_amdgcn_exp2f|__builtin_amdgcn_logf)\b")
+    found = [(f, m) for f in sorted(os.listdir(csrc)) if f.endswith((".hip", ".h", ".cpp"))
+             for m in fast.findall(open(os.path.join(csrc, f)).read())]
+    assert not found
