@@ -70,7 +70,18 @@ WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window);
 // every unit, unit 0's status word at kStatusSlot, the score kernel's tile counters of every unit from
 // kTicketSlot on.  The launch that clears the histograms clears them all.
 constexpr int kStatusSlot = 1030;
-constexpr int kTicketSlot = 1040;
+constexpr int kTicketSlot = 1056;
+constexpr int kTicketWays = 8;       // tile counters per (unit, pass)
+// Where counter `way` of a pass stands among them: neighbours on different lines of 128 bytes, of which there are 31.
+// Next to each other, eight of them on one line dealt a tile every 23 ns whatever the chip did.  Operands + score, one
+// unit x 131072 keys, before and now: d = 128, G = 1 51 and 29 us, 8 77 and 44, 12 80 and 60, 16 81 and 69; d = 64, G = 8
+// 113 and 35; d = 256, G = 2 99 and 60; two units, d = 128, G = 5 79 and 56; from eight units on the same.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+constexpr int ticket_word(int pass, int way) {
+  return (pass * kTicketWays + way) % 31 * 32 + (pass * kTicketWays + way) / 31;
+}
 // Status bits (see ea_debug_status)
 constexpr uint32_t kStatusBadScore = 1u;      // ea_select met a negative or NaN score
 constexpr uint32_t kStatusCompactWait = 2u;   // in-place ea_compact, or a block of ea_select, gave up waiting: stores skipped

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
   const int ways = max(1, min(kTicketWays, a.nchunk / 8));
   const HwDeal deal = hw_deal(chunk, a.nchunk, ways);
   const int way = deal.way, nth = deal.nth, peers = deal.peers;
-  uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + pass * kTicketWays + way;
+  uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + ticket_word(pass, way);
   auto tile_of = [&](int raw) { return max(ntiles - 1 - (raw * ways + way), -1); };
   int t_cur = tile_of(nth), t_n1 = tile_of(peers + nth);
   const int dealt = a.spare ? 0 : 2 * peers; // tiles of the class that are dealt by number

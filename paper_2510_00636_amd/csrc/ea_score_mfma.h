@@ -20,8 +20,6 @@ typedef float floatx4m __attribute__((ext_vector_type(4)));
 // a struct whose copies go through memcpy)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kTicketWays = 8;
-
 struct ScoreArgs {
   const u32x4* k;
   const u32x4* v;
@@ -33,7 +31,7 @@ struct ScoreArgs {
   float2* part;           // register-fragment kernel only: its (max, sum exp) partials
   int G, passes, nchunk, units, unit_frags;     // nchunk: workgroups per (unit, pass)
   int npart;              // that kernel: partials per query head, partial j covers keys [pg*j, pg*j + pg)
-  uint32_t* tickets;      // tickets + unit * ticket_stride + pass * kTicketWays + way: tile counters, zero at launch
+  uint32_t* tickets;      // tickets + unit * ticket_stride + ticket_word(pass, way): tile counters, zero at launch
   int ticket_stride;
   PageMap pm;             // pm.table != nullptr: k and v are block pools (CLAMP instances only)
   const float* kscale;    // FP8 instances: real key = kscale[unit] * stored value (nullptr: 1)
@@ -271,7 +269,7 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
     if (chunk > 0) {
       uint32_t* left = reinterpret_cast<uint32_t*>(smem);
       if (tid == 0)
-        *left = __hip_atomic_load(a.tickets + (size_t)unit * a.ticket_stride + pass * kTicketWays, __ATOMIC_RELAXED,
+        *left = __hip_atomic_load(a.tickets + (size_t)unit * a.ticket_stride + ticket_word(pass, 0), __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_AGENT);
       __syncthreads();
       const bool none = *left >= (uint32_t)((a.n + 31) / 32);
@@ -289,11 +287,11 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   const int ntiles = (int)((a.n + 31) / 32);
   // Up to kTicketWays counters per (unit, pass), each dealing the tiles of one residue class, so
   // that a head scored by hundreds of workgroups (few KV heads per call) does not queue up on one
-  // address: an atomic on one address takes about 13 ns.  A workgroup uses the counter of its
-  // index modulo the number of counters in use.
+  // address or line (ticket_word): an atomic on one address takes about 13 ns.  A workgroup uses the
+  // counter of its index modulo the number of counters in use.
   const int ways = a.spare ? 1 : max(1, min(kTicketWays, a.nchunk / 8));    // at least 8 workgroups per counter
   const int way = chunk % ways;
-  uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + pass * kTicketWays + way;
+  uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + ticket_word(pass, way);
   // The counter's value is only turned into a tile number where it is used, an iteration later:
   // any arithmetic on it here would make the wave wait for the atomic's round trip on the spot
   // (the library is also built with the compiler's wave-aggregation of atomics switched off,

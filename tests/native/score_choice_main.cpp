@@ -46,6 +46,19 @@ int main() {
                 CHECK(sp.passes * 4 >= G && sp.passes * 4 < G + 4, "G %d: %d passes", G, sp.passes);
               }
   CHECK(registers > 1000, "%d plans", registers);
+  // the tile counters of up to 32 passes: every one a word of its own behind kTicketSlot in the unit's third histogram,
+  // those of a pass on lines of their own
+  std::vector<int> taken(ea::kSelBins, 0);
+  static_assert(ea::kTicketSlot % 32 == 0, "lines of 128 bytes");
+  for (int pass = 0; pass < 32; ++pass) {
+    std::vector<int> lines;
+    for (int way = 0; way < ea::kTicketWays; ++way) {
+      const int word = ea::kTicketSlot + ea::ticket_word(pass, way);
+      CHECK(word < ea::kSelBins && !taken[word]++, "pass %d way %d: word %d", pass, way, word);
+      for (int line : lines) CHECK(line != word / 32, "pass %d way %d: line %d", pass, way, line);
+      lines.push_back(word / 32);
+    }
+  }
   for (int nchunk = 1; nchunk <= 600; ++nchunk) {
     const int ways = nchunk / 8 < 1 ? 1 : nchunk / 8 > 8 ? 8 : nchunk / 8;
     std::vector<std::vector<int>> members(ways);
