@@ -932,12 +932,18 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
         for (int jj = 0; jj < 2; ++jj) {
           const int ol = 8 * (m >> 2) + 4 * jj + (m & 3);
           _Float16 h[8];
+          float val[8];
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int il = 8 * grp + i;
-            const float mirrored = patch[il * 33 + ol];        // (Sigma[in][out]; off the diagonal Sigma[out][in] too)
-            h[i] = (_Float16)((rb < ct ? mirrored + mirrored : folded_entry(il, ol, patch[ol * 33 + il], mirrored)) * sM);
+          for (int i = 0; i < 8; ++i) val[i] = patch[(8 * grp + i) * 33 + ol];    // Sigma[in][out]
+          if (rb < ct) {                                 // (Sigma[out][in] too)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) val[i] += val[i];
+          } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) val[i] = folded_entry(8 * grp + i, ol, patch[ol * 33 + 8 * grp + i], val[i]);
           }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) h[i] = (_Float16)(val[i] * sM);
           out[(ct * (ct + 1) + jj * (ct + 1) + rb) * 64 + lane] = pack_half8(h);
         }
         if (rb == ct && lane < 4) {
