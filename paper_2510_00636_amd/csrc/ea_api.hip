@@ -57,7 +57,7 @@ static ea_status run_stats_for_score(const Dims& d, const void* q_win, int64_t w
                                      const double* inv_freq, int64_t t_next, int64_t n, bool paged, float* mu, float* sigma,
                                      char* ws, const WsLayout& L, hipStream_t st, uint32_t* clear, size_t clear_words,
                                      bool* frags_ready) {
-  const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), paged);
+  const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), paged, true);
   *frags_ready = stats_makes_frags(d, sp);
   if (!*frags_ready) return run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, ws, L, st, clear, clear_words);
   float2* tab = (float2*)(ws + L.tab);
@@ -82,7 +82,7 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
   float* vnorm = (float*)(ws + L.vnorm);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
   if (d.dtype == EA_BF16) {
-    ScorePlan sp = choose_score_plan(d, n, device_num_cu(), pm != nullptr);
+    const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), pm != nullptr, frags_ready);
     uint4* frags = (uint4*)(ws + L.frags);
     float* post = (float*)(ws + L.post);
     // frags_ready comes with hist_zeroed: the caller's own first launch has cleared the words then

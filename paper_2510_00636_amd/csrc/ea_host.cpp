@@ -140,24 +140,12 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
 }
 
 // The register-fragment kernel (d = 128): four query heads per pass, one wavefront each, two workgroups of four
-// wavefronts on a CU, whatever the cache layout.  Operands + score, LDS-fragment kernel and this one, us:
-//   as many passes, and every wavefront (or all but the last pass's fourth) with a head: always.  G = 4, 8 heads x 16384
-//     38 and 31, x 131072 155 and 130, 32 x 131072 515 and 479, 192 x 4608 144 and 132, one head x 100000 84 and 46,
-//     320 x 700 91 and 76; G = 7, 4 x 30000 67 and 41, 192 x 4608 238 and 230
-//   as many passes with more idle wavefronts: its cheaper start (20 KiB of fragments per wavefront, not 36 and more per
-//     query head through LDS) has to pay for them, so only calls of few tiles.  G = 1, 8 x 30000 42 and 38, x 131072 110
-//     and 109; G = 3, 8 x 60000 70 and 65, 192 x 4608 125 and 125; G = 6, 4 x 131072 154 and 113, 192 x 4608 206 and 227
-//   more passes (G = 5 in two instead of one, 9 in three instead of two): fewer still.  G = 5, 8 x 12000 40 and 36,
-//     x 30000 59 and 61; G = 9, 4 x 30000 72 and 55, x 131072 161 and 172; G = 13, 4 x 20000 67 and 49
-ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
-  ScorePlan s = make_score_plan(d, n, num_cu, paged);
-  if (d.D != 128 || d.dtype != EA_BF16 || n < kHwTile) return s;
-  const int64_t ntiles = (n + kHwTile - 1) / kHwTile, tiles = ntiles * d.units();
-  const int passes = (d.G + 3) / 4;
-  if (passes > s.passes ? tiles * passes > 6000 : passes * 4 - d.G > (passes > 1) && tiles > 10000) return s;
+// wavefronts on a CU, whatever the cache layout.
+static ScorePlan register_plan(const Dims& d, int64_t n, int num_cu) {
+  ScorePlan s;
   s.hw = 1;
   s.GH = 4;
-  s.passes = passes;
+  s.passes = (d.G + 3) / 4;
   s.NW = 4;
   s.spare = 0;
   s.lse_pass = 0;
@@ -168,6 +156,7 @@ ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   // Two workgroups per CU.  Where whole ones for every (unit, pass) leave more than a twentieth of them out, one more for
   // each, as in make_score_plan: 192 units x 4608, G = 4, two and three per unit 138 and 132 us; G = 7 251 and 230;
   // 384 jobs (G = 6) 248 and 227, 576 (G = 9) 375 and 337.
+  const int64_t ntiles = (n + kHwTile - 1) / kHwTile;
   const int64_t jobs = (int64_t)d.units() * s.passes, slots = 2 * (int64_t)num_cu;
   int64_t wgs = slots / jobs;
   if (wgs < 8) {
@@ -183,6 +172,50 @@ ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   s.pg = kHwTile;
   s.npart = (int)ntiles;
   return s;
+}
+
+// Which of the two kernels serves a call that both can: the lines are where operands + score take as long with either, over
+// 2400 shapes.  Figures: us with the LDS-fragment kernel and with this one, 8-bit rows behind the bar.
+static bool registers_serve(const Dims& d, int64_t n, int num_cu, const ScorePlan& lds, const ScorePlan& hw, bool from_stats) {
+  // As many passes, and every wavefront (or all but the last pass's fourth) with a head: this one.  G = 4, 8 x 16384 38
+  // and 31, 192 x 4608 150 and 140, 64 x 9000 85 and 86; G = 7, 8 x 45000 104 and 104; G = 12, 64 x 9000 186 and 175
+  if (hw.passes <= lds.passes && hw.passes * 4 - d.G <= (hw.passes > 1)) return true;
+  // Else wavefronts without a head, or a pass more, have to be paid for by the cheaper start: 20 KiB of fragments per
+  // wavefront, not 36 and more per query head through LDS, and no pass of its own for the partials.  So only calls of few
+  // (tile, pass) pairs, the fewer the more is lost on each:
+  //   idle wavefronts: G = 1, 8 x 9000 24 and 22, 20 x 20000 48 and 49, 8-bit 20 x 2000 20 and 17, x 4608 21 and 22;
+  //     G = 2, 8-bit 8 x 20000 29 and 28, 3 x 131072 41 and 47; G = 6, 20 x 9000 60 and 56, 64 x 9000 128 and 141
+  //   a pass more: G = 5, 20 x 2000 35 and 30, x 4608 37 and 40; G = 9, 8 x 9000 47 and 42, x 20000 63 and 68; G = 13 to 15,
+  //     20 x 9000 98 and 93, 12 x 40000 203 and 210; G = 17 and more, 12 x 12000 128 and 120, 6 x 40000 135 and 145
+  const int64_t tiles = (int64_t)d.units() * ((n + kHwTile - 1) / kHwTile);
+  const bool more = hw.passes > lds.passes;
+  int64_t most = hw.passes > 1 ? 6000 : 5000;
+  if (more) most = lds.passes == 1 ? 2300 : lds.passes == 2 ? 6800 : lds.passes == 3 ? 20000 : 12000;
+  else if (d.kv_fp8 && d.G <= 2) most = d.G == 1 ? 1100 : 2800;
+  // (in a compress call of fewer heads than kStatsFragsMin the statistics make this kernel's operands only, which is a launch less:
+  // compress_layer, G = 5, 16 x 5000 74 and 67; G = 1, 56 x 1143 54 and 50)
+  const bool saves = from_stats && d.qheads() < kStatsFragsMin;
+  if (saves) most += most / 2 + 1000;
+  if (tiles * hw.passes > most) return false;
+  if (d.units() <= 32 || saves || tiles * hw.passes <= 330) return true;
+  // More units fill the chip with either.  One pass: very short heads, and where the LDS-fragment kernel leaves a fifth of the
+  // CUs out.  G = 2, 64 x 350 25 and 24, x 700 27 and 29, 100 x 700 31 and 28.
+  const int64_t share = num_cu / d.units();
+  if (hw.passes == 1) return tiles <= 390 || (share >= 2 && share * d.units() * 5 <= num_cu * 4);
+  // Several: where its workgroups take one round, fill three quarters of it and, with a job each, not more than seven eighths
+  // (above that some of them run after the others): G = 9, 64 x 2500 82 and 77, 100 x 2500 116 and 130; G = 14, 100 x 700
+  // 129 and 88, 128 x 2500 199 and 208; G = 18, 80 x 700 102 and 88, 100 x 700 133 and 151; G = 28, compress, 61 x 778 163
+  // and 143.  But G = 5, 64 x 700 37 and 42, and G = 6, 64 x 700, where a workgroup has less than three tiles, 39 and 43.
+  const int64_t each = hw.nchunk - hw.spare, wgs = d.units() * hw.passes * each, slots = 2 * (int64_t)num_cu;
+  if (more ? lds.passes == 1 : hw.npart < 3 * each) return false;
+  return wgs <= slots && wgs * 4 >= slots * 3 && (each > 1 || wgs * 8 <= slots * 7);
+}
+
+ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged, bool from_stats) {
+  const ScorePlan lds = make_score_plan(d, n, num_cu, paged);
+  if (d.D != 128 || d.dtype != EA_BF16 || n < kHwTile) return lds;
+  const ScorePlan hw = register_plan(d, n, num_cu);
+  return registers_serve(d, n, num_cu, lds, hw, from_stats) ? hw : lds;
 }
 
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window) {

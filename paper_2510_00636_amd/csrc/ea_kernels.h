@@ -28,7 +28,6 @@ hipError_t launch_stats(const Dims& d, const void* q_win, int w, const float2* t
 // which mix rows of several tiles, a head is one workgroup's, and that is slower while the heads leave the chip idle (whole
 // pass, n = 3000, w = 128, LDS-fragment kernel, two launches against one: 32 heads 60 and 63 us, 128 85 and 86, 192 105 and
 // 102, 352 152 and 144; decode-time shape, 960 heads, w = 512: 422 and 396).  At d = 256 Sigma does not fit in LDS.
-constexpr int kStatsFragsMin = 192;
 inline bool stats_makes_frags(const Dims& d, const ScorePlan& sp) {
   return d.dtype == EA_BF16 && (d.D == 64 || (d.D == 128 && (sp.hw || d.qheads() >= kStatsFragsMin)));
 }

@@ -26,7 +26,7 @@ int main() {
       for (int units : {1, 2, 3, 8, 33, 192, 600})
         for (int64_t n : {(int64_t)1, (int64_t)63, (int64_t)64, (int64_t)65, (int64_t)4608, (int64_t)131072})
           for (int fp8 = 0; fp8 <= (d >= 128); ++fp8)
-            for (int paged = 0; paged <= !fp8; ++paged)
+            for (int mode = 0; mode <= 2; mode += 1 + fp8)   // (1: block pools, 2: operands from the statistics)
               for (int cu : {64, 256, 304}) {
                 ea_params p;
                 memset(&p, 0, sizeof p);
@@ -36,7 +36,7 @@ int main() {
                 CHECK(ea::check_params(&p, &dims) == EA_OK, "d %d G %d", d, G);
                 dims.kv_fp8 = fp8;
                 const ea::WsLayout L = ea::make_ws_layout(dims, n, 64);
-                const ea::ScorePlan sp = ea::choose_score_plan(dims, n, cu, paged);
+                const ea::ScorePlan sp = ea::choose_score_plan(dims, n, cu, mode == 1, mode == 2);
                 CHECK((size_t)units * sp.unit_frags * 1024 <= L.post - L.frags, "d %d G %d units %d n %ld fragments", d, G, units, (long)n);
                 CHECK((size_t)dims.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
                 if (!sp.hw) continue;
@@ -46,6 +46,25 @@ int main() {
                 CHECK(sp.passes * 4 >= G && sp.passes * 4 < G + 4, "G %d: %d passes", G, sp.passes);
               }
   CHECK(registers > 1000, "%d plans", registers);
+  // shapes at d = 128 of which one kernel is the faster one by 5 % or more
+  const struct { int G, units; int64_t n; int fp8, hw; } measured[] = {
+      {1, 300, 2000, 1, 0}, {1, 64, 9000, 1, 0}, {1, 20, 20000, 1, 0}, {1, 192, 700, 0, 0}, {1, 8, 9000, 0, 1}, {1, 1, 4608, 1, 1},
+      {2, 300, 2000, 1, 0}, {2, 3, 131072, 1, 0}, {3, 64, 9000, 1, 0}, {4, 8, 131072, 0, 1}, {4, 192, 4608, 0, 1},
+      {5, 32, 4608, 0, 0}, {5, 192, 700, 0, 0}, {5, 192, 4608, 0, 0}, {5, 8, 2000, 0, 1}, {6, 192, 2000, 0, 0}, {6, 20, 4608, 1, 1},
+      {9, 8, 9000, 0, 1}, {9, 2, 131072, 0, 0}, {10, 100, 700, 0, 0}, {13, 100, 700, 0, 1}, {13, 20, 9000, 1, 1}, {40, 51, 1459, 1, 0}};
+  for (const auto& m : measured) {
+    ea_params p;
+    memset(&p, 0, sizeof p);
+    p.batch = m.units; p.n_q_heads = m.G; p.n_kv_heads = 1; p.head_dim = 128; p.dtype = EA_BF16;
+    p.q_is_rotated = 1; p.horizon_T = 512;
+    ea::Dims dims;
+    CHECK(ea::check_params(&p, &dims) == EA_OK, "G %d", m.G);
+    dims.kv_fp8 = m.fp8;
+    CHECK(ea::choose_score_plan(dims, m.n, 256).hw == m.hw, "G %d, %d units x %ld keys, fp8 %d", m.G, m.units, (long)m.n, m.fp8);
+    // operands from the statistics change the choice one way only, and not from 192 heads on
+    const int with = ea::choose_score_plan(dims, m.n, 256, 0, true).hw;
+    CHECK(with >= m.hw && (dims.qheads() < ea::kStatsFragsMin || with == m.hw), "G %d, %d units x %ld keys", m.G, m.units, (long)m.n);
+  }
   // the tile counters of up to 32 passes: every one a word of its own behind kTicketSlot in the unit's third histogram,
   // those of a pass on lines of their own
   std::vector<int> taken(ea::kSelBins, 0);

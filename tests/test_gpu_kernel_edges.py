@@ -75,7 +75,8 @@ def test_scores_with_spare_workgroups(d, hq, hkv, batch, n):
 ])
 @pytest.mark.parametrize("w,layout", [(2, 0), (17, 1), (64, 0), (65, 1), (130, 0)])
 def test_fused_statistics_give_the_same_operands(d, hq, hkv, batch, w, layout):
-    """compress_layer's scores are those of query_stats followed by score, bit for bit: the statistics
+    """compress_layer's scores are those of query_stats followed by score, bit for bit (both calls go to the same score
+    kernel at this length): the statistics
     kernel that writes the score kernel's operands itself makes the ones that the separate kernels
     make of mu and sigma.  (Those are compared with the oracle elsewhere.)"""
     import torch
@@ -256,6 +257,35 @@ def test_statistics_do_not_hang_on_layout_or_call_size(dtype, d, many):
     mu_many, sigma_many = stats(q, 0)
     assert np.array_equal(mu_many, plain) and np.array_equal(sigma_many, sigma)
     assert np.array_equal(stats(q[..., half_to_inter], 1)[0], plain[..., half_to_inter])
+
+
+@pytest.mark.parametrize("form", ["layer", "fp8"])
+def test_compress_takes_the_other_score_kernel(form):
+    """Five query heads per KV head, 16 x 4600 keys: the score call goes to the LDS-fragment kernel, the compress call,
+    whose statistics make the other one's operands, to the register-fragment kernel.  The scores agree to 2e-5, the
+    bound between kernels that add the same fp16 products in another order."""
+    import torch
+    from ea_inputs import quantize_fp8
+    n, w = 4600, 64
+    cfg = CONFIGS["c2"].with_(n_q_heads=10, n_kv_heads=2, batch=8)
+    lay = make_layer(cfg, n=n, window=w)
+    p = P.params_for(cfg)
+    ws = P.workspace(p, n, w)
+    win = (P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"])
+    mu, sigma = torch.empty(8, 10, 128, device="cuda"), torch.empty(8, 10, 128, 128, device="cuda")
+    want, got = (torch.empty(8, 2, n, device="cuda") for _ in range(2))
+    ea.query_stats(p, *win, mu, sigma, ws)
+    if form == "fp8":
+        (k8, ks), (v8, vs) = quantize_fp8(widen(lay["k"])), quantize_fp8(widen(lay["v"]))
+        k, v, ks, vs = (torch.from_numpy(x).cuda() for x in (k8, v8, ks, vs))
+        ea.score_fp8(p, k, v, ks, vs, n, n, mu, sigma, want, ws)
+        ea.compress_layer_fp8(p, *win, k, v, ks, vs, n, n, 2000, 0, got, None, None, ws)
+    else:
+        k, v = P.to_dev(lay["k"]), P.to_dev(lay["v"])
+        ea.score(p, k, v, n, n, mu, sigma, want, ws)
+        ea.compress_layer(p, *win, k, v, n, n, 2000, got, None, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(got.cpu().numpy(), want.cpu().numpy(), rtol=2e-5, atol=0)
 
 
 @pytest.mark.parametrize("form,d,hq,hkv,batch,w", [
