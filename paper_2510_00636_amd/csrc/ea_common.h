@@ -143,6 +143,22 @@ inline HwDeal hw_deal(int chunk, int nchunk, int ways) {
   return x;
 }
 
+// Keys per workgroup of k_score_f32_whole, whole 64 of them, a head in at most 1024 spans.  The workgroups that fit the chip
+// at once do the same amount each, so what counts is rounds of them x (tiles per wavefront + what a workgroup pays at
+// its start).  Of the cuts with the same steps of 64 keys per span the one into fewest spans is looked at: 90 instead of
+// 1024 of them for 131072 keys, with the same result.
+inline int64_t f32_span(int64_t heads, int64_t n, int64_t slots) {
+  const int64_t steps = (n + 63) / 64;
+  int64_t best = steps, best_cost = 0;
+  for (int64_t c = 1, per = steps; c <= 1024; c = (steps + per - 2) / (per - 1)) {
+    per = (steps + c - 1) / c;
+    const int64_t cost = (heads * c + slots - 1) / slots * (2 * per + 1);
+    if (best_cost == 0 || cost < best_cost) { best = per; best_cost = cost; }
+    if (per == 1) break;
+  }
+  return best * 64;
+}
+
 // fragments per head of the triangular Sigma tiling, and per pass
 inline int frags_per_head(int D) { int njt = D / 32; return njt * (njt + 1); }
 inline int ksteps(int D) { return D / 16; }

@@ -414,15 +414,7 @@ static hipError_t launch_f32_whole(const Dims& d, const float* k, const float* v
   static LdsOptIn opt;
   hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
-  // Spans of whole 64 keys.  The workgroups that fit the chip at once do the same amount each, so what counts is rounds of
-  // them x (tiles per wavefront + what a workgroup pays at its start).
-  const int64_t heads = d.qheads(), steps = (n + 63) / 64, slots = (int64_t)device_num_cu() * (D == 64 ? 4 : 2);
-  int64_t best = 0, best_cost = 0;
-  for (int64_t c = 1; c <= steps && c <= 1024; ++c) {
-    const int64_t per = (steps + c - 1) / c, rounds = (heads * c + slots - 1) / slots, cost = rounds * (2 * per + 1);
-    if (best == 0 || cost < best_cost) { best = c; best_cost = cost; }
-  }
-  const int64_t span = (steps + best - 1) / best * 64;
+  const int64_t heads = d.qheads(), span = f32_span(heads, n, (int64_t)device_num_cu() * (D == 64 ? 4 : 2));
   const int nchunk = (int)((n + span - 1) / span);
   *nchunk_out = nchunk;
   kern<<<(unsigned)(heads * nchunk), 256, lds, st>>>(k, v, n, n_cap, mu, sigma, d.G, d.units(), (int)span, nchunk, logits, vnorm, part);

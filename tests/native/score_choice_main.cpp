@@ -78,6 +78,18 @@ int main() {
       lines.push_back(word / 32);
     }
   }
+  // spans of fp32 caches: those of the cheapest of all cuts
+  for (int heads : {1, 4, 28, 32, 500, 4096})
+    for (int slots : {128, 512, 1024})
+      for (int64_t n : {(int64_t)1, (int64_t)64, (int64_t)65, (int64_t)1024, (int64_t)5003, (int64_t)16000, (int64_t)70001, (int64_t)131072, (int64_t)1 << 20, (int64_t)1 << 26}) {
+        const int64_t steps = (n + 63) / 64;
+        int64_t best = 0, best_cost = 0;
+        for (int64_t c = 1; c <= steps && c <= 1024; ++c) {
+          const int64_t per = (steps + c - 1) / c, cost = (heads * c + slots - 1) / slots * (2 * per + 1);
+          if (best == 0 || cost < best_cost) { best = c; best_cost = cost; }
+        }
+        CHECK(ea::f32_span(heads, n, slots) == (steps + best - 1) / best * 64, "%d heads x %ld keys, %d slots", heads, (long)n, slots);
+      }
   for (int nchunk = 1; nchunk <= 600; ++nchunk) {
     const int ways = nchunk / 8 < 1 ? 1 : nchunk / 8 > 8 ? 8 : nchunk / 8;
     std::vector<std::vector<int>> members(ways);
