@@ -34,7 +34,7 @@ struct ScorePlan {
   int GH;       // query heads whose Sigma fragments are LDS-resident in one pass
   int passes;   // ceil(G / GH); K is streamed once per pass
   int NW;       // wavefronts per workgroup
-  int nfrag;    // 1 KiB fragments per (unit, pass) (LDS-fragment kernels)
+  int nfrag;    // 1 KiB fragments per (unit, pass) (LDS-fragment kernels; at d = 256 with two heads those of the extra rows are in registers)
   int unit_frags;   // 1 KiB fragments per unit
   int nchunk;   // workgroups per (unit, pass)
   int spare;    // 1: more workgroups than CUs; the ones dispatched late join heads that still have tiles
@@ -161,6 +161,7 @@ inline int64_t f32_span(int64_t heads, int64_t n, int64_t slots) {
 
 // fragments per head of the triangular Sigma tiling, and per pass
 inline int frags_per_head(int D) { int njt = D / 32; return njt * (njt + 1); }
-inline int ksteps(int D) { return D / 16; }
+// those of the extra rows of a pass of GH heads: a tile of 16 rows for up to five of them, on k and on k^2
+inline int extra_frags_of(int D, int GH) { return (GH > 5 ? 2 : 1) * D / 16; }
 
 }  // namespace ea

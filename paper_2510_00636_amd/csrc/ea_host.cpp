@@ -57,7 +57,7 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   s.hw = 0;
   s.spare = 0;
   s.lse_pass = 0;
-  const int NF = frags_per_head(d.D), NKS = ksteps(d.D);
+  const int NF = frags_per_head(d.D);
   const size_t lds_max = 160 * 1024, slack = 1024;
   const int inst64[] = {1, 2, 4, 8}, inst128[] = {1, 2, 3, 4, 5}, inst256[] = {1};
   const int* inst = d.D == 64 ? inst64 : d.D == 128 ? inst128 : inst256;
@@ -66,13 +66,13 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
   const size_t stage = (size_t)s.NW * 16 * d.D * 2;
   int ghmax = 1;
   for (int i = 0; i < ninst; ++i)
-    if ((size_t)(inst[i] * NF + 2 * NKS) * 1024 + stage + slack <= lds_max) ghmax = inst[i];
+    if ((size_t)(inst[i] * NF + extra_frags_of(d.D, inst[i])) * 1024 + stage + slack <= lds_max) ghmax = inst[i];
   s.passes = (d.G + ghmax - 1) / ghmax;
   int need = (d.G + s.passes - 1) / s.passes;
   s.GH = ghmax;
   for (int i = ninst - 1; i >= 0; --i)
     if (inst[i] >= need) s.GH = inst[i];
-  s.nfrag = s.GH * NF + 2 * NKS;
+  s.nfrag = s.GH * NF + extra_frags_of(d.D, s.GH);
   s.unit_frags = s.passes * s.nfrag;
   s.lds_bytes = (size_t)s.nfrag * 1024 + stage + slack;
   if (d.D == 256 && d.G >= 2) {
@@ -80,7 +80,7 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
     // registers, K staged through 4 KiB per wave: exactly the 160 KiB a workgroup may have
     s.GH = 2;
     s.passes = (d.G + 1) / 2;
-    s.nfrag = 2 * NF + 2 * NKS;
+    s.nfrag = 2 * NF + extra_frags_of(d.D, 2);
     s.unit_frags = s.passes * s.nfrag;
     s.lds_bytes = (size_t)2 * NF * 1024 + (size_t)s.NW * 4096;
   }
@@ -150,9 +150,9 @@ static ScorePlan register_plan(const Dims& d, int64_t n, int num_cu) {
   s.spare = 0;
   s.lse_pass = 0;
   s.lds_bytes = 0;
-  // the fragments of the unit's heads, then those of the extra rows of every pass: no more than the other kernel's
+  // the fragments of the unit's heads, then those of the extra rows of every pass
   s.nfrag = 0;
-  s.unit_frags = d.G * frags_per_head(128) + s.passes * ksteps(128);
+  s.unit_frags = d.G * frags_per_head(128) + s.passes * extra_frags_of(128, 4);
   // Two workgroups per CU.  Where whole ones for every (unit, pass) leave more than a twentieth of them out, one more for
   // each, as in make_score_plan: 192 units x 4608, G = 4, two and three per unit 138 and 132 us; G = 7 251 and 230;
   // 384 jobs (G = 6) 248 and 227, 576 (G = 9) 375 and 337.
@@ -227,11 +227,10 @@ WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window) {
     return at;
   };
   const size_t qh = (size_t)d.qheads(), un = (size_t)d.units();
-  // the fragments: the register-fragment kernel's are never more than the LDS-fragment kernel's, and these do not
-  // depend on the cache layout
-  Dims contiguous = d;
-  contiguous.kv_fp8 = 0;
-  const size_t frags_per_unit = (size_t)make_score_plan(contiguous, n, 256, 0).unit_frags * 1024;
+  // the fragments: those of whichever kernel needs more of them, whatever the cache layout
+  int unit_frags = make_score_plan(d, n, 256).unit_frags;
+  if (d.D == 128 && register_plan(d, n, 256).unit_frags > unit_frags) unit_frags = register_plan(d, n, 256).unit_frags;
+  const size_t frags_per_unit = (size_t)unit_frags * 1024;
   w.tab = take((size_t)window * d.half * 2 * sizeof(float));
   w.qproj = take(qh * (size_t)window * d.D * sizeof(float));   // projected queries of ea_query_stats_hidden
   w.mu = take(qh * d.D * sizeof(float));

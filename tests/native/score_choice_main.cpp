@@ -37,6 +37,11 @@ int main() {
                 dims.kv_fp8 = fp8;
                 const ea::WsLayout L = ea::make_ws_layout(dims, n, 64);
                 const ea::ScorePlan sp = ea::choose_score_plan(dims, n, cu, mode == 1, mode == 2);
+                if (!sp.hw) {     // fragments of a pass: the heads' triangles, and a tile of extra rows on k and on k^2 per five heads
+                  CHECK(sp.nfrag == sp.GH * ea::frags_per_head(d) + (sp.GH > 5 ? 2 : 1) * d / 16 && sp.unit_frags == sp.passes * sp.nfrag,
+                        "d %d G %d: %d fragments", d, G, sp.nfrag);
+                  CHECK(sp.lds_bytes <= 160 * 1024, "d %d G %d: %zu bytes of LDS", d, G, sp.lds_bytes);
+                }
                 CHECK((size_t)units * sp.unit_frags * 1024 <= L.post - L.frags, "d %d G %d units %d n %ld fragments", d, G, units, (long)n);
                 CHECK((size_t)dims.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
                 if (!sp.hw) continue;
