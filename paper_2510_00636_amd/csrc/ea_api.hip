@@ -54,10 +54,10 @@ static ea_status run_stats(const Dims& d, const void* q_win, int64_t window, int
 // Statistics for a score pass that follows in the same call.  Returns through *frags_ready whether the score
 // kernel's operands stand in the workspace already (then mu and sigma were not written).
 static ea_status run_stats_for_score(const Dims& d, const void* q_win, int64_t window, int64_t q_pos0,
-                                     const double* inv_freq, int64_t t_next, int64_t n, bool paged, float* mu, float* sigma,
+                                     const double* inv_freq, int64_t t_next, int64_t n, float* mu, float* sigma,
                                      char* ws, const WsLayout& L, hipStream_t st, uint32_t* clear, size_t clear_words,
                                      bool* frags_ready) {
-  const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), paged, true);
+  const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), true);
   *frags_ready = stats_makes_frags(d, sp);
   if (!*frags_ready) return run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, ws, L, st, clear, clear_words);
   float2* tab = (float2*)(ws + L.tab);
@@ -82,7 +82,7 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
   float* vnorm = (float*)(ws + L.vnorm);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
   if (d.dtype == EA_BF16) {
-    const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), pm != nullptr, frags_ready);
+    const ScorePlan sp = choose_score_plan(d, n, device_num_cu(), frags_ready);
     uint4* frags = (uint4*)(ws + L.frags);
     float* post = (float*)(ws + L.post);
     // frags_ready comes with hist_zeroed: the caller's own first launch has cleared the words then
@@ -385,7 +385,7 @@ static ea_status compress_impl(const ea_params* p, const void* q_win, int64_t wi
   // status word and the tile counters in their free words), block counts and the compaction flags
   const size_t clear_words = (L.flags - L.hist) / 4 + flag_words(d, n_keep);
   bool frags_ready = false;
-  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, pm != nullptr, mu, sigma, w, L, st, hist,
+  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, mu, sigma, w, L, st, hist,
                                clear_words, &frags_ready)) != EA_OK)
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[1], st));
@@ -491,7 +491,7 @@ ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int6
   bool frags_ready = false;
   // one clearing launch for both sets of histograms, the block counts and the compaction flags
   uint32_t* hist = (uint32_t*)(w + L.hist);
-  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, false, mu, sigma, w, L, st, hist,
+  if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, mu, sigma, w, L, st, hist,
                                (L.flags - L.hist) / 4 + flag_words(d, n), &frags_ready)) != EA_OK)
     return s;
   const bool hist0 = floor > 0 && n_keep > 0 && !select_in_one_launch(n);

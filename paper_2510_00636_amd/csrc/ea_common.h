@@ -61,10 +61,10 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // rows_only: the call only moves cache rows, so p->dtype may also be EA_FP8_E4M3
 ea_status check_params(const ea_params* p, Dims* d, bool rows_only = false);
-// the LDS-fragment kernels' plan, and the plan of the kernel that serves the call; paged: the caches are block pools;
-// from_stats: the operands come from the statistics kernel of the same call where it can make them (stats_makes_frags)
-ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged = 0);
-ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged = 0, bool from_stats = false);
+// the LDS-fragment kernels' plan, and the plan of the kernel that serves the call; from_stats: the
+// operands come from the statistics kernel of the same call where it can make them (stats_makes_frags)
+ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu);
+ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats = false);
 constexpr int kStatsFragsMin = 192;           // query heads from which the statistics kernel makes the operands of either kernel
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window);
 

@@ -38,8 +38,6 @@ ea_status check_params(const ea_params* p, Dims* d, bool rows_only) {
   return EA_OK;
 }
 
-// Largest number of query heads whose fragments fit the 160 KiB LDS next to the per-wave
-// staging buffers, and the template instance (GH) that covers ceil(G / passes) heads.
 // Of the workgroups that k_score_mfma's launch starts with, one per CU, how many the head with the fewest has (its
 // order: transposed over the eight dies where the grid is a multiple of eight, units innermost).
 static int least_served(int units, int64_t grid, int num_cu) {
@@ -51,9 +49,10 @@ static int least_served(int units, int64_t grid, int num_cu) {
   return least;
 }
 
-ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu, int paged) {
+// Heads per pass: as many as fit the 160 KiB of LDS with their fragments, next to the per-wave staging buffers; of the
+// template instances (GH) the smallest that covers ceil(G / passes) of them.
+ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu) {
   ScorePlan s;
-  (void)paged;                               // (a tile lies inside one block, or two of 16 rows: nothing to plan)
   s.hw = 0;
   s.spare = 0;
   s.lse_pass = 0;
@@ -211,8 +210,8 @@ static bool registers_serve(const Dims& d, int64_t n, int num_cu, const ScorePla
   return wgs <= slots && wgs * 4 >= slots * 3 && (each > 1 || wgs * 8 <= slots * 7);
 }
 
-ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, int paged, bool from_stats) {
-  const ScorePlan lds = make_score_plan(d, n, num_cu, paged);
+ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats) {
+  const ScorePlan lds = make_score_plan(d, n, num_cu);
   if (d.D != 128 || d.dtype != EA_BF16 || n < kHwTile) return lds;
   const ScorePlan hw = register_plan(d, n, num_cu);
   return registers_serve(d, n, num_cu, lds, hw, from_stats) ? hw : lds;

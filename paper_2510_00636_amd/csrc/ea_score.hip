@@ -64,7 +64,7 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
 // of the 16-channel blocks fb(c) = (c mod d/4) / 4 (the sum of two fp32 numbers, exact in fp64):
 // (d/16 + 1) / (2 d/16) of the dense work is left.  The rows of M of one output tile, a slab of up
 // to d/16 KiB x 2, are put together in LDS from Sigma by the four wavefronts and then used by each
-// for its KT x 16 keys, which stay in registers as fp32.
+// for its 16 keys, which stay in registers as fp32.
 //
 // What bounds it is the matrix cores' fp64 rate (64 cycles per instruction, 37 us of the 63 that the first shape below
 // takes) and the latency around it.  Slabs of M per step, in turn with their use, left the matrix cores idle 60 % of the
@@ -74,13 +74,12 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
 // slabs (16 x 2000 72 us).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-template <int D>
 __global__ __launch_bounds__(256, 2) void k_score_f32(const float* __restrict__ k, const float* __restrict__ v, long long n,
                                                    long long n_cap, const float* __restrict__ mu,
                                                    const float* __restrict__ sigma, int G, int units, int span,
                                                    int nchunk, double* __restrict__ logits, float* __restrict__ vnorm,
                                                    double2* __restrict__ part) {
-  constexpr int QW = D / 4, NT = D / 16, KT = 1;
+  constexpr int D = 256, QW = D / 4, NT = D / 16;
   __shared__ double s_a[NT * 4 * 64];       // fragments of a slab, [k-step][lane]
   __shared__ double s_mu[D];
   __shared__ double s_ms[4][2];
@@ -122,44 +121,29 @@ __global__ __launch_bounds__(256, 2) void k_score_f32(const float* __restrict__ 
       }
     }
   };
-  for (long long key0 = key_lo; key0 < key_hi; key0 += 64 * KT) {
-    float kf[KT][QW];
-    long long key[KT];
+  for (long long key0 = key_lo; key0 < key_hi; key0 += 64) {
+    float kf[QW];
+    const long long key = key0 + wave * 16 + r;
+    const float4* kp = reinterpret_cast<const float4*>(kb + min(key, n - 1) * D + q * QW);
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      key[t] = key0 + (wave * KT + t) * 16 + r;
-      const float4* kp = reinterpret_cast<const float4*>(kb + min(key[t], n - 1) * D + q * QW);
-#pragma unroll
-      for (int x = 0; x < QW / 4; ++x) {
-        const float4 f = kp[x];
-        kf[t][4 * x] = f.x; kf[t][4 * x + 1] = f.y; kf[t][4 * x + 2] = f.z; kf[t][4 * x + 3] = f.w;
-      }
+    for (int x = 0; x < QW / 4; ++x) {
+      const float4 f = kp[x];
+      kf[4 * x] = f.x; kf[4 * x + 1] = f.y; kf[4 * x + 2] = f.z; kf[4 * x + 3] = f.w;
     }
-    double lin[KT], quad[KT];
+    double lin = 0.0, quad = 0.0;
 #pragma unroll
-    for (int t = 0; t < KT; ++t) { lin[t] = 0.0; quad[t] = 0.0; }
-#pragma unroll
-    for (int x = 0; x < QW; ++x) {
-      const double m = s_mu[q * QW + x];
-#pragma unroll
-      for (int t = 0; t < KT; ++t) lin[t] = fma(m, (double)kf[t][x], lin[t]);
-    }
-#pragma unroll
-    for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(lin[t]));
+    for (int x = 0; x < QW; ++x) lin = fma(s_mu[q * QW + x], (double)kf[x], lin);
+    asm volatile("" : "+v"(lin));
     static_for<NT>([&](auto jt_) {
       constexpr int jt = decltype(jt_)::value;
       // (keeps the compiler from holding the keys widened to 64 bits across the slabs: the conversions are
       // hidden by the matrix instructions, twice the registers are not)
 #pragma unroll
-      for (int t = 0; t < KT; ++t)
-#pragma unroll
-        for (int x = 0; x < QW; ++x) asm volatile("" : "+v"(kf[t][x]));
+      for (int x = 0; x < QW; ++x) asm volatile("" : "+v"(kf[x]));
       __syncthreads();                      // the previous slab has been consumed
       build_slab(jt);
       __syncthreads();
-      doublex4 acc[KT];
-#pragma unroll
-      for (int t = 0; t < KT; ++t) acc[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+      doublex4 acc = doublex4{0.0, 0.0, 0.0, 0.0};
       // four k-steps at a time, the next four fragments on their way; nothing moves across the blocks
       // (left alone, the scheduler widens every key and fetches every fragment of the slab at once)
       double f[2][4];
@@ -173,44 +157,36 @@ __global__ __launch_bounds__(256, 2) void k_score_f32(const float* __restrict__ 
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int t = 0; t < KT; ++t)
-            acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[b & 1][e], (double)kf[t][4 * b + e], acc[t], 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(f[b & 1][e], (double)kf[4 * b + e], acc, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       });
 #pragma unroll
-      for (int t = 0; t < KT; ++t)
-#pragma unroll
-        for (int x = 0; x < 4; ++x) quad[t] = fma(acc[t][x], (double)kf[t][4 * jt + x], quad[t]);
-#pragma unroll
-      for (int t = 0; t < KT; ++t) asm volatile("" : "+v"(quad[t]));     // dotted here, not at the end of all slabs
+      for (int x = 0; x < 4; ++x) quad = fma(acc[x], (double)kf[4 * jt + x], quad);
+      asm volatile("" : "+v"(quad));       // dotted here, not at the end of all slabs
     });
+    double lg = lin / sqrt((double)D) + quad / (2.0 * D);
+    lg += __shfl_xor(lg, 16);
+    lg += __shfl_xor(lg, 32);
+    if (key < n) {
+      if (q == 0) logits[((size_t)unit * G + gq) * n + key] = lg;
+      const double mn = fmax(m_run, lg);
+      s_run = s_run * exp(m_run - mn) + exp(lg - mn);
+      m_run = mn;
+    }
+    if (do_v) {
+      const float4* vp = reinterpret_cast<const float4*>(vb + min(key, n - 1) * D + q * QW);
+      double ss = 0.0;
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      double lg = lin[t] / sqrt((double)D) + quad[t] / (2.0 * D);
-      lg += __shfl_xor(lg, 16);
-      lg += __shfl_xor(lg, 32);
-      if (key[t] < n) {
-        if (q == 0) logits[((size_t)unit * G + gq) * n + key[t]] = lg;
-        const double mn = fmax(m_run, lg);
-        s_run = s_run * exp(m_run - mn) + exp(lg - mn);
-        m_run = mn;
+      for (int x = 0; x < QW / 4; ++x) {
+        const float4 f = vp[x];
+        ss = fma((double)f.x, (double)f.x, ss);
+        ss = fma((double)f.y, (double)f.y, ss);
+        ss = fma((double)f.z, (double)f.z, ss);
+        ss = fma((double)f.w, (double)f.w, ss);
       }
-      if (do_v) {
-        const float4* vp = reinterpret_cast<const float4*>(vb + min(key[t], n - 1) * D + q * QW);
-        double ss = 0.0;
-#pragma unroll
-        for (int x = 0; x < QW / 4; ++x) {
-          const float4 f = vp[x];
-          ss = fma((double)f.x, (double)f.x, ss);
-          ss = fma((double)f.y, (double)f.y, ss);
-          ss = fma((double)f.z, (double)f.z, ss);
-          ss = fma((double)f.w, (double)f.w, ss);
-        }
-        ss += __shfl_xor(ss, 16);
-        ss += __shfl_xor(ss, 32);
-        if (q == 0 && key[t] < n) vnorm[(size_t)unit * n + key[t]] = (float)sqrt(ss);
-      }
+      ss += __shfl_xor(ss, 16);
+      ss += __shfl_xor(ss, 32);
+      if (q == 0 && key < n) vnorm[(size_t)unit * n + key] = (float)sqrt(ss);
     }
   }
   // (max, sum exp) of the span: the 16 key slots of each wavefront, then the four wavefronts
@@ -432,7 +408,7 @@ hipError_t launch_score_f32(const Dims& d, const void* k, const void* v, int64_t
   const int nchunk = (int)((n + span - 1) / span);
   *nchunk_out = nchunk;
   if (d.D != 256) return hipErrorInvalidValue;
-  k_score_f32<256><<<(unsigned)((int64_t)d.qheads() * nchunk), 256, 0, st>>>((const float*)k, (const float*)v, n, n_cap, mu, sigma, d.G,
+  k_score_f32<<<(unsigned)((int64_t)d.qheads() * nchunk), 256, 0, st>>>((const float*)k, (const float*)v, n, n_cap, mu, sigma, d.G,
                                                                    d.units(), (int)span, nchunk, logits, vnorm, part);
   return hipGetLastError();
 }

@@ -13,7 +13,6 @@ namespace ea {
 constexpr int kFragPrefetch = 4;  // LDS fragments in flight ahead of the MFMA that consumes them
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx4m __attribute__((ext_vector_type(4)));
 // native 16-byte vector: plain loads/stores the optimiser can keep in registers (HIP's uint4 is
@@ -148,31 +147,6 @@ __device__ __forceinline__ float group_sum(float x) {
   if (N >= 16) x = dpp_add<0x140>(x);         // row_mirror
   if (N >= 32) x += __shfl_xor(x, 16);
   return x;
-}
-
-// Max / sum over the first 32 lanes of the wavefront as a wave-uniform value: butterfly inside
-// each row of 16 lanes, then the two row totals are read out with v_readlane (no trip through
-// LDS, no wait).  The callers hold the same data in lanes l and l + 32.
-template <int CTRL>
-__device__ __forceinline__ float dpp_max(float x) {
-  int y = __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, 0xf, 0xf, false);
-  return fmaxf(x, __int_as_float(y));
-}
-__device__ __forceinline__ float max_lanes32(float x) {
-  x = dpp_max<0xB1>(x);
-  x = dpp_max<0x4E>(x);
-  x = dpp_max<0x141>(x);
-  x = dpp_max<0x140>(x);
-  return fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0)),
-               __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16)));
-}
-__device__ __forceinline__ float sum_lanes32(float x) {
-  x = dpp_add<0xB1>(x);
-  x = dpp_add<0x4E>(x);
-  x = dpp_add<0x141>(x);
-  x = dpp_add<0x140>(x);
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0)) +
-         __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16));
 }
 
 // compile-time loop: f(std::integral_constant<int, 0>) ... f(<N-1>), so that every register

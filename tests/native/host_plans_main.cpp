@@ -1,4 +1,4 @@
-// Host-only driver: every score plan that a call on some cache layout can take (contiguous, paged, 8-bit)
+// Host-only driver: every score plan of the LDS-fragment kernels, for rows of 16 and 8 bits,
 // fits the one workspace layout that callers size their buffers by, and the table launch covers what it clears.  Exits 0 when every check holds.
 #include <initializer_list>
 #include <stdio.h>
@@ -35,14 +35,13 @@ int main() {
             // ea_workspace_bytes and ea_debug_status do not know how the cache is stored
             CHECK(L.total == bytes && L.hist == plain.hist, "d %d G %d units %d n %ld fp8 %d: %zu bytes, %zu reserved", d, G,
                   units, (long)n, fp8, L.total, bytes);
-            for (int paged = 0; paged <= !fp8; ++paged)
-              for (int cu : {64, 256, 304}) {
-                const ea::ScorePlan sp = ea::make_score_plan(dd, n, cu, paged);
-                const size_t need = (size_t)units * sp.passes * sp.nfrag * 1024;
-                CHECK(need <= L.post - L.frags, "d %d G %d units %d n %ld paged %d fp8 %d: fragments %zu, reserved %zu", d, G,
-                      units, (long)n, paged, fp8, need, L.post - L.frags);
-                CHECK((size_t)dd.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
-              }
+            for (int cu : {64, 256, 304}) {
+              const ea::ScorePlan sp = ea::make_score_plan(dd, n, cu);
+              const size_t need = (size_t)units * sp.passes * sp.nfrag * 1024;
+              CHECK(need <= L.post - L.frags, "d %d G %d units %d n %ld fp8 %d: fragments %zu, reserved %zu", d, G,
+                    units, (long)n, fp8, need, L.post - L.frags);
+              CHECK((size_t)dd.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
+            }
           }
         }
   // workgroups per head: no more than finish in the same number of tiles per wavefront, while these are few and, in

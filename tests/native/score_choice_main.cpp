@@ -26,7 +26,7 @@ int main() {
       for (int units : {1, 2, 3, 8, 33, 192, 600})
         for (int64_t n : {(int64_t)1, (int64_t)63, (int64_t)64, (int64_t)65, (int64_t)4608, (int64_t)131072})
           for (int fp8 = 0; fp8 <= (d >= 128); ++fp8)
-            for (int mode = 0; mode <= 2; mode += 1 + fp8)   // (1: block pools, 2: operands from the statistics)
+            for (bool from_stats : {false, true})
               for (int cu : {64, 256, 304}) {
                 ea_params p;
                 memset(&p, 0, sizeof p);
@@ -36,7 +36,7 @@ int main() {
                 CHECK(ea::check_params(&p, &dims) == EA_OK, "d %d G %d", d, G);
                 dims.kv_fp8 = fp8;
                 const ea::WsLayout L = ea::make_ws_layout(dims, n, 64);
-                const ea::ScorePlan sp = ea::choose_score_plan(dims, n, cu, mode == 1, mode == 2);
+                const ea::ScorePlan sp = ea::choose_score_plan(dims, n, cu, from_stats);
                 if (!sp.hw) {     // fragments of a pass: the heads' triangles, and a tile of extra rows on k and on k^2 per five heads
                   CHECK(sp.nfrag == sp.GH * ea::frags_per_head(d) + (sp.GH > 5 ? 2 : 1) * d / 16 && sp.unit_frags == sp.passes * sp.nfrag,
                         "d %d G %d: %d fragments", d, G, sp.nfrag);
@@ -67,7 +67,7 @@ int main() {
     dims.kv_fp8 = m.fp8;
     CHECK(ea::choose_score_plan(dims, m.n, 256).hw == m.hw, "G %d, %d units x %ld keys, fp8 %d", m.G, m.units, (long)m.n, m.fp8);
     // operands from the statistics change the choice one way only, and not from 192 heads on
-    const int with = ea::choose_score_plan(dims, m.n, 256, 0, true).hw;
+    const int with = ea::choose_score_plan(dims, m.n, 256, true).hw;
     CHECK(with >= m.hw && (dims.qheads() < ea::kStatsFragsMin || with == m.hw), "G %d, %d units x %ld keys", m.G, m.units, (long)m.n);
   }
   // the tile counters of up to 32 passes: every one a word of its own behind kTicketSlot in the unit's third histogram,
