@@ -143,6 +143,20 @@ inline HwDeal hw_deal(int chunk, int nchunk, int ways) {
   return x;
 }
 
+// How many counters a (unit, pass) of nchunk workgroups uses, at least eight workgroups each; and the tile with number `raw`
+// of residue class `way`, the last tile of the head first, -1 past the first one.
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int hw_ways(int nchunk) { return nchunk < 16 ? 1 : nchunk < 8 * kTicketWays ? nchunk / 8 : kTicketWays; }
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int hw_tile(int raw, int way, int ways, int ntiles) {
+  const int t = ntiles - 1 - (raw * ways + way);
+  return t < 0 ? -1 : t;
+}
+
 // Keys per workgroup of k_score_f32_whole, whole 64 of them, a head in at most 1024 spans.  The workgroups that fit the chip
 // at once do the same amount each, so what counts is rounds of them x (tiles per wavefront + what a workgroup pays at
 // its start).  Of the cuts with the same steps of 64 keys per span the one into fewest spans is looked at: 90 instead of

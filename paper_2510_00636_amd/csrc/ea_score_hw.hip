@@ -121,11 +121,11 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
 
   // Tiles of a (unit, pass): the first two of a workgroup by its number, the others as they are drawn from its counter,
   // the last tile of the head first (see k_score_mfma).
-  const int ways = max(1, min(kTicketWays, a.nchunk / 8));
+  const int ways = hw_ways(a.nchunk);
   const HwDeal deal = hw_deal(chunk, a.nchunk, ways);
   const int way = deal.way, nth = deal.nth, peers = deal.peers;
   uint32_t* tk = a.tickets + (size_t)unit * a.ticket_stride + ticket_word(pass, way);
-  auto tile_of = [&](int raw) { return max(ntiles - 1 - (raw * ways + way), -1); };
+  auto tile_of = [&](int raw) { return hw_tile(raw, way, ways, ntiles); };
   int t_cur = tile_of(nth), t_n1 = tile_of(peers + nth);
   const int dealt = a.spare ? 0 : 2 * peers; // tiles of the class that are dealt by number
   uint32_t draw2 = 0, draw3 = 0;
@@ -140,8 +140,9 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     __syncthreads();
     t_cur = __builtin_amdgcn_readfirstlane(s_tk[0]);
     t_n1 = __builtin_amdgcn_readfirstlane(s_tk[1]);
-    if (t_cur < 0) return;
-  } else if (tid == 0) {
+  }
+  if (t_cur < 0) return;                     // it came too late; or (short heads) its class has fewer tiles than workgroups
+  if (!a.spare && tid == 0) {
     draw2 = atomicAdd(tk, 1u);
     draw3 = atomicAdd(tk, 1u);
   }

@@ -1,6 +1,6 @@
-// Host-only driver: whatever kernel a call's score plan names, its fragments and partials fit the workspace, no
-// workgroup is without a tile at the start, and the tiles that the register-fragment kernel deals out (two to every
-// workgroup by its number, the rest by counters, one per residue class) are every tile of a head once.
+// Host-only driver: whatever kernel a call's score plan names, its fragments and partials fit the workspace, and the
+// tiles that the register-fragment kernel deals out (two to every workgroup by its number and the rest by counters, one
+// per residue class; with spare workgroups all of them by counters) are every tile of a head once.
 #include <initializer_list>
 #include <stdio.h>
 #include <string.h>
@@ -95,8 +95,47 @@ int main() {
         }
         CHECK(ea::f32_span(heads, n, slots) == (steps + best - 1) / best * 64, "%d heads x %ld keys, %d slots", heads, (long)n, slots);
       }
+  // the deal, played with the kernel's own functions: a workgroup works through what it is given until the first tile
+  // that is none; draws that it made ahead are lost with it
+  for (int nchunk = 1; nchunk <= 600; nchunk += nchunk < 80 ? 1 : 37)
+    for (int ntiles : {nchunk, nchunk + 1, nchunk + 7, 2 * nchunk - 1, 2 * nchunk, 3 * nchunk + 5, 17 * nchunk + 3, 2048})
+      for (bool spare : {false, true}) {
+        if (ntiles < nchunk) continue;
+        const int ways = ea::hw_ways(nchunk);
+        CHECK(ways >= 1 && ways <= ea::kTicketWays && (ways == 1 || nchunk / ways >= 8), "%d workgroups: %d counters", nchunk, ways);
+        std::vector<int> counter(ways, 0), scored(ntiles, 0);
+        struct Workgroup { int way, dealt; std::vector<int> queue; bool done; };
+        std::vector<Workgroup> wgs;
+        auto draw = [&](Workgroup& w) { w.queue.push_back(ea::hw_tile(w.dealt + counter[w.way]++, w.way, ways, ntiles)); };
+        for (int c = 0; c < nchunk; ++c) {
+          const ea::HwDeal x = ea::hw_deal(c, nchunk, ways);
+          Workgroup w{x.way, spare ? 0 : 2 * x.peers, {}, false};
+          if (spare) { draw(w); draw(w); }
+          else {
+            w.queue.push_back(ea::hw_tile(x.nth, x.way, ways, ntiles));
+            w.queue.push_back(ea::hw_tile(x.peers + x.nth, x.way, ways, ntiles));
+          }
+          if (spare || w.queue[0] >= 0) { draw(w); draw(w); }      // two ahead
+          wgs.push_back(w);
+        }
+        int round = 0;
+        for (bool busy = true; busy; ++round) {
+          busy = false;
+          for (int c = 0; c < nchunk; ++c) {
+            Workgroup& w = wgs[(c + 13 * round) % nchunk];
+            if (w.done) continue;
+            const int t = w.queue.front();
+            w.queue.erase(w.queue.begin());
+            if (t < 0) { w.done = true; continue; }
+            ++scored[t];
+            draw(w);
+            busy = true;
+          }
+        }
+        for (int t = 0; t < ntiles; ++t) CHECK(scored[t] == 1, "%d workgroups, %d tiles, spare %d: tile %d %d times", nchunk, ntiles, spare, t, scored[t]);
+      }
   for (int nchunk = 1; nchunk <= 600; ++nchunk) {
-    const int ways = nchunk / 8 < 1 ? 1 : nchunk / 8 > 8 ? 8 : nchunk / 8;
+    const int ways = ea::hw_ways(nchunk);
     std::vector<std::vector<int>> members(ways);
     for (int chunk = 0; chunk < nchunk; ++chunk) {
       const ea::HwDeal x = ea::hw_deal(chunk, nchunk, ways);
