@@ -1,5 +1,5 @@
-// Host-only driver: every score plan of the LDS-fragment kernels, for rows of 16 and 8 bits,
-// fits the one workspace layout that callers size their buffers by, and the table launch covers what it clears.  Exits 0 when every check holds.
+// Host-only driver: every score plan that a call can take, for rows of 16 and 8 bits, with operands of its own or
+// from the statistics, fits the one workspace layout that callers size their buffers by, and the table launch covers what it clears.  Exits 0 when every check holds.
 #include <initializer_list>
 #include <stdio.h>
 #include <string.h>
@@ -36,11 +36,13 @@ int main() {
             CHECK(L.total == bytes && L.hist == plain.hist, "d %d G %d units %d n %ld fp8 %d: %zu bytes, %zu reserved", d, G,
                   units, (long)n, fp8, L.total, bytes);
             for (int cu : {64, 256, 304}) {
-              const ea::ScorePlan sp = ea::make_score_plan(dd, n, cu);
-              const size_t need = (size_t)units * sp.passes * sp.nfrag * 1024;
-              CHECK(need <= L.post - L.frags, "d %d G %d units %d n %ld fp8 %d: fragments %zu, reserved %zu", d, G,
-                    units, (long)n, fp8, need, L.post - L.frags);
-              CHECK((size_t)dd.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
+              for (bool from_stats : {false, true}) {
+                const ea::ScorePlan sp = ea::choose_score_plan(dd, n, cu, from_stats);
+                const size_t need = (size_t)units * sp.unit_frags * 1024;
+                CHECK(need <= L.post - L.frags, "d %d G %d units %d n %ld fp8 %d: fragments %zu, reserved %zu", d, G,
+                      units, (long)n, fp8, need, L.post - L.frags);
+                CHECK((size_t)dd.qheads() * sp.npart * 8 <= L.lse - L.part, "d %d G %d units %d n %ld partials", d, G, units, (long)n);
+              }
             }
           }
         }
@@ -49,14 +51,18 @@ int main() {
   // Spare workgroups: where the last round of CUs is short, and at d = 256 with fewer jobs than CUs only on
   // heads long enough for the fragments that a spare workgroup loads
   struct { int d, G, units; int64_t n; int spare, nchunk; } plan[] = {
-      {128, 3, 1, 100000, 0, 196}, {128, 3, 8, 9999, 0, 20}, {128, 3, 1, 131072, 0, 256}, {128, 3, 1, 700000, 0, 256},
+      {128, 3, 1, 700000, 0, 256}, {128, 3, 8, 70000, 0, 32}, {128, 5, 3, 90000, 0, 71},
       {64, 8, 1, 100000, 0, 196}, {64, 4, 8, 300, 0, 2}, {256, 2, 32, 1500, 0, 6}, {256, 2, 2, 30000, 0, 128},
       {256, 1, 4, 25000, 0, 64}, {256, 8, 1, 100000, 0, 196}, {256, 4, 8, 9999, 0, 27}, {256, 2, 8, 50000, 0, 32},
-      {128, 6, 50, 4000, 0, 5}, {128, 6, 12, 30000, 0, 21}, {128, 16, 5, 40000, 0, 40}, {256, 4, 2, 40000, 0, 128},
-      {128, 7, 48, 2043, 0, 5}, {128, 7, 20, 4915, 0, 10}, {128, 7, 6, 27931, 0, 42}, {256, 8, 1, 180219, 0, 256},
-      {256, 4, 3, 11963, 0, 47}, {256, 4, 6, 12091, 0, 42}, {128, 8, 8, 30698, 0, 32}, {128, 16, 3, 91387, 0, 72},
-      {128, 4, 300, 1024, 1, 4}, {128, 4, 300, 1000, 0, 1}, {128, 4, 436, 2000, 0, 1}, {128, 7, 140, 2000, 1, 3},
-      {128, 4, 200, 8000, 0, 1}, {128, 4, 128, 8000, 0, 2}, {128, 4, 1800, 2000, 0, 1},
+      {128, 6, 50, 4000, 0, 5}, {128, 6, 12, 30000, 0, 21}, {256, 4, 2, 40000, 0, 128}, {128, 10, 20, 14915, 0, 12},
+      {128, 9, 6, 60000, 0, 42}, {256, 8, 1, 180219, 0, 256}, {128, 10, 48, 20043, 0, 5},
+      {256, 4, 3, 11963, 0, 47}, {256, 4, 6, 12091, 0, 42}, {128, 5, 8, 30698, 0, 32}, {128, 10, 3, 191387, 0, 85},
+      {128, 5, 300, 1024, 1, 4}, {128, 5, 300, 1000, 0, 1}, {128, 5, 436, 2000, 0, 1}, {128, 9, 140, 2000, 1, 3},
+      {128, 5, 200, 8000, 0, 1}, {128, 5, 1800, 2000, 0, 1},
+      // the register-fragment kernel: two workgroups per CU, one more for each (unit, pass) where whole ones leave CUs out
+      {128, 4, 8, 16384, 0, 64}, {128, 4, 32, 131072, 0, 16}, {128, 4, 1, 3000, 0, 47}, {128, 4, 3, 64, 0, 1}, {128, 4, 192, 4608, 1, 3},
+      {128, 4, 128, 8000, 0, 4}, {128, 4, 300, 1000, 0, 1}, {128, 4, 300, 1024, 1, 2}, {128, 7, 20, 4915, 0, 12}, {128, 7, 48, 2043, 1, 6},
+      {128, 7, 140, 2000, 1, 2}, {128, 9, 8, 9000, 0, 21}, {128, 16, 5, 40000, 0, 25},
       {256, 2, 160, 1024, 0, 1}, {256, 2, 160, 1500, 1, 3}, {256, 2, 200, 1500, 0, 1}, {256, 2, 200, 3999, 0, 1},
       {256, 2, 200, 4000, 1, 3}, {256, 1, 200, 1999, 0, 1}, {256, 1, 200, 2000, 1, 3}, {256, 1, 160, 1024, 1, 3},
       {256, 2, 260, 1024, 1, 4}, {256, 4, 140, 1024, 1, 3}, {256, 2, 240, 9000, 0, 1}};
@@ -67,7 +73,7 @@ int main() {
     p.q_is_rotated = 1; p.horizon_T = 512;
     ea::Dims dims;
     CHECK(ea::check_params(&p, &dims) == EA_OK, "d %d G %d", c.d, c.G);
-    const ea::ScorePlan sp = ea::make_score_plan(dims, c.n, 256);
+    const ea::ScorePlan sp = ea::choose_score_plan(dims, c.n, 256);
     CHECK(sp.spare == c.spare && sp.nchunk == c.nchunk, "d %d G %d units %d n %ld: spare %d, %d workgroups", c.d, c.G, c.units,
           (long)c.n, sp.spare, sp.nchunk);
   }

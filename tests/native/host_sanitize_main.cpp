@@ -42,9 +42,9 @@ int main() {
             CHECK(dd.units() == B * Hkv && dd.qheads() == B * G * Hkv && dd.G == G);
             for (int64_t n : sizes) {
               for (int cu : cus) {
-                ea::ScorePlan sp = ea::make_score_plan(dd, n, cu);
+                ea::ScorePlan sp = ea::choose_score_plan(dd, n, cu);
                 CHECK(sp.passes >= 1 && sp.GH >= 1 && sp.passes * sp.GH >= G);
-                CHECK(sp.nfrag >= 1 && sp.npart >= 1 && sp.nchunk >= 1);
+                CHECK(sp.unit_frags >= 1 && sp.npart >= 1 && sp.nchunk >= 1);
                 CHECK((int64_t)sp.npart * sp.pg >= n);             // the partial blocks cover every key
                 if (!sp.hw) CHECK(sp.lds_bytes <= 160 * 1024);
               }
@@ -59,8 +59,8 @@ int main() {
                 CHECK(ea_workspace_bytes(&p, n, w) == L.total);
                 // the plan the launch uses (real CU count) never needs more than the layout reserved
                 for (int cu : cus) {
-                  ea::ScorePlan sp = ea::make_score_plan(dd, n, cu);
-                  CHECK((size_t)dd.units() * sp.passes * sp.nfrag * 1024 <= L.post - L.frags);
+                  ea::ScorePlan sp = ea::choose_score_plan(dd, n, cu);
+                  CHECK((size_t)dd.units() * sp.unit_frags * 1024 <= L.post - L.frags);
                   if (dtype == EA_BF16) CHECK((size_t)dd.qheads() * sp.npart * 8 <= L.lse - L.part);
                 }
               }

@@ -408,7 +408,8 @@ def test_register_fragment_scores_at_tile_edges(hq, hkv, n):
     P.check_scores(sc.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), 0.02), 2e-3)
 
 
-@pytest.mark.parametrize("w,dm,hq", [(16, 64, 2), (17, 512, 2), (33, 520, 2), (65, 2056, 2), (100, 4104, 24)])
+@pytest.mark.parametrize("w,dm,hq", [(16, 64, 2), (17, 512, 2), (33, 520, 2), (65, 2056, 2), (100, 4104, 24),
+                                     (100, 2040, 32), (50, 4104, 32)])     # 64 samples x four parts, 32 x eight
 def test_projection_tile_edges(w, dm, hq):
     """bf16 projections around the edges of their tiles of 16, 32 and 64 samples, four and eight parts of the d_model
     axis, parts that are empty and parts that end inside a block of 64 entries.  Against Eq. 5 in fp64 at the tolerance
@@ -466,3 +467,49 @@ def test_bf16_scores_with_a_sigma_that_is_not_symmetric(d, hq, hkv, n):
         ea.score(p, P.to_dev(lay["k"]), P.to_dev(lay["v"]), n, n, P.to_dev(mu), P.to_dev(bad), got, ws)
         torch.cuda.synchronize()
         assert torch.isnan(got[0, 0]).all() and torch.isfinite(got[0, 1:]).all(), (i, j)
+
+
+@pytest.mark.parametrize("hq,batch", [(4, 300), (7, 150)])
+def test_register_fragment_scores_with_spare_workgroups(hq, batch):
+    """d = 128, more jobs than whole workgroups per job fill the chip with: all tiles are drawn, and workgroups come when
+    their unit has none left.  On contiguous tensors, block pools and 8-bit caches, and in the two forms without a value
+    side, with a ragged last tile.  Against the oracle at the bf16 tolerance; norms at half of it (a square root)."""
+    import torch
+    from ea_inputs import make_block_pools, quantize_fp8
+    n, eps = 1030, 0.02
+    cfg = CONFIGS["c2"].with_(n_q_heads=hq, n_kv_heads=1, batch=batch)
+    lay = make_layer(cfg, n=n, window=32)
+    p = P.params_for(cfg, epsilon=eps)
+    mu, sigma = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T)
+    mu, sigma = mu.astype(np.float32), sigma.astype(np.float32)
+    mud, sgd, k, v = (P.to_dev(x) for x in (mu, sigma, lay["k"], lay["v"]))
+    ws = P.workspace(p, n, 1)
+    sc = torch.empty(batch, 1, n, device="cuda")
+    ref = O.scores(widen(lay["k"]), widen(lay["v"]), mu, sigma, eps)
+    ea.score(p, k, v, n, n, mud, sgd, sc, ws)
+    torch.cuda.synchronize()
+    contiguous = sc.cpu().numpy()
+    P.check_scores(contiguous, ref, 2e-3)
+    kp, vp, tab, nb = make_block_pools(lay["k"], lay["v"], 16, 3)
+    tabd = torch.from_numpy(tab).cuda()
+    ea.score_paged(p, P.to_dev(kp), P.to_dev(vp), ea.make_paged(tabd, 16, nb), n, mud, sgd, sc, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(sc.cpu().numpy(), contiguous, rtol=2e-5, atol=0)
+    (k8, ks), (v8, vs) = quantize_fp8(widen(lay["k"])), quantize_fp8(widen(lay["v"]))
+    k8d, v8d, ksd, vsd = (torch.from_numpy(x).cuda() for x in (k8, v8, ks, vs))
+    ea.score_fp8(p, k8d, v8d, ksd, vsd, n, n, mud, sgd, sc, ws)
+    torch.cuda.synchronize()
+    real = [X.fp8_e4m3_decode(c) * s.astype(np.float64)[:, :, None, None] for c, s in ((k8, ks), (v8, vs))]
+    P.check_scores(sc.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), eps), 2e-3)
+    wo = np.random.default_rng(5).standard_normal((hq, 128, 128)) / 12
+    gram = np.ascontiguousarray(np.swapaxes(wo, 1, 2) @ wo, np.float32)
+    wn = torch.empty(batch, hq, n, device="cuda")
+    ea.value_norms_wo(p, v, n, n, torch.from_numpy(gram).cuda(), wn, ws)
+    torch.cuda.synchronize()
+    vals = widen(lay["v"]).astype(np.float64)[:, 0]
+    norms = np.stack([np.sqrt(np.maximum(((vals @ m.astype(np.float64)) * vals).sum(-1), 0)) for m in gram], 1)
+    np.testing.assert_allclose(wn.cpu().numpy(), norms, rtol=1e-3)
+    # the same attention, weighed by ones: (mean_g a + eps)
+    ea.score_wo(p, k, v, n, n, mud, sgd, torch.ones(batch, hq, n, device="cuda"), sc, ws)
+    torch.cuda.synchronize()
+    P.check_scores(sc.cpu().numpy(), ref / np.linalg.norm(vals, axis=-1)[:, None], 2e-3)
