@@ -570,8 +570,9 @@ constexpr int stats_split_chunk(int D) { return D >= 256 ? 32 : 64; }
 // row operand once for two tiles, took 104 us to 94; keeping Sigma on the chip took the 64 MB it wrote, half of
 // them in 4-byte pieces, and the 27 us of k_prep_frags off (whole pass 422 -> 396 us; with the order of tiles that
 // needs no scratch memory 390 -> 381).
-// FUSED (d <= 128, one workgroup per head): Sigma stays in LDS and leaves as the fragments that k_prep_frags
-// would have made of it, bit for bit.
+// FUSED (d <= 128): Sigma leaves as the fragments that k_prep_frags would have made of it.  One workgroup per head: it stands
+// in LDS and they are the same bit for bit.  Two (OWN below): each makes those of its own tiles, the same up to the head's
+// power of two.
 template <int D, int LAYOUT, int PARTS = 0, bool FUSED = false>
 __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSED)) ? 3 : 2)) void k_stats_split(const void* __restrict__ q_win, int w,
                                                                          int ddof,

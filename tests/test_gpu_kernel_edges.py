@@ -68,6 +68,13 @@ def test_scores_with_spare_workgroups(d, hq, hkv, batch, n):
     P.check_scores(got, O.scores(widen(lay["k"]), widen(lay["v"]), mu, sigma, 0.02), 2e-3)
 
 
+def _same_operands(d, heads, a, b):
+    if d == 64 or heads >= 192:
+        assert np.array_equal(a, b)
+    else:
+        np.testing.assert_allclose(a, b, rtol=1e-6, atol=0)
+
+
 @pytest.mark.parametrize("d,hq,hkv,batch", [
     (64, 8, 1, 1), (64, 5, 1, 3),           # G = 5 in an eight-head instance: rows and fragments of no head
     (128, 4, 1, 47), (128, 4, 1, 48),       # 188 and 192 heads: either side of the rule
@@ -78,7 +85,9 @@ def test_fused_statistics_give_the_same_operands(d, hq, hkv, batch, w, layout):
     """compress_layer's scores are those of query_stats followed by score, bit for bit (both calls go to the same score
     kernel at this length): the statistics
     kernel that writes the score kernel's operands itself makes the ones that the separate kernels
-    make of mu and sigma.  (Those are compared with the oracle elsewhere.)"""
+    make of mu and sigma.  (Those are compared with the oracle elsewhere.)  Where two workgroups share a head (d = 128, under
+    192 heads) its power of two may differ, and with it the rounding of entries under 2^-26 of the largest: d^2 of them
+    move a logit by less than d 2^-37 of the quadratic term, 1e-8 here, next to fp32 sums of 2^-24."""
     import torch
     n = 300
     cfg = CONFIGS["c2"].with_(head_dim=d, n_q_heads=hq, n_kv_heads=hkv, batch=batch)
@@ -93,7 +102,7 @@ def test_fused_statistics_give_the_same_operands(d, hq, hkv, batch, w, layout):
     ea.score(p, k, v, n, n, mu, sigma, sc[0], ws)
     ea.compress_layer(p, q, w, lay["q_pos0"], inv, lay["t_next"], k, v, n, n, n // 2, sc[1], None, ws)
     torch.cuda.synchronize()
-    assert np.array_equal(sc[0].cpu().numpy(), sc[1].cpu().numpy())
+    _same_operands(d, hq * batch, sc[0].cpu().numpy(), sc[1].cpu().numpy())
 
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 4095, 4096, 4097, 8192, 8193, 9217, 16383, 16384, 16385])
@@ -295,7 +304,7 @@ def test_compress_takes_the_other_score_kernel(form):
 def test_fused_statistics_behind_every_compress_call(form, d, hq, hkv, batch, w):
     """The other compress calls, on either side of the number of heads from which the statistics kernel writes
     the score kernel's operands: their scores are those of query_stats followed by the score call of the
-    same cache layout, bit for bit."""
+    same cache layout, bit for bit, or to the bound given there."""
     import torch
     from ea_inputs import make_block_pools, quantize_fp8
     n, n_keep = 300, 120
@@ -330,7 +339,7 @@ def test_fused_statistics_behind_every_compress_call(form, d, hq, hkv, batch, w)
         else:
             ea.compress_layer_adaptive(p, *win, k, v, n, n, n_keep, 30, got, idx, lengths, ws)
     torch.cuda.synchronize()
-    assert np.array_equal(got.cpu().numpy(), want.cpu().numpy())
+    _same_operands(d, hq * batch, got.cpu().numpy(), want.cpu().numpy())
 
 
 @pytest.mark.parametrize("n,w,floor", [(16385, 64, 300), (20481, 2, 300), (20481, 64, 0), (16385, 3, 6000)])
