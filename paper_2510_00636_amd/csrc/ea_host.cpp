@@ -85,19 +85,16 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu) {
   }
   // A CU holds one workgroup.  Up to half as many units as CUs: every unit gets its share of the CUs, rounded down.
   // Where that leaves a wavefront at most three tiles, only as many workgroups as finish in the same number of tiles
-  // per wavefront: more of them draw more tickets for nothing.  score, with the share and with fewer: d = 128, G = 3,
-  // one head x 100000 keys (256 and 196 workgroups) 99.3 and 89.2 us; 8 heads x 9999 34.2 and 31.4; 32 x 4608 39.9
-  // and 38.8; d = 256, G = 2, one head x 100000 87 and 80, 32 x 1500 45.2 and 42.9.  With four to seven tiles it
-  // gives 1 % or costs 5 (G = 8, 8 heads x 30698 79 and 85), but for heads of 40 workgroups and more (G = 3, one head
-  // x 200000 138 and 126; G = 7, 5 x 44385 88.5 and 84.3; G = 16, 3 x 91387 232 and 157) that lose more than a few of
-  // them (G = 7, 4 x 95757, 63 and not 64: 126 and 131).
-  // In several passes not all workgroups are on the chip at once, and a head that the first ones leave out starts late:
-  // there the smaller launch has to serve every head as the share does (G = 7, 48 x 2043, four workgroups each and
-  // not five, leave 16 heads out: 54.5 and 59.2; 20 x 4915, ten and not twelve, leave none behind: 62.8 and 57.7), and
-  // keep a grid of a multiple of eight (G = 7, 6 x 27931, 37 and not 42: 69 and 71; d = 256, G = 8, one x 180219,
-  // 235 and not 256: 229 and 373).  Few long heads at d = 256 keep their share (4 x 25000, G = 1, 43.4 and 48.6;
-  // 2 x 30000, G = 2, 50.8 and 54.5; 6 x 12091, G = 4, 71.1 and 73.8) unless nearly half of the workgroups go
-  // (3 x 11963, G = 4, 63.8 and 52.2).
+  // per wavefront: more of them load fragments and draw tickets for nothing.  score, with the share and with fewer: d = 256,
+  // G = 1, 32 x 1500 36.0 and 31.9 us, 8 x 5000 30.6 and 29.4; G = 2, 8 x 9999 48.0 and 46.2; d = 128, G = 5, 32 x 4608 47.9
+  // and 46.9.  In one pass not for fewer than eight units, at d = 64 than 32 (d = 256, G = 1, one x 100000 38.7 and 44.9; d = 64,
+  // G = 8, 8 x 9999 28.9 and 30.1), and not with more tiles per wavefront (one x 360443 53.1 and 62.9).
+  // In several passes also with four to seven tiles, for heads of 40 workgroups and more that lose more than a few of them
+  // (d = 64, G = 16, 3 x 91387 70.9 and 66.1; d = 256, G = 8, 3 x 45691 177 and 159).  There not all workgroups are on the chip
+  // at once, and a head that the first ones leave out starts late: the smaller launch has to serve every head as the share
+  // does, and keep a grid of a multiple of eight (d = 256, G = 8, one x 180219, 256 and not 235: 196 and 203).  Few long heads
+  // at d = 256 in two passes keep their share (6 x 12091, G = 4, 65.4 and 68.4) unless nearly half of the workgroups go
+  // (3 x 11963, G = 4, 52.8 and 44.4).
   //
   // More units: one workgroup per (unit, pass) job, and where these leave the last round of CUs to 85 % full
   // or less, spare ones behind them, three per job (two while the units do not exceed the CUs: fewer CUs are
@@ -123,7 +120,8 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu) {
   } else {
     const int64_t per_wave = (ntiles + wgs * s.NW - 1) / (wgs * s.NW), fewer = (ntiles + per_wave * s.NW - 1) / (per_wave * s.NW);
     bool take = per_wave <= 3 || (per_wave < 8 && wgs >= 40 && fewer * 20 <= wgs * 19);
-    if (d.D == 256 && s.passes <= 2 && d.units() >= 2 && d.units() <= 6) take = take && fewer * 5 < wgs * 3;
+    if (s.passes == 1) take = per_wave <= 3 && d.units() >= (d.D == 64 ? 32 : 8);
+    if (d.D == 256 && s.passes == 2 && d.units() >= 2 && d.units() <= 6) take = take && fewer * 5 < wgs * 3;
     if (take && fewer < wgs && s.passes > 1)
       take = least_served(d.units(), jobs * fewer, num_cu) * 10 >= least_served(d.units(), jobs * wgs, num_cu) * 9 &&
              ((jobs * wgs) % 8 != 0 || (jobs * fewer) % 8 == 0);

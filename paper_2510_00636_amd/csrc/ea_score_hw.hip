@@ -17,7 +17,7 @@
 //   * softmax partials: (max, sum exp) per tile of 64 keys, so that the finalize pass combines the same numbers in the
 //     same order on every run, whichever workgroup scored the tile.
 //
-// What bounds it: instruction issue (88 matrix and about 320 vector instructions per wavefront and tile, 2100 cycles of the
+// What bounds it: instruction issue (88 matrix and 300 to 350 vector instructions per wavefront and tile, 2100 cycles of the
 // issue port; two wavefronts per SIMD take 4900 for one each) and, in long runs, the power the chip may draw: it then clocks at 1.5 to
 // 1.8 GHz, and the energy per key is what counts.  Of the 16-bit forms the 16x16x32 one draws least (sustained with random
 // data 1850 TFLOP/s, 32x32x16 1650, bf16 1400), and every zero in the operands helps, which is why the fragments on the

@@ -47,12 +47,13 @@ int main() {
           }
         }
   // workgroups per head: no more than finish in the same number of tiles per wavefront, while these are few and, in
-  // several passes, no head is left out of the workgroups that start first.
+  // one pass, the units many; in several no head is left out of the workgroups that start first.
   // Spare workgroups: where the last round of CUs is short, and at d = 256 with fewer jobs than CUs only on
   // heads long enough for the fragments that a spare workgroup loads
   struct { int d, G, units; int64_t n; int spare, nchunk; } plan[] = {
-      {128, 3, 1, 700000, 0, 256}, {128, 3, 8, 70000, 0, 32}, {128, 5, 3, 90000, 0, 71},
-      {64, 8, 1, 100000, 0, 196}, {64, 4, 8, 300, 0, 2}, {256, 2, 32, 1500, 0, 6}, {256, 2, 2, 30000, 0, 128},
+      {128, 3, 1, 700000, 0, 256}, {128, 3, 8, 70000, 0, 32}, {128, 5, 3, 90000, 0, 85},
+      {64, 8, 1, 100000, 0, 256}, {256, 1, 1, 100000, 0, 256}, {64, 8, 8, 9999, 0, 32}, {256, 1, 32, 1500, 0, 6},
+      {64, 4, 8, 300, 0, 2}, {256, 2, 32, 1500, 0, 6}, {256, 2, 2, 30000, 0, 128},
       {256, 1, 4, 25000, 0, 64}, {256, 8, 1, 100000, 0, 196}, {256, 4, 8, 9999, 0, 27}, {256, 2, 8, 50000, 0, 32},
       {128, 6, 50, 4000, 0, 5}, {128, 6, 12, 30000, 0, 21}, {256, 4, 2, 40000, 0, 128}, {128, 10, 20, 14915, 0, 12},
       {128, 9, 6, 60000, 0, 42}, {256, 8, 1, 180219, 0, 256}, {128, 10, 48, 20043, 0, 5},
