@@ -18,12 +18,13 @@
 //     same order on every run, whichever workgroup scored the tile.
 //
 // What bounds it: instruction issue (88 matrix and 300 to 350 vector instructions per wavefront and tile, 2100 cycles of the
-// issue port; two wavefronts per SIMD take 4900 for one each) and, in long runs, the power the chip may draw: it then clocks at 1.5 to
-// 1.8 GHz, and the energy per key is what counts.  Of the 16-bit forms the 16x16x32 one draws least (sustained with random
-// data 1850 TFLOP/s, 32x32x16 1650, bf16 1400), and every zero in the operands helps, which is why the fragments on the
-// diagonal are folded onto their triangle too (8-bit cache, 8 x 131072 keys: 115 -> 112.5 us).  Against the kernel it
+// issue port; two wavefronts per SIMD take 4900 for one each) and the clock, which falls with what the operands make the matrix cores
+// draw: 2.4 GHz in a copy, 1.9 for one call of 4 x 8 heads x 131072 keys after a pause, 1.7 with such calls in a row.  Of the
+// 16-bit forms the 16x16x32 one then gets most done (random data 1900 TFLOP/s, 32x32x16 1660, bf16 1440; zeros 2450), and
+// every zero in the operands helps, which is why the fragments on the diagonal are folded onto their triangle too (8-bit
+// cache, 8 x 131072 keys: 115 -> 112.5 us).  Against the kernel it
 // replaces (32x32x16, tiles of 32 keys, four fragments re-read from LDS; contiguous bf16 only) and, for 8-bit caches and
-// block pools, the LDS-fragment one: operands + score, 8 heads of 4 x 131072 keys 155 -> 130 us, 8-bit 120 -> 113, x 16384
+// block pools, the LDS-fragment one: operands + score, 8 heads of 4 x 131072 keys 155 -> 128 us, 8-bit 120 -> 110, x 16384
 // 38 -> 31, keys only x 32768 46 -> 43, pools of 16-row blocks x 20011 44 -> 39.
 //
 // Scales and the meaning of `post` are those of k_prep_frags (ea_stats.hip).
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
   half8 F[NF], X[2 * NKS];                   // this head's fragments, and those of the extra rows
   {
     const u32x4* src = a.frags + (size_t)unit * a.unit_frags * 64;
-    const bool mine = g0 + w < a.G;          // a wavefront without a head multiplies zeros, which draw little power
+    const bool mine = g0 + w < a.G;          // a wavefront without a head multiplies zeros, which cost the clock least
 #pragma unroll
     for (int i = 0; i < NF; ++i)
       F[i] = mine ? __builtin_bit_cast(half8, src[((g0 + w) * NF + i) * 64 + lane]) : (half8)(_Float16)0.f;

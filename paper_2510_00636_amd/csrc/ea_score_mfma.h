@@ -181,7 +181,7 @@ constexpr int load_slot(int i) { return NX + (i * (NS - NX)) / (2 * NL); }
 // ---------------------------------------------------------------------------------------
 // One wavefront scores 32 keys per iteration, two groups of 16.  Lane l = (c, q) = (l % 16, l / 16) owns the channels
 // 32 b + 8 q .. + 7 (b = 0 .. d/32 - 1) of key c of both groups as fp16 (B operands of the 16x16x32 MFMA, the 16-bit form
-// that draws least power; these passes run at the power limit), the fragments of M (A operand, used for both groups in a
+// with the highest sustained rate on random data), the fragments of M (A operand, used for both groups in a
 // row) come from LDS, and the accumulator layout hands the lane channels back that it holds, so  sum_j acc_j k_j  is 4
 // mixed-precision FMAs per output tile of 16 channels.
 // K rows reach that layout through a per-wave LDS staging buffer (coalesced 16-byte global

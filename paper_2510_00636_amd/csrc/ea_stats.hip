@@ -432,8 +432,8 @@ __device__ __forceinline__ size_t extra_frags(const FragsOut& fo, int unit, int 
 // What lane l of fragment f of a head holds: eight entries of M, output channel `out`, input channels from `in0` on.
 // Fragments are 16 x 32 operands: k-step b is the channels 32 b .. 32 b + 31, lane l's key operand the eight from
 // 32 b + 8 (l / 16) on, output tile j has the rows 4 q + v for channel 32 (j / 2) + 8 q + 4 (j % 2) + v, so that a lane gets
-// back channels it holds, and takes the k-steps 0 .. j / 2.  The zeros of the block on the diagonal draw less power than
-// the same form spread over all of it.
+// back channels it holds, and takes the k-steps 0 .. j / 2.  The zeros of the block on the diagonal cost the clock
+// less than the same form spread over all of it.
 struct FragItem { int out, in0; };
 __device__ __forceinline__ FragItem frag_item(int f, int l) {
   FragItem x;
