@@ -182,10 +182,9 @@ def test_fp32_statistics_window_edges(d, layout, w):
 
 @pytest.mark.parametrize("hq,n", [(20, 2048), (24, 2048), (28, 4100), (32, 2100)])
 def test_one_kv_head_with_many_query_heads_on_every_cache_layout(hq, n):
-    """One KV head, five to eight passes at d = 128: paged and 8-bit caches take another plan than contiguous
-    tensors, with more fragments from 24 heads on and fewer at 20, in the one workspace that
+    """One KV head, five to eight passes at d = 128, on every cache layout in the one workspace that
     workspace_bytes gives.  Scores against the oracle at the bf16 tolerance, the paged ones against the
-    contiguous call's to 2e-5 (other kernel, the same fp16 products), and a NaN value row of the 8-bit cache
+    contiguous call's to 2e-5 (the same fp16 products), and a NaN value row of the 8-bit cache
     shows in the status word."""
     import torch
     from ea_inputs import make_block_pools, quantize_fp8
