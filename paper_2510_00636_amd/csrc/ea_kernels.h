@@ -69,7 +69,9 @@ hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D,
 // ea_select.hip
 // heads this short are selected by one workgroup per unit out of registers, in one launch (no global
 // histograms: hist0 from the finalize pass is not needed then)
-constexpr int64_t kSelSmallMax = 16384;   // (whole pass at 20000 keys per head, one launch and four: 117 us either way; 32768: 142 and 140)
+// (select + compact, one launch and three behind the clearing, us: 8 heads x 17000 30.3 and 34.5, x 20000 32.2 and 36.1,
+// x 24000 35.7 and 39.1, x 32768 46.5 and 45.1; one x 20000 24.3 and 32; 48 x 20000 431 and 450)
+constexpr int64_t kSelSmallMax = 24 * 1024;
 inline bool select_in_one_launch(int64_t n) { return n <= kSelSmallMax; }
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
                          uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st, uint32_t* status_hist = nullptr);

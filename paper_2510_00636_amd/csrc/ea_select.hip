@@ -28,52 +28,100 @@ hipError_t launch_zero(uint32_t* p, size_t count, hipStream_t st, uint32_t* extr
   return hipGetLastError();
 }
 
-// Bin b (counting down from the top) with  count(bins > b) < target <= count(bins >= b);
-// *rem = target - count(bins > b).  Called by all 64 lanes of ONE wavefront; the result is
-// uniform.  nbins is 2048 or 1024; lane l owns the nbins/64 bins just below nbins - l*nbins/64.
-__device__ int find_bin_wave(const uint32_t* __restrict__ hist, int nbins, uint32_t target,
-                             uint32_t* rem, int lane) {
-  const int per = nbins / 64;                        // 32 or 16
-  const int lo = nbins - per * (lane + 1);
-  uint32_t loc[32];
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+#define EA_SCAN_STEP(CTRL, ROWS)                                                       \
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, ROWS == 0xf)
+  EA_SCAN_STEP(0x111, 0xf);                          // lanes 1, 2, 4 and 8 to the left in the row of 16
+  EA_SCAN_STEP(0x112, 0xf);
+  EA_SCAN_STEP(0x114, 0xf);
+  EA_SCAN_STEP(0x118, 0xf);
+  EA_SCAN_STEP(0x142, 0xa);                          // the last lane of the row in front, into rows 1 and 3
+  EA_SCAN_STEP(0x143, 0xc);                          // lane 31, into rows 2 and 3
+#undef EA_SCAN_STEP
+  return x;
+}
+
+// The digit search.  Bin b (counting down from the top) with  count(bins > b) < target <= count(bins >= b), and
+// rem = target - count(bins > b), by all NT threads of a workgroup: thread t holds the PER bins below nbins - t * PER,
+// the lowest of them first.  One barrier between the wavefronts' sums and one in front of the result.  (By one wavefront,
+// 32 bins per lane, it took some 300 instructions in a row, 64 lines of cache or 64 lanes on the same banks of LDS per load,
+// and as much code again for every digit: k_sel_hist 4.5 to 4.9 -> 3.9 us at 8 units x 20011, k_sel_emit 12.1 -> 9.8 at 8 x
+// 131072.)
+template <int NT>
+struct BinSearch {
+  uint32_t sum[NT / 64];
+  uint32_t bin, rem;
+};
+template <int NT, int PER>
+__device__ __forceinline__ void find_bin(BinSearch<NT>& s, const uint32_t (&cnt)[PER], uint32_t target, uint32_t* bin,
+                                         uint32_t* rem) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint32_t sum = 0;
-  const uint4* hp = reinterpret_cast<const uint4*>(hist + lo);
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    if (4 * j < per) {
-      const uint4 v = hp[j];
-      loc[4 * j] = v.x; loc[4 * j + 1] = v.y; loc[4 * j + 2] = v.z; loc[4 * j + 3] = v.w;
-      sum += v.x + v.y + v.z + v.w;
-    } else {
-      loc[4 * j] = loc[4 * j + 1] = loc[4 * j + 2] = loc[4 * j + 3] = 0;
+  for (int j = 0; j < PER; ++j) sum += cnt[j];
+  const uint32_t incl = wave_scan(sum);
+  if (lane == 63) s.sum[wave] = incl;
+  if (tid == 0) { s.bin = 0u; s.rem = 0u; }          // (counters that do not add up to the target: as good as any)
+  __syncthreads();
+  uint32_t front = 0;                                // in the wavefronts in front of this one
+  if constexpr (NT > 256) {
+    front = wave_scan(lane < wave ? s.sum[lane % (NT / 64)] : 0u);
+    front = __builtin_amdgcn_readlane(front, 63);
+  } else {
+#pragma unroll
+    for (int w = 0; w < NT / 64 - 1; ++w) front += w < wave ? s.sum[w] : 0u;
+  }
+  front += incl - sum;                               // and in the lanes
+  uint32_t r = target - front;
+  if (front < target && r <= sum) {
+    uint32_t b = PER - 1;
+#pragma unroll
+    for (int j = PER - 1; j >= 1; --j)
+      if (b == (uint32_t)j && r > cnt[j]) { r -= cnt[j]; --b; }
+    s.bin = (uint32_t)((NT - 1 - tid) * PER) + b;
+    s.rem = r;
+  }
+  __syncthreads();
+  *bin = s.bin;
+  *rem = s.rem;
+}
+// this thread's bins of a histogram of NT * PER
+template <int NT, int PER>
+__device__ __forceinline__ void load_bins(const uint32_t* hist, uint32_t (&cnt)[PER]) {
+  const uint32_t* p = hist + (NT - 1 - (int)threadIdx.x) * PER;
+  if constexpr (PER % 4 == 0) {
+#pragma unroll
+    for (int j = 0; j < PER / 4; ++j) {
+      const uint4 v = reinterpret_cast<const uint4*>(p)[j];
+      cnt[4 * j] = v.x; cnt[4 * j + 1] = v.y; cnt[4 * j + 2] = v.z; cnt[4 * j + 3] = v.w;
     }
-  }
-  uint32_t incl = sum;                               // inclusive scan over lanes (lane 0 = top bins)
+  } else if constexpr (PER == 2) {
+    const uint2 v = *reinterpret_cast<const uint2*>(p);
+    cnt[0] = v.x; cnt[1] = v.y;
+  } else {
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t up = __shfl_up(incl, o);
-    if (lane >= o) incl += up;
+    for (int j = 0; j < PER; ++j) cnt[j] = p[j];
   }
-  const uint32_t excl = incl - sum;
-  const bool mine = excl < target && target <= incl;
-  int b = 0;
-  uint32_t r = 0;
-  if (mine) {
-    uint32_t cum = excl;
-    b = lo;
-    r = target - cum;
-#pragma unroll
-    for (int j = 31; j >= 0; --j) {                  // walk this lane's bins from the top down
-      if (j < per) {
-        if (target > cum && target <= cum + loc[j]) { b = lo + j; r = target - cum; }
-        cum += loc[j];
-      }
-    }
+}
+
+// The kept ones among 64 consecutive scores, a lane each: above T, or at T and one of the first q such of the head, to
+// out[pos ..] in order.  pos, eq_before (scores at T in front): the same in all lanes, taken past the row.  Rows with a score
+// at T are few, and the others are spared the counting of them.
+// (Lane masks as numbers: kept as conditions they went through vector registers.)
+__device__ __forceinline__ void emit_row(unsigned long long in, uint32_t u, uint32_t T, uint32_t q, uint32_t& pos,
+                                         uint32_t& eq_before, int32_t* out, uint32_t n_keep, int at) {
+  unsigned long long mask = __ballot(u > T) & in;
+  const unsigned long long ties = __ballot(u == T) & in;
+  if (ties != 0ull) {
+    const uint32_t nth = eq_before + __builtin_amdgcn_mbcnt_hi((uint32_t)(ties >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ties, 0u));
+    mask |= __ballot(nth < q) & ties;
+    eq_before += __popcll(ties);
   }
-  const unsigned long long m = __ballot(mine);
-  const int src = m ? __ffsll((long long)m) - 1 : 0;
-  *rem = __shfl(r, src);
-  return __shfl(b, src);
+  const uint32_t to = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, pos));
+  if (__builtin_amdgcn_inverse_ballot_w64(mask) && to < n_keep) out[to] = at;
+  pos += __popcll(mask);
 }
 
 struct SelArgs {
@@ -87,35 +135,35 @@ struct SelArgs {
   uint32_t* status;  // status word
 };
 
-// Digits fixed by the histogram passes before pass P: wavefront 0 re-derives them (a few
-// hundred cycles, cheaper than another launch) and the workgroup reads them from s_res.
+// Digits fixed by the histogram passes before pass P: every workgroup searches for them again (cheaper than a
+// launch), the histograms requested ahead of everything else.
 template <int P>
-__device__ void resolve(const SelArgs& a, int unit, uint32_t* s_res, uint32_t* prefix, uint32_t* rem) {
-  if (P >= 1 && threadIdx.x < 64) {
-    const int lane = threadIdx.x;
+struct Digits {
+  uint32_t c0[P >= 1 ? kSelBins / kSelThreads : 1], c1[P >= 2 ? kSelBins / kSelThreads : 1], c2[P >= 3 ? kSelBins / 2 / kSelThreads : 1];
+  __device__ __forceinline__ void load(const SelArgs& a, int unit) {
     const uint32_t* h = a.hist + (size_t)unit * 3 * kSelBins;
-    uint32_t r = a.n_keep, pre = 0;
-    const int b0 = find_bin_wave(h, 2048, r, &r, lane);
-    pre = (uint32_t)b0;
-    if (P >= 2) { const int b1 = find_bin_wave(h + kSelBins, 2048, r, &r, lane); pre = (pre << 11) | (uint32_t)b1; }
-    if (P >= 3) { const int b2 = find_bin_wave(h + 2 * kSelBins, 1024, r, &r, lane); pre = (pre << 10) | (uint32_t)b2; }
-    if (lane == 0) { s_res[0] = pre; s_res[1] = r; }
+    if constexpr (P >= 1) load_bins<kSelThreads>(h, c0);
+    if constexpr (P >= 2) load_bins<kSelThreads>(h + kSelBins, c1);
+    if constexpr (P >= 3) load_bins<kSelThreads>(h + 2 * kSelBins, c2);
   }
-  __syncthreads();
-  *prefix = P >= 1 ? s_res[0] : 0u;
-  *rem = P >= 1 ? s_res[1] : a.n_keep;
-  __syncthreads();
-}
+  // prefix: the digits' bits; rem: what is left of n_keep among the scores that start with them
+  __device__ __forceinline__ void find(BinSearch<kSelThreads>* s, uint32_t n_keep, uint32_t* prefix, uint32_t* rem) {
+    uint32_t pre = 0, r = n_keep, b;
+    if constexpr (P >= 1) { find_bin<kSelThreads>(s[0], c0, r, &b, &r); pre = b; }
+    if constexpr (P >= 2) { find_bin<kSelThreads>(s[1], c1, r, &b, &r); pre = (pre << 11) | b; }
+    if constexpr (P >= 3) { find_bin<kSelThreads>(s[2], c2, r, &b, &r); pre = (pre << 10) | b; }
+    *prefix = pre;
+    *rem = r;
+  }
+};
 
 template <int P>
 __global__ __launch_bounds__(kSelThreads) void k_sel_hist(SelArgs a) {
   __shared__ uint32_t s_hist[kSelBins];
-  __shared__ uint32_t s_tmp[258];
+  __shared__ BinSearch<kSelThreads> s_find[P + 1];
   const int tid = threadIdx.x, unit = blockIdx.x;
-  uint32_t prefix = 0, rem;
-  resolve<P>(a, unit, s_tmp, &prefix, &rem);
-  for (int i = tid; i < kSelBins; i += kSelThreads) s_hist[i] = 0;
-  __syncthreads();
+  Digits<P> dig;
+  dig.load(a, unit);
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
   const long long base = (long long)blockIdx.y * kSelBlock;
   // All loads first and none under a condition (indices past the end are clamped): a load inside
@@ -123,6 +171,10 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_hist(SelArgs a) {
   uint32_t uu[kSelPer];
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) uu[j] = sc[min(base + j * kSelThreads + tid, a.n - 1)];
+  for (int i = tid; i < kSelBins; i += kSelThreads) s_hist[i] = 0;
+  uint32_t prefix = 0, rem;
+  dig.find(s_find, a.n_keep, &prefix, &rem);
+  if (P == 0) __syncthreads();                       // (else the search's barriers lie behind the zeros)
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) {
     const long long i = base + j * kSelThreads + tid;
@@ -165,13 +217,15 @@ constexpr int kEmitSpinLimit = 1 << 20;
 
 __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
   constexpr int W = kSelThreads / 64, U = 2;
-  __shared__ uint32_t s_tmp[258];
+  __shared__ BinSearch<kSelThreads> s_find[3];
   __shared__ uint32_t s_w[2][W];
   __shared__ uint32_t s_front[3];
   __shared__ uint32_t s_blk;
   const int tid = threadIdx.x, lane = tid & 63, unit = blockIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (tid == 0) s_blk = atomicAdd(a.hist + ((size_t)unit * 3 + 2) * kSelBins + kEmitTicket, 1u);
+  Digits<3> dig;
+  dig.load(a, unit);
   __syncthreads();
   const int blk = __builtin_amdgcn_readfirstlane((int)s_blk);
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
@@ -179,13 +233,21 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
   uint32_t u[kSelPer];
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) u[j] = sc[min(base + 64 * j, a.n - 1)];
+  // which lanes' u[j] are scores of the head, as a number
+  const long long left = a.n - ((long long)blk * kSelBlock + wave * (kSelBlock / W));
+  auto inside = [&](int j) -> unsigned long long {
+    const int m = (int)min(max(left - 64 * j, 0ll), 64ll);
+    return m >= 64 ? ~0ull : (1ull << m) - 1ull;
+  };
   uint32_t T, q;
-  resolve<3>(a, unit, s_tmp, &T, &q);
+  dig.find(s_find, a.n_keep, &T, &q);
+  T = __builtin_amdgcn_readfirstlane(T);
+  q = __builtin_amdgcn_readfirstlane(q);
   uint32_t gt = 0, eq = 0;
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) {
-    gt += __popcll(__ballot(base + 64 * j < a.n && u[j] > T));
-    eq += __popcll(__ballot(base + 64 * j < a.n && u[j] == T));
+    gt += __popcll(__ballot(u[j] > T) & inside(j));
+    eq += __popcll(__ballot(u[j] == T) & inside(j));
   }
   if (lane == 0) { s_w[0][wave] = gt; s_w[1][wave] = eq; }
   __syncthreads();
@@ -232,18 +294,10 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
   for (int w = 0; w < wave; ++w) { pos += s_w[0][w]; eq_before += s_w[1][w]; }
   pos += eq_before < q ? eq_before : q;
   int32_t* out = a.idx + (size_t)unit * a.n_keep;
-  const unsigned long long below = (1ull << lane) - 1ull;
+  pos = __builtin_amdgcn_readfirstlane(pos);
+  eq_before = __builtin_amdgcn_readfirstlane(eq_before);
 #pragma unroll
-  for (int j = 0; j < kSelPer; ++j) {
-    const bool in = base + 64 * j < a.n;
-    const unsigned long long ties = __ballot(in && u[j] == T);
-    const bool keep = in && (u[j] > T || (u[j] == T && eq_before + __popcll(ties & below) < q));
-    const unsigned long long mask = __ballot(keep);
-    const uint32_t at = pos + __popcll(mask & below);
-    if (keep && at < a.n_keep) out[at] = (int32_t)(base + 64 * j);
-    pos += __popcll(mask);
-    eq_before += __popcll(ties);
-  }
+  for (int j = 0; j < kSelPer; ++j) emit_row(inside(j), u[j], T, q, pos, eq_before, out, a.n_keep, (int)(base + 64 * j));
 }
 
 // ---------------------------------------------------------------------------------------
@@ -252,114 +306,97 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
 // consecutive positions (R = ceil(n / 1024)), lane l the l-th of each row of 64, so that positions are
 // counted with ballots and the kept ones leave in order.  Same result as the multi-launch path, bit for bit.
 //
-// What bounds it is the chain of three histograms.  Scores crowd into a few bins of the first digit (four
-// bins per factor of two), and LDS atomics on one address go one by one, so that digit's histogram is kept in
-// four copies, copies of a bin in neighbouring banks.  Against the version that kept the scores in LDS and
-// gave every thread a run of positions (bank conflicts of n / 1024 ways): 8 units x 16384 19.5 -> 14.4 us,
-// 8 x 8000 11.4 -> 9.7, 8 x 1000 8.8 -> 7.4, 192 x 4608 10.1 -> 9.4.
+// What bounds it is the issue of instructions on the one CU that a head gets (four wavefronts per SIMD), then the chain of
+// three histograms.  So lane masks, counts and positions of whole rows are scalar, a row without a score at the threshold is
+// spared the counting of ties, and the digits are searched for by all threads: 1000 -> 670 vector instructions per
+// wavefront, 8 units x 16384 12.0 -> 8.5 us, 192 x 4608 10.3 -> 8.0, 2 x 1024 6.1 -> 4.5.  Scores crowd into a few bins of
+// the first digit (four bins per factor of two), and LDS atomics on one address go one by one, so that digit's histogram is
+// kept in four copies, copies of a bin in neighbouring banks.
 constexpr int kSelSmallThreads = 1024;
 constexpr int kSelCopies = 4;
 
 template <int PER, bool HIST0>
 __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
-  __shared__ uint32_t s_hist[kSelBins * kSelCopies];
-  __shared__ uint32_t s_w[2][kSelSmallThreads / 64];
-  __shared__ uint32_t s_res[2];
+  constexpr int NT = kSelSmallThreads;
+  __shared__ __align__(16) uint32_t s_hist0[HIST0 ? 1 : kSelBins * kSelCopies];
+  __shared__ __align__(16) uint32_t s_hist1[kSelBins], s_hist2[kSelBins / 2];
+  __shared__ BinSearch<NT> s_find[3];
+  __shared__ uint32_t s_w[2][NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, unit = blockIdx.x, n = (int)a.n;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rows = (n + kSelSmallThreads - 1) / kSelSmallThreads;      // <= PER
+  const int rows = (n + NT - 1) / NT;                                  // <= PER
   const int base = wave * 64 * rows + lane;                            // position of u[it]: base + 64 it
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
+  uint32_t c0[kSelBins / NT], c1[kSelBins / NT], c2[kSelBins / 2 / NT];
+  if (HIST0) load_bins<NT>(a.hist + (size_t)unit * 3 * kSelBins, c0);   // the caller's first histogram
   uint32_t u[PER];
 #pragma unroll
   for (int it = 0; it < PER; ++it) u[it] = sc[min(base + 64 * min(it, rows - 1), n - 1)];
-  // u[it] is a score of the head and of this wavefront's share; `lim` is made opaque in front of every phase,
-  // or the compiler keeps PER lane masks alive through all of them
-  int lim = min(n - base, 64 * rows - lane);
-  auto inside = [&](int it) { return 64 * it < lim; };
+  // Which lanes' u[it] are scores of the head and of this wavefront's share, as a number.  (What is the same for all lanes is
+  // kept out of the vector instructions: on the one CU that a head gets, their number is what takes the time.)
+  const int left = __builtin_amdgcn_readfirstlane(min(max(n - wave * 64 * rows, 0), 64 * rows));
+  auto inside = [&](int it) -> unsigned long long {
+    const int m = left - 64 * it;
+    return m >= 64 ? ~0ull : m > 0 ? (1ull << m) - 1ull : 0ull;
+  };
+  if (!HIST0)
+    for (int i = tid; i < kSelBins * kSelCopies; i += NT) s_hist0[i] = 0;
+  for (int i = tid; i < kSelBins; i += NT) s_hist1[i] = 0;
+  if (tid < kSelBins / 2) s_hist2[tid] = 0;
 
-  uint32_t prefix = 0, rem = a.n_keep;
+  uint32_t T, q, bin;                             // threshold pattern so far, what is left to keep among the scores that start with it
   bool bad = false;
-#pragma unroll
-  for (int P = 0; P < 3; ++P) {
-    if (HIST0 && P == 0) {                          // the caller's first histogram
-      if (wave == 0) {
-        uint32_t r;
-        const int b = find_bin_wave(a.hist + (size_t)unit * 3 * kSelBins, 2048, rem, &r, lane);
-        if (lane == 0) { s_res[0] = (uint32_t)b; s_res[1] = r; }
-      }
-      for (int i = tid; i < kSelBins; i += kSelSmallThreads) s_hist[i] = 0;
-      __syncthreads();
-      prefix = s_res[0];
-      rem = s_res[1];
-      continue;
-    }
-    if (!(HIST0 && P == 1)) {
-      for (int i = tid; i < (P == 0 ? kSelBins * kSelCopies : kSelBins); i += kSelSmallThreads) s_hist[i] = 0;
-      __syncthreads();
-    }
-    asm volatile("" : "+v"(lim));
+  if (!HIST0) {
+    __syncthreads();
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
-      if (!inside(it)) continue;
-      if (P == 0) {
-        atomicAdd(&s_hist[(u[it] >> 21) * kSelCopies + (lane & (kSelCopies - 1))], 1u);
-        bad |= u[it] > 0x7f800000u;
-      }
-      if (P == 1 && (u[it] >> 21) == prefix) atomicAdd(&s_hist[(u[it] >> 10) & 2047u], 1u);
-      if (P == 2 && (u[it] >> 10) == prefix) atomicAdd(&s_hist[u[it] & 1023u], 1u);
+      if (!__builtin_amdgcn_inverse_ballot_w64(inside(it))) continue;
+      atomicAdd(&s_hist0[(u[it] >> 21) * kSelCopies + (lane & (kSelCopies - 1))], 1u);
+      bad |= u[it] > 0x7f800000u;
     }
     __syncthreads();
-    if (P == 0) {                                   // the copies of every bin, added up in place
-      uint32_t sum[kSelBins / kSelSmallThreads];
 #pragma unroll
-      for (int j = 0; j < kSelBins / kSelSmallThreads; ++j) {
-        const uint4 c = reinterpret_cast<const uint4*>(s_hist)[tid + j * kSelSmallThreads];
-        sum[j] = c.x + c.y + c.z + c.w;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kSelBins / kSelSmallThreads; ++j) s_hist[tid + j * kSelSmallThreads] = sum[j];
-      __syncthreads();
+    for (int j = 0; j < kSelBins / NT; ++j) {     // the copies of every bin
+      const uint4 c = reinterpret_cast<const uint4*>(s_hist0)[(NT - 1 - tid) * (kSelBins / NT) + j];
+      c0[j] = c.x + c.y + c.z + c.w;
     }
-    if (wave == 0) {
-      uint32_t r;
-      const int b = find_bin_wave(s_hist, P == 2 ? 1024 : 2048, rem, &r, lane);
-      if (lane == 0) { s_res[0] = (prefix << (P == 2 ? 10 : 11)) | (uint32_t)b; s_res[1] = r; }
-    }
-    __syncthreads();
-    prefix = s_res[0];
-    rem = s_res[1];
   }
+  find_bin<NT>(s_find[0], c0, a.n_keep, &T, &q);  // (its barriers lie behind the zeros)
+#pragma unroll
+  for (int it = 0; it < PER; ++it)
+    if (__builtin_amdgcn_inverse_ballot_w64(__ballot((u[it] >> 21) == T) & inside(it))) atomicAdd(&s_hist1[(u[it] >> 10) & 2047u], 1u);
+  __syncthreads();
+  load_bins<NT>(s_hist1, c1);
+  find_bin<NT>(s_find[1], c1, q, &bin, &q);
+  T = (T << 11) | bin;
+#pragma unroll
+  for (int it = 0; it < PER; ++it)
+    if (__builtin_amdgcn_inverse_ballot_w64(__ballot((u[it] >> 10) == T) & inside(it))) atomicAdd(&s_hist2[u[it] & 1023u], 1u);
+  __syncthreads();
+  load_bins<NT>(s_hist2, c2);
+  find_bin<NT>(s_find[2], c2, q, &bin, &q);
+  T = (T << 10) | bin;
   if (__ballot(bad) != 0ull && lane == 0) atomicOr(a.status, kStatusBadScore);
-  const uint32_t T = prefix, q = rem;             // threshold pattern, ties at T to keep
+  // T: threshold pattern, q: ties at T to keep
 
+  T = __builtin_amdgcn_readfirstlane(T);
+  q = __builtin_amdgcn_readfirstlane(q);
   // scores above T and at T per wavefront, then what lies in front of this wavefront
-  asm volatile("" : "+v"(lim));
   uint32_t gt = 0, eq = 0;
 #pragma unroll
   for (int it = 0; it < PER; ++it) {
-    gt += __popcll(__ballot(inside(it) && u[it] > T));
-    eq += __popcll(__ballot(inside(it) && u[it] == T));
+    gt += __popcll(__ballot(u[it] > T) & inside(it));
+    eq += __popcll(__ballot(u[it] == T) & inside(it));
   }
   if (lane == 0) { s_w[0][wave] = gt; s_w[1][wave] = eq; }
   __syncthreads();
   uint32_t pos = 0, eq_before = 0;
   for (int w = 0; w < wave; ++w) { pos += s_w[0][w]; eq_before += s_w[1][w]; }
-  pos += eq_before < q ? eq_before : q;
+  pos = __builtin_amdgcn_readfirstlane(pos + (eq_before < q ? eq_before : q));
+  eq_before = __builtin_amdgcn_readfirstlane(eq_before);
   int32_t* out = a.idx + (size_t)unit * a.n_keep;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  asm volatile("" : "+v"(lim));
 #pragma unroll
-  for (int it = 0; it < PER; ++it) {
-    const unsigned long long ties = __ballot(inside(it) && u[it] == T);
-    const bool keep = inside(it) && (u[it] > T || (u[it] == T && eq_before + __popcll(ties & below) < q));
-    const unsigned long long kept = __ballot(keep);
-    const uint32_t at = pos + __popcll(kept & below);
-    if (keep && at < a.n_keep) out[at] = base + 64 * it;
-    pos += __popcll(kept);
-    eq_before += __popcll(ties);
-  }
+  for (int it = 0; it < PER; ++it) emit_row(inside(it), u[it], T, q, pos, eq_before, out, a.n_keep, base + 64 * it);
 }
 
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
@@ -373,14 +410,15 @@ hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t 
   a.blk = blk;
   a.idx = idx;
   a.nblk = (int)((n + kSelBlock - 1) / kSelBlock);
-  static_assert(kSelSmallMax <= 16 * kSelSmallThreads, "scores per thread");
+  static_assert(kSelSmallMax <= 24 * kSelSmallThreads, "scores per thread");
   if (select_in_one_launch(n)) {
 #define EA_SMALL(PP)                                                                                  \
   if (hist0_done) k_sel_small<PP, true><<<d.units(), kSelSmallThreads, 0, st>>>(a);                   \
   else k_sel_small<PP, false><<<d.units(), kSelSmallThreads, 0, st>>>(a)
     if (n <= 4 * kSelSmallThreads) { EA_SMALL(4); }
     else if (n <= 8 * kSelSmallThreads) { EA_SMALL(8); }
-    else { EA_SMALL(16); }
+    else if (n <= 16 * kSelSmallThreads) { EA_SMALL(16); }
+    else { EA_SMALL(24); }
 #undef EA_SMALL
     return hipGetLastError();
   }

@@ -521,3 +521,21 @@ def test_register_fragment_scores_with_spare_workgroups(hq, batch):
     ea.score_wo(p, k, v, n, n, mud, sgd, torch.ones(batch, hq, n, device="cuda"), sc, ws)
     torch.cuda.synchronize()
     P.check_scores(sc.cpu().numpy(), ref / np.linalg.norm(vals, axis=-1)[:, None], 2e-3)
+
+
+@pytest.mark.parametrize("n", [20480, 24575, 24576, 24577, 28673])
+@pytest.mark.parametrize("kind", ["spread", "ties", "special"])
+def test_select_around_the_one_launch_limit(n, kind):
+    """Heads on both sides of the longest that one workgroup selects, with last rows of one score, of 63 and of 64, ties that run
+    across rows and wavefronts, and scores among zero, denormals, the largest number and infinity: exactly the stable top-k."""
+    rng = np.random.default_rng(n)
+    shape = (1, 3, n)
+    sc = np.exp(rng.standard_normal(shape)).astype(np.float32)
+    if kind == "ties":
+        sc = rng.integers(0, 3, shape).astype(np.float32)
+    elif kind == "special":
+        sc = rng.choice(np.array([0.0, 1e-45, 1e-40, 1.0, 3.4028235e38, np.inf], dtype=np.float32), shape)
+    cfg = CONFIGS["c1"].with_(n_q_heads=3, n_kv_heads=3)
+    for n_keep in (1, 64, n // 2, n - 1, n):
+        idx = P.run_select(cfg, sc, n_keep)
+        assert np.array_equal(idx.astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
