@@ -539,3 +539,23 @@ def test_select_around_the_one_launch_limit(n, kind):
     for n_keep in (1, 64, n // 2, n - 1, n):
         idx = P.run_select(cfg, sc, n_keep)
         assert np.array_equal(idx.astype(np.int64), O.select(sc.astype(np.float64), n_keep)), n_keep
+
+
+@pytest.mark.parametrize("w,dm,hq,hkv", [(520, 200, 16, 2), (513, 72, 16, 2), (40, 136, 3, 1), (1, 8, 1, 1), (127, 1000, 5, 1)])
+def test_projection_blocks_of_whole_lines(w, dm, hq, hkv):
+    """bf16 projections with 64 samples per workgroup (enough of them for that), d_model of less than one block of 64 entries
+    and ends inside a block (rows then start in the middle of a line of memory), and channel counts that the eight dies do not
+    divide.  Against Eq. 5 in fp64 at the tolerance of the statistics, as in the test above of the same tiles."""
+    import torch
+    from ea_inputs import bf16_bits_from_f64, inv_freq_table
+    cfg = CONFIGS["c2"].with_(n_q_heads=hq, n_kv_heads=hkv)
+    r = np.random.default_rng(w + dm)
+    hb = bf16_bits_from_f64(r.standard_normal((1, w, dm)) * 1.5 + r.standard_normal(dm))
+    wb = bf16_bits_from_f64(r.standard_normal((hq, 128, dm)) / np.sqrt(dm))
+    inv = inv_freq_table(128, cfg.rope_base)
+    p = P.params_for(cfg)
+    mu, sg = torch.empty(1, hq, 128, device="cuda"), torch.empty(1, hq, 128, 128, device="cuda")
+    ea.query_stats_hidden(p, P.to_dev(hb), P.to_dev(wb), dm, w, P.to_dev(inv), 70000, mu, sg, P.workspace(p, 8, w))
+    torch.cuda.synchronize()
+    rmu, rsg = X.query_stats_hidden(widen(hb), widen(wb), inv, 70000, T=cfg.horizon_T)
+    P.check_stats(mu.cpu().numpy(), sg.cpu().numpy(), rmu, rsg)
