@@ -414,38 +414,6 @@ ea_status ea_compress_layer(const ea_params* p, const void* q_win, int64_t windo
                        scores_out, idx_out, ws, ws_bytes, stream, nullptr);
 }
 
-// Pooled selection of ea_select_adaptive on the caller's stream.  `lifted`: a buffer of units * n
-// floats that is not `scores` (only used with a floor); `top`: units * floor ints of scratch.  The
-// histograms of the heads and of the pooled lists, and the block counts, are zero on entry; hist0_done: the heads' first one
-// is filled.
-static ea_status run_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor,
-                                     int32_t* idx, int32_t* lengths, float* lifted, int32_t* top, char* w,
-                                     const WsLayout& L, bool hist0_done, hipStream_t st) {
-  uint32_t* hist = (uint32_t*)(w + L.hist);
-  uint32_t* pool_hist = (uint32_t*)(w + L.pool_hist);
-  // block counts of the heads' selection, then of the pooled one (never more of them)
-  uint32_t* blk = (uint32_t*)(w + L.blk);
-  uint32_t* pool_blk = blk + (size_t)d.units() * (size_t)((n + kSelBlock - 1) / kSelBlock);
-  int32_t* flat = (int32_t*)(w + L.idx);                // [B][Hkv * n_keep], ascending in [0, Hkv * n)
-  Dims layer = d;                                       // one pooled list per sequence
-  layer.Hq = d.G;
-  layer.Hkv = 1;
-  const float* pooled = scores;
-  bool pool_hist0 = false;
-  if (floor > 0 && n_keep > 0) {
-    // every head's own best `floor` pairs, then a copy of the scores with those lifted to +inf
-    EA_TRY(launch_select(d, scores, n, floor, top, hist, blk, hist0_done, st));
-    pool_hist0 = !select_in_one_launch((int64_t)d.Hkv * n);
-    EA_TRY(launch_lift(d, scores, top, n, floor, lifted, pool_hist0 ? pool_hist : nullptr, st));
-    pooled = lifted;
-  }
-  if (n_keep > 0)
-    EA_TRY(launch_select(layer, pooled, (int64_t)d.Hkv * n, (int64_t)d.Hkv * n_keep, flat, pool_hist, pool_blk, pool_hist0, st,
-                         hist));
-  EA_TRY(launch_split_pooled(flat, d.B, d.Hkv, n, n_keep, idx, lengths, st));
-  return EA_OK;
-}
-
 ea_status ea_select_adaptive(const ea_params* p, const float* scores, int64_t n, int64_t n_keep,
                              int64_t floor, int32_t* idx, int32_t* lengths, void* ws, size_t ws_bytes,
                              void* stream) {
@@ -459,8 +427,9 @@ ea_status ea_select_adaptive(const ea_params* p, const float* scores, int64_t n,
   if ((s = check_ws(d, n, 1, ws, ws_bytes, &L)) != EA_OK) return s;
   char* w = (char*)ws;
   EA_TRY(launch_zero((uint32_t*)(w + L.hist), (L.flags - L.hist) / 4, (hipStream_t)stream));
-  return run_select_adaptive(d, scores, n, n_keep, floor, idx, lengths, (float*)(w + L.scores),
-                             (int32_t*)(w + L.logits), w, L, false, (hipStream_t)stream);
+  EA_TRY(launch_select_adaptive(d, scores, n, n_keep, floor, idx, lengths, (uint32_t*)(w + L.hist), (uint32_t*)(w + L.pool_hist),
+                                (uint32_t*)(w + L.blk), false, (hipStream_t)stream));
+  return EA_OK;
 }
 
 ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int64_t window, int64_t q_pos0,
@@ -494,15 +463,11 @@ ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int6
   if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, mu, sigma, w, L, st, hist,
                                (L.flags - L.hist) / 4 + flag_words(d, n), &frags_ready)) != EA_OK)
     return s;
-  const bool hist0 = floor > 0 && n_keep > 0 && !select_in_one_launch(n);
-  if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores, hist0 ? hist : nullptr, true, w, L, st, nullptr, nullptr, nullptr,
+  if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores, hist, true, w, L, st, nullptr, nullptr, nullptr,
                      nullptr, nullptr, nullptr, frags_ready)) != EA_OK)
     return s;
-  // after pass B the logit and value-norm scratch is free: the floor's lists and the lifted copy
-  // of the scores go there
-  if ((s = run_select_adaptive(d, scores, n, n_keep, floor, idx_out, lengths_out, (float*)(w + L.vnorm),
-                               (int32_t*)(w + L.logits), w, L, hist0, st)) != EA_OK)
-    return s;
+  EA_TRY(launch_select_adaptive(d, scores, n, n_keep, floor, idx_out, lengths_out, hist, (uint32_t*)(w + L.pool_hist),
+                                (uint32_t*)(w + L.blk), true, st));
   uint32_t* flags = (uint32_t*)(w + L.flags);
   uint32_t* status = hist + 2 * kSelBins + kStatusSlot;
   EA_TRY(launch_compact(d, k, v, n, n_cap, idx_out, n, k, v, flags, status, st, lengths_out, n));

@@ -74,8 +74,7 @@ hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D,
 constexpr int64_t kSelSmallMax = 24 * 1024;
 inline bool select_in_one_launch(int64_t n) { return n <= kSelSmallMax; }
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
-                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st, uint32_t* status_hist = nullptr);
-// status_hist: the histograms whose free words hold the status word, if not `hist`
+                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st);
 hipError_t launch_zero(uint32_t* p, size_t count, hipStream_t st, uint32_t* extra = nullptr);
 
 // ea_compact.hip
@@ -86,13 +85,11 @@ hipError_t launch_compact(const Dims& d, const void* k, const void* v, int64_t n
 // pm != nullptr: k and v are block pools (in place only; n_cap unused)
 // lengths != nullptr: unit u keeps lengths[u] <= n_keep rows, listed from idx + u * idx_stride
 
-// ea_select.hip, head-adaptive budgets: lifted = scores with +inf at [unit][top[unit][j]], j < n_mark
-// (ascending lists); pool_hist (nullable, zero): first radix digit of each sequence's lifted scores.  Then the
-// split of a pooled, ascending list flat[b][0 .. H*n_keep) over [H][n] into per-head lists
-hipError_t launch_lift(const Dims& d, const float* scores, const int32_t* top, int64_t n, int64_t n_mark, float* lifted,
-                       uint32_t* pool_hist, hipStream_t st);
-hipError_t launch_split_pooled(const int32_t* flat, int B, int H, int64_t n, int64_t n_keep, int32_t* idx,
-                               int32_t* lengths, hipStream_t st);
+// ea_select.hip, head-adaptive budgets: ascending lists idx [units][n] and their lengths.  All of the scratch is zero at launch
+// (hist0_done: but for the heads' first histograms, which are filled)
+hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor, int32_t* idx,
+                                  int32_t* lengths, uint32_t* hist, uint32_t* pool_hist, uint32_t* blk, bool hist0_done,
+                                  hipStream_t st);
 
 // order-free variant, in place: only the kept rows at or beyond n_keep move, into the evicted
 // positions below it; perm (nullable) [units][n_keep] receives the source row of every position

@@ -400,9 +400,9 @@ __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
 }
 
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
-                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st, uint32_t* status_hist) {
+                         uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st) {
   SelArgs a;
-  a.status = (status_hist ? status_hist : hist) + 2 * kSelBins + kStatusSlot;
+  a.status = hist + 2 * kSelBins + kStatusSlot;
   a.scores = scores;
   a.n = n;
   a.n_keep = (uint32_t)n_keep;
@@ -431,103 +431,357 @@ hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t 
 }
 
 // ---------------------------------------------------------------------------------------
-// Head-adaptive budgets (Sec. 2.2, "Head-Adaptive Compression"): the selection runs once over the
-// pooled scores of a layer's KV heads, [H][n] read as one list of H*n, after every head's own
-// `floor` best pairs have been lifted to +inf so that the pooled selection takes them first.
+// Head-adaptive budgets (Sec. 2.2, "Head-Adaptive Compression"): every KV head keeps its own `floor` best scores, and what
+// is left of the layer's budget goes to the best of all the others, wherever they are.
 //
-// One workgroup = kSelBlock scores of a head: copied into LDS, those on the head's list of its `n_mark` best
-// (the stretch of it that lies in the block: two 64-ary searches) set to +inf, written out, and the first
-// digit of the pooled list's radix select counted on the way: a copy, a marking and a histogram launch in one.
-// (With it, one clearing launch instead of four and the heads' first digit taken from the finalize pass, the
-// adaptive pass of 8 heads x 50001 keys went from 24 launches and 266 us to 18 and 253.)
-__global__ __launch_bounds__(kSelThreads) void k_lift(const float* __restrict__ scores, const int32_t* __restrict__ top,
-                                                      long long n, int n_mark, int Hkv, float* __restrict__ lifted,
-                                                      uint32_t* __restrict__ pool_hist) {
-  __shared__ float s_sc[kSelBlock];
-  __shared__ uint32_t s_hist[kSelBins];
-  __shared__ int s_j[2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, unit = blockIdx.x;
-  const long long base = (long long)blockIdx.y * kSelBlock;
-  const int m = (int)min((long long)kSelBlock, n - base);
-  const int32_t* list = top + (size_t)unit * n_mark;
-  float x[kSelPer];
+// Both searches walk down the digits side by side, and neither list is ever written down: of a head's scores those above
+// its floor's threshold are out of the pool, so its part in a pooled histogram is
+//   where the pool's prefix lies below the head's:  all its scores with that prefix (counted into the pool's histogram),
+//   where they are the same:                        the head's own histogram, cut off at the head's next digit,
+//   where it lies above:                            nothing,
+// and the first one is the sum of the heads' first histograms, cut off.  The emit pass then writes every head's list
+// straight away: with T the pool's threshold and T_h the floor's it keeps what lies above the lower of them, and of
+// the scores at it the first ones: the floor's share where that is T_h, the pool's where it is T, which depends on the
+// scores at T in the heads in front.
+// As two selections, with a copy of the scores in between (the floor's lifted to infinity) and a pooled list that was
+// cut into the heads' afterwards, it took eight launches and 57 us behind the finalize pass at 8 heads x 50001 with a
+// quarter of the budget by head; now three and 26 (whole pass 236 -> 205 us).  What bounds it now is the latency of three
+// rounds through the histograms: every workgroup searches all of a layer's first ones.
+struct AdaptArgs {
+  const float* scores;
+  long long n;
+  uint32_t floor, rest;   // scores that every head keeps, and that the layer keeps besides
+  uint32_t* hist;         // [units][3][2048], the first one filled; see kPrefixSlot
+  uint32_t* pool;         // [B][3][2048], the first one not used
+  uint32_t* blk;          // [units][nblk], zero at launch: kEmitSeen | kEmitPool | count == threshold << 13 | count > threshold
+  int32_t* idx;           // [units][n]
+  int32_t* lengths;       // [units]
+  int B, H, nblk, first_done;
+  uint32_t* status;
+};
+// Free words of a third histogram: (prefix, rest) of the unit, or of the pool, after each of the first two digits
+constexpr int kPrefixSlot = 1032;
+constexpr uint32_t kNoPrefix = ~0u;        // no floor: above every prefix; nothing besides the floor: the same for the pool
+constexpr uint32_t kEmitPool = 1u << 30;
+constexpr int kAdaptHeads = 8;             // heads whose digits are searched for at a time
+
+struct AdaptShared {
+  BinSearch<kSelThreads> own, pool;
+  uint32_t sum[kAdaptHeads][kSelThreads / 64];
+  uint32_t bin[kAdaptHeads], rem[kAdaptHeads];
+};
+struct AdaptPrefix { uint32_t own, own_rem, pool, pool_rem, ties_front; };
+__device__ __forceinline__ uint32_t* adapt_slot(uint32_t* hist, int level) { return hist + 2 * kSelBins + kPrefixSlot + 2 * level; }
+
+// A head's part in the pool's histogram: its own one below the bin where its floor's threshold is, and the `rem` best of
+// that bin left out.
+template <int PER>
+__device__ __forceinline__ void add_cut(uint32_t (&pool)[PER], const uint32_t (&cnt)[PER], uint32_t bin, uint32_t rem) {
+  const uint32_t lo = (uint32_t)((kSelThreads - 1 - (int)threadIdx.x) * PER);
 #pragma unroll
-  for (int j = 0; j < kSelPer; ++j) x[j] = scores[(size_t)unit * n + min(base + j * kSelThreads + tid, n - 1)];
-  for (int i = tid; i < kSelBins; i += kSelThreads) s_hist[i] = 0;
-  if (wave < 2) {                                        // first list entry at or past the block's start, and past its end
-    const long long key = wave == 0 ? base : base + m;
-    int lo = 0, hi = n_mark;                             // entries below lo are < key, from hi on >= key
-    while (lo < hi) {
-      const int stride = (hi - lo + 63) / 64, at = lo + lane * stride;
-      const unsigned long long ge = __ballot(at >= hi || list[min(at, n_mark - 1)] >= key);
-      const int first = ge ? __ffsll((long long)ge) - 1 : 64;
-      hi = first < 64 ? min(hi, lo + first * stride) : hi;
-      if (first > 0) lo = lo + (first - 1) * stride + 1;
+  for (int i = 0; i < PER; ++i) pool[i] += lo + i < bin ? cnt[i] : lo + i == bin ? cnt[i] - rem : 0u;
+}
+
+// The first digit of head `own` of sequence b and of the pool, by a workgroup: a search in every head's histogram, kAdaptHeads
+// of them at a time (find_bin above, side by side).  own == -1: every head's digit is stored instead.
+__device__ __forceinline__ AdaptPrefix adapt_first_digit(const AdaptArgs& a, int b, int own, AdaptShared& s) {
+  constexpr int PER = kSelBins / kSelThreads, W = kSelThreads / 64, NH = kAdaptHeads;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t* hist = a.hist + (size_t)b * a.H * 3 * kSelBins;
+  AdaptPrefix x = {kNoPrefix, 0u, kNoPrefix, 0u, 0u};
+  uint32_t pool[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) pool[j] = 0u;
+#pragma unroll 1
+  for (int h0 = 0; h0 < a.H; h0 += NH) {
+    uint32_t cnt[NH][PER], sum[NH], excl[NH];
+#pragma unroll
+    for (int j = 0; j < NH; ++j) load_bins<kSelThreads>(hist + (size_t)min(h0 + j, a.H - 1) * 3 * kSelBins, cnt[j]);
+#pragma unroll
+    for (int j = 0; j < NH; ++j) {
+      sum[j] = 0;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) sum[j] += cnt[j][i];
+      const uint32_t incl = wave_scan(sum[j]);
+      if (lane == 63) s.sum[j][wave] = incl;
+      excl[j] = incl - sum[j];
     }
-    if (lane == 0) s_j[wave] = hi;
-  }
+    __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kSelPer; ++j) s_sc[j * kSelThreads + tid] = x[j];
-  __syncthreads();
-  for (int j = s_j[0] + tid; j < s_j[1]; j += kSelThreads) {
-    const long long at = list[j] - base;
-    if (at >= 0 && at < m) s_sc[at] = INFINITY;
+    for (int j = 0; j < NH; ++j) {
+#pragma unroll
+      for (int w = 0; w < W - 1; ++w) excl[j] += w < wave ? s.sum[j][w] : 0u;
+      uint32_t r = a.floor - excl[j];
+      if (excl[j] < a.floor && r <= sum[j]) {
+        uint32_t at = PER - 1;
+#pragma unroll
+        for (int i = PER - 1; i >= 1; --i)
+          if (at == (uint32_t)i && r > cnt[j][i]) { r -= cnt[j][i]; --at; }
+        s.bin[j] = (uint32_t)((kSelThreads - 1 - tid) * PER) + at;
+        s.rem[j] = r;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NH; ++j) {
+      if (h0 + j >= a.H) break;
+      const uint32_t bin = a.floor ? s.bin[j] : kNoPrefix, r = a.floor ? s.rem[j] : 0u;
+      if (h0 + j == own) { x.own = bin; x.own_rem = r; }
+      if (own < 0 && tid == 0) {
+        uint32_t* to = adapt_slot(hist + (size_t)(h0 + j) * 3 * kSelBins, 0);
+        to[0] = bin;
+        to[1] = r;
+      }
+      add_cut(pool, cnt[j], bin, r);
+    }
+  }
+  if (a.rest) find_bin<kSelThreads>(s.pool, pool, a.rest, &x.pool, &x.pool_rem);
+  return x;
+}
+
+// The second (P == 1) and third digit likewise.  The other heads matter only where they share the pool's prefix, which is
+// seldom.  P == 2: ties_front, the scores at the pool's threshold that belong to the floors of the heads in front of this one.
+template <int P>
+__device__ __forceinline__ AdaptPrefix adapt_digit(const AdaptArgs& a, int b, int own, AdaptShared& s) {
+  constexpr int PER = (P == 2 ? kSelBins / 2 : kSelBins) / kSelThreads, BITS = P == 2 ? 10 : 11;
+  const int lane = threadIdx.x & 63;
+  uint32_t* hist = a.hist + (size_t)b * a.H * 3 * kSelBins;
+  uint32_t* pool_hist = a.pool + (size_t)b * 3 * kSelBins;
+  uint32_t pool[PER], mine[PER];
+  load_bins<kSelThreads>(hist + ((size_t)own * 3 + P) * kSelBins, mine);
+  load_bins<kSelThreads>(pool_hist + P * kSelBins, pool);
+  const uint32_t own_pre = adapt_slot(hist + (size_t)own * 3 * kSelBins, P - 1)[0], own_rem = adapt_slot(hist + (size_t)own * 3 * kSelBins, P - 1)[1];
+  const uint32_t pool_pre = adapt_slot(pool_hist, P - 1)[0], pool_rem = adapt_slot(pool_hist, P - 1)[1];
+  AdaptPrefix x = {kNoPrefix, 0u, kNoPrefix, 0u, 0u};
+  uint32_t bin;
+  if (a.floor) {
+    find_bin<kSelThreads>(s.own, mine, own_rem, &bin, &x.own_rem);
+    x.own = (own_pre << BITS) | bin;
+    if (own_pre == pool_pre) add_cut(pool, mine, bin, x.own_rem);
+  }
+  if (a.rest == 0u) return x;
+#pragma unroll 1
+  for (int phase = 0; phase < (P == 2 ? 2 : 1); ++phase) {       // into the pool; then, its threshold known, the heads in front
+    const int heads = !a.floor ? 0 : phase == 0 ? a.H : own;
+#pragma unroll 1
+    for (int h0 = 0; h0 < heads; h0 += 64) {
+      const int h = min(h0 + lane, heads - 1);
+      const uint32_t pre = adapt_slot(hist + (size_t)h * 3 * kSelBins, P - 1)[0];
+      unsigned long long todo = __ballot(h0 + lane < heads && h != own && pre == pool_pre);
+      while (todo) {
+        const int g = h0 + __ffsll((long long)todo) - 1;
+        todo &= todo - 1;
+        uint32_t cnt[PER], r;
+        load_bins<kSelThreads>(hist + ((size_t)g * 3 + P) * kSelBins, cnt);
+        __syncthreads();                                          // the search in front of this one has been read
+        find_bin<kSelThreads>(s.own, cnt, adapt_slot(hist + (size_t)g * 3 * kSelBins, P - 1)[1], &bin, &r);
+        if (phase == 0) add_cut(pool, cnt, bin, r);
+        else if (((pool_pre << BITS) | bin) == x.pool) x.ties_front += r;
+      }
+    }
+    if (phase == 0) {
+      find_bin<kSelThreads>(s.pool, pool, pool_rem, &bin, &x.pool_rem);
+      x.pool = (pool_pre << BITS) | bin;
+    }
+  }
+  return x;
+}
+
+// layers of many heads: the first digits by one workgroup per sequence (elsewhere every workgroup searches for them)
+constexpr int kAdaptFirstMin = 16;
+__global__ __launch_bounds__(kSelThreads) void k_adapt_first(AdaptArgs a) {
+  __shared__ AdaptShared s;
+  const AdaptPrefix x = adapt_first_digit(a, blockIdx.x, -1, s);
+  if (threadIdx.x == 0) {
+    uint32_t* to = adapt_slot(a.pool + (size_t)blockIdx.x * 3 * kSelBins, 0);
+    to[0] = x.pool;
+    to[1] = x.pool_rem;
+  }
+}
+
+// second (P == 1) and third histogram of the heads, where their floors' thresholds are, and of the pool
+template <int P>
+__global__ __launch_bounds__(kSelThreads) void k_adapt_hist(AdaptArgs a) {
+  constexpr int SHIFT = P == 1 ? 21 : 10;
+  __shared__ uint32_t s_own[kSelBins], s_pool[kSelBins];
+  __shared__ AdaptShared s;
+  const int tid = threadIdx.x, unit = blockIdx.x, b = unit / a.H, h = unit - b * a.H;
+  const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
+  const long long base = (long long)blockIdx.y * kSelBlock;
+  uint32_t u[kSelPer];
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) u[j] = sc[min(base + j * kSelThreads + tid, a.n - 1)];
+  for (int i = tid; i < kSelBins; i += kSelThreads) s_own[i] = s_pool[i] = 0;
+  uint32_t* hist = a.hist + (size_t)unit * 3 * kSelBins;
+  uint32_t* pool = a.pool + (size_t)b * 3 * kSelBins;
+  AdaptPrefix x;
+  if (P == 1 && a.first_done) {
+    const uint32_t *own = adapt_slot(hist, 0), *all = adapt_slot(pool, 0);
+    x = AdaptPrefix{own[0], own[1], all[0], all[1], 0u};
+  } else {
+    if constexpr (P == 1) x = adapt_first_digit(a, b, h, s);
+    else x = adapt_digit<1>(a, b, h, s);
+    if (tid == 0 && blockIdx.y == 0) {                   // for the launches behind this one
+      uint32_t* to = adapt_slot(hist, P - 1);
+      to[0] = x.own;
+      to[1] = x.own_rem;
+      if (h == 0) {
+        to = adapt_slot(pool, P - 1);
+        to[0] = x.pool;
+        to[1] = x.pool_rem;
+      }
+    }
   }
   __syncthreads();
+  const bool own = a.floor != 0u, pooled = a.rest != 0u && x.own > x.pool;
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) {
-    const int i = j * kSelThreads + tid;
-    if (i < m) {
-      const float v = s_sc[i];
-      lifted[(size_t)unit * n + base + i] = v;
-      if (pool_hist) atomicAdd(&s_hist[__float_as_uint(v) >> 21], 1u);
+    if (base + j * kSelThreads + tid < a.n) {
+      const uint32_t digit = P == 1 ? (u[j] >> 10) & 2047u : u[j] & 1023u;
+      if (own && (u[j] >> SHIFT) == x.own) atomicAdd(&s_own[digit], 1u);
+      if (pooled && (u[j] >> SHIFT) == x.pool) atomicAdd(&s_pool[digit], 1u);
     }
   }
-  if (!pool_hist) return;
   __syncthreads();
-  uint32_t* out = pool_hist + (size_t)(unit / Hkv) * 3 * kSelBins;
-  for (int i = tid; i < kSelBins; i += kSelThreads) {
-    const uint32_t c = s_hist[i];
-    if (c) atomicAdd(&out[i], c);
+  for (int i = tid; i < kSelBins / P; i += kSelThreads) {
+    const uint32_t c = s_own[i], d = s_pool[i];
+    if (c) atomicAdd(&hist[P * kSelBins + i], c);
+    if (d) atomicAdd(&pool[P * kSelBins + i], d);
   }
 }
 
-hipError_t launch_lift(const Dims& d, const float* scores, const int32_t* top, int64_t n, int64_t n_mark, float* lifted,
-                       uint32_t* pool_hist, hipStream_t st) {
-  const dim3 grid(d.units(), (unsigned)((n + kSelBlock - 1) / kSelBlock));
-  k_lift<<<grid, kSelThreads, 0, st>>>(scores, top, n, (int)n_mark, d.Hkv, lifted, pool_hist);
-  return hipGetLastError();
-}
-
-// kSplitChunks workgroups per (sequence, head): the head's stretch of the pooled ascending list is
-// found by two binary searches (every workgroup repeats them: forty loads), then copied with the
-// head's offset taken off, each workgroup one slice of it.
-constexpr int kSplitChunks = 32;
-__global__ __launch_bounds__(256) void k_split_pooled(const int32_t* __restrict__ flat, int H, long long n,
-                                                      long long n_keep, int32_t* __restrict__ idx,
-                                                      int32_t* __restrict__ lengths) {
-  const int b = blockIdx.x / H, h = blockIdx.x % H, chunk = blockIdx.y;
-  const long long total = (long long)H * n_keep;
-  const int32_t* f = flat + (size_t)b * total;
-  auto lower = [&](long long key) {
-    long long lo = 0, hi = total;
-    while (lo < hi) {
-      const long long mid = (lo + hi) >> 1;
-      if (f[mid] < key) lo = mid + 1; else hi = mid;
-    }
-    return lo;
+// The heads' lists and lengths, see k_sel_emit: blocks by ticket in the order of (head, block), waiting for lower ones only.
+__global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
+  constexpr int W = kSelThreads / 64, U = 2;
+  __shared__ AdaptShared s;
+  __shared__ uint32_t s_w[2][W];
+  __shared__ uint32_t s_front[4];
+  __shared__ uint32_t s_blk;
+  const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x % a.B;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid == 0) s_blk = atomicAdd(a.pool + ((size_t)b * 3 + 2) * kSelBins + kEmitTicket, 1u);
+  __syncthreads();
+  const int ticket = __builtin_amdgcn_readfirstlane((int)s_blk);
+  if (ticket >= a.H * a.nblk) return;           // (a counter that did not start at zero)
+  const int h = ticket / a.nblk, blk = ticket - h * a.nblk, unit = b * a.H + h;
+  const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
+  const long long base = (long long)blk * kSelBlock + wave * (kSelBlock / W) + lane;    // of u[0]; u[j]: 64 j further
+  uint32_t u[kSelPer];
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) u[j] = sc[min(base + 64 * j, a.n - 1)];
+  const long long left = a.n - ((long long)blk * kSelBlock + wave * (kSelBlock / W));
+  auto inside = [&](int j) -> unsigned long long {
+    const int m = (int)min(max(left - 64 * j, 0ll), 64ll);
+    return m >= 64 ? ~0ull : (1ull << m) - 1ull;
   };
-  const long long lo = lower((long long)h * n), hi = lower((long long)(h + 1) * n);
-  if (threadIdx.x == 0 && chunk == 0) lengths[blockIdx.x] = (int32_t)(hi - lo);
-  int32_t* out = idx + (size_t)blockIdx.x * n;
-  const long long per = (hi - lo + kSplitChunks - 1) / kSplitChunks;
-  const long long j0 = lo + chunk * per, j1 = min(hi, j0 + per);
-  for (long long j = j0 + threadIdx.x; j < j1; j += 256) out[j - lo] = f[j] - (int32_t)(h * n);
+  const AdaptPrefix x = adapt_digit<2>(a, b, h, s);
+  const uint32_t T = __builtin_amdgcn_readfirstlane(min(x.own, x.pool));
+  uint32_t gt = 0, eq = 0;
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) {
+    gt += __popcll(__ballot(u[j] > T) & inside(j));
+    eq += __popcll(__ballot(u[j] == T) & inside(j));
+  }
+  if (lane == 0) { s_w[0][wave] = gt; s_w[1][wave] = eq; }
+  __syncthreads();
+  uint32_t* pub = a.blk + (size_t)b * a.H * a.nblk;
+  if (tid == 0) {
+    uint32_t g = 0, e = 0;
+    for (int w = 0; w < W; ++w) { g += s_w[0][w]; e += s_w[1][w]; }
+    __hip_atomic_store(&pub[ticket], kEmitSeen | (T == x.pool ? kEmitPool : 0u) | (e << 13) | g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // in the head's blocks in front of this one: above T and at T; in the heads in front: at the pool's threshold
+  if (wave == 0) {
+    uint32_t gf = 0, ef = 0, pf = 0;
+    int spin = 0;
+    const int own0 = h * a.nblk;
+    // (without a tie to share out the heads in front do not matter)
+    for (int j0 = (T == x.pool ? 0 : own0) + lane; j0 < ticket && spin < kEmitSpinLimit; j0 += U * 64) {
+      uint32_t word[U];
+#pragma unroll
+      for (int y = 0; y < U; ++y)
+        word[y] = j0 + 64 * y < ticket ? __hip_atomic_load(&pub[j0 + 64 * y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kEmitSeen;
+#pragma unroll
+      for (int y = 0; y < U; ++y) {
+        while ((word[y] & kEmitSeen) == 0u && ++spin < kEmitSpinLimit) {
+          __builtin_amdgcn_s_sleep(1);
+          word[y] = __hip_atomic_load(&pub[j0 + 64 * y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const uint32_t e = (word[y] >> 13) & 0x1fffu;
+        if (j0 + 64 * y >= own0) { gf += word[y] & 0x1fffu; ef += e; }
+        else if (word[y] & kEmitPool) pf += e;
+      }
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) { gf += __shfl_xor(gf, o); ef += __shfl_xor(ef, o); pf += __shfl_xor(pf, o); }
+    const bool ok = __ballot(spin >= kEmitSpinLimit) == 0ull;
+    if (lane == 0) {
+      s_front[0] = gf;
+      s_front[1] = ef;
+      s_front[2] = pf;
+      s_front[3] = ok;
+      if (!ok) atomicOr(a.status, kStatusCompactWait);
+    }
+  }
+  __syncthreads();
+  if (!s_front[3]) return;
+  // scores at T to keep: the floor's, and the pool's that the heads in front have left
+  uint32_t q = T == x.own ? x.own_rem : 0u;
+  if (T == x.pool) {
+    const uint32_t taken = s_front[2] - x.ties_front;
+    q += taken < x.pool_rem ? x.pool_rem - taken : 0u;
+  }
+  q = __builtin_amdgcn_readfirstlane(q);
+  uint32_t pos = s_front[0], eq_before = s_front[1];
+  for (int w = 0; w < W; ++w) {
+    if (w == wave) break;
+    pos += s_w[0][w];
+    eq_before += s_w[1][w];
+  }
+  pos = __builtin_amdgcn_readfirstlane(pos + min(eq_before, q));
+  eq_before = __builtin_amdgcn_readfirstlane(eq_before);
+  int32_t* out = a.idx + (size_t)unit * a.n;
+#pragma unroll
+  for (int j = 0; j < kSelPer; ++j) emit_row(inside(j), u[j], T, q, pos, eq_before, out, (uint32_t)a.n, (int)(base + 64 * j));
+  if (blk == a.nblk - 1 && tid == kSelThreads - 1) a.lengths[unit] = (int32_t)pos;
 }
 
-hipError_t launch_split_pooled(const int32_t* flat, int B, int H, int64_t n, int64_t n_keep, int32_t* idx,
-                               int32_t* lengths, hipStream_t st) {
-  k_split_pooled<<<dim3(B * H, kSplitChunks), 256, 0, st>>>(flat, H, n, n_keep, idx, lengths);
+hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor, int32_t* idx,
+                                  int32_t* lengths, uint32_t* hist, uint32_t* pool_hist, uint32_t* blk, bool hist0_done,
+                                  hipStream_t st) {
+  if (n_keep == 0) return launch_zero((uint32_t*)lengths, d.units(), st);
+  const int nblk = (int)((n + kSelBlock - 1) / kSelBlock);
+  AdaptArgs a;
+  a.scores = scores;
+  a.n = n;
+  a.floor = (uint32_t)floor;
+  a.rest = (uint32_t)((n_keep - floor) * d.Hkv);
+  a.hist = hist;
+  a.pool = pool_hist;
+  a.blk = blk;
+  a.idx = idx;
+  a.lengths = lengths;
+  a.B = d.B;
+  a.H = d.Hkv;
+  a.nblk = nblk;
+  a.first_done = d.Hkv > kAdaptFirstMin;
+  a.status = hist + 2 * kSelBins + kStatusSlot;
+  const dim3 grid(d.units(), nblk);
+  if (!hist0_done) {
+    SelArgs f = {};
+    f.scores = scores;
+    f.n = n;
+    f.n_keep = (uint32_t)n_keep;
+    f.hist = hist;
+    f.nblk = nblk;
+    f.status = a.status;
+    k_sel_hist<0><<<grid, kSelThreads, 0, st>>>(f);
+  }
+  if (a.first_done) k_adapt_first<<<d.B, kSelThreads, 0, st>>>(a);
+  k_adapt_hist<1><<<grid, kSelThreads, 0, st>>>(a);
+  k_adapt_hist<2><<<grid, kSelThreads, 0, st>>>(a);
+  k_adapt_emit<<<(unsigned)(d.units() * nblk), kSelThreads, 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -559,3 +559,41 @@ def test_projection_blocks_of_whole_lines(w, dm, hq, hkv):
     torch.cuda.synchronize()
     rmu, rsg = X.query_stats_hidden(widen(hb), widen(wb), inv, 70000, T=cfg.horizon_T)
     P.check_stats(mu.cpu().numpy(), sg.cpu().numpy(), rmu, rsg)
+
+
+@pytest.mark.parametrize("hkv,n", [(3, 4096), (5, 4097), (16, 300), (17, 300), (40, 5000), (2, 25000)])
+@pytest.mark.parametrize("kind", ["spread", "ties", "equal", "special", "shared"])
+def test_adaptive_selection_shares_out_ties(hkv, n, kind):
+    """Budgets shared by a layer's heads where the floor's threshold of a head lies above the pool's, at it and below it: few
+    distinct values and a single one (all that decides is the order of heads and positions), zero, denormals and infinity,
+    and heads whose first digits agree and whose later ones do not; layers on both sides of the head count from which the
+    first digits have a launch of their own; floors of none, one, some and all of the budget.  Exactly the oracle's lists."""
+    import torch
+    cfg = CONFIGS["c2"].with_(batch=2, n_kv_heads=hkv, n_q_heads=hkv)
+    p = P.params_for(cfg)
+    rng = np.random.default_rng(n + hkv)
+    shape = (2, hkv, n)
+    sc = np.exp(rng.standard_normal(shape)).astype(np.float32)
+    if kind == "ties":
+        sc = rng.integers(0, 4, shape).astype(np.float32)
+    elif kind == "equal":
+        sc = np.ones(shape, dtype=np.float32)
+    elif kind == "special":
+        sc = rng.choice(np.array([0.0, 1e-45, 1e-40, 1.0, 3.4028235e38, np.inf], dtype=np.float32), shape)
+    elif kind == "shared":
+        sc = (1.0 + rng.integers(0, 3000, shape) * 2.0 ** -23).astype(np.float32)
+        sc[:, 0] = (1.0 + rng.integers(0, 3, (2, n)) * 2.0 ** -13).astype(np.float32)
+    ws = P.workspace(p, n, 1)
+    for n_keep, floor in ((n // 2, 0), (n // 2, n // 8), (n // 2, n // 2), (n // 3, n // 3 - 1), (n, 1), (n, n), (1, 1), (1, 0), (0, 0)):
+        idx = torch.full(shape, -7, dtype=torch.int32, device="cuda")
+        lengths = torch.full((2, hkv), -1, dtype=torch.int32, device="cuda")
+        ea.select_adaptive(p, P.to_dev(sc), n, n_keep, floor, idx, lengths, ws)
+        torch.cuda.synchronize()
+        rl, rk = X.select_adaptive(sc.astype(np.float64), n_keep, floor)
+        gl, gi = lengths.cpu().numpy(), idx.cpu().numpy()
+        assert np.array_equal(gl, rl), (n_keep, floor)
+        for b in range(2):
+            for h in range(hkv):
+                assert np.array_equal(gi[b, h, :gl[b, h]], rk[b][h]), (n_keep, floor, b, h)
+                assert np.all(gi[b, h, gl[b, h]:] == -7)
+        assert ea.debug_status(p, n, 1, ws) == 0
