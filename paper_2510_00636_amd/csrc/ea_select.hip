@@ -445,30 +445,27 @@ hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t 
 // scores at T in the heads in front.
 // As two selections, with a copy of the scores in between (the floor's lifted to infinity) and a pooled list that was
 // cut into the heads' afterwards, it took eight launches and 57 us behind the finalize pass at 8 heads x 50001 with a
-// quarter of the budget by head; now three and 26 (whole pass 236 -> 205 us).  What bounds it now is the latency of three
-// rounds through the histograms: every workgroup searches all of a layer's first ones.
+// quarter of the budget by head; now four and 25 (whole pass 236 -> 203 us).  What bounds it now is the latency of the
+// rounds through the histograms.
 struct AdaptArgs {
   const float* scores;
   long long n;
   uint32_t floor, rest;   // scores that every head keeps, and that the layer keeps besides
   uint32_t* hist;         // [units][3][2048], the first one filled; see kPrefixSlot
-  uint32_t* pool;         // [B][3][2048], the first one not used
+  uint32_t* pool;         // [B][3][2048], zero at launch
   uint32_t* blk;          // [units][nblk], zero at launch: kEmitSeen | kEmitPool | count == threshold << 13 | count > threshold
   int32_t* idx;           // [units][n]
   int32_t* lengths;       // [units]
-  int B, H, nblk, first_done;
+  int B, H, nblk;
   uint32_t* status;
 };
 // Free words of a third histogram: (prefix, rest) of the unit, or of the pool, after each of the first two digits
 constexpr int kPrefixSlot = 1032;
 constexpr uint32_t kNoPrefix = ~0u;        // no floor: above every prefix; nothing besides the floor: the same for the pool
 constexpr uint32_t kEmitPool = 1u << 30;
-constexpr int kAdaptHeads = 8;             // heads whose digits are searched for at a time
 
 struct AdaptShared {
   BinSearch<kSelThreads> own, pool;
-  uint32_t sum[kAdaptHeads][kSelThreads / 64];
-  uint32_t bin[kAdaptHeads], rem[kAdaptHeads];
 };
 struct AdaptPrefix { uint32_t own, own_rem, pool, pool_rem, ties_front; };
 __device__ __forceinline__ uint32_t* adapt_slot(uint32_t* hist, int level) { return hist + 2 * kSelBins + kPrefixSlot + 2 * level; }
@@ -482,65 +479,7 @@ __device__ __forceinline__ void add_cut(uint32_t (&pool)[PER], const uint32_t (&
   for (int i = 0; i < PER; ++i) pool[i] += lo + i < bin ? cnt[i] : lo + i == bin ? cnt[i] - rem : 0u;
 }
 
-// The first digit of head `own` of sequence b and of the pool, by a workgroup: a search in every head's histogram, kAdaptHeads
-// of them at a time (find_bin above, side by side).  own == -1: every head's digit is stored instead.
-__device__ __forceinline__ AdaptPrefix adapt_first_digit(const AdaptArgs& a, int b, int own, AdaptShared& s) {
-  constexpr int PER = kSelBins / kSelThreads, W = kSelThreads / 64, NH = kAdaptHeads;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint32_t* hist = a.hist + (size_t)b * a.H * 3 * kSelBins;
-  AdaptPrefix x = {kNoPrefix, 0u, kNoPrefix, 0u, 0u};
-  uint32_t pool[PER];
-#pragma unroll
-  for (int j = 0; j < PER; ++j) pool[j] = 0u;
-#pragma unroll 1
-  for (int h0 = 0; h0 < a.H; h0 += NH) {
-    uint32_t cnt[NH][PER], sum[NH], excl[NH];
-#pragma unroll
-    for (int j = 0; j < NH; ++j) load_bins<kSelThreads>(hist + (size_t)min(h0 + j, a.H - 1) * 3 * kSelBins, cnt[j]);
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-      sum[j] = 0;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) sum[j] += cnt[j][i];
-      const uint32_t incl = wave_scan(sum[j]);
-      if (lane == 63) s.sum[j][wave] = incl;
-      excl[j] = incl - sum[j];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-#pragma unroll
-      for (int w = 0; w < W - 1; ++w) excl[j] += w < wave ? s.sum[j][w] : 0u;
-      uint32_t r = a.floor - excl[j];
-      if (excl[j] < a.floor && r <= sum[j]) {
-        uint32_t at = PER - 1;
-#pragma unroll
-        for (int i = PER - 1; i >= 1; --i)
-          if (at == (uint32_t)i && r > cnt[j][i]) { r -= cnt[j][i]; --at; }
-        s.bin[j] = (uint32_t)((kSelThreads - 1 - tid) * PER) + at;
-        s.rem[j] = r;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < NH; ++j) {
-      if (h0 + j >= a.H) break;
-      const uint32_t bin = a.floor ? s.bin[j] : kNoPrefix, r = a.floor ? s.rem[j] : 0u;
-      if (h0 + j == own) { x.own = bin; x.own_rem = r; }
-      if (own < 0 && tid == 0) {
-        uint32_t* to = adapt_slot(hist + (size_t)(h0 + j) * 3 * kSelBins, 0);
-        to[0] = bin;
-        to[1] = r;
-      }
-      add_cut(pool, cnt[j], bin, r);
-    }
-  }
-  if (a.rest) find_bin<kSelThreads>(s.pool, pool, a.rest, &x.pool, &x.pool_rem);
-  return x;
-}
-
-// The second (P == 1) and third digit likewise.  The other heads matter only where they share the pool's prefix, which is
+// The second (P == 1) and third digit of head `own` of sequence b and of the pool, by a workgroup.  The other heads matter only where they share the pool's prefix, which is
 // seldom.  P == 2: ties_front, the scores at the pool's threshold that belong to the floors of the heads in front of this one.
 template <int P>
 __device__ __forceinline__ AdaptPrefix adapt_digit(const AdaptArgs& a, int b, int own, AdaptShared& s) {
@@ -588,16 +527,28 @@ __device__ __forceinline__ AdaptPrefix adapt_digit(const AdaptArgs& a, int b, in
   return x;
 }
 
-// layers of many heads: the first digits by one workgroup per sequence (elsewhere every workgroup searches for them)
-constexpr int kAdaptFirstMin = 16;
+// The first digits, by a workgroup per head, which adds the head's part to the pool's first histogram.  (With every workgroup
+// of the next launch searching through all heads instead: 8 heads x 3000 68.1 and 65.7 us of the whole pass, 16 x 9000 109.4
+// and 104.6, 8 x 50001 203.0 and 202.1, 32 x 9000 177 and 161.)
 __global__ __launch_bounds__(kSelThreads) void k_adapt_first(AdaptArgs a) {
-  __shared__ AdaptShared s;
-  const AdaptPrefix x = adapt_first_digit(a, blockIdx.x, -1, s);
-  if (threadIdx.x == 0) {
-    uint32_t* to = adapt_slot(a.pool + (size_t)blockIdx.x * 3 * kSelBins, 0);
-    to[0] = x.pool;
-    to[1] = x.pool_rem;
+  constexpr int PER = kSelBins / kSelThreads;
+  __shared__ BinSearch<kSelThreads> s;
+  const int tid = threadIdx.x;
+  uint32_t* hist = a.hist + (size_t)blockIdx.x * 3 * kSelBins;
+  uint32_t* pool_hist = a.pool + (size_t)(blockIdx.x / a.H) * 3 * kSelBins;
+  uint32_t cnt[PER], part[PER], bin = kNoPrefix, rem = 0u;
+  load_bins<kSelThreads>(hist, cnt);
+  if (a.floor) find_bin<kSelThreads>(s, cnt, a.floor, &bin, &rem);
+  if (tid == 0) {
+    adapt_slot(hist, 0)[0] = bin;
+    adapt_slot(hist, 0)[1] = rem;
   }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) part[i] = 0u;
+  add_cut(part, cnt, bin, rem);
+#pragma unroll
+  for (int i = 0; i < PER; ++i)
+    if (part[i]) atomicAdd(&pool_hist[(kSelThreads - 1 - tid) * PER + i], part[i]);
 }
 
 // second (P == 1) and third histogram of the heads, where their floors' thresholds are, and of the pool
@@ -616,21 +567,24 @@ __global__ __launch_bounds__(kSelThreads) void k_adapt_hist(AdaptArgs a) {
   uint32_t* hist = a.hist + (size_t)unit * 3 * kSelBins;
   uint32_t* pool = a.pool + (size_t)b * 3 * kSelBins;
   AdaptPrefix x;
-  if (P == 1 && a.first_done) {
-    const uint32_t *own = adapt_slot(hist, 0), *all = adapt_slot(pool, 0);
-    x = AdaptPrefix{own[0], own[1], all[0], all[1], 0u};
+  if constexpr (P == 1) {
+    uint32_t cnt[kSelBins / kSelThreads];
+    load_bins<kSelThreads>(pool, cnt);
+    x = AdaptPrefix{adapt_slot(hist, 0)[0], adapt_slot(hist, 0)[1], kNoPrefix, 0u, 0u};
+    if (a.rest) find_bin<kSelThreads>(s.pool, cnt, a.rest, &x.pool, &x.pool_rem);
   } else {
-    if constexpr (P == 1) x = adapt_first_digit(a, b, h, s);
-    else x = adapt_digit<1>(a, b, h, s);
-    if (tid == 0 && blockIdx.y == 0) {                   // for the launches behind this one
-      uint32_t* to = adapt_slot(hist, P - 1);
+    x = adapt_digit<1>(a, b, h, s);
+  }
+  if (tid == 0 && blockIdx.y == 0) {                     // for the launches behind this one
+    if (P == 2) {
+      uint32_t* to = adapt_slot(hist, 1);
       to[0] = x.own;
       to[1] = x.own_rem;
-      if (h == 0) {
-        to = adapt_slot(pool, P - 1);
-        to[0] = x.pool;
-        to[1] = x.pool_rem;
-      }
+    }
+    if (h == 0) {
+      uint32_t* to = adapt_slot(pool, P - 1);
+      to[0] = x.pool;
+      to[1] = x.pool_rem;
     }
   }
   __syncthreads();
@@ -765,7 +719,6 @@ hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n,
   a.B = d.B;
   a.H = d.Hkv;
   a.nblk = nblk;
-  a.first_done = d.Hkv > kAdaptFirstMin;
   a.status = hist + 2 * kSelBins + kStatusSlot;
   const dim3 grid(d.units(), nblk);
   if (!hist0_done) {
@@ -778,7 +731,7 @@ hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n,
     f.status = a.status;
     k_sel_hist<0><<<grid, kSelThreads, 0, st>>>(f);
   }
-  if (a.first_done) k_adapt_first<<<d.B, kSelThreads, 0, st>>>(a);
+  k_adapt_first<<<d.units(), kSelThreads, 0, st>>>(a);
   k_adapt_hist<1><<<grid, kSelThreads, 0, st>>>(a);
   k_adapt_hist<2><<<grid, kSelThreads, 0, st>>>(a);
   k_adapt_emit<<<(unsigned)(d.units() * nblk), kSelThreads, 0, st>>>(a);
