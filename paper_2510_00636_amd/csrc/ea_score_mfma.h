@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "ea_kernels.h"
+#include "ea_lanes.h"
 
 namespace ea {
 
@@ -109,33 +110,6 @@ __device__ __forceinline__ float sumsq_bf16x8(u32x4 r) {
   s = __builtin_amdgcn_fdot2_f32_bf16(c, c, s, false);
   s = __builtin_amdgcn_fdot2_f32_bf16(d, d, s, false);
   return s;
-}
-
-// x of lane l plus x of lane l ^ 32, in every lane: one v_permlane32_swap (it hands both
-// halves of the wavefront the other half's registers) instead of a trip through LDS.
-__device__ __forceinline__ float sum_halves(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// x of lane l plus x of lane l ^ 16
-__device__ __forceinline__ float sum_xor16(float x) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// x + (x of another lane of the same 16-lane row), selected by a DPP control word
-template <int CTRL>
-__device__ __forceinline__ float dpp_add(float x) {
-  int y = __builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true);
-  return x + __int_as_float(y);
-}
-
-// x + (y of another lane of the same 16-lane row)
-template <int CTRL>
-__device__ __forceinline__ float dpp_add_of(float x, float y) {
-  const int z = __builtin_amdgcn_update_dpp(0, __float_as_int(y), CTRL, 0xf, 0xf, true);
-  return x + __int_as_float(z);
 }
 
 // Sum over aligned groups of N consecutive lanes (N = 8, 16 or 32); every lane gets the total.

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ea_kernels.h"
+#include "ea_lanes.h"
 
 namespace ea {
 
@@ -147,6 +148,14 @@ __device__ __forceinline__ void stats_rotate(float2 t, float qa, float qb, float
   const float pa = t.y * qb, pb = t.x * qb;
   xa = fmaf(t.x, qa, -pa) - sha;
   xb = fmaf(t.y, qa, pb) - shb;
+}
+
+// the sum over the lanes that share a channel group (stride G8)
+template <int G8>
+__device__ __forceinline__ float stats_lane_sum(float x) {
+  if (G8 <= 4) x += __shfl_xor(x, 4);
+  if (G8 <= 8) x = dpp_add<0x128>(x);
+  return sum_halves(sum_xor16(x));
 }
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
@@ -343,11 +352,8 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __
   // column sums: lanes that share a channel group (stride G8) first, then the four wavefronts
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-#pragma unroll
-    for (int o = G8; o < 64; o <<= 1) {
-      suma[e] += __shfl_xor(suma[e], o);
-      sumb[e] += __shfl_xor(sumb[e], o);
-    }
+    suma[e] = stats_lane_sum<G8>(suma[e]);
+    sumb[e] = stats_lane_sum<G8>(sumb[e]);
   }
   if (lane < G8) {
 #pragma unroll
@@ -370,14 +376,18 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __
   for (int t = 0; t < TPW; ++t) {
     if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
       const int i0 = t_rb[t] * 32, j = t_ct[t] * 32 + r32;
-      const bool mirror = t_rb[t] != t_ct[t];
       const float xj = s_xbar[j];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int i = i0 + 8 * (v / 4) + 4 * hh + v % 4;
-        const float val = (acc[t][v] - fw * s_xbar[i] * xj) * inv;
-        sigma[((size_t)head * D + i) * D + j] = val;
-        if (mirror) sigma[((size_t)head * D + j) * D + i] = val;
+        acc[t][v] = (acc[t][v] - fw * s_xbar[i] * xj) * inv;
+        sigma[((size_t)head * D + i) * D + j] = acc[t][v];
+      }
+      if (t_rb[t] != t_ct[t]) {                          // four rows in a row: 16 bytes of the transposed tile
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          *reinterpret_cast<float4*>(sigma + ((size_t)head * D + j) * D + i0 + 8 * c + 4 * hh) =
+              make_float4(acc[t][4 * c], acc[t][4 * c + 1], acc[t][4 * c + 2], acc[t][4 * c + 3]);
       }
     }
   }
@@ -467,79 +477,6 @@ __device__ __forceinline__ ExtraItem extra_item(int GH, int fe, int l) {
   return ExtraItem{g, kind, 32 * (fe % NK) + 8 * (l >> 4)};
 }
 
-// an odd pitch: neither rows nor columns of Sigma in LDS pile up in a bank; three more than D rather than one, because a
-// fragment's 16 rows times four runs of eight columns then meet three deep in a bank instead of four
-constexpr int stats_sigma_pitch(int D) { return D + 3; }
-
-// The fragments of one head (see above) out of its Sigma in LDS [D][pitch] and its mean shift + xbar, by the
-// 256 threads of a workgroup: the head's own fragments of the triangle, and its rows of the extra tile's.
-// The first head of a (unit, pass) also writes the rows and fragments that belong to no head.
-template <int D>
-__device__ __forceinline__ void stats_write_frags(const float* S, const float* s_shift, const float* s_xbar, int head,
-                                                  const FragsOut& fo) {
-  constexpr int NJT = D / 32, NF = NJT * (NJT + 1), SP = stats_sigma_pitch(D);
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a fragment is one wavefront's: its numbers stay scalar)
-  const int unit = head / fo.G, gq = head - unit * fo.G, pass = gq / fo.GH, g = gq - pass * fo.GH;
-  const int nhere = min(fo.GH, fo.G - pass * fo.GH);          // heads of this (unit, pass)
-  float mxS = 0.f, mxM = 0.f;                                 // every wavefront for itself
-  for (int e = lane; e < D; e += 64) {
-    mxS = fmaxf(mxS, fabsf(S[e * SP + e]));
-    mxM = fmaxf(mxM, fabsf(s_shift[e] + s_xbar[e]));
-  }
-  for (int o = 32; o >= 1; o >>= 1) {
-    mxS = fmaxf(mxS, __shfl_xor(mxS, o));
-    mxM = fmaxf(mxM, __shfl_xor(mxM, o));
-  }
-  const float sM = scale_for(2.0f * mxS), smu = scale_for(mxM);
-  if (tid == 0) {
-    fo.post[(size_t)head * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
-    fo.post[(size_t)head * 2 + 1] = 1.0f / (sqrtf((float)D) * smu);
-  }
-  uint4* out = fo.frags + head_frags(fo, unit, gq, NF) * 64;
-#pragma unroll
-  for (int it = 0; it < (NF * 64 + 255) / 256; ++it) {
-    const int item = it * 256 + tid;
-    if (NF * 64 % 256 != 0 && item >= NF * 64) break;
-    const FragItem x = frag_item(it * 4 + wave, lane);
-    _Float16 h[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      h[i] = (_Float16)(folded_entry(x.in0 + i, x.out, S[x.out * SP + x.in0 + i], S[(x.in0 + i) * SP + x.out]) * sM);
-    }
-    out[item] = pack_half8(h);
-  }
-  constexpr int NK = D / 32;
-  out = fo.frags + extra_frags(fo, unit, pass, NF, NK) * 64;
-  for (int fe = wave; fe < extra_tiles(fo.GH) * 2 * NK; fe += 4) {
-    const int item = fe * 64 + lane;
-    const ExtraItem x = extra_item<D>(fo.GH, fe, lane);
-    const bool mine = x.g == g, nobodys = g == 0 && (x.g < 0 || x.g >= nhere);
-    if (!mine && !nobodys) continue;
-    _Float16 h[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int c = x.c0 + i;
-      float val = 0.f;
-      if (mine && x.kind == 2) {
-        const float m = S[c * SP + c] * sM;
-        val = m - (float)(_Float16)m;
-      } else if (mine && x.kind >= 0) {
-        const float m = (s_shift[c] + s_xbar[c]) * smu;
-        const float hi = (float)(_Float16)m;
-        val = x.kind == 0 ? hi : m - hi;
-      }
-      h[i] = (_Float16)val;
-    }
-    out[item] = pack_half8(h);
-  }
-  if (g == 0 && !fo.hw) {                                     // heads that the last pass has room for but not
-    const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-    out = fo.frags + head_frags(fo, unit, gq, NF) * 64;
-    for (int item = nhere * NF * 64 + tid; item < fo.GH * NF * 64; item += 256) out[item] = z;
-  }
-}
-
 // ---------------------------------------------------------------------------------------
 // The same statistics for bf16 windows with the outer products on the fp16 matrix cores.
 //
@@ -563,16 +500,16 @@ typedef _Float16 stats_half2 __attribute__((ext_vector_type(2)));
 // chunk's queries and table rows in flight during the matrix-core loop)
 constexpr int stats_split_chunk(int D) { return D >= 256 ? 32 : 64; }
 
-// What bounds it at the decode-time shape (960 heads, w = 512, two workgroups of four wavefronts per CU) is the
-// work between the barriers of a chunk, not memory: 101 us, and 84 with every load on one cached line.  Taking
-// the conditions out of the staging (a shift read under "inside the chunk" was a branch and an LDS round trip
-// per element) and out of the matrix loop (each tile's operands were waited for on the spot), and reading a
-// row operand once for two tiles, took 104 us to 94; keeping Sigma on the chip took the 64 MB it wrote, half of
-// them in 4-byte pieces, and the 27 us of k_prep_frags off (whole pass 422 -> 396 us; with the order of tiles that
-// needs no scratch memory 390 -> 381).
-// FUSED (d <= 128): Sigma leaves as the fragments that k_prep_frags would have made of it.  One workgroup per head: it stands
-// in LDS and they are the same bit for bit.  Two (OWN below): each makes those of its own tiles, the same up to the head's
-// power of two.
+// What bounds it at the decode-time shape (960 heads, w = 512, two workgroups of four wavefronts per CU) is the work
+// between the barriers of a chunk, 5000 cycles of which 1000 are matrix instructions and the rest the conversions, the
+// issue of the next chunk's loads (a CU's address unit takes 64 bytes per clock, and the table is two thirds of them) and
+// LDS; then the 14000 of the first chunk and the end.  In calls of few heads it is the latter two: a workgroup of a window
+// of 128 samples takes 24000 cycles, 12000 of them behind its last chunk, when every entry of Sigma is an LDS round trip of
+// its own and sums and maxima over the lanes go through LDS as well; 18000 without those (one layer of 32 heads 13.1 -> 10.8
+// us, decode-time shape 93 -> 82, 32 heads without operands 9.2 -> 7.4).
+// FUSED (d <= 128): Sigma leaves as the fragments that k_prep_frags would have made of it, tile by tile.  One workgroup per
+// head: they are the same bit for bit.  Two (OWN below): each makes those of its own tiles, the same up to the head's power of
+// two.
 template <int D, int LAYOUT, int PARTS = 0, bool FUSED = false>
 __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSED)) ? 3 : 2)) void k_stats_split(const void* __restrict__ q_win, int w,
                                                                          int ddof,
@@ -600,13 +537,11 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
   extern __shared__ __align__(16) float s_dyn[];
   _Float16* s_hi = reinterpret_cast<_Float16*>(s_dyn);            // [D][P]
   _Float16* s_lo = s_hi + D * P;                                   // [D][P]
-  // FUSED: Sigma [D][pitch] takes the planes' place at the end (and more than that)
-  constexpr int SP = stats_sigma_pitch(D);
-  float* s_part = FUSED && StatsTiling<D, PARTS>::PARTS == 1 && D * SP * 4 > 2 * D * P * 2 ? s_dyn + D * SP
-                                                      : reinterpret_cast<float*>(s_lo + D * P);   // [4][D] column sums per wavefront
+  float* s_part = reinterpret_cast<float*>(s_lo + D * P);          // [4][D] column sums per wavefront
   float* s_shift = s_part + 4 * D;                                 // [D] u~_0
   float* s_xbar = s_shift + D;                                     // [D]
   float* s_max = s_xbar + D;                                       // [4]
+  float* s_sq = s_max + 4;                                         // OWN: [4][D] sums of squares per wavefront
   const int head = blockIdx.x, part = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t qbase = (size_t)head * w * D;
@@ -728,8 +663,7 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
       for (int it = 0; it < ITEMS; ++it)
 #pragma unroll
         for (int c16 = 0; c16 < 16; ++c16) amax = fmaxf(amax, fabsf(xs[it][c16]));
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
+      amax = wave_max(amax);
       if (lane == 0) s_max[wave] = amax;
       __syncthreads();
       const float m = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
@@ -829,31 +763,42 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
 #pragma unroll
       for (int v = 0; v < 16; ++v) s_u[((r * 4 + wave) * 16 + v) * 64 + lane] = acc[TL::WHOLE + r][v];
     __syncthreads();
-    if (wave == 0) {
+    // (shared tile r by wavefront 3 - r: the first ones come from the diagonal, which has more to do behind this)
 #pragma unroll
-      for (int r = 0; r < TL::SHARED; ++r)
+    for (int r = 0; r < TL::SHARED; ++r)
+      if (wave == 3 - r) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const float* pp = s_u + (r * 4 * 16 + v) * 64 + lane;
           acc[TL::WHOLE + r][v] = (pp[0] + pp[16 * 64]) + (pp[2 * 16 * 64] + pp[3 * 16 * 64]);
         }
-    }
+      }
   }
+  auto mine = [&](int t) { return t_rb[t] >= 0 && (t < TL::WHOLE || wave == 3 - (t - TL::WHOLE)); };   // tiles to hand on
 
   // column sums: lanes that share a channel group (stride G8) first, then the four wavefronts
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
+    suma[e] = stats_lane_sum<G8>(suma[e]);
+    sumb[e] = stats_lane_sum<G8>(sumb[e]);
+  }
+  if constexpr (OWN) {
 #pragma unroll
-    for (int o = G8; o < 64; o <<= 1) {
-      suma[e] += __shfl_xor(suma[e], o);
-      sumb[e] += __shfl_xor(sumb[e], o);
+    for (int e = 0; e < 8; ++e) {
+      sqa[e] = stats_lane_sum<G8>(sqa[e]);
+      sqb[e] = stats_lane_sum<G8>(sqb[e]);
     }
   }
   if (lane < G8) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      s_part[wave * D + stats_ja<D>(layout, g, e)] = suma[e];
-      s_part[wave * D + stats_jb<D>(layout, g, e)] = sumb[e];
+      const int ca = wave * D + stats_ja<D>(layout, g, e), cb = wave * D + stats_jb<D>(layout, g, e);
+      s_part[ca] = suma[e];
+      s_part[cb] = sumb[e];
+      if constexpr (OWN) {
+        s_sq[ca] = sqa[e];
+        s_sq[cb] = sqb[e];
+      }
     }
   }
   __syncthreads();
@@ -864,24 +809,6 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
     if (!FUSED && part == 0) mu[(size_t)head * D + c] = s_shift[c] + xb;
   }
   __syncthreads();
-  if constexpr (OWN) {                                 // largest diagonal entry, from the sums of squares
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-#pragma unroll
-      for (int o = G8; o < 64; o <<= 1) {
-        sqa[e] += __shfl_xor(sqa[e], o);
-        sqb[e] += __shfl_xor(sqb[e], o);
-      }
-    }
-    if (lane < G8) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        s_part[wave * D + stats_ja<D>(layout, g, e)] = sqa[e];
-        s_part[wave * D + stats_jb<D>(layout, g, e)] = sqb[e];
-      }
-    }
-    __syncthreads();
-  }
   // In the matrix-core product a lane's B operand is column r32 and its A rows come back as
   // accumulator register v = row 8 (v / 4) + 4 kg + v % 4: the tile's entry (row, column r32).
   const float fw = (float)w, inv = 1.0f / (float)(w - ddof), unscale = 1.0f / (scale * scale);
@@ -889,6 +816,20 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
 #pragma clang fp contract(off)
     return fmaf(unscale, sum, -(xj * (fw * xi))) * inv;
   };
+  // The entries of tile t, in the accumulators' place.  (All of xbar first: read next to the stores of the entries, which it
+  // may alias, every entry was an LDS round trip of its own, 2200 cycles per tile.)
+  auto finish_tile = [&](int t) __attribute__((always_inline)) {
+    const float xj = s_xbar[t_ct[t] * 32 + r32];
+    float xi[16];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float4 f = *reinterpret_cast<const float4*>(s_xbar + t_rb[t] * 32 + 8 * c + 4 * kg);
+      xi[4 * c] = f.x; xi[4 * c + 1] = f.y; xi[4 * c + 2] = f.z; xi[4 * c + 3] = f.w;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[t][v] = sigma_entry(acc[t][v], xi[v], xj);
+  };
+  auto row_of = [&](int v) { return 8 * (v / 4) + 4 * kg + v % 4; };      // in the tile, of accumulator register v
   // A tile above the diagonal is also stored transposed.  Straight from the accumulators that is
   // 64 separate 4-byte writes per instruction (a lane holds one column).  At d = 256 (28 of 36 tiles
   // are mirrored, 64 MB of Sigma per launch of the four-sequence shape) the tile takes a trip
@@ -896,69 +837,87 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
   // d <= 128 that costs the registers that keep three workgroups on a CU without scratch memory,
   // and the direct stores are the faster ones (5.6 against 10.4 us per layer at the decode shape).
   constexpr bool kViaLds = D >= 256;
-  if constexpr (OWN) {
-    float mxS = 0.f, mxM = 0.f;                          // every wavefront for itself
+  if constexpr (FUSED) {
+    // Largest diagonal entry and largest mean.  OWN: the entry from the sums of squares, by every wavefront for itself
+    // (the same for both workgroups of the head); else from the diagonal, in three steps.
+    float mxS = 0.f, mxM = 0.f;
     for (int c = lane; c < D; c += 64) {
-      const float sq = (s_part[c] + s_part[D + c]) + (s_part[2 * D + c] + s_part[3 * D + c]);
-      mxS = fmaxf(mxS, fabsf((sq - fw * s_xbar[c] * s_xbar[c]) * inv));
+      if constexpr (OWN) {
+        const float sq = (s_sq[c] + s_sq[D + c]) + (s_sq[2 * D + c] + s_sq[3 * D + c]);
+        mxS = fmaxf(mxS, fabsf((sq - fw * s_xbar[c] * s_xbar[c]) * inv));
+      }
       mxM = fmaxf(mxM, fabsf(s_shift[c] + s_xbar[c]));
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      mxS = fmaxf(mxS, __shfl_xor(mxS, o));
-      mxM = fmaxf(mxM, __shfl_xor(mxM, o));
+    for (int t = 0; t < TPW; ++t) {
+      if (!mine(t)) continue;
+      finish_tile(t);
+      if (!OWN && t_rb[t] == t_ct[t]) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mxS = row_of(v) == r32 ? fmaxf(mxS, fabsf(acc[t][v])) : mxS;
+      }
+    }
+    mxS = wave_max(mxS);
+    mxM = wave_max(mxM);
+    if constexpr (!OWN) {
+      if (lane == 0) s_max[wave] = mxS;
+      __syncthreads();
+      mxS = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
     }
     const float sM = scale_for(2.0f * mxS), smu = scale_for(mxM);
     constexpr int NF = NCT * (NCT + 1), nks = NCT;
     const int unit = head / fo.G, gq = head - unit * fo.G, pass = gq / fo.GH, gp = gq - pass * fo.GH;
+    const int nhere = min(fo.GH, fo.G - pass * fo.GH);    // heads of this (unit, pass)
     uint4* out = fo.frags + head_frags(fo, unit, gq, NF) * 64;
     uint4* extra = fo.frags + extra_frags(fo, unit, pass, NF, nks) * 64;
+    // the head's row of kind `kind` in the extra rows' fragments, see extra_item
+    const int etile = D == 64 && fo.GH > 5 ? gp / 4 : 0;
+    auto extra_row = [&](int kind) { return gp - 4 * etile < 4 ? 4 * kind + gp - 4 * etile : 12 + kind; };
     float* patch = s_dyn + wave * (32 * 33);
+    static_assert(4 * 32 * 33 * 4 <= 2 * D * P * 2, "patches fit in the planes");
     // The tile (rows of block rb, columns of block ct) is fragments (2 ct, rb) and (2 ct + 1, rb), see frag_item: through
     // the wavefront's own patch of LDS.  On the diagonal also the residuals of the extra rows.
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
-      if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
-        const int rb = t_rb[t], ct = t_ct[t];
-        const float xj = s_xbar[ct * 32 + r32];
+      if (!mine(t)) continue;
+      const int rb = t_rb[t], ct = t_ct[t];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int il = 8 * (v / 4) + 4 * kg + v % 4;
-          patch[il * 33 + r32] = sigma_entry(acc[t][v], s_xbar[rb * 32 + il], xj);
+      for (int v = 0; v < 16; ++v) patch[row_of(v) * 33 + r32] = acc[t][v];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int m = lane & 15, grp = lane >> 4;
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const int ol = 8 * (m >> 2) + 4 * jj + (m & 3);
+        _Float16 h[8];
+        float val[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) val[i] = patch[(8 * grp + i) * 33 + ol];    // Sigma[in][out]
+        if (rb < ct) {                                   // (Sigma[out][in] too)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) val[i] += val[i];
+        } else {
+          float other[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) other[i] = patch[ol * 33 + 8 * grp + i];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) val[i] = folded_entry(8 * grp + i, ol, other[i], val[i]);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int m = lane & 15, grp = lane >> 4;
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          const int ol = 8 * (m >> 2) + 4 * jj + (m & 3);
-          _Float16 h[8];
-          float val[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) val[i] = patch[(8 * grp + i) * 33 + ol];    // Sigma[in][out]
-          if (rb < ct) {                                 // (Sigma[out][in] too)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) val[i] += val[i];
-          } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) val[i] = folded_entry(8 * grp + i, ol, patch[ol * 33 + 8 * grp + i], val[i]);
-          }
-#pragma unroll
-          for (int i = 0; i < 8; ++i) h[i] = (_Float16)(val[i] * sM);
-          out[(ct * (ct + 1) + jj * (ct + 1) + rb) * 64 + lane] = pack_half8(h);
-        }
-        if (rb == ct && lane < 4) {
-          _Float16 h[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const float x = patch[(8 * lane + i) * 34] * sM;
-            h[i] = (_Float16)(x - (float)(_Float16)x);
-          }
-          extra[(nks + rb) * 64 + lane * 16 + 8 + gp] = pack_half8(h);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        for (int i = 0; i < 8; ++i) h[i] = (_Float16)(val[i] * sM);
+        out[(ct * (ct + 1) + jj * (ct + 1) + rb) * 64 + lane] = pack_half8(h);
       }
+      if (rb == ct && lane < 4) {
+        _Float16 h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float x = patch[(8 * lane + i) * 34] * sM;
+          h[i] = (_Float16)(x - (float)(_Float16)x);
+        }
+        extra[((2 * etile + 1) * nks + rb) * 64 + lane * 16 + extra_row(2)] = pack_half8(h);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
     if (part == 0) {
       if (tid == 0) {
@@ -975,48 +934,31 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
           const float hi = (float)(_Float16)x;
           h[i] = (_Float16)(kind == 0 ? hi : x - hi);
         }
-        extra[b * 64 + grp * 16 + 4 * kind + gp] = pack_half8(h);
+        extra[(2 * etile * nks + b) * 64 + grp * 16 + extra_row(kind)] = pack_half8(h);
       }
-      if (gp == 0) {                                     // rows that belong to no head
-        const int nhere = min(fo.GH, fo.G - pass * fo.GH);
-        for (int item = tid; item < 2 * nks * 64; item += 256) {
+      if (gp == 0) {                                     // rows that belong to no head, and heads that the last pass has room
+        const uint4 z = make_uint4(0u, 0u, 0u, 0u);      // for but not
+        for (int item = tid; item < extra_tiles(fo.GH) * 2 * nks * 64; item += 256) {
           const ExtraItem x = extra_item<D>(fo.GH, item >> 6, item & 63);
-          if (x.g < 0 || x.g >= nhere) extra[item] = make_uint4(0u, 0u, 0u, 0u);
+          if (x.g < 0 || x.g >= nhere) extra[item] = z;
         }
+        if (!fo.hw)
+          for (int item = nhere * NF * 64 + tid; item < fo.GH * NF * 64; item += 256) out[item] = z;
       }
     }
-  } else if constexpr (FUSED) {
-    float* S = s_dyn;                                  // [D][SP]
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
-        const int i0 = t_rb[t] * 32, j = t_ct[t] * 32 + r32;
-        const bool mirror = t_rb[t] != t_ct[t];
-        const float xj = s_xbar[j];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int i = i0 + 8 * (v / 4) + 4 * kg + v % 4;
-          const float val = sigma_entry(acc[t][v], s_xbar[i], xj);
-          S[i * SP + j] = val;
-          if (mirror) S[j * SP + i] = val;
-        }
-      }
-    }
-    __syncthreads();
-    stats_write_frags<D>(S, s_shift, s_xbar, head, fo);
   } else if constexpr (!kViaLds) {
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
-      if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
+      if (mine(t)) {
         const int i0 = t_rb[t] * 32, j = t_ct[t] * 32 + r32;
-        const bool mirror = t_rb[t] != t_ct[t];
-        const float xj = s_xbar[j];
+        finish_tile(t);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int i = i0 + 8 * (v / 4) + 4 * kg + v % 4;
-          const float val = sigma_entry(acc[t][v], s_xbar[i], xj);
-          sigma[((size_t)head * D + i) * D + j] = val;
-          if (mirror) sigma[((size_t)head * D + j) * D + i] = val;
+        for (int v = 0; v < 16; ++v) sigma[((size_t)head * D + i0 + row_of(v)) * D + j] = acc[t][v];
+        if (t_rb[t] != t_ct[t]) {                        // four rows in a row: 16 bytes of the transposed tile
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            *reinterpret_cast<float4*>(sigma + ((size_t)head * D + j) * D + i0 + 8 * c + 4 * kg) =
+                make_float4(acc[t][4 * c], acc[t][4 * c + 1], acc[t][4 * c + 2], acc[t][4 * c + 3]);
         }
       }
     }
@@ -1026,16 +968,14 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
     __syncthreads();                 // every wavefront is done with the planes (and the partial tiles)
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
-      if (t_rb[t] >= 0 && (t < TL::WHOLE || wave == 0)) {
+      if (mine(t)) {
         const int i0 = t_rb[t] * 32, j0 = t_ct[t] * 32, j = j0 + r32;
         const bool mirror = t_rb[t] != t_ct[t];
-        const float xj = s_xbar[j];
+        finish_tile(t);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int il = 8 * (v / 4) + 4 * kg + v % 4;
-          const float val = sigma_entry(acc[t][v], s_xbar[i0 + il], xj);
-          sigma[((size_t)head * D + i0 + il) * D + j] = val;
-          if (mirror) s_tr[r32 * 33 + il] = val;         // [column][row]
+          sigma[((size_t)head * D + i0 + row_of(v)) * D + j] = acc[t][v];
+          if (mirror) s_tr[r32 * 33 + row_of(v)] = acc[t][v];         // [column][row]
         }
         if (mirror) {
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1227,10 +1167,7 @@ template <int D, int LAYOUT, int PARTS>
 static hipError_t launch_stats_frags_one(const Dims& d, const void* q_win, int w, const float2* tab, const FragsOut& fo,
                                          hipStream_t st) {
   auto kern = k_stats_split<D, LAYOUT, PARTS, true>;
-  const size_t planes = (size_t)2 * D * (stats_split_chunk(D) + 8) * sizeof(_Float16);
-  // one workgroup per head: Sigma takes the planes' place
-  const size_t sig = StatsTiling<D, PARTS>::PARTS == 1 ? (size_t)D * stats_sigma_pitch(D) * sizeof(float) : 0;
-  const size_t lds = (planes > sig ? planes : sig) + (size_t)(6 * D + 4) * sizeof(float);
+  const size_t lds = (size_t)2 * D * (stats_split_chunk(D) + 8) * sizeof(_Float16) + (size_t)(10 * D + 4) * sizeof(float);
   static LdsOptIn opt;
   hipError_t e = opt.ensure(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
