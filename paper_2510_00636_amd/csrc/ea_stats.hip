@@ -157,12 +157,37 @@ __device__ __forceinline__ void stats_rotate(float2 t, float qa, float qb, float
   xb = fmaf(t.y, qa, pb) - shb;
 }
 
-// the sum over the lanes that share a channel group (stride G8)
+// Sums over the lanes that share a channel group (stride G8), of eight values each: on return v[0 .. n) of a lane are those of
+// the values stats_sum_at(lane, 0 .. n), n = stats_sums(G8).  Every step but the first of G8 = 4 hands half of the values to
+// each side.
+template <int G8> constexpr int stats_sums = G8 <= 8 ? 1 : 2;
 template <int G8>
-__device__ __forceinline__ float stats_lane_sum(float x) {
-  if (G8 <= 4) x += __shfl_xor(x, 4);
-  if (G8 <= 8) x = dpp_add<0x128>(x);
-  return sum_halves(sum_xor16(x));
+__device__ __forceinline__ int stats_sum_at(int lane, int i) {
+  const int hi = lane >> 5, mid = lane >> 4 & 1, lo = lane >> 3 & 1;
+  return G8 <= 8 ? 4 * hi + 2 * mid + lo : 4 * i + 2 * hi + mid;
+}
+template <int G8>
+__device__ __forceinline__ void stats_lane_sums(float (&v)[8], int lane) {
+  if (G8 <= 4) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += __shfl_xor(v[e], 4);
+  }
+  constexpr int N = G8 <= 8 ? 4 : 8;
+  if (G8 <= 8) {
+    const bool odd = lane & 8;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = dpp_add_of<0x128>(odd ? v[2 * e + 1] : v[2 * e], odd ? v[2 * e] : v[2 * e + 1]);
+  }
+#pragma unroll
+  for (int e = 0; e < N / 2; ++e) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[2 * e]), __float_as_uint(v[2 * e + 1]), false, false);
+    v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int e = 0; e < N / 4; ++e) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2 * e]), __float_as_uint(v[2 * e + 1]), false, false);
+    v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
 }
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
@@ -357,17 +382,13 @@ __global__ __launch_bounds__(256, (D == 64 ? 4 : 2)) void k_stats(const void* __
   }
 
   // column sums: lanes that share a channel group (stride G8) first, then the four wavefronts
+  stats_lane_sums<G8>(suma, lane);
+  stats_lane_sums<G8>(sumb, lane);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    suma[e] = stats_lane_sum<G8>(suma[e]);
-    sumb[e] = stats_lane_sum<G8>(sumb[e]);
-  }
-  if (lane < G8) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      s_part[wave * D + stats_ja<D>(layout, g, e)] = suma[e];
-      s_part[wave * D + stats_jb<D>(layout, g, e)] = sumb[e];
-    }
+  for (int i = 0; i < stats_sums<G8>; ++i) {
+    const int e = stats_sum_at<G8>(lane, i);
+    s_part[wave * D + stats_ja<D>(layout, g, e)] = suma[i];
+    s_part[wave * D + stats_jb<D>(layout, g, e)] = sumb[i];
   }
   __syncthreads();
   const float invw = 1.0f / (float)w;
@@ -622,21 +643,15 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
     return (blk * 32 * P + ((u & ~LM) << 3)) + (r32 * P + ((lswz ^ (u & LM)) << 3));
   };
 
-  // x = u~ - u~_0 of item `it` of the chunk in flight (zeros past the chunk's end): [0, 8) the first,
+  // x = u~ - u~_0 of item `it` of the chunk in flight: [0, 8) the first,
   // [8, 16) the second channels of the group's pairs.  Nothing in it sits under a condition: a shift
   // read inside "if (inside the chunk)" was a branch and an LDS round trip per element.
-  auto item_x = [&](int it, int ns, const float (&sh)[16], float (&x)[16]) __attribute__((always_inline)) {
+  auto item_x = [&](int it, const float (&sh)[16], float (&x)[16]) __attribute__((always_inline)) {
     float qa[8], qb[8];
     float2 tb[8];
     stats_unpack_item<true>(raw[it], layout, qa, qb, tb);
-    const bool ok = sl_t + it < ns;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float xa, xb;
-      stats_rotate(tb[e], qa[e], qb[e], sh[e], sh[8 + e], xa, xb);
-      x[e] = ok ? xa : 0.f;
-      x[8 + e] = ok ? xb : 0.f;
-    }
+    for (int e = 0; e < 8; ++e) stats_rotate(tb[e], qa[e], qb[e], sh[e], sh[8 + e], x[e], x[8 + e]);
   };
 
   float scale = 1.0f;
@@ -660,8 +675,16 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
         }
       }
 #pragma unroll
-      for (int it = 0; it < ITEMS; ++it) item_x(it, ns, sh, xs[it]);
+      for (int it = 0; it < ITEMS; ++it) item_x(it, sh, xs[it]);
     }
+    if (ns < WC) {                                    // zeros past the chunk's end
+#pragma unroll
+      for (int it = 0; it < ITEMS; ++it)
+#pragma unroll
+        for (int c16 = 0; c16 < 16; ++c16) xs[it][c16] = sl_t + it < ns ? xs[it][c16] : 0.f;
+    }
+    // (nothing moves across: loads in front of the last use of the registers they go to cost 50 copies per chunk)
+    __builtin_amdgcn_sched_barrier(0);
     load_chunk(ch + 1);                               // (behind the last chunk: its last sample)
     if (ch == 0) {
       // the head's scale: a power of two that puts the first chunk's largest |x| into [16, 32)
@@ -784,28 +807,21 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
   auto mine = [&](int t) { return t_rb[t] >= 0 && (t < TL::WHOLE || wave == 3 - (t - TL::WHOLE)); };   // tiles to hand on
 
   // column sums: lanes that share a channel group (stride G8) first, then the four wavefronts
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    suma[e] = stats_lane_sum<G8>(suma[e]);
-    sumb[e] = stats_lane_sum<G8>(sumb[e]);
-  }
+  stats_lane_sums<G8>(suma, lane);
+  stats_lane_sums<G8>(sumb, lane);
   if constexpr (OWN) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      sqa[e] = stats_lane_sum<G8>(sqa[e]);
-      sqb[e] = stats_lane_sum<G8>(sqb[e]);
-    }
+    stats_lane_sums<G8>(sqa, lane);
+    stats_lane_sums<G8>(sqb, lane);
   }
-  if (lane < G8) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int ca = wave * D + stats_ja<D>(layout, g, e), cb = wave * D + stats_jb<D>(layout, g, e);
-      s_part[ca] = suma[e];
-      s_part[cb] = sumb[e];
-      if constexpr (OWN) {
-        s_sq[ca] = sqa[e];
-        s_sq[cb] = sqb[e];
-      }
+  for (int i = 0; i < stats_sums<G8>; ++i) {
+    const int e = stats_sum_at<G8>(lane, i);
+    const int ca = wave * D + stats_ja<D>(layout, g, e), cb = wave * D + stats_jb<D>(layout, g, e);
+    s_part[ca] = suma[i];
+    s_part[cb] = sumb[i];
+    if constexpr (OWN) {
+      s_sq[ca] = sqa[i];
+      s_sq[cb] = sqb[i];
     }
   }
   __syncthreads();
