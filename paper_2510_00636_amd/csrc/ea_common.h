@@ -39,6 +39,7 @@ struct ScorePlan {
   int nchunk;   // workgroups per (unit, pass)
   int spare;    // 1: more workgroups than CUs; the ones dispatched late join heads that still have tiles
   int hw;       // 1: the register-fragment kernel (one wavefront per query head, d = 128, four heads per pass)
+  int five;     // 1: its form for five heads per pass, on the LDS-fragment kernels' layout of the fragments
   int pg;       // keys per softmax partial (max, sum exp): partial j covers keys [j*pg, (j+1)*pg)
   int npart;    // partials per query head = ceil(n / pg)
   int lse_pass; // 1: pass A leaves only logits; the partials are taken from them by a pass of their own
@@ -65,6 +66,8 @@ ea_status check_params(const ea_params* p, Dims* d, bool rows_only = false);
 // operands come from the statistics kernel of the same call where it can make them (stats_makes_frags)
 ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu);
 ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats = false);
+// what a call launches: that plan, or on its fragments the register-fragment kernel's form for five heads
+ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats, bool paged);
 constexpr int kStatsFragsMin = 192;           // query heads from which the statistics kernel makes the operands of either kernel
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window);
 

@@ -54,6 +54,7 @@ static int least_served(int units, int64_t grid, int num_cu) {
 ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu) {
   ScorePlan s;
   s.hw = 0;
+  s.five = 0;
   s.spare = 0;
   s.lse_pass = 0;
   const int NF = frags_per_head(d.D);
@@ -136,11 +137,34 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu) {
   return s;
 }
 
+// How the register-fragment kernel cuts the keys of its (unit, pass) jobs.
+static void deal_register_workgroups(const Dims& d, int64_t n, int num_cu, ScorePlan* s) {
+  // Two workgroups per CU.  Where whole ones for every (unit, pass) leave more than a twentieth of them out, one more for
+  // each, as in make_score_plan: 192 units x 4608, G = 4, two and three per unit 138 and 132 us; G = 7 251 and 230;
+  // 384 jobs (G = 6) 248 and 227, 576 (G = 9) 375 and 337.
+  const int64_t ntiles = (n + kHwTile - 1) / kHwTile;
+  const int64_t jobs = (int64_t)d.units() * s->passes, slots = 2 * (int64_t)num_cu;
+  int64_t wgs = slots / jobs;
+  if (wgs < 8) {
+    const int64_t rounds = (jobs + slots - 1) / slots, used = wgs ? wgs * jobs : jobs;
+    s->spare = n >= 1024 && used * 20 < rounds * slots * 19;
+    wgs = s->spare ? (wgs ? wgs + 1 : 2) : wgs;
+  }
+  if (wgs > 1024) wgs = 1024;
+  if (wgs > ntiles) wgs = ntiles;
+  if (wgs < 1) wgs = 1;
+  if (wgs < 2) s->spare = 0;
+  s->nchunk = (int)wgs;
+  s->pg = kHwTile;
+  s->npart = (int)ntiles;
+}
+
 // The register-fragment kernel (d = 128): four query heads per pass, one wavefront each, two workgroups of four
 // wavefronts on a CU, whatever the cache layout.
 static ScorePlan register_plan(const Dims& d, int64_t n, int num_cu) {
   ScorePlan s;
   s.hw = 1;
+  s.five = 0;
   s.GH = 4;
   s.passes = (d.G + 3) / 4;
   s.NW = 4;
@@ -150,24 +174,7 @@ static ScorePlan register_plan(const Dims& d, int64_t n, int num_cu) {
   // the fragments of the unit's heads, then those of the extra rows of every pass
   s.nfrag = 0;
   s.unit_frags = d.G * frags_per_head(128) + s.passes * extra_frags_of(128, 4);
-  // Two workgroups per CU.  Where whole ones for every (unit, pass) leave more than a twentieth of them out, one more for
-  // each, as in make_score_plan: 192 units x 4608, G = 4, two and three per unit 138 and 132 us; G = 7 251 and 230;
-  // 384 jobs (G = 6) 248 and 227, 576 (G = 9) 375 and 337.
-  const int64_t ntiles = (n + kHwTile - 1) / kHwTile;
-  const int64_t jobs = (int64_t)d.units() * s.passes, slots = 2 * (int64_t)num_cu;
-  int64_t wgs = slots / jobs;
-  if (wgs < 8) {
-    const int64_t rounds = (jobs + slots - 1) / slots, used = wgs ? wgs * jobs : jobs;
-    s.spare = n >= 1024 && used * 20 < rounds * slots * 19;
-    wgs = s.spare ? (wgs ? wgs + 1 : 2) : wgs;
-  }
-  if (wgs > 1024) wgs = 1024;
-  if (wgs > ntiles) wgs = ntiles;
-  if (wgs < 1) wgs = 1;
-  if (wgs < 2) s.spare = 0;
-  s.nchunk = (int)wgs;
-  s.pg = kHwTile;
-  s.npart = (int)ntiles;
+  deal_register_workgroups(d, n, num_cu, &s);
   return s;
 }
 
@@ -213,6 +220,28 @@ ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stat
   if (d.D != 128 || d.dtype != EA_BF16 || n < kHwTile) return lds;
   const ScorePlan hw = register_plan(d, n, num_cu);
   return registers_serve(d, n, num_cu, lds, hw, from_stats) ? hw : lds;
+}
+
+// Where the LDS-fragment kernel would take five heads per pass, the register-fragment one does too.  In a row both do the same
+// work at the clock that the chip grants; this one starts sooner (26 KiB of fragments per wavefront, not 108 through LDS), leaves
+// the softmax partials on its way, and cuts the keys finer.  query_stats + score, us with the LDS-fragment kernel and with
+// this one: G = 5, 8 x 20000 54.4 and 50.9, 192 x 4608 184 and 177, 320 x 1500 171 and 163, 8 x 131072 156 and 155, 32 x 32768
+// 162 and 163; G = 13, 4 x 131072 222 and 207.  Not where that is all there is: two passes over long heads (G = 9, 8 x 20000 73.0
+// and 71.6, 8 x 60000 138 and 143; 8-bit 128 and 129), one over more than a few 8-bit rows (G = 5, 32 x 4608 54.5 and 51.8,
+// 128 x 2000 80.9 and 82.1, 32 x 32768 142 and 147).  Block pools: two registers short, and 0.5 % slower.
+ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats, bool paged) {
+  ScorePlan s = choose_score_plan(d, n, num_cu, from_stats);
+  if (s.hw || d.D != 128 || d.dtype != EA_BF16 || s.GH != 5 || n < kHwTile || paged) return s;
+  const int64_t tiles = (int64_t)d.units() * ((n + kHwTile - 1) / kHwTile);
+  if (s.passes == 2 && tiles * 2 > 12000) return s;
+  if (s.passes == 1 && d.kv_fp8 && tiles > 2600) return s;
+  s.five = 1;
+  s.NW = 4;
+  s.spare = 0;
+  s.lse_pass = 0;
+  s.lds_bytes = 0;
+  deal_register_workgroups(d, n, num_cu, &s);
+  return s;
 }
 
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window) {

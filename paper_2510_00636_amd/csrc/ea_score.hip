@@ -42,7 +42,7 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
   a.unit_frags = sp.unit_frags;
   a.tickets = tickets;
   a.ticket_stride = ticket_stride;
-  if (sp.hw) return launch_score_hw(a, sp, d.kv_fp8 != 0, st);
+  if (sp.hw || sp.five) return launch_score_hw(a, sp, d.kv_fp8 != 0, st);
   if (d.kv_fp8) return launch_score_mfma_fp8(d.D, a, sp, st);
   switch (d.D) {
     case 64: return launch_score_mfma_d64(a, sp, st);

@@ -27,6 +27,12 @@
 // block pools, the LDS-fragment one: operands + score, 8 heads of 4 x 131072 keys 155 -> 128 us, 8-bit 120 -> 110, x 16384
 // 38 -> 31, keys only x 32768 46 -> 43, pools of 16-row blocks x 20011 44 -> 39.
 //
+// FIVE: five query heads per pass, each wavefront with a head of its own and a quarter of the fifth one's triangle; the extra
+// rows' fragments then stand in LDS, and the fifth head's logits and softmax partials are the wavefronts' in turn.  In a
+// row it does what the LDS-fragment kernel does (8 heads of 5 x 131072 keys 155 and 156 us: the clock), but it starts
+// sooner and leaves no partials to another launch: x 20000 54.4 -> 50.9, 192 x 4608 184 -> 177, 320 x 1500 171 -> 163; where
+// which of them is taken stands at serving_score_plan.
+//
 // Scales and the meaning of `post` are those of k_prep_frags (ea_stats.hip).
 #include "ea_score_mfma.h"
 
@@ -34,7 +40,7 @@ namespace ea {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// The 40 steps of an iteration, two 16x16x32 instructions with the same fragment each: the output tiles 0 .. 7 of the
+// The 40 steps of an iteration (52 for five heads), two 16x16x32 instructions with the same fragment each: the output tiles 0 .. 7 of the
 // quadratic form of keys 0-15 and 16-31, then of keys 32-47 and 48-63.  Tile j takes the k-steps 0 .. j / 2.
 
 // Sums over the four groups of 16 lanes of four values per lane: value m, complete, in the lanes of group m.
@@ -70,26 +76,37 @@ __device__ __forceinline__ float max_dpp(float x) {
   return max_of(x, __int_as_float(y));
 }
 
+// FIVE heads per pass: every wavefront also multiplies a quarter of the fifth head's triangle, output tiles w and 7 - w of
+// wavefront w: one or two k-steps of the first and three or four of the second, taken as two and four (a step that the
+// tile does not have multiplies zeros), as tiles 8 and 9 of the schedule and fragments 20 .. 25 of the wavefront.
 struct HwStep { int sub, tile, kt, frag, set; };
-constexpr int hw_end(int u) {              // last step of tile u of the iteration (u = 0 .. 15)
+template <bool FIVE> constexpr int kHwTiles = FIVE ? 10 : 8;         // output tiles per pair of key groups
+template <bool FIVE> constexpr int kHwSteps = FIVE ? 26 : 20;        // and steps
+template <bool FIVE>
+constexpr int hw_end(int u) {              // last step of tile u of the iteration (u = 0 .. 2 kHwTiles - 1)
   int e = -1;
-  for (int i = 0; i <= u; ++i) e += (i % 8) / 2 + 1;
+  for (int i = 0; i <= u; ++i) {
+    const int j = i % kHwTiles<FIVE>;
+    e += j < 8 ? j / 2 + 1 : j == 8 ? 2 : 4;
+  }
   return e;
 }
+template <bool FIVE>
 constexpr HwStep hw_step(int f) {
   int u = 0;
-  while (hw_end(u) < f) ++u;
-  const int first = u == 0 ? 0 : hw_end(u - 1) + 1, j = u % 8;
-  return HwStep{u / 8, j, f - first, j / 2 * (j / 2 + 1) + j % 2 * (j / 2 + 1) + f - first, u % 4};
+  while (hw_end<FIVE>(u) < f) ++u;
+  const int first = u == 0 ? 0 : hw_end<FIVE>(u - 1) + 1, j = u % kHwTiles<FIVE>, kt = f - first;
+  return HwStep{u / kHwTiles<FIVE>, j, kt, (j < 8 ? j / 2 * (j / 2 + 1) + j % 2 * (j / 2 + 1) : j == 8 ? 20 : 22) + kt, u % 4};
 }
 
 // MODE kHwNoV: the caller has weights of its own, V is not read.  kHwNorms: neither, nor a softmax; the quadratic forms
 // leave as norms sqrt(k^T M k) (the rows are values then, M = W_o^T W_o, mu = 0).
 constexpr int kHwScores = 0, kHwNoV = 1, kHwNorms = 2;
 
-template <bool FP8, bool PAGED, int MODE>
+template <bool FP8, bool PAGED, int MODE, bool FIVE>
 __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
-  constexpr int NKS = 4, NF = 20, GH = 4;
+  constexpr int NKS = 4, NF = 20, GH = FIVE ? 5 : 4;
+  constexpr int HT = kHwTiles<FIVE>, HS = kHwSteps<FIVE>;
   constexpr int RB = FP8 ? 128 : 256;        // bytes of a row
   constexpr int NL = FP8 ? 2 : 4;            // wave-wide loads of a wavefront's 16 rows
   constexpr int S = kHwTile;                 // slots between the 16-byte chunks of a row in LDS
@@ -99,6 +116,9 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
   constexpr int SP = 68;                     // pitch of the extra rows: the four rows a wavefront touches at once in different banks
   __shared__ float s_p[2][16 * SP];          // extra rows: [buffer][row][key]
   __shared__ int s_tk[8];                    // ring of tiles, by ordinal
+  // FIVE: fragments of the extra rows (registers otherwise); the wavefronts' parts of the fifth head's form: [buffer][wavefront][key]
+  __shared__ u32x4 s_x[FIVE ? 2 * NKS * 64 : 1];
+  __shared__ float s_q5[2][FIVE ? 4 * S : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, q = lane >> 4;  // matrix-core column (key of a group of 16) and group of rows / channels
@@ -190,16 +210,30 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     }
   }
 
-  half8 F[NF], X[2 * NKS];                   // this head's fragments, and those of the extra rows
+  // this head's fragments (and this wavefront's of the fifth head), and those of the extra rows
+  half8 F[FIVE ? NF + 6 : NF], X[FIVE ? 1 : 2 * NKS];
   {
-    const u32x4* src = a.frags + (size_t)unit * a.unit_frags * 64;
+    // (five heads per pass: the layout of the LDS-fragment kernels)
+    const u32x4* src = a.frags + ((size_t)unit * a.unit_frags + (FIVE ? pass * (5 * NF + 2 * NKS) : g0 * NF)) * 64;
+    const u32x4* ext = FIVE ? src + 5 * NF * 64 : a.frags + ((size_t)unit * a.unit_frags + a.G * NF + pass * 2 * NKS) * 64;
     const bool mine = g0 + w < a.G;          // a wavefront without a head multiplies zeros, which cost the clock least
 #pragma unroll
     for (int i = 0; i < NF; ++i)
-      F[i] = mine ? __builtin_bit_cast(half8, src[((g0 + w) * NF + i) * 64 + lane]) : (half8)(_Float16)0.f;
+      F[i] = mine ? __builtin_bit_cast(half8, src[(w * NF + i) * 64 + lane]) : (half8)(_Float16)0.f;
+    if constexpr (FIVE) {
+      const int j0 = w, j1 = 7 - w;
+      const u32x4* fifth = src + 4 * NF * 64;
 #pragma unroll
-    for (int i = 0; i < 2 * NKS; ++i)
-      X[i] = __builtin_bit_cast(half8, src[(a.G * NF + pass * 2 * NKS + i) * 64 + lane]);
+      for (int i = 0; i < 6; ++i) {
+        const int j = i < 2 ? j0 : j1, kt = i < 2 ? i : i - 2, h = j / 2 + 1;
+        F[NF + i] = g0 + 4 < a.G && kt < h ? __builtin_bit_cast(half8, fifth[((j / 2 + j % 2) * h + kt) * 64 + lane]) : (half8)(_Float16)0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) s_x[i * 256 + tid] = ext[i * 256 + tid];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2 * NKS; ++i) X[i] = __builtin_bit_cast(half8, ext[i * 64 + lane]);
+    }
   }
   const float ks = (FP8 && a.kscale) ? a.kscale[unit] : 1.0f;
   const float vs2 = (FP8 && a.vscale) ? a.vscale[unit] * a.vscale[unit] : 1.0f;
@@ -209,6 +243,14 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     pq_mine = a.post[((size_t)unit * a.G + g0 + w) * 2 + 0] * (ks * ks);
     sc_mine = a.post[((size_t)unit * a.G + g0 + w) * 2 + 1] * ks;
     sc_mine = q < 2 ? sc_mine : q == 2 ? 256.0f * pq_mine : 0.f;
+  }
+  float pq5 = 0.f, sc5 = 0.f;                // of the fifth head
+  const bool five = FIVE && g0 + 4 < a.G;
+  if (five) {
+    auto scalar = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+    pq5 = scalar(a.post[((size_t)unit * a.G + g0 + 4) * 2 + 0] * (ks * ks));
+    sc5 = scalar(a.post[((size_t)unit * a.G + g0 + 4) * 2 + 1] * ks);
+    pq_mine = scalar(pq_mine);
   }
 
   float* dump = a.dump;                                     // at least n floats; contents never read
@@ -295,7 +337,30 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
   int kh_idx[NKS];
 #pragma unroll
   for (int b = 0; b < NKS; ++b) kh_idx[b] = (4 * b + q) * S + (c16 ^ (4 * b + q));
-  const int p_out = 4 * q * SP + 16 * w + c16, p_in = (4 * q + w) * SP + c16;
+  // (the last rows are the fifth head's: what the fourth group of lanes adds nothing of is its own head's, too)
+  const int p_out = 4 * q * SP + 16 * w + c16, p_in = (4 * (FIVE ? min(q, 2) : q) + w) * SP + c16;
+  // FIVE: the fifth head's logit of key `lane` of tile t, from the buffers of its iteration
+  auto fifth_logit = [&](int pb) __attribute__((always_inline)) -> float {
+    const float* qp = s_q5[pb] + lane;
+    const float* ep = s_p[pb] + 12 * SP + lane;
+    const float quad5 = (qp[0] + qp[S]) + (qp[2 * S] + qp[3 * S]);
+    return fmaf(quad5, pq5, fmaf(ep[0] + ep[SP], sc5, ep[2 * SP] * (256.0f * pq5)));
+  };
+  // logit of key `lane` and softmax partial of a finished tile, where that is not spread over the steps
+  auto finish_row = [&](float lg, int t, float* lg_to, float2* part_to, bool here) __attribute__((always_inline)) {
+    const int row = base_row(t) + lane;
+    lg_to[out_row(row)] = out_value(lg);
+    if constexpr (MODE != kHwNorms) {
+      const bool valid = PAGED ? row < n : row >= t * kHwTile;
+      float m = valid ? lg : -INFINITY;
+      m = max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(max_xor32(max_xor16(m))))));
+      float e = expf((valid ? lg : -INFINITY) - m);
+      e = sum_halves(sum_xor16(dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(e))))));
+      if (here && lane == 0) part_to[t] = make_float2(m, e);
+    }
+  };
+  float* lg5_out = five ? a.logits + ((size_t)unit * a.G + g0 + 4) * a.n : dump;
+  float2* part5_out = a.part + ((size_t)unit * a.G + g0 + (five ? 4 : 0)) * a.npart;
 
   // One body, the buffers by a number that the compiler does not know: unrolled for the two of them, the loop gets two
   // exits, and the paths that then join in front of it make every wavefront wait there for all the loads in flight.
@@ -303,8 +368,12 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     const int PB = s & 1;
     constexpr floatx4 zero4 = {0.f, 0.f, 0.f, 0.f};
     half8 K[2][2][NKS], Kx[NKS];
+    // (FIVE has no registers to keep the four addresses in; they differ from the first in two bits of the key's place)
+    int k_at = kh_idx[0];
+    if constexpr (FIVE) asm volatile("" : "+v"(k_at));
+    auto k_index = [&](int kt) __attribute__((always_inline)) { return FIVE ? (k_at ^ (4 * kt)) + 4 * kt * S : kh_idx[kt]; };
     auto read_k = [&](int m, int kt) __attribute__((always_inline)) {
-      return __builtin_bit_cast(half8, s_k[PB][kh_idx[kt] + 16 * m]);
+      return __builtin_bit_cast(half8, s_k[PB][k_index(kt) + 16 * m]);
     };
     auto read_pair = [&](auto sub_, auto kt_) __attribute__((always_inline)) {
       constexpr int sub = decltype(sub_)::value, kt = decltype(kt_)::value;
@@ -325,37 +394,47 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
 
     floatx4 acc[4][2], ex;
     half8 sq;
-    float dot[4] = {0.f, 0.f, 0.f, 0.f};
+    float dot[4] = {0.f, 0.f, 0.f, 0.f}, dot5[4] = {0.f, 0.f, 0.f, 0.f};
+    uint2 k5[2][2];                          // FIVE: this lane's channels of output tiles w and 7 - w, both key groups
+    half8 xf[FIVE ? 2 * NKS : 1];
     float sv[NL], lg = 0.f, lm = 0.f, le = 0.f, vn = 0.f;
     const int row_prev = base_row(t_prev) + lane;
     auto dots = [&](auto u_, auto h_) __attribute__((always_inline)) {     // rows 2 h, 2 h + 1 of the tile, both groups
-      constexpr int u = decltype(u_)::value, h = decltype(h_)::value, sub = u / 8, j = u % 8;
+      constexpr int u = decltype(u_)::value, h = decltype(h_)::value, sub = u / HT, j = u % HT;
       static_for<2>([&](auto v_) {
         constexpr int v = 2 * h + decltype(v_)::value;
-        dot[2 * sub] = fmaf(acc[u % 4][0][v], (float)K[sub][0][j / 2][4 * (j % 2) + v], dot[2 * sub]);
-        dot[2 * sub + 1] = fmaf(acc[u % 4][1][v], (float)K[sub][1][j / 2][4 * (j % 2) + v], dot[2 * sub + 1]);
+        if constexpr (j < 8) {
+          dot[2 * sub] = fmaf(acc[u % 4][0][v], (float)K[sub][0][j / 2][4 * (j % 2) + v], dot[2 * sub]);
+          dot[2 * sub + 1] = fmaf(acc[u % 4][1][v], (float)K[sub][1][j / 2][4 * (j % 2) + v], dot[2 * sub + 1]);
+        } else {
+          typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+          dot5[2 * sub] = fmaf(acc[u % 4][0][v], (float)__builtin_bit_cast(half4, k5[j - 8][0])[v], dot5[2 * sub]);
+          dot5[2 * sub + 1] = fmaf(acc[u % 4][1][v], (float)__builtin_bit_cast(half4, k5[j - 8][1])[v], dot5[2 * sub + 1]);
+        }
       });
-      asm volatile("" : "+v"(dot[2 * sub]), "+v"(dot[2 * sub + 1]));
+      if constexpr (j < 8) asm volatile("" : "+v"(dot[2 * sub]), "+v"(dot[2 * sub + 1]));
+      else asm volatile("" : "+v"(dot5[2 * sub]), "+v"(dot5[2 * sub + 1]));
     };
     __builtin_amdgcn_s_setprio(1);
-    static_for<43>([&](auto f_) {
+    static_for<2 * HS + 3>([&](auto f_) {
       constexpr int f = decltype(f_)::value;
-      if constexpr (f < 40) {
-        constexpr HwStep st = hw_step(f);
+      if constexpr (f < 2 * HS) {
+        constexpr HwStep st = hw_step<FIVE>(f);
 #pragma unroll
         for (int m = 0; m < 2; ++m)
           acc[st.set][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(F[st.frag], K[st.sub][m][st.kt], st.kt == 0 ? zero4 : acc[st.set][m], 0, 0, 0);
       }
       // -- extra rows of key group w
+      if constexpr (FIVE && f < 2 * NKS) xf[f] = __builtin_bit_cast(half8, s_x[(f / 2 + f % 2 * NKS) * 64 + lane]);
       if constexpr (f >= 2 && f < 2 + 2 * NKS) {
         constexpr int b = (f - 2) / 2;
         if constexpr (f % 2 == 0) {
           const half8 t = Kx[b] * (_Float16)0.0625f;
           // saturate instead of overflowing for |k| > 4096: infinity times a zero residual is NaN
           sq = __builtin_elementwise_min(t * t, (half8)(_Float16)65504.0f);
-          ex = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[b], Kx[b], b == 0 ? zero4 : ex, 0, 0, 0);
+          ex = __builtin_amdgcn_mfma_f32_16x16x32_f16(FIVE ? xf[FIVE ? 2 * b : 0] : X[FIVE ? 0 : b], Kx[b], b == 0 ? zero4 : ex, 0, 0, 0);
         } else {
-          ex = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[NKS + b], sq, ex, 0, 0, 0);
+          ex = __builtin_amdgcn_mfma_f32_16x16x32_f16(FIVE ? xf[FIVE ? 2 * b + 1 : 0] : X[FIVE ? 0 : NKS + b], sq, ex, 0, 0, 0);
         }
       }
       if constexpr (f == 12) {
@@ -365,10 +444,19 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
       // -- operands, a few steps ahead of their first use
       if constexpr (f == 2) read_pair(std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
       if constexpr (f == 6) read_pair(std::integral_constant<int, 0>{}, std::integral_constant<int, 3>{});
-      if constexpr (f == 16) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
-      if constexpr (f == 18) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
-      if constexpr (f == 22) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
-      if constexpr (f == 26) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{});
+      if constexpr (f == (FIVE ? HS - 2 : HS - 4)) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
+      if constexpr (f == (FIVE ? HS : HS - 2)) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+      if constexpr (f == HS + 2) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+      if constexpr (f == HS + 6) read_pair(std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{});
+      if constexpr (FIVE) {                  // (tiles 8 and 9 start at steps 20 and 22 of a pair of key groups)
+        if constexpr (f % HS == 17 || f % HS == 19) {
+          constexpr int i = f % HS == 17 ? 0 : 1, sub = f / HS;
+          const int j = i == 0 ? w : 7 - w;  // the lane's four channels of output tile j
+          const uint2* at = reinterpret_cast<const uint2*>(s_k[PB]) + k_index(j >> 1) * 2 + (j & 1) + 64 * sub;
+          k5[i][0] = at[0];
+          k5[i][1] = at[32];
+        }
+      }
       // -- the previous tile's logits, key `lane` of 64
       if constexpr (f == 0) {
         float p[4];
@@ -400,21 +488,22 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
         if constexpr (f == 27) le = sum_halves(le);
       }
       // -- staging of the next tile, each chunk requested again for the one after it
-      if constexpr (f >= 30 && f < 30 + 2 * NL && (f & 1) == 0) {
-        constexpr int j = (f - 30) / 2;
+      constexpr int L0 = 2 * HS - 10;
+      if constexpr (f >= L0 && f < L0 + 2 * NL && (f & 1) == 0) {
+        constexpr int j = (f - L0) / 2;
         stage_k(j, PB ^ 1);
         load_k(j, at_n2, lim_n2);
       }
-      if constexpr (kV && f >= 31 && f < 31 + 2 * NL && (f & 1) == 1) {
-        constexpr int j = (f - 31) / 2;
+      if constexpr (kV && f >= L0 + 1 && f < L0 + 1 + 2 * NL && (f & 1) == 1) {
+        constexpr int j = (f - L0 - 1) / 2;
         sv[j] = square_v(j);
         load_v(j, at_n2, lim_n2);
       }
-      if constexpr (kV && f == 39) vn = reduce_v(sv);
-      if constexpr (kV && f == 40) *(float*)((char*)vn_eff + (uint32_t)(4 * out_row(base_row(t_n1) + vn_row))) = __builtin_amdgcn_sqrtf(FP8 ? vn * vs2 : vn);
+      if constexpr (kV && f == L0 + 9) vn = reduce_v(sv);
+      if constexpr (kV && f == L0 + 10) *(float*)((char*)vn_eff + (uint32_t)(4 * out_row(base_row(t_n1) + vn_row))) = __builtin_amdgcn_sqrtf(FP8 ? vn * vs2 : vn);
       // -- dot products of finished output tiles with k
-      static_for<16>([&](auto u_) {
-        constexpr int u = decltype(u_)::value, e = hw_end(u);
+      static_for<2 * HT>([&](auto u_) {
+        constexpr int u = decltype(u_)::value, e = hw_end<FIVE>(u);
         if constexpr (f == e + 2) dots(u_, std::integral_constant<int, 0>{});
         if constexpr (f == e + 3) dots(u_, std::integral_constant<int, 1>{});
       });
@@ -422,6 +511,11 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     });
     __builtin_amdgcn_s_setprio(0);
     // ---- tail: the parts that need a branch
+    if constexpr (FIVE) {
+      s_q5[PB][w * S + lane] = sum_groups(dot5);
+      // the fifth head's previous tile, by the wavefronts in turn
+      if (five && t_prev >= 0 && w == (s & 3)) finish_row(fifth_logit(PB ^ 1), t_prev, lg5_out, part5_out, true);
+    }
     if (MODE != kHwNorms && t_prev >= 0 && mine && lane == 0) part_out[t_prev] = make_float2(lm, le);
     if (tid == 0) {
       if (s >= 1) s_tk[(s + 3) & 7] = tile_of(dealt + (int)pend);
@@ -445,27 +539,24 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     for (int m = 0; m < 4; ++m) {
       p[m] = fmaf(quad[m], pq_mine, s_p[pb][p_in + 16 * m] * sc_mine);
     }
-    const float lg = sum_groups(p);
-    const int row = base_row(t_prev) + lane;
-    lg_out[out_row(row)] = out_value(lg);
-    if constexpr (MODE != kHwNorms) {
-      const bool valid = PAGED ? row < n : row >= t_prev * kHwTile;
-      float m = valid ? lg : -INFINITY;
-      m = max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(max_xor32(max_xor16(m))))));
-      float e = expf((valid ? lg : -INFINITY) - m);
-      e = sum_halves(sum_xor16(dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(e))))));
-      if (mine && lane == 0) part_out[t_prev] = make_float2(m, e);
-    }
+    finish_row(sum_groups(p), t_prev, lg_out, part_out, mine);
+    if (five && w == (s & 3)) finish_row(fifth_logit(pb), t_prev, lg5_out, part5_out, true);
   }
 }
 
-hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, bool fp8, hipStream_t st) {
+template <bool FIVE>
+static void launch_score_hw_heads(const ScoreArgs& a, bool fp8, hipStream_t st) {
   const int grid = a.units * a.nchunk * a.passes;
-  if (a.pm.table) k_score_hw<false, true, kHwScores><<<grid, 256, 0, st>>>(a);
-  else if (fp8) k_score_hw<true, false, kHwScores><<<grid, 256, 0, st>>>(a);
-  else if (a.norms_out) k_score_hw<false, false, kHwNorms><<<grid, 256, 0, st>>>(a);
-  else if (a.skip_v) k_score_hw<false, false, kHwNoV><<<grid, 256, 0, st>>>(a);
-  else k_score_hw<false, false, kHwScores><<<grid, 256, 0, st>>>(a);
+  if (!FIVE && a.pm.table) k_score_hw<false, true, kHwScores, false><<<grid, 256, 0, st>>>(a);
+  else if (fp8) k_score_hw<true, false, kHwScores, FIVE><<<grid, 256, 0, st>>>(a);
+  else if (a.norms_out) k_score_hw<false, false, kHwNorms, FIVE><<<grid, 256, 0, st>>>(a);
+  else if (a.skip_v) k_score_hw<false, false, kHwNoV, FIVE><<<grid, 256, 0, st>>>(a);
+  else k_score_hw<false, false, kHwScores, FIVE><<<grid, 256, 0, st>>>(a);
+}
+
+hipError_t launch_score_hw(const ScoreArgs& a, const ScorePlan& sp, bool fp8, hipStream_t st) {
+  if (sp.five) launch_score_hw_heads<true>(a, fp8, st);
+  else launch_score_hw_heads<false>(a, fp8, st);
   return hipGetLastError();
 }
 

@@ -597,3 +597,55 @@ def test_adaptive_selection_shares_out_ties(hkv, n, kind):
                 assert np.array_equal(gi[b, h, :gl[b, h]], rk[b][h]), (n_keep, floor, b, h)
                 assert np.all(gi[b, h, gl[b, h]:] == -7)
         assert ea.debug_status(p, n, 1, ws) == 0
+
+
+@pytest.mark.parametrize("hq,batch,n", [(5, 36, 4100), (5, 36, 4097), (5, 300, 1030), (5, 40, 64 * 65), (9, 9, 16449), (10, 64, 2049)])
+def test_five_heads_per_pass_in_registers(hq, batch, n):
+    """d = 128, passes of five query heads of which the wavefronts share the last: heads whose last tile of 64 keys holds 1, 4,
+    6 or all of them, spare workgroups, a second pass of four heads and of five, on contiguous tensors, 8-bit caches and the
+    forms without a value side, and behind the statistics that make the operands tile by tile.  Against the oracle at the bf16
+    tolerance (norms at half of it, a square root); twice with the same bits; a head's NaN stays its own."""
+    import torch
+    from ea_inputs import quantize_fp8
+    eps, w = 0.02, 32
+    cfg = CONFIGS["c2"].with_(n_q_heads=hq, n_kv_heads=1, batch=batch)
+    lay = make_layer(cfg, n=n, window=w)
+    p = P.params_for(cfg, epsilon=eps)
+    mu, sigma = O.query_stats(widen(lay["q_win"]), lay["q_pos0"], lay["inv_freq"], lay["t_next"], T=cfg.horizon_T)
+    mu, sigma = mu.astype(np.float32), sigma.astype(np.float32)
+    mud, sgd, k, v = (P.to_dev(x) for x in (mu, sigma, lay["k"], lay["v"]))
+    ws = P.workspace(p, n, w)
+    ref = O.scores(widen(lay["k"]), widen(lay["v"]), mu, sigma, eps)
+    sc, again, fused = (torch.empty(batch, 1, n, device="cuda") for _ in range(3))
+    ea.score(p, k, v, n, n, mud, sgd, sc, ws)
+    ea.score(p, k, v, n, n, mud, sgd, again, ws)
+    torch.cuda.synchronize()
+    P.check_scores(sc.cpu().numpy(), ref, 2e-3)
+    assert torch.equal(sc, again)
+    ea.compress_layer(p, P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"], k.clone(), v.clone(),
+                      n, n, n // 2, fused, None, ws)
+    torch.cuda.synchronize()
+    P.check_scores(fused.cpu().numpy(), ref, 2e-3)
+    gram = np.stack([np.eye(128) * (1 + g) for g in range(hq)]).astype(np.float32)
+    wn = torch.empty(batch, hq, n, device="cuda")
+    ea.value_norms_wo(p, v, n, n, P.to_dev(gram), wn, ws)
+    torch.cuda.synchronize()
+    norms = np.linalg.norm(widen(lay["v"]), axis=-1)
+    P.check_scores(wn.cpu().numpy(), norms * np.sqrt(1.0 + np.arange(hq))[None, :, None], 1e-3)
+    ones = torch.ones(batch, hq, n, device="cuda")
+    ea.score_wo(p, k, v, n, n, mud, sgd, ones, again, ws)
+    torch.cuda.synchronize()
+    P.check_scores(again.cpu().numpy(), ref / norms, 2e-3)
+    if batch * n <= 150000:
+        (k8, ks), (v8, vs) = quantize_fp8(widen(lay["k"])), quantize_fp8(widen(lay["v"]))
+        k8d, v8d, ksd, vsd = (torch.from_numpy(x).cuda() for x in (k8, v8, ks, vs))
+        ea.score_fp8(p, k8d, v8d, ksd, vsd, n, n, mud, sgd, again, ws)
+        torch.cuda.synchronize()
+        real = [X.fp8_e4m3_decode(c) * s.astype(np.float64)[:, :, None, None] for c, s in ((k8, ks), (v8, vs))]
+        P.check_scores(again.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), eps), 2e-3)
+    for g in (0, 4):                                       # of the first sequence: all its scores, and no other sequence's
+        bad = mu.copy()
+        bad[0, g, 5] = np.nan
+        ea.score(p, k, v, n, n, P.to_dev(bad), sgd, again, ws)
+        torch.cuda.synchronize()
+        assert torch.isnan(again[0]).all() and torch.equal(again[1:], sc[1:]), g
