@@ -58,7 +58,7 @@ static ea_status run_stats_for_score(const Dims& d, const void* q_win, int64_t w
                                      char* ws, const WsLayout& L, hipStream_t st, uint32_t* clear, size_t clear_words,
                                      bool paged, bool* frags_ready) {
   const ScorePlan sp = serving_score_plan(d, n, device_num_cu(), true, paged);
-  *frags_ready = stats_makes_frags(d, sp);
+  *frags_ready = stats_makes_frags(d);
   if (!*frags_ready) return run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, ws, L, st, clear, clear_words);
   float2* tab = (float2*)(ws + L.tab);
   EA_TRY(launch_rope_table(d, inv_freq, q_pos0, t_next, (int)window, tab, clear, clear_words, st));

@@ -22,18 +22,14 @@ hipError_t launch_stats(const Dims& d, const void* q_win, int w, const float2* t
                         float* sigma, hipStream_t st);
 // the two of them in one for bf16 windows: mu and Sigma stay on the chip, the operands are those
 // launch_prep_frags makes of what launch_stats writes.  At d = 64 a head is one workgroup's either
-// way and the one launch wins at every size.  At d = 128 two workgroups that share a head can each make the
-// register-fragment kernel's fragments of their own tiles of Sigma (whole pass, 8 heads x 16384, 94.5 -> 91.2 us with the
-// histogram of the finalize pass, x 3000 57.3 -> 53.7; 32 x 9000 138 -> 132); from 192 heads on, and for the other kernel's
-// fragments, which mix rows of several tiles, a head is one workgroup's, and that is slower while the heads leave the chip
-// idle (whole pass, n = 3000, w = 128, LDS-fragment kernel, two launches against one: 32 heads 60 and 63 us, 128 85 and 86,
-// 192 105 and 102, 352 152 and 144; decode-time shape, 960 heads, w = 512: 422 and 396).  At d = 256 Sigma does not fit in
-// LDS.  One workgroup: the same operands bit for bit.  Two: up to the power of two by which a head's M is scaled, which
+// way.  At d = 128 two workgroups that share a head each make the fragments of their own tiles of Sigma, in either score
+// kernel's layout (whole pass, 8 heads x 16384, 94.5 -> 91.2 us with the
+// histogram of the finalize pass, x 3000 57.3 -> 53.7; 32 x 9000 138 -> 132); from 192 heads on a head is one workgroup's
+// (decode-time shape, 960 heads, w = 512: 422 and 396).  At d = 256 Sigma's tiles stay apart.
+// One workgroup: the same operands bit for bit.  Two: up to the power of two by which a head's M is scaled, which
 // comes from sums of squares there and from Sigma's diagonal else; where the largest entry lies within rounding of a power
 // of two they can differ by a factor of two, which moves only entries under 2^-26 of it (fp16 subnormals).
-inline bool stats_makes_frags(const Dims& d, const ScorePlan& sp) {
-  return d.dtype == EA_BF16 && (d.D == 64 || (d.D == 128 && (sp.hw || d.qheads() >= kStatsFragsMin)));
-}
+inline bool stats_makes_frags(const Dims& d) { return d.dtype == EA_BF16 && d.D <= 128; }
 hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_win, int w, const float2* tab,
                               uint4* frags, float* post, hipStream_t st);
 // mu == nullptr: zero means; sigma_shared: sigma holds one set of Hq heads for all sequences; clear /
