@@ -17,10 +17,9 @@ extern "C" {
  * the layer to finish, and writes the milliseconds of each stage to stage_ms (HOST pointer,
  * EA_N_STAGES floats):
  *   0 clear + rotary table + statistics   1 matrix-core operand preparation (empty, next to 0, where the
- *     statistics kernel writes the operands itself: bf16 windows at d = 64, and at d = 128 from 192
- *     query heads per call on)
+ *     statistics kernel writes the operands itself: bf16 windows at d <= 128)
  *   2 score pass A (K/V streaming kernel)  3 score pass B (normalise, weight by ||v||)
- *   4 selection                            5 compaction */
+ *   4 selection (empty where short heads are selected from in the launch of stage 3)   5 compaction */
 #define EA_N_STAGES 6
 ea_status ea_compress_layer_timed(const ea_params* p, const void* q_win, int64_t window,
                                   int64_t q_pos0, const double* inv_freq, int64_t t_next, void* k,

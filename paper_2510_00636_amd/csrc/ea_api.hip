@@ -76,8 +76,8 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
                            bool hist_zeroed, char* ws, const WsLayout& L, hipStream_t st,
                            hipEvent_t* ev = nullptr, const float* wnorm = nullptr, float* wnorm_out = nullptr,
                            const PageMap* pm = nullptr, const float* kscale = nullptr, const float* vscale = nullptr,
-                           bool frags_ready = false) {
-  // wnorm: Eq. 9 with per-query-head norms ||W_o v||.  wnorm_out: stop after pass A and turn its
+                           bool frags_ready = false, const KeepOut* sel = nullptr) {
+  // sel: the selection too, in the finalize pass's launch (hist0 given).  wnorm: Eq. 9 with per-query-head norms ||W_o v||.  wnorm_out: stop after pass A and turn its
   // quadratic forms into such norms (the caller passed the values as keys, mu = 0, Sigma = M_g).
   float* vnorm = (float*)(ws + L.vnorm);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
@@ -97,7 +97,7 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
     if (wnorm_out) return launch_wnorm(ws + L.logits, 0, (size_t)d.qheads() * n, d.D, wnorm_out, st) == hipSuccess
                               ? EA_OK : EA_ERR_DEVICE;
     EA_TRY(launch_finalize(d, n, ws + L.logits, 0, vnorm, ws + L.part, sp.npart, ws + L.lse, scores,
-                           hist0, st, wnorm, sp.lse_pass));
+                           hist0, st, wnorm, sp.lse_pass, sel));
   } else {
     int nchunk = 0;
     if (ev) EA_TRY(hipEventRecord(ev[0], st));
@@ -107,7 +107,7 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
     if (wnorm_out) return launch_wnorm(ws + L.logits, 1, (size_t)d.qheads() * n, d.D, wnorm_out, st) == hipSuccess
                               ? EA_OK : EA_ERR_DEVICE;
     EA_TRY(launch_finalize(d, n, ws + L.logits, 1, vnorm, ws + L.part, nchunk, ws + L.lse, scores,
-                           hist0, st, wnorm));
+                           hist0, st, wnorm, 0, sel));
   }
   return EA_OK;
 }
@@ -389,12 +389,14 @@ static ea_status compress_impl(const ea_params* p, const void* q_win, int64_t wi
                                clear_words, pm != nullptr, &frags_ready)) != EA_OK)
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[1], st));
+  const bool finish = n_keep > 0 && finish_in_one_launch(d, n);
+  const KeepOut keep = {idx, n_keep};
   if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores,
                      n_keep > 0 ? hist : nullptr, true, w, L, st,
-                     ev ? ev + 2 : nullptr, nullptr, nullptr, pm, kscale, vscale, frags_ready)) != EA_OK)
+                     ev ? ev + 2 : nullptr, nullptr, nullptr, pm, kscale, vscale, frags_ready, finish ? &keep : nullptr)) != EA_OK)
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[4], st));
-  if (n_keep > 0)
+  if (n_keep > 0 && !finish)
     EA_TRY(launch_select(d, scores, n, n_keep, idx, hist, (uint32_t*)(w + L.blk), true, st));
   if (ev) EA_TRY(hipEventRecord(ev[5], st));
   if (n_keep > 0 && unordered)

@@ -38,6 +38,8 @@ hipError_t launch_prep_frags(const Dims& d, const ScorePlan& sp, const float* mu
                              const float* sigma, uint4* frags, float* post, hipStream_t st, uint32_t* clear = nullptr,
                              size_t clear_words = 0, bool sigma_shared = false);
 
+struct KeepOut { int32_t* idx; int64_t n_keep; };
+
 // ea_score.hip
 // tickets + unit * ticket_stride: the tile counters of the unit (ticket_word), zero at launch
 hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, const void* v,
@@ -57,7 +59,10 @@ hipError_t launch_score_f32(const Dims& d, const void* k, const void* v, int64_t
 // one LT per query head (used when a head has too many partials to reduce inside pass B)
 hipError_t launch_finalize(const Dims& d, int64_t n, const void* logits, int logits_f64,
                            const float* vnorm, const void* part, int npart, void* lse, float* scores,
-                           uint32_t* hist0, hipStream_t st, const float* wnorm = nullptr, int lse_pass = 0);
+                           uint32_t* hist0, hipStream_t st, const float* wnorm = nullptr, int lse_pass = 0,
+                           const KeepOut* sel = nullptr);
+// sel: the n_keep best pairs of every head are selected too, in the same launch (finish_in_one_launch; without wnorm; hist0:
+// the histograms whose free words hold the status word)
 // lse_pass: the partials do not exist yet; take them from the (fp32) logits, one per kLseBlock keys
 // wnorm[i] = sqrt(max(2 d logits[i], 0)) for i < count
 hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D, float* wnorm, hipStream_t st);
@@ -69,6 +74,16 @@ hipError_t launch_wnorm(const void* logits, int logits_f64, size_t count, int D,
 // x 24000 35.7 and 39.1, x 32768 46.5 and 45.1; one x 20000 24.3 and 32; 48 x 20000 431 and 450)
 constexpr int64_t kSelSmallMax = 24 * 1024;
 inline bool select_in_one_launch(int64_t n) { return n <= kSelSmallMax; }
+// Finalize and selection together, a workgroup per unit that keeps the scores in registers: a launch less, as long as what
+// the finalize pass spreads over the chip is not too much for one CU (whole pass, us, two launches and one: 8 heads x 700
+// 37.9 and 34.3, x 2500 44.2 and 41.7, x 5000 50.0 and 48.2, x 8192 55.8 and 56.5; 192 x 4608 319 and 314; 32 heads of G = 8 x
+// 5000 103.3 and 102.0; fp32, 2 heads x 700 35.7 and 32.3, 4 heads of G = 7 x 3000 83.9 and 82.5, x 3900 95.0 and 96.2).
+constexpr int64_t kFinishMax = 5 * 1024, kFinishMaxF32 = 4 * 1024;
+inline bool finish_in_one_launch(const Dims& d, int64_t n) {
+  return d.dtype == EA_BF16 ? n <= kFinishMax && n * d.G <= 40 * 1024 : n <= kFinishMaxF32 && n * d.G <= 21 * 1024;
+}
+hipError_t launch_finish_select(const Dims& d, int64_t n, const void* logits, int logits_f64, const float* vnorm, const void* part,
+                                int npart, float* scores, const KeepOut& sel, uint32_t* hist, hipStream_t st);
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,
                          uint32_t* hist, uint32_t* blk, bool hist0_done, hipStream_t st);
 hipError_t launch_zero(uint32_t* p, size_t count, hipStream_t st, uint32_t* extra = nullptr);

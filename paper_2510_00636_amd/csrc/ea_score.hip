@@ -7,6 +7,7 @@
 //           them on the way, for k_score_mfma k_lse_part takes them from the stored logits.
 //   pass B  k_finalize : combine the pairs into log-sum-exp per head, then
 //           score = (mean_g exp(l_g - lse_g) + eps) * ||v||.
+#include "ea_lse.h"
 #include "ea_score_mfma.h"
 
 namespace ea {
@@ -422,67 +423,6 @@ hipError_t launch_score_f32(const Dims& d, const void* k, const void* v, int64_t
 // covers the same keys in every run) and are combined here in index order, so the log-sum-exp,
 // and with it every score, comes out bit-identical from run to run however pass A's tiles were
 // dealt to workgroups.
-template <typename LT>
-struct LT2;
-template <>
-struct LT2<float> { typedef float2 type; };
-template <>
-struct LT2<double> { typedef double2 type; };
-
-__device__ __forceinline__ float ea_exp(float x) { return expf(x); }
-__device__ __forceinline__ double ea_exp(double x) { return exp(x); }
-__device__ __forceinline__ float ea_log(float x) { return logf(x); }
-__device__ __forceinline__ double ea_log(double x) { return log(x); }
-
-template <typename LT>
-__device__ __forceinline__ void merge_lt(LT& m, LT& s, LT m2, LT s2) {
-  LT mn = m > m2 ? m : m2;
-  if (mn == -INFINITY) { s = 0; m = mn; }
-  else { s = s * ea_exp(m - mn) + s2 * ea_exp(m2 - mn); m = mn; }
-}
-
-// (max, sum exp) of partials c0, c0 + step, .. of a head: four at a time, requested together, the largest maximum first
-// and one exponential per partial then (merged one by one they cost two exponentials and a memory latency each).
-template <typename LT>
-__device__ __forceinline__ void gather_lt(const typename LT2<LT>::type* __restrict__ p, int npart, int c0, int step, LT& m, LT& s) {
-  constexpr int U = 4;
-  m = -INFINITY;
-  s = 0;
-  if (npart <= step) {                      // one, or none
-    if (c0 < npart) { m = p[c0].x; s = p[c0].y; }
-    return;
-  }
-  for (int c = c0; c < npart; c += U * step) {
-    typename LT2<LT>::type x[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      x[u] = p[min(c + u * step, npart - 1)];
-      if (c + u * step >= npart) x[u].x = -INFINITY;
-    }
-    LT mn = m;
-#pragma unroll
-    for (int u = 0; u < U; ++u) mn = mn > x[u].x ? mn : x[u].x;
-    if (mn == -INFINITY) continue;
-    s *= ea_exp(m - mn);
-#pragma unroll
-    for (int u = 0; u < U; ++u) s += c + u * step < npart ? x[u].y * ea_exp(x[u].x - mn) : (LT)0;
-    m = mn;
-  }
-}
-
-// log-sum-exp of one head from its npart partials, by one wavefront: lane l takes partials
-// l, l + 64, ... in increasing order, then a fixed butterfly over the lanes.
-template <typename LT>
-__device__ __forceinline__ LT wave_lse(const typename LT2<LT>::type* __restrict__ p, int npart, int lane) {
-  LT m, s;
-  gather_lt<LT>(p, npart, lane, 64, m, s);
-  for (int o = 32; o >= 1; o >>= 1) {
-    LT m2 = __shfl_xor(m, o), s2 = __shfl_xor(s, o);
-    merge_lt<LT>(m, s, m2, s2);
-  }
-  return m + ea_log(s);
-}
-
 // (max, sum exp) of one block of kLseBlock keys of one query head, from the logits pass A stored:
 // the LDS-fragment kernels leave the softmax to this pass, so the partial of a block is the same
 // number on every run whichever waves scored its keys (fixed reduction tree), and the score
@@ -655,13 +595,18 @@ constexpr int kLseInlineMax = 1024;   // more partials per head than this: reduc
 
 hipError_t launch_finalize(const Dims& d, int64_t n, const void* logits, int logits_f64,
                            const float* vnorm, const void* part, int npart, void* lse, float* scores,
-                           uint32_t* hist0, hipStream_t st, const float* wnorm, int lse_pass) {
+                           uint32_t* hist0, hipStream_t st, const float* wnorm, int lse_pass, const KeepOut* sel) {
   // 1024 keys per workgroup; four rounds of them (fewer histogram flushes) once that still leaves
   // a few thousand workgroups: the pass is bound by memory latency and wants the chip full
   const int rounds = (n + 1023) / 1024 * d.units() >= 4096 ? 4 : 1;
   const int64_t nblk = (n + 1024 * rounds - 1) / (1024 * rounds);
   const unsigned grid = (unsigned)(nblk * d.units());
   const bool pre = npart > kLseInlineMax;
+  if (sel) {                       // short heads: their selection in the same launch
+    if (lse_pass)
+      k_lse_part<<<(unsigned)((size_t)d.qheads() * npart), 256, 0, st>>>((const float*)logits, n, npart, (float2*)part);
+    return launch_finish_select(d, n, logits, logits_f64, vnorm, part, npart, scores, *sel, hist0, st);
+  }
   if (logits_f64) {
     if (pre) k_lse<double><<<d.qheads(), 256, 0, st>>>((const double2*)part, npart, (double*)lse);
     k_finalize<double><<<grid, 256, 0, st>>>((const double*)logits, vnorm, (const double2*)part,

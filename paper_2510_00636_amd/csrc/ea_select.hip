@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ea_kernels.h"
+#include "ea_lse.h"
 
 namespace ea {
 
@@ -315,23 +316,26 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_emit(SelArgs a) {
 constexpr int kSelSmallThreads = 1024;
 constexpr int kSelCopies = 4;
 
+// position of u[0] of a thread, and the rows per wavefront
+struct SmallShare { int rows, base; };
+__device__ __forceinline__ SmallShare small_share(int n) {
+  const int rows = (n + kSelSmallThreads - 1) / kSelSmallThreads;
+  return SmallShare{rows, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * 64 * rows + ((int)threadIdx.x & 63)};
+}
+
+// The selection out of the registers of the workgroup.  HIST0: the caller's first histogram.
 template <int PER, bool HIST0>
-__global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
+__device__ __forceinline__ void select_unit(const SelArgs& a, int unit, const uint32_t (&u)[PER]) {
   constexpr int NT = kSelSmallThreads;
   __shared__ __align__(16) uint32_t s_hist0[HIST0 ? 1 : kSelBins * kSelCopies];
   __shared__ __align__(16) uint32_t s_hist1[kSelBins], s_hist2[kSelBins / 2];
   __shared__ BinSearch<NT> s_find[3];
   __shared__ uint32_t s_w[2][NT / 64];
-  const int tid = threadIdx.x, lane = tid & 63, unit = blockIdx.x, n = (int)a.n;
+  const int tid = threadIdx.x, lane = tid & 63, n = (int)a.n;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rows = (n + NT - 1) / NT;                                  // <= PER
-  const int base = wave * 64 * rows + lane;                            // position of u[it]: base + 64 it
-  const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
+  const int rows = small_share(n).rows, base = small_share(n).base;
   uint32_t c0[kSelBins / NT], c1[kSelBins / NT], c2[kSelBins / 2 / NT];
   if (HIST0) load_bins<NT>(a.hist + (size_t)unit * 3 * kSelBins, c0);   // the caller's first histogram
-  uint32_t u[PER];
-#pragma unroll
-  for (int it = 0; it < PER; ++it) u[it] = sc[min(base + 64 * min(it, rows - 1), n - 1)];
   // Which lanes' u[it] are scores of the head and of this wavefront's share, as a number.  (What is the same for all lanes is
   // kept out of the vector instructions: on the one CU that a head gets, their number is what takes the time.)
   const int left = __builtin_amdgcn_readfirstlane(min(max(n - wave * 64 * rows, 0), 64 * rows));
@@ -397,6 +401,95 @@ __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
   int32_t* out = a.idx + (size_t)unit * a.n_keep;
 #pragma unroll
   for (int it = 0; it < PER; ++it) emit_row(inside(it), u[it], T, q, pos, eq_before, out, a.n_keep, base + 64 * it);
+}
+
+template <int PER, bool HIST0>
+__global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
+  const SmallShare x = small_share((int)a.n);
+  const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)blockIdx.x * a.n;
+  uint32_t u[PER];
+#pragma unroll
+  for (int it = 0; it < PER; ++it) u[it] = sc[min(x.base + 64 * min(it, x.rows - 1), (int)a.n - 1)];
+  select_unit<PER, HIST0>(a, blockIdx.x, u);
+}
+
+// The finalize pass of a unit (k_finalize, the same numbers) in front of its selection.
+template <typename LT, int PER>
+__global__ __launch_bounds__(kSelSmallThreads) void k_finish_select(SelArgs a, const LT* __restrict__ logits,
+                                                                    const float* __restrict__ vnorm,
+                                                                    const typename LT2<LT>::type* __restrict__ part, int G,
+                                                                    int npart, float eps, float* __restrict__ scores) {
+  constexpr int NH = 4;                                  // heads' logits requested together
+  __shared__ LT s_lse[64];
+  const int lane = threadIdx.x & 63, unit = blockIdx.x, n = (int)a.n;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const SmallShare x = small_share(n);
+  int at[PER];
+  float vn[PER];
+  LT acc[PER], lv[NH][PER];
+#pragma unroll
+  for (int it = 0; it < PER; ++it) {
+    at[it] = min(x.base + 64 * min(it, x.rows - 1), n - 1);
+    vn[it] = vnorm[(size_t)unit * n + at[it]];
+    acc[it] = 0;
+  }
+  auto fetch = [&](int g0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NH; ++j)
+#pragma unroll
+      for (int it = 0; it < PER; ++it) lv[j][it] = logits[((size_t)unit * G + min(g0 + j, G - 1)) * n + at[it]];
+  };
+  fetch(0);
+  for (int g = wave; g < G; g += kSelSmallThreads / 64) {
+    const LT v = wave_lse<LT>(part + ((size_t)unit * G + g) * npart, npart, lane);
+    if (lane == 0) s_lse[g] = v;
+  }
+  __syncthreads();
+  for (int g0 = 0; g0 < G; g0 += NH) {
+    if (g0 > 0) fetch(g0);
+#pragma unroll
+    for (int j = 0; j < NH; ++j) {
+      if (g0 + j >= G) break;
+      const LT lse = s_lse[g0 + j];
+#pragma unroll
+      for (int it = 0; it < PER; ++it) acc[it] += ea_exp(lv[j][it] - lse);
+    }
+  }
+  const LT invG = (LT)1 / (LT)G;
+  uint32_t u[PER];
+#pragma unroll
+  for (int it = 0; it < PER; ++it) {
+    const float sc = (float)((acc[it] * invG + (LT)eps) * (LT)vn[it]);
+    u[it] = __float_as_uint(sc);
+    scores[(size_t)unit * n + at[it]] = sc;              // (rows past the share's end: its last one, or the head's, again)
+  }
+  select_unit<PER, false>(a, unit, u);
+}
+
+hipError_t launch_finish_select(const Dims& d, int64_t n, const void* logits, int logits_f64, const float* vnorm, const void* part,
+                                int npart, float* scores, const KeepOut& sel, uint32_t* hist, hipStream_t st) {
+  SelArgs a = {};
+  a.status = hist + 2 * kSelBins + kStatusSlot;
+  a.n = n;
+  a.n_keep = (uint32_t)sel.n_keep;
+  a.idx = sel.idx;
+  static_assert(kFinishMax <= 5 * kSelSmallThreads && kFinishMaxF32 <= 4 * kSelSmallThreads, "scores per thread");
+#define EA_FINISH(LT, LT2T, PP) \
+  k_finish_select<LT, PP><<<d.units(), kSelSmallThreads, 0, st>>>(a, (const LT*)logits, vnorm, (const LT2T*)part, d.G, npart, d.eps, scores)
+  switch ((n + kSelSmallThreads - 1) / kSelSmallThreads * 2 + (logits_f64 ? 1 : 0)) {      // (a row too many costs 6 % of the pass)
+    case 2: EA_FINISH(float, float2, 1); break;
+    case 4: EA_FINISH(float, float2, 2); break;
+    case 6: EA_FINISH(float, float2, 3); break;
+    case 8: EA_FINISH(float, float2, 4); break;
+    case 10: EA_FINISH(float, float2, 5); break;
+    case 3: EA_FINISH(double, double2, 1); break;
+    case 5: EA_FINISH(double, double2, 2); break;
+    case 7: EA_FINISH(double, double2, 3); break;
+    case 9: EA_FINISH(double, double2, 4); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef EA_FINISH
+  return hipGetLastError();
 }
 
 hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int32_t* idx,

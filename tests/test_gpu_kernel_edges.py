@@ -649,3 +649,44 @@ def test_five_heads_per_pass_in_registers(hq, batch, n):
         ea.score(p, k, v, n, n, P.to_dev(bad), sgd, again, ws)
         torch.cuda.synchronize()
         assert torch.isnan(again[0]).all() and torch.equal(again[1:], sc[1:]), g
+
+
+@pytest.mark.parametrize("dtype,n", [(t, n) for t in ("bf16", "f32") for n in (1, 63, 64, 1023, 1024, 1025, 2048, 2049, 3073, 4095, 4096, 4097)] +
+                         [("bf16", 5120), ("bf16", 5121)])
+def test_finalize_and_selection_in_one_launch(dtype, n):
+    """Compress calls around the rows per thread of the launch that finishes the scores of a head and selects from them, and on
+    both sides of its limits, with five and nine query heads per KV head (four are added up at a time).  The scores are the
+    score call's bit for bit where the operands are (fp32), the positions the stable top-k of the call's own scores, the
+    rows moved accordingly, and a NaN value row shows in the status word."""
+    import torch
+    for hq in (5, 9):
+        cfg = CONFIGS["c2" if dtype == "bf16" else "c1"].with_(n_q_heads=hq, n_kv_heads=1, batch=2)
+        w = min(n, 20)
+        lay = make_layer(cfg, n=n, window=w)
+        p = P.params_for(cfg, epsilon=0.02)
+        ws = P.workspace(p, n, w)
+        win = (P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"])
+        d = cfg.head_dim
+        mu, sigma = torch.empty(2, hq, d, device="cuda"), torch.empty(2, hq, d, d, device="cuda")
+        want, got = torch.empty(2, 1, n, device="cuda"), torch.empty(2, 1, n, device="cuda")
+        k, v = P.to_dev(lay["k"]), P.to_dev(lay["v"])
+        ea.query_stats(p, *win, mu, sigma, ws)
+        ea.score(p, k, v, n, n, mu, sigma, want, ws)
+        for n_keep in {1, (n + 1) // 2, n}:
+            k, v = P.to_dev(lay["k"]), P.to_dev(lay["v"])
+            idx = torch.full((2, 1, n_keep), -1, dtype=torch.int32, device="cuda")
+            ea.compress_layer(p, *win, k, v, n, n, n_keep, got, idx, ws)
+            torch.cuda.synchronize()
+            if dtype == "f32":
+                assert torch.equal(got, want)
+            else:                                          # other operands by at most 2^-26 of the largest, other kernels' sums
+                np.testing.assert_allclose(got.cpu().numpy(), want.cpu().numpy(), rtol=2e-5, atol=0)
+            own = O.select(got.cpu().numpy().astype(np.float64), n_keep)
+            assert np.array_equal(idx.cpu().numpy(), own)
+            rk, rv = O.compact(lay["k"], lay["v"], own)
+            assert np.array_equal(P.to_host(k)[:, :, :n_keep], rk) and np.array_equal(P.to_host(v)[:, :, :n_keep], rv)
+            assert ea.debug_status(p, n, w, ws) == 0
+        v = P.to_dev(lay["v"])
+        v[1, 0, n // 2] = float("nan")
+        ea.compress_layer(p, *win, P.to_dev(lay["k"]), v, n, n, n, got, None, ws)
+        assert ea.debug_status(p, n, w, ws) & ea.STATUS_BAD_SCORE
