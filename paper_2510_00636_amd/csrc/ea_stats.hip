@@ -1017,9 +1017,10 @@ __global__ __launch_bounds__(256, (D <= 128 && !(D == 128 && (PARTS == 1 || FUSE
 }
 
 // ---------------------------------------------------------------------------------------
-// The operands from (mu, Sigma) in memory, kPrepSplit workgroups per (unit, pass).
-constexpr int kPrepSplit = 16;   // workgroups per (unit, pass)
-
+// The operands from (mu, Sigma) in memory, a wavefront per fragment: it requests the fragment's entries and what its scale
+// needs together and waits once.  (With the scales of a pass's heads in front of a barrier, and the fragments dealt to 16
+// workgroups behind it, three trips to memory: one sequence of 32 heads 6.2 us, now 4.9; four 8.0 and 6.3; the literal pass,
+// which prepares twice, 98.9 and 97.6.)
 template <int D>
 __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu, const float* __restrict__ sigma,
                                                     FragsOut fo, int shared_heads, uint32_t* __restrict__ clear,
@@ -1029,97 +1030,113 @@ __global__ __launch_bounds__(256) void k_prep_frags(const float* __restrict__ mu
   for (size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < clear_words;
        i += (size_t)gridDim.x * gridDim.y * 256)
     clear[i] = 0u;
-  auto sigma_of = [&](int unit_, int gq_) {
-    const int head = unit_ * fo.G + gq_;
-    return sigma + (size_t)(shared_heads ? head % shared_heads : head) * D * D;
-  };
-  constexpr int NJT = D / 32, NF = NJT * (NJT + 1);
-  constexpr int NK = D / 32;
+  constexpr int NJT = D / 32, NF = NJT * (NJT + 1), NK = D / 32, PL = D / 64;
   const int G = fo.G, GH = fo.GH, passes = fo.passes, nextra = extra_tiles(GH) * 2 * NK;
-  __shared__ float s_scale[16];       // [2g] = sM, [2g+1] = smu   (GH <= 8)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int unit = blockIdx.x / passes, pass = blockIdx.x % passes;
   const int g0 = pass * GH;
-  // Per-head scales, one wavefront per head.  Sigma is a covariance matrix, so
-  // |Sigma[a][b]| <= max_c Sigma[c][c]: the diagonal alone bounds every entry of M (<= 2x).
-  for (int g = wave; g < GH; g += 4) {
-    const int gq = g0 + g;
-    float mxS = 0.f, mxM = 0.f;
+  const int f = blockIdx.y * 4 + wave;
+  if (f >= GH * NF + nextra) return;
+  auto sigma_of = [&](int gq_) {
+    const int head = unit * G + gq_;
+    return sigma + (size_t)(shared_heads ? head % shared_heads : head) * D * D;
+  };
+  // Sigma is a covariance matrix, so |Sigma[a][b]| <= max_c Sigma[c][c]: the diagonal alone bounds every entry of M (<= 2x).
+  auto load_diagonal = [&](int gq, float (&x)[PL]) __attribute__((always_inline)) {
+    const float* S = sigma_of(gq);
+#pragma unroll
+    for (int i = 0; i < PL; ++i) x[i] = S[(size_t)(lane + 64 * i) * (D + 1)];
+  };
+  auto load_mean = [&](int gq, float (&x)[PL]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PL; ++i) x[i] = mu ? mu[((size_t)unit * G + gq) * D + lane + 64 * i] : 0.f;
+  };
+  auto largest = [&](const float (&x)[PL]) __attribute__((always_inline)) {
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < PL; ++i) m = fmaxf(m, fabsf(x[i]));
+    return wave_max(m);
+  };
+  _Float16 h[8];
+  uint4* out;
+  if (f < GH * NF) {
+    const int g = f / NF, gq = g0 + g;
+    if (fo.hw && gq >= G) return;
+    out = fo.frags + (head_frags(fo, unit, gq, NF) + (f - g * NF)) * 64 + lane;
     if (gq < G) {
-      const float* S = sigma_of(unit, gq);
-      for (int e = lane; e < D; e += 64) {
-        mxS = fmaxf(mxS, fabsf(S[(size_t)e * D + e]));
-        if (mu) mxM = fmaxf(mxM, fabsf(mu[((size_t)unit * G + gq) * D + e]));
+      const FragItem x = frag_item(f - g * NF, lane);
+      const float* S = sigma_of(gq);
+      // the pair (c_in, c_out) and its mirror contribute the same product k_in * k_out: the row's run and the column's
+      float diag[PL], mean[PL], mirrored[8];
+      constexpr bool kShared = D >= 128;                  // (then a workgroup's four fragments are one head's)
+      static_assert(!kShared || (NF % 4 == 0 && 2 * NK % 4 == 0), "one head per workgroup");
+      __shared__ float s_max[4];
+      const float4 lo = *reinterpret_cast<const float4*>(S + (size_t)x.out * D + x.in0);
+      const float4 hi = *reinterpret_cast<const float4*>(S + (size_t)x.out * D + x.in0 + 4);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) mirrored[i] = S[(size_t)(x.in0 + i) * D + x.out];
+      if constexpr (kShared) diag[0] = (int)threadIdx.x < D ? S[(size_t)threadIdx.x * (D + 1)] : 0.f;
+      else load_diagonal(gq, diag);
+      const bool first = f == g * NF;                     // the wavefront that writes the head's factors
+      if (first) load_mean(gq, mean);
+      float mxS;
+      if constexpr (kShared) {                            // (256 lines for every wavefront to itself: 64 heads of d = 256 11.0 us,
+        const float m = wave_max(fabsf(diag[0]));         // now 9.2)
+        if (lane == 0) s_max[wave] = m;
+        __syncthreads();
+        mxS = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+      } else {
+        mxS = largest(diag);
       }
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-      mxS = fmaxf(mxS, __shfl_xor(mxS, o));
-      mxM = fmaxf(mxM, __shfl_xor(mxM, o));
-    }
-    if (lane == 0) {
-      const float sM = scale_for(2.0f * mxS), sm = scale_for(mxM);
-      s_scale[2 * g] = sM;
-      s_scale[2 * g + 1] = sm;
-      if (gq < G && blockIdx.y == 0) {
-        fo.post[((size_t)unit * G + gq) * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
-        fo.post[((size_t)unit * G + gq) * 2 + 1] = 1.0f / (sqrtf((float)D) * sm);
-      }
-    }
-  }
-  __syncthreads();
-
-  for (int item = blockIdx.y * 256 + tid; item < (GH * NF + nextra) * 64; item += kPrepSplit * 256) {
-    const int f = item >> 6, l = item & 63;
-    uint4* out;
-    _Float16 h[8];
-    if (f < GH * NF) {
-      const int g = f / NF, gq = g0 + g;
-      if (fo.hw && gq >= G) continue;
-      out = fo.frags + (head_frags(fo, unit, gq, NF) + (f - g * NF)) * 64 + l;
-      const FragItem x = frag_item(f - g * NF, l);
-      const int c_out = x.out, c_in0 = x.in0;
-      const float sM = s_scale[2 * g];
-      float val[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) val[i] = 0.f;
-      if (gq < G) {
-        const float* S = sigma_of(unit, gq);
-        // the pair (c_in, c_out) and its mirror contribute the same product k_in * k_out, so the
-        // contiguous row S[c_out][c_in0 .. c_in0+7] serves for the block on and above the
-        // diagonal; blocks strictly above also take the mirrored entries S[c_in][c_out]
-        const float4 lo = *reinterpret_cast<const float4*>(S + (size_t)c_out * D + c_in0);
-        const float4 hi = *reinterpret_cast<const float4*>(S + (size_t)c_out * D + c_in0 + 4);
-        val[0] = lo.x; val[1] = lo.y; val[2] = lo.z; val[3] = lo.w;
-        val[4] = hi.x; val[5] = hi.y; val[6] = hi.z; val[7] = hi.w;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) val[i] = folded_entry(c_in0 + i, c_out, val[i], S[(size_t)(c_in0 + i) * D + c_out]);
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) h[i] = (_Float16)(val[i] * sM);
-    } else {
-      const int fe = f - GH * NF;
-      out = fo.frags + (extra_frags(fo, unit, pass, NF, NK) + fe) * 64 + l;
-      const ExtraItem x = extra_item<D>(GH, fe, l);
-      const int gq = g0 + x.g;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int c_in = x.c0 + i;
-        float val = 0.f;
-        if (x.g >= 0 && gq < G) {
-          if (x.kind == 2) {
-            float m = sigma_of(unit, gq)[(size_t)c_in * D + c_in] * s_scale[2 * x.g];
-            val = m - (float)(_Float16)m;
-          } else {
-            float m = mu ? mu[((size_t)unit * G + gq) * D + c_in] * s_scale[2 * x.g + 1] : 0.f;
-            float hi = (float)(_Float16)m;
-            val = x.kind == 0 ? hi : m - hi;
-          }
+      const float sM = scale_for(2.0f * mxS);
+      if (first) {
+        const float sm = scale_for(largest(mean));
+        if (lane == 0) {
+          fo.post[((size_t)unit * G + gq) * 2 + 0] = 1.0f / (2.0f * (float)D * sM);
+          fo.post[((size_t)unit * G + gq) * 2 + 1] = 1.0f / (sqrtf((float)D) * sm);
         }
-        h[i] = (_Float16)val;
       }
+      const float val[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) h[i] = (_Float16)(folded_entry(x.in0 + i, x.out, val[i], mirrored[i]) * sM);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) h[i] = (_Float16)0.f;
     }
-    *out = pack_half8(h);
+  } else {
+    const int fe = f - GH * NF, nhere = min(GH, G - g0);
+    const bool residual = fe / NK % 2 != 0;               // the fragment's rows: residuals of the diagonals, or heads and tails of the means
+    out = fo.frags + (extra_frags(fo, unit, pass, NF, NK) + fe) * 64 + lane;
+    const ExtraItem x = extra_item<D>(GH, fe, lane);
+    float scale = 0.f, val[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) val[i] = 0.f;
+    if (x.g >= 0 && x.g < nhere) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        val[i] = residual ? sigma_of(g0 + x.g)[(size_t)(x.c0 + i) * (D + 1)] : mu ? mu[((size_t)unit * G + g0 + x.g) * D + x.c0 + i] : 0.f;
+    }
+    float all[8][PL];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      if (g >= nhere) break;
+      if (residual) load_diagonal(g0 + g, all[g]);
+      else load_mean(g0 + g, all[g]);
+    }
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+      if (g >= nhere) break;
+      const float m = largest(all[g]), sc = scale_for(residual ? 2.0f * m : m);
+      if (x.g == g) scale = sc;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float m = val[i] * scale, hi = (float)(_Float16)m;
+      h[i] = (_Float16)(x.g < 0 || x.g >= nhere ? 0.f : x.kind == 0 ? hi : m - hi);
+    }
   }
+  *out = pack_half8(h);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1215,7 +1232,8 @@ hipError_t launch_stats_frags(const Dims& d, const ScorePlan& sp, const void* q_
 hipError_t launch_prep_frags(const Dims& d, const ScorePlan& sp, const float* mu,
                              const float* sigma, uint4* frags, float* post, hipStream_t st, uint32_t* clear,
                              size_t clear_words, bool sigma_shared) {
-  dim3 grid(d.units() * sp.passes, kPrepSplit);
+  const int nfrag = sp.GH * frags_per_head(d.D) + extra_tiles(sp.GH) * 2 * (d.D / 32);
+  dim3 grid(d.units() * sp.passes, (nfrag + 3) / 4);
   const int shared = sigma_shared ? d.Hq : 0;
   const FragsOut fo{frags, post, d.G, sp.GH, sp.passes, sp.nfrag, sp.unit_frags, sp.hw};
   if (d.D == 64) k_prep_frags<64><<<grid, 256, 0, st>>>(mu, sigma, fo, shared, clear, clear_words);
