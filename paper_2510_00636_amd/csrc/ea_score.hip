@@ -12,6 +12,21 @@
 
 namespace ea {
 
+// Consecutive workgroups run on different dies, and with as many heads as dies a head's are on one: its fragments, which every
+// workgroup starts with, then come out of that die's L2, and its counters are near.  In the transposed order every head has
+// workgroups on all dies, and all of them share the heads evenly, which is what counts in a long call of several passes.
+// Operands + score, us, transposed and plain.  Register-fragment kernel, one pass: 8 x 20000 40.6 and 38.6, 32 x 8000 54.6 and
+// 51.4, 8 x 100000 108.6 and 104.9, 8 x 131072 even; two: 8 x 20000 58.2 and 55.6, 16 x 3000 33.7 and 28.9, but 8 x 131072 227
+// and 235; three heads of G = 12 x 40000 81.0 and 83.5.  LDS-fragment kernel, one pass: d = 256, G = 2, 8 x 3000 46.8 and 42.8,
+// 8 x 20000 73.1 and 70.1, 8 x 100000 of G = 1 164 and 167; d = 64, 16 x 8000 38.8 and 36.6, 32 x 32768 66.2 and 66.7, 2 x 100000 32.4 and 34.2; in
+// several passes plain is up to 16 % slower (d = 64, G = 16, one x 100000 48.7 and 56.6; d = 256, G = 8, 8 x 8000 104 and 119).
+static bool transposed_order(const Dims& d, const ScorePlan& sp, int64_t n) {
+  if (sp.spare) return false;                 // (their order is the order of coming)
+  const int64_t units = d.units();
+  if (!sp.hw && !sp.five) return sp.passes > 1 || n > 40000 || units * n > (d.D == 64 ? 300000 : 100000);
+  return sp.passes > 1 && (units % 8 != 0 || units * sp.npart * sp.passes > 8500);
+}
+
 hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, const void* v,
                              int64_t n, int64_t n_cap, const uint4* frags, const float* post,
                              float* logits, float* vnorm, float2* part, uint32_t* tickets,
@@ -39,6 +54,7 @@ hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, 
   a.nchunk = sp.nchunk;
   a.npart = sp.npart;
   a.spare = sp.spare;
+  a.transposed = transposed_order(d, sp, n) ? 1 : 0;
   a.units = d.units();
   a.unit_frags = sp.unit_frags;
   a.tickets = tickets;

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
   const int lrow = FP8 ? lane >> 3 : lane >> 4, lch = FP8 ? lane & 7 : lane & 15;
 
   int bid = blockIdx.x;
-  if (!a.spare && (gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);   // every unit on all dies
+  if (a.transposed && (gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);
   int unit = bid % a.units;
   const int t2 = bid / a.units;
   int chunk = t2 % a.nchunk, pass = t2 / a.nchunk;

@@ -37,6 +37,7 @@ struct ScoreArgs {
   const float* kscale;    // FP8 instances: real key = kscale[unit] * stored value (nullptr: 1)
   const float* vscale;    // likewise for the values
   int spare;              // 1: more workgroups than CUs, see ScorePlan
+  int transposed;         // 1: the order of workgroups that puts every head on all dies (grids of a multiple of eight)
   float* dump;            // register-fragment kernel: n floats for stores that must not be seen
   int norms_out;          // that kernel: norms instead of logits (skip_v is then 1)
   int skip_v;             // 1: the caller has its own per-pair weights; V is not read, vnorm not written
@@ -199,11 +200,11 @@ __global__ __launch_bounds__(NW * 64) void k_score_mfma(ScoreArgs a) {
   u32x4* stg = smem + NLF * 64 + wave * (32 * RP);
 
   // Workgroups are dealt to the chip's 8 dies round-robin by index; the transposition below
-  // gives every unit workgroups on all of them.  Together with the tile tickets further down it
+  // gives every unit workgroups on all of them (where that pays: transposed_order).  Together with the tile tickets further down it
   // lets the faster dies (clocks under matrix-core load differ by 15 % and more) take a larger
   // share of a head instead of idling while the slowest one finishes.
   int bid = blockIdx.x;
-  if (!a.spare && (gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);
+  if (a.transposed && (gridDim.x & 7u) == 0) bid = (bid & 7) * (int)(gridDim.x >> 3) + (bid >> 3);
   int unit = bid % a.units;
   const int t2 = bid / a.units;
   int chunk = t2 % a.nchunk, pass = t2 / a.nchunk;
