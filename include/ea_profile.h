@@ -34,7 +34,7 @@ ea_status ea_compress_layer_timed(const ea_params* p, const void* q_win, int64_t
  *   EA_STATUS_COMPACT_WAIT  an in-place compaction chunk gave up waiting for the chunks whose
  *                           source rows it would overwrite (idx not strictly ascending); its
  *                           stores were skipped, so those destination rows are stale; or a block
- *                           of a selection over more than 16384 scores did (workspace overwritten
+ *                           of a selection in several launches did (workspace overwritten
  *                           while in use) and its part of idx was not written
  *   EA_STATUS_BAD_INDEX     ea_compact met an idx list that is not strictly ascending with
  *                           j <= idx[j] < n (the rows were still moved, clamped into the tensor;

@@ -196,8 +196,9 @@ static bool registers_serve(const Dims& d, int64_t n, int num_cu, const ScorePla
   int64_t most = hw.passes > 1 ? 6000 : 5000;
   if (more) most = lds.passes == 1 ? 2300 : lds.passes == 2 ? 6800 : lds.passes == 3 ? 20000 : 12000;
   else if (d.kv_fp8 && d.G <= 2) most = d.G == 1 ? 1100 : 2800;
-  // (in a compress call of fewer heads than kStatsFragsMin the statistics make this kernel's operands only, which is a launch less:
-  // compress_layer, G = 5, 16 x 5000 74 and 67; G = 1, 56 x 1143 54 and 50)
+  // (in a compress call of fewer heads than kStatsFragsMin further out: the statistics make either kernel's operands; with the lines
+  // of a score call, the whole pass of G = 3, 40 x 5000 93.8 us and 90.7 with these, G = 6, 20 x 12000 132 and 128, 16 x 12000
+  // 112 and 110)
   const bool saves = from_stats && d.qheads() < kStatsFragsMin;
   if (saves) most += most / 2 + 1000;
   if (tiles * hw.passes > most) return false;
@@ -229,12 +230,15 @@ ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stat
 // 162 and 163; G = 13, 4 x 131072 222 and 207.  Not where that is all there is: two passes over long heads (G = 9, 8 x 20000 73.0
 // and 71.6, 8 x 60000 138 and 143; 8-bit 128 and 129), one over more than a few 8-bit rows (G = 5, 32 x 4608 54.5 and 51.8,
 // 128 x 2000 80.9 and 82.1, 32 x 32768 142 and 147).  Block pools: two registers short, and 0.5 % slower.
+// In a compress call it comes before the one of four heads per pass, whose lines are drawn further out there (registers_serve):
+// the whole pass, us, that one and this one: G = 5, 8 x 12000 73.2 and 69.7, 20 x 5000 73.5 and 68.7; G = 9, 8 x 25000 140 and
+// 131; G = 10, 16 x 12000 130 and 123.
 ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats, bool paged) {
-  ScorePlan s = choose_score_plan(d, n, num_cu, from_stats);
-  if (s.hw || d.D != 128 || d.dtype != EA_BF16 || s.GH != 5 || n < kHwTile || paged) return s;
+  ScorePlan s = choose_score_plan(d, n, num_cu);
   const int64_t tiles = (int64_t)d.units() * ((n + kHwTile - 1) / kHwTile);
-  if (s.passes == 2 && tiles * 2 > 12000) return s;
-  if (s.passes == 1 && d.kv_fp8 && tiles > 2600) return s;
+  const bool long_call = (s.passes == 2 && tiles * 2 > 12000) || (s.passes == 1 && d.kv_fp8 && tiles > 2600);
+  if (s.hw || d.D != 128 || d.dtype != EA_BF16 || s.GH != 5 || n < kHwTile || paged || long_call)
+    return choose_score_plan(d, n, num_cu, from_stats);
   s.five = 1;
   s.NW = 4;
   s.spare = 0;
