@@ -68,7 +68,7 @@ ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu);
 ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats = false);
 // what a call launches: that plan, or on its fragments the register-fragment kernel's form for five heads
 ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats, bool paged);
-constexpr int kStatsFragsMin = 192;           // query heads from which the statistics kernel makes the operands of either kernel
+constexpr int kStatsFragsMin = 192;           // query heads from which one workgroup takes a whole head and makes its operands
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window);
 
 // Free words of the third radix histogram (its last digit has 1024 bins): the emit pass's block counter of
