@@ -56,8 +56,8 @@ static ea_status run_stats(const Dims& d, const void* q_win, int64_t window, int
 static ea_status run_stats_for_score(const Dims& d, const void* q_win, int64_t window, int64_t q_pos0,
                                      const double* inv_freq, int64_t t_next, int64_t n, float* mu, float* sigma,
                                      char* ws, const WsLayout& L, hipStream_t st, uint32_t* clear, size_t clear_words,
-                                     bool paged, bool* frags_ready) {
-  const ScorePlan sp = serving_score_plan(d, n, device_num_cu(), true, paged);
+                                     bool* frags_ready) {
+  const ScorePlan sp = serving_score_plan(d, n, device_num_cu(), true);
   *frags_ready = stats_makes_frags(d);
   if (!*frags_ready) return run_stats(d, q_win, window, q_pos0, inv_freq, t_next, mu, sigma, ws, L, st, clear, clear_words);
   float2* tab = (float2*)(ws + L.tab);
@@ -82,7 +82,7 @@ static ea_status run_score(const Dims& d, const void* k, const void* v, int64_t 
   float* vnorm = (float*)(ws + L.vnorm);
   uint32_t* hist = (uint32_t*)(ws + L.hist);
   if (d.dtype == EA_BF16) {
-    const ScorePlan sp = serving_score_plan(d, n, device_num_cu(), frags_ready, pm != nullptr);
+    const ScorePlan sp = serving_score_plan(d, n, device_num_cu(), frags_ready);
     uint4* frags = (uint4*)(ws + L.frags);
     float* post = (float*)(ws + L.post);
     // frags_ready comes with hist_zeroed: the caller's own first launch has cleared the words then
@@ -386,7 +386,7 @@ static ea_status compress_impl(const ea_params* p, const void* q_win, int64_t wi
   const size_t clear_words = (L.flags - L.hist) / 4 + flag_words(d, n_keep);
   bool frags_ready = false;
   if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, mu, sigma, w, L, st, hist,
-                               clear_words, pm != nullptr, &frags_ready)) != EA_OK)
+                               clear_words, &frags_ready)) != EA_OK)
     return s;
   if (ev) EA_TRY(hipEventRecord(ev[1], st));
   const bool finish = n_keep > 0 && finish_in_one_launch(d, n);
@@ -463,7 +463,7 @@ ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int6
   // one clearing launch for both sets of histograms, the block counts and the compaction flags
   uint32_t* hist = (uint32_t*)(w + L.hist);
   if ((s = run_stats_for_score(d, q_win, window, q_pos0, inv_freq, t_next, n, mu, sigma, w, L, st, hist,
-                               (L.flags - L.hist) / 4 + flag_words(d, n), false, &frags_ready)) != EA_OK)
+                               (L.flags - L.hist) / 4 + flag_words(d, n), &frags_ready)) != EA_OK)
     return s;
   if ((s = run_score(d, k, v, n, n_cap, mu, sigma, scores, hist, true, w, L, st, nullptr, nullptr, nullptr,
                      nullptr, nullptr, nullptr, frags_ready)) != EA_OK)

@@ -67,7 +67,7 @@ ea_status check_params(const ea_params* p, Dims* d, bool rows_only = false);
 ScorePlan make_score_plan(const Dims& d, int64_t n, int num_cu);
 ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats = false);
 // what a call launches: that plan, or on its fragments the register-fragment kernel's form for five heads
-ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats, bool paged);
+ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats);
 constexpr int kStatsFragsMin = 192;           // query heads from which one workgroup takes a whole head and makes its operands
 WsLayout make_ws_layout(const Dims& d, int64_t n, int64_t window);
 

@@ -229,15 +229,16 @@ ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stat
 // this one: G = 5, 8 x 20000 54.4 and 50.9, 192 x 4608 184 and 177, 320 x 1500 171 and 163, 8 x 131072 156 and 155, 32 x 32768
 // 162 and 163; G = 13, 4 x 131072 222 and 207.  Not where that is all there is: two passes over long heads (G = 9, 8 x 20000 73.0
 // and 71.6, 8 x 60000 138 and 143; 8-bit 128 and 129), one over more than a few 8-bit rows (G = 5, 32 x 4608 54.5 and 51.8,
-// 128 x 2000 80.9 and 82.1, 32 x 32768 142 and 147).  Block pools: two registers short, and 0.5 % slower.
+// 128 x 2000 80.9 and 82.1, 32 x 32768 142 and 147).  Block pools take what tensors
+// take, so that a cache's scores do not hang on its layout: 8 x 20000 53 and 51, 64 x 9000 117 and 117, 100 x 20000 334 and 319.
 // In a compress call it comes before the one of four heads per pass, whose lines are drawn further out there (registers_serve):
 // the whole pass, us, that one and this one: G = 5, 8 x 12000 73.2 and 69.7, 20 x 5000 73.5 and 68.7; G = 9, 8 x 25000 140 and
 // 131; G = 10, 16 x 12000 130 and 123.
-ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats, bool paged) {
+ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats) {
   ScorePlan s = choose_score_plan(d, n, num_cu);
   const int64_t tiles = (int64_t)d.units() * ((n + kHwTile - 1) / kHwTile);
   const bool long_call = (s.passes == 2 && tiles * 2 > 12000) || (s.passes == 1 && d.kv_fp8 && tiles > 2600);
-  if (s.hw || d.D != 128 || d.dtype != EA_BF16 || s.GH != 5 || n < kHwTile || paged || long_call)
+  if (s.hw || d.D != 128 || d.dtype != EA_BF16 || s.GH != 5 || n < kHwTile || long_call)
     return choose_score_plan(d, n, num_cu, from_stats);
   s.five = 1;
   s.NW = 4;

@@ -338,13 +338,22 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
 #pragma unroll
   for (int b = 0; b < NKS; ++b) kh_idx[b] = (4 * b + q) * S + (c16 ^ (4 * b + q));
   // (the last rows are the fifth head's: what the fourth group of lanes adds nothing of is its own head's, too)
-  const int p_out = 4 * q * SP + 16 * w + c16, p_in = (4 * (FIVE ? min(q, 2) : q) + w) * SP + c16;
+  const int p_out = 4 * q * SP + 16 * w + c16;
+  auto row_in = [&](int l) { return (4 * (FIVE ? min(l >> 4, 2) : l >> 4) + w) * SP + (l & 15); };
+  const int p_in = row_in(lane);
   // FIVE: the fifth head's logit of key `lane` of tile t, from the buffers of its iteration
-  auto fifth_logit = [&](int pb) __attribute__((always_inline)) -> float {
+  auto fifth_logit = [&](int pb, int lane) __attribute__((always_inline)) -> float {
     const float* qp = s_q5[pb] + lane;
     const float* ep = s_p[pb] + 12 * SP + lane;
     const float quad5 = (qp[0] + qp[S]) + (qp[2 * S] + qp[3 * S]);
     return fmaf(quad5, pq5, fmaf(ep[0] + ep[SP], sc5, ep[2 * SP] * (256.0f * pq5)));
+  };
+  // PAGED: the keys of the head's last tile to the lanes that have them where that tile ends at row n, so that the partial is
+  // the same sum, in the same order, on either cache layout.
+  auto to_end = [&](float x, int t) __attribute__((always_inline)) -> float {
+    if constexpr (!PAGED) return x;
+    const int here = min(n - base_row(t), kHwTile);
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * (lane + here), __float_as_int(x)));
   };
   // logit of key `lane` and softmax partial of a finished tile, where that is not spread over the steps
   auto finish_row = [&](float lg, int t, float* lg_to, float2* part_to, bool here) __attribute__((always_inline)) {
@@ -352,9 +361,10 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     lg_to[out_row(row)] = out_value(lg);
     if constexpr (MODE != kHwNorms) {
       const bool valid = PAGED ? row < n : row >= t * kHwTile;
-      float m = valid ? lg : -INFINITY;
+      lg = to_end(valid ? lg : -INFINITY, t);
+      float m = lg;
       m = max_dpp<0x140>(max_dpp<0x141>(max_dpp<0x4E>(max_dpp<0xB1>(max_xor32(max_xor16(m))))));
-      float e = expf((valid ? lg : -INFINITY) - m);
+      float e = expf(lg - m);
       e = sum_halves(sum_xor16(dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(e))))));
       if (here && lane == 0) part_to[t] = make_float2(m, e);
     }
@@ -468,9 +478,10 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
         char* dst = (char*)(t_prev >= 0 ? lg_out : dump);
         *(float*)(dst + (uint32_t)(4 * out_row(row_prev))) = out_value(lg);
         const bool valid = PAGED ? row_prev < n : row_prev >= t_prev * kHwTile;
-        lg = valid ? lg : -INFINITY;
-        lm = lg;
+        lg = to_end(valid ? lg : -INFINITY, t_prev);
+        if constexpr (!PAGED) lm = lg;
       }
+      if constexpr (PAGED && f == 5) lm = lg;
       // -- its softmax partial: max and sum over the 64 lanes, one step of the butterflies at a time
       if constexpr (MODE != kHwNorms) {
         if constexpr (f == 5) lm = max_xor16(lm);
@@ -514,7 +525,7 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
     if constexpr (FIVE) {
       s_q5[PB][w * S + lane] = sum_groups(dot5);
       // the fifth head's previous tile, by the wavefronts in turn
-      if (five && t_prev >= 0 && w == (s & 3)) finish_row(fifth_logit(PB ^ 1), t_prev, lg5_out, part5_out, true);
+      if (five && t_prev >= 0 && w == (s & 3)) finish_row(fifth_logit(PB ^ 1, lane), t_prev, lg5_out, part5_out, true);
     }
     if (MODE != kHwNorms && t_prev >= 0 && mine && lane == 0) part_out[t_prev] = make_float2(lm, le);
     if (tid == 0) {
@@ -534,20 +545,20 @@ __global__ __launch_bounds__(256, 2) void k_score_hw(ScoreArgs a) {
   // the last tile's logits
   if (t_prev >= 0) {
     const int pb = (s - 1) & 1;
+    int l = lane;
+    if constexpr (FIVE) asm volatile("" : "+v"(l));          // (the addresses once more, not kept in registers through the loop)
     float p[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      p[m] = fmaf(quad[m], pq_mine, s_p[pb][p_in + 16 * m] * sc_mine);
-    }
+    for (int m = 0; m < 4; ++m) p[m] = fmaf(quad[m], pq_mine, s_p[pb][row_in(l) + 16 * m] * sc_mine);
     finish_row(sum_groups(p), t_prev, lg_out, part_out, mine);
-    if (five && w == (s & 3)) finish_row(fifth_logit(pb), t_prev, lg5_out, part5_out, true);
+    if (five && w == (s & 3)) finish_row(fifth_logit(pb, l), t_prev, lg5_out, part5_out, true);
   }
 }
 
 template <bool FIVE>
 static void launch_score_hw_heads(const ScoreArgs& a, bool fp8, hipStream_t st) {
   const int grid = a.units * a.nchunk * a.passes;
-  if (!FIVE && a.pm.table) k_score_hw<false, true, kHwScores, false><<<grid, 256, 0, st>>>(a);
+  if (a.pm.table) k_score_hw<false, true, kHwScores, FIVE><<<grid, 256, 0, st>>>(a);
   else if (fp8) k_score_hw<true, false, kHwScores, FIVE><<<grid, 256, 0, st>>>(a);
   else if (a.norms_out) k_score_hw<false, false, kHwNorms, FIVE><<<grid, 256, 0, st>>>(a);
   else if (a.skip_v) k_score_hw<false, false, kHwNoV, FIVE><<<grid, 256, 0, st>>>(a);

@@ -690,3 +690,38 @@ def test_finalize_and_selection_in_one_launch(dtype, n):
         v[1, 0, n // 2] = float("nan")
         ea.compress_layer(p, *win, P.to_dev(lay["k"]), v, n, n, n, got, None, ws)
         assert ea.debug_status(p, n, w, ws) & ea.STATUS_BAD_SCORE
+
+
+@pytest.mark.parametrize("d,hq,hkv,n", [(128, 40, 8, 20011), (128, 180, 36, 4100), (128, 81, 9, 16449), (128, 90, 9, 16420), (128, 1000, 100, 1030),
+                                        (128, 2250, 150, 1030), (128, 5, 1, 2049), (128, 4, 1, 1001), (128, 14, 2, 777), (128, 2, 2, 64),
+                                        (128, 3, 1, 63), (64, 8, 2, 1037), (256, 6, 2, 1037)])
+def test_scores_do_not_hang_on_the_cache_layout(d, hq, hkv, n):
+    """The same logical rows in one tensor and in block pools of the smallest and of larger blocks: the same scores bit for bit,
+    by the score call and by the compress call, and the same kept set.  Passes of five and of four query heads in
+    registers, several of them and spare workgroups, and passes with fragments in LDS; heads whose last tile is short (it ends
+    at the head's last row in one tensor and starts at a multiple of the tile in pools)."""
+    import torch
+    from ea_inputs import make_block_pools
+    cfg = CONFIGS["c2"].with_(n_q_heads=hq, n_kv_heads=hkv, head_dim=d)
+    w = min(n, 40)
+    lay = make_layer(cfg, n=n, window=w)
+    p = P.params_for(cfg, epsilon=0.02)
+    ws = P.workspace(p, n, w)
+    win = (P.to_dev(lay["q_win"]), w, lay["q_pos0"], P.to_dev(lay["inv_freq"]), lay["t_next"])
+    mu, sigma = torch.empty(1, hq, d, device="cuda"), torch.empty(1, hq, d, d, device="cuda")
+    ea.query_stats(p, *win, mu, sigma, ws)
+    want, fused, got = (torch.empty(1, hkv, n, device="cuda") for _ in range(3))
+    n_keep = (n + 1) // 2
+    kept, other = (torch.empty(1, hkv, n_keep, dtype=torch.int32, device="cuda") for _ in range(2))
+    ea.score(p, P.to_dev(lay["k"]), P.to_dev(lay["v"]), n, n, mu, sigma, want, ws)
+    ea.compress_layer(p, *win, P.to_dev(lay["k"]), P.to_dev(lay["v"]), n, n, n_keep, fused, kept, ws)
+    for bs in (16, 64):
+        kp, vp, tab, nb = make_block_pools(lay["k"], lay["v"], bs, n + bs)
+        table = torch.from_numpy(tab).cuda()
+        pools = (P.to_dev(kp), P.to_dev(vp), ea.make_paged(table, bs, nb))
+        ea.score_paged(p, *pools, n, mu, sigma, got, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), bs
+        ea.compress_layer_paged(p, *win, *pools, n, n_keep, 0, got, other, None, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(got, fused) and torch.equal(other, kept), bs
