@@ -223,21 +223,32 @@ ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stat
   return registers_serve(d, n, num_cu, lds, hw, from_stats) ? hw : lds;
 }
 
-// Where the LDS-fragment kernel would take five heads per pass, the register-fragment one does too.  In a row both do the same
+// Where the LDS-fragment kernel would take five heads per pass, the register-fragment one does too, on tensors and on block pools
+// alike (a cache's scores do not hang on its layout).  In a row both do the same
 // work at the clock that the chip grants; this one starts sooner (26 KiB of fragments per wavefront, not 108 through LDS), leaves
 // the softmax partials on its way, and cuts the keys finer.  query_stats + score, us with the LDS-fragment kernel and with
-// this one: G = 5, 8 x 20000 54.4 and 50.9, 192 x 4608 184 and 177, 320 x 1500 171 and 163, 8 x 131072 156 and 155, 32 x 32768
-// 162 and 163; G = 13, 4 x 131072 222 and 207.  Not where that is all there is: two passes over long heads (G = 9, 8 x 20000 73.0
-// and 71.6, 8 x 60000 138 and 143; 8-bit 128 and 129), one over more than a few 8-bit rows (G = 5, 32 x 4608 54.5 and 51.8,
-// 128 x 2000 80.9 and 82.1, 32 x 32768 142 and 147).  Block pools take what tensors
-// take, so that a cache's scores do not hang on its layout: 8 x 20000 53 and 51, 64 x 9000 117 and 117, 100 x 20000 334 and 319.
+// this one, block pools behind the bar: G = 5, 8 x 20000 53 and 48 | 53 and 51, 64 x 9000 119 and 109 | 117 and 117, 100 x 20000 327
+// and 298 | 334 and 319, 150 x 4608 173 and 156; G = 10, 64 x 2900 111 and 98 | 112 and 101; G = 18, 100 x 5000 391 and 339.
+// Not where that is all there is:
+//   one pass whose workgroups fill the chip with the other kernel, too: 16 x 60000 147 and 153 | 155 and 162, 32 x 131072 544 and
+//     562 (but 8 x 60000, 7500 tiles, 92 and 89 | 90 and 94); over more than a few 8-bit rows 128 x 2000 80.9 and 82.1, 32 x 32768
+//     142 and 147;
+//   two passes over long heads: G = 9, 8 x 20000 73.0 and 71.6, 8 x 60000 138 and 143, 8-bit 128 and 129.
+// Nor where its two workgroups per job share out the chip worse than the other kernel's three, which takes heads of some length:
+//   one pass, jobs for every CU: 320 x 1500 170 and 168, x 4000 258 and 274, x 13000 610 and 684; 300 x 9000 441 and 498;
+//   several, a little more than two per CU: G = 14, 180 x 4608 465 and 483, 200 x 4608 491 and 517; G = 18, 140 x 4000 426 and 459
+//     (but G = 14, 230 x 3000 479 and 460).
 // In a compress call it comes before the one of four heads per pass, whose lines are drawn further out there (registers_serve):
 // the whole pass, us, that one and this one: G = 5, 8 x 12000 73.2 and 69.7, 20 x 5000 73.5 and 68.7; G = 9, 8 x 25000 140 and
 // 131; G = 10, 16 x 12000 130 and 123.
 ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stats) {
   ScorePlan s = choose_score_plan(d, n, num_cu);
   const int64_t tiles = (int64_t)d.units() * ((n + kHwTile - 1) / kHwTile);
-  const bool long_call = (s.passes == 2 && tiles * 2 > 12000) || (s.passes == 1 && d.kv_fp8 && tiles > 2600);
+  const int64_t jobs = (int64_t)d.units() * s.passes, share = num_cu / d.units();
+  const bool filled = share == 0 || share * d.units() * 10 >= (int64_t)num_cu * 9;
+  bool long_call = s.passes == 2 && tiles * 2 > 12000;
+  if (s.passes == 1) long_call = (d.kv_fp8 && tiles > 2600) || (filled && tiles > 10000) || (jobs >= num_cu && n > 2000);
+  else if (s.passes > 2) long_call = n > 2000 && jobs > 2 * num_cu && jobs * 2 < 5 * num_cu;
   if (s.hw || d.D != 128 || d.dtype != EA_BF16 || s.GH != 5 || n < kHwTile || long_call)
     return choose_score_plan(d, n, num_cu, from_stats);
   s.five = 1;

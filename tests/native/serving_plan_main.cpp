@@ -56,7 +56,9 @@ int main() {
   const struct { int G, units; int64_t n; int fp8, stats, five; } measured[] = {
       {5, 8, 20000, 0, 0, 1}, {5, 192, 4608, 0, 0, 1}, {5, 320, 1500, 0, 0, 1}, {9, 32, 4608, 0, 0, 1}, {9, 8, 60000, 0, 0, 0},
       {5, 32, 4608, 1, 0, 1}, {5, 32, 32768, 1, 0, 0}, {13, 4, 131072, 0, 0, 1}, {9, 8, 25000, 0, 1, 1}, {5, 8, 12000, 0, 1, 1},
-      {4, 8, 20000, 0, 0, 0}, {3, 40, 5000, 0, 1, 0}, {5, 8, 63, 0, 0, 0}};
+      {4, 8, 20000, 0, 0, 0}, {3, 40, 5000, 0, 1, 0}, {5, 8, 63, 0, 0, 0}, {5, 16, 60000, 0, 0, 0}, {5, 150, 4608, 0, 0, 1},
+      {5, 320, 6940, 0, 0, 0}, {5, 300, 9000, 0, 1, 0}, {14, 200, 4608, 0, 0, 0}, {18, 140, 4000, 0, 1, 0}, {14, 230, 3000, 0, 0, 1},
+      {18, 100, 5000, 0, 0, 1}};
   for (const auto& m : measured) {
     ea_params p;
     memset(&p, 0, sizeof p);
