@@ -430,7 +430,7 @@ ea_status ea_select_adaptive(const ea_params* p, const float* scores, int64_t n,
   char* w = (char*)ws;
   EA_TRY(launch_zero((uint32_t*)(w + L.hist), (L.flags - L.hist) / 4, (hipStream_t)stream));
   EA_TRY(launch_select_adaptive(d, scores, n, n_keep, floor, idx, lengths, (uint32_t*)(w + L.hist), (uint32_t*)(w + L.pool_hist),
-                                (uint32_t*)(w + L.blk), false, (hipStream_t)stream));
+                                (uint32_t*)(w + L.blk), (uint2*)(w + L.lse), false, (hipStream_t)stream));
   return EA_OK;
 }
 
@@ -469,7 +469,7 @@ ea_status ea_compress_layer_adaptive(const ea_params* p, const void* q_win, int6
                      nullptr, nullptr, nullptr, frags_ready)) != EA_OK)
     return s;
   EA_TRY(launch_select_adaptive(d, scores, n, n_keep, floor, idx_out, lengths_out, hist, (uint32_t*)(w + L.pool_hist),
-                                (uint32_t*)(w + L.blk), true, st));
+                                (uint32_t*)(w + L.blk), (uint2*)(w + L.lse), true, st));     // (the log-sum-exps are done with)
   uint32_t* flags = (uint32_t*)(w + L.flags);
   uint32_t* status = hist + 2 * kSelBins + kStatusSlot;
   EA_TRY(launch_compact(d, k, v, n, n_cap, idx_out, n, k, v, flags, status, st, lengths_out, n));

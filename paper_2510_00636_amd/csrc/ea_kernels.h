@@ -97,10 +97,10 @@ hipError_t launch_compact(const Dims& d, const void* k, const void* v, int64_t n
 // lengths != nullptr: unit u keeps lengths[u] <= n_keep rows, listed from idx + u * idx_stride
 
 // ea_select.hip, head-adaptive budgets: ascending lists idx [units][n] and their lengths.  All of the scratch is zero at launch
-// (hist0_done: but for the heads' first histograms, which are filled)
+// (hist0_done: but for the heads' first histograms, which are filled), but own, of one entry per unit, need not be
 hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor, int32_t* idx,
-                                  int32_t* lengths, uint32_t* hist, uint32_t* pool_hist, uint32_t* blk, bool hist0_done,
-                                  hipStream_t st);
+                                  int32_t* lengths, uint32_t* hist, uint32_t* pool_hist, uint32_t* blk, uint2* own,
+                                  bool hist0_done, hipStream_t st);
 
 // order-free variant, in place: only the kept rows at or beyond n_keep move, into the evicted
 // positions below it; perm (nullable) [units][n_keep] receives the source row of every position

@@ -540,174 +540,153 @@ hipError_t launch_select(const Dims& d, const float* scores, int64_t n, int64_t 
 // cut into the heads' afterwards, it took eight launches and 57 us behind the finalize pass at 8 heads x 50001 with a
 // quarter of the budget by head; now four and 25 (whole pass 236 -> 203 us).  What bounds it now is the latency of the
 // rounds through the histograms.
+// A head's digits are found once, behind its counts.  With every block of the next launch finding those of all the heads that
+// share the pool's prefix (most of them where the floors are close to the budget or the heads of one scale), select_adaptive took
+// 88 us over 32 heads x 9000 of equal scale with nine tenths of the budget by head and 928 over 512 x 9000: now 34 and 156.
+// (Two selections took 55 and 205.)
 struct AdaptArgs {
   const float* scores;
   long long n;
   uint32_t floor, rest;   // scores that every head keeps, and that the layer keeps besides
   uint32_t* hist;         // [units][3][2048], the first one filled; see kPrefixSlot
   uint32_t* pool;         // [B][3][2048], zero at launch
+  uint2* own;             // [units]: (threshold, rest of the floor) of a head, side by side: every block may read those in front
   uint32_t* blk;          // [units][nblk], zero at launch: kEmitSeen | kEmitPool | count == threshold << 13 | count > threshold
   int32_t* idx;           // [units][n]
   int32_t* lengths;       // [units]
   int B, H, nblk;
   uint32_t* status;
 };
-// Free words of a third histogram: (prefix, rest) of the unit, or of the pool, after each of the first two digits
-constexpr int kPrefixSlot = 1032;
+// Free words of a third histogram: (prefix, rest) after each of the first two digits, the unit's or the pool's, and how many of
+// the head's blocks have counted the second and the third.  The former on a line without counters (the score kernel's are done
+// with): next to the emit pass's, whose blocks all read them, select_adaptive
+// took 199 us over 512 heads x 9000, and 137 so.
+constexpr int kPrefixSlot = 1088, kCountedSlot = 1040;
 constexpr uint32_t kNoPrefix = ~0u;        // no floor: above every prefix; nothing besides the floor: the same for the pool
 constexpr uint32_t kEmitPool = 1u << 30;
 
-struct AdaptShared {
-  BinSearch<kSelThreads> own, pool;
-};
-struct AdaptPrefix { uint32_t own, own_rem, pool, pool_rem, ties_front; };
 __device__ __forceinline__ uint32_t* adapt_slot(uint32_t* hist, int level) { return hist + 2 * kSelBins + kPrefixSlot + 2 * level; }
 
-// A head's part in the pool's histogram: its own one below the bin where its floor's threshold is, and the `rem` best of
-// that bin left out.
-template <int PER>
-__device__ __forceinline__ void add_cut(uint32_t (&pool)[PER], const uint32_t (&cnt)[PER], uint32_t bin, uint32_t rem) {
-  const uint32_t lo = (uint32_t)((kSelThreads - 1 - (int)threadIdx.x) * PER);
-#pragma unroll
-  for (int i = 0; i < PER; ++i) pool[i] += lo + i < bin ? cnt[i] : lo + i == bin ? cnt[i] - rem : 0u;
-}
-
-// The second (P == 1) and third digit of head `own` of sequence b and of the pool, by a workgroup.  The other heads matter only where they share the pool's prefix, which is
-// seldom.  P == 2: ties_front, the scores at the pool's threshold that belong to the floors of the heads in front of this one.
+// Digit P of a head by a workgroup, its histogram in LDS or (nullptr) in memory: the digit, and the head's part to the pool's histogram if
+// it shares the pool's prefix: what lies below the bin of its floor's threshold, and of that bin all but the `rem` best.
 template <int P>
-__device__ __forceinline__ AdaptPrefix adapt_digit(const AdaptArgs& a, int b, int own, AdaptShared& s) {
+__device__ __forceinline__ void adapt_cut(const AdaptArgs& a, int unit, uint32_t* hist, uint32_t* pool_hist, uint32_t prefix, uint32_t rem,
+                                          bool pooled, const uint32_t* whole, BinSearch<kSelThreads>& s) {
   constexpr int PER = (P == 2 ? kSelBins / 2 : kSelBins) / kSelThreads, BITS = P == 2 ? 10 : 11;
-  const int lane = threadIdx.x & 63;
-  uint32_t* hist = a.hist + (size_t)b * a.H * 3 * kSelBins;
-  uint32_t* pool_hist = a.pool + (size_t)b * 3 * kSelBins;
-  uint32_t pool[PER], mine[PER];
-  load_bins<kSelThreads>(hist + ((size_t)own * 3 + P) * kSelBins, mine);
-  load_bins<kSelThreads>(pool_hist + P * kSelBins, pool);
-  const uint32_t own_pre = adapt_slot(hist + (size_t)own * 3 * kSelBins, P - 1)[0], own_rem = adapt_slot(hist + (size_t)own * 3 * kSelBins, P - 1)[1];
-  const uint32_t pool_pre = adapt_slot(pool_hist, P - 1)[0], pool_rem = adapt_slot(pool_hist, P - 1)[1];
-  AdaptPrefix x = {kNoPrefix, 0u, kNoPrefix, 0u, 0u};
-  uint32_t bin;
-  if (a.floor) {
-    find_bin<kSelThreads>(s.own, mine, own_rem, &bin, &x.own_rem);
-    x.own = (own_pre << BITS) | bin;
-    if (own_pre == pool_pre) add_cut(pool, mine, bin, x.own_rem);
-  }
-  if (a.rest == 0u) return x;
-#pragma unroll 1
-  for (int phase = 0; phase < (P == 2 ? 2 : 1); ++phase) {       // into the pool; then, its threshold known, the heads in front
-    const int heads = !a.floor ? 0 : phase == 0 ? a.H : own;
-#pragma unroll 1
-    for (int h0 = 0; h0 < heads; h0 += 64) {
-      const int h = min(h0 + lane, heads - 1);
-      const uint32_t pre = adapt_slot(hist + (size_t)h * 3 * kSelBins, P - 1)[0];
-      unsigned long long todo = __ballot(h0 + lane < heads && h != own && pre == pool_pre);
-      while (todo) {
-        const int g = h0 + __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        uint32_t cnt[PER], r;
-        load_bins<kSelThreads>(hist + ((size_t)g * 3 + P) * kSelBins, cnt);
-        __syncthreads();                                          // the search in front of this one has been read
-        find_bin<kSelThreads>(s.own, cnt, adapt_slot(hist + (size_t)g * 3 * kSelBins, P - 1)[1], &bin, &r);
-        if (phase == 0) add_cut(pool, cnt, bin, r);
-        else if (((pool_pre << BITS) | bin) == x.pool) x.ties_front += r;
-      }
-    }
-    if (phase == 0) {
-      find_bin<kSelThreads>(s.pool, pool, pool_rem, &bin, &x.pool_rem);
-      x.pool = (pool_pre << BITS) | bin;
+  const uint32_t lo = (uint32_t)((kSelThreads - 1 - (int)threadIdx.x) * PER);
+  uint32_t cnt[PER], bin = kNoPrefix;
+#pragma unroll
+  for (int i = 0; i < PER; ++i)                      // (P > 0: counted in this launch)
+    cnt[i] = P == 0 ? hist[lo + i] : whole ? whole[lo + i] : __hip_atomic_load(&hist[P * kSelBins + lo + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (a.floor) find_bin<kSelThreads>(s, cnt, rem, &bin, &rem);
+  if (threadIdx.x == 0) {
+    const uint32_t pre = a.floor ? (prefix << BITS) | bin : kNoPrefix;
+    if (P == 2) {
+      a.own[unit] = make_uint2(pre, rem);
+    } else {
+      adapt_slot(hist, P)[0] = pre;
+      adapt_slot(hist, P)[1] = rem;
     }
   }
-  return x;
+  if (!pooled) return;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const uint32_t part = lo + i < bin ? cnt[i] : lo + i == bin ? cnt[i] - rem : 0u;
+    if (part) atomicAdd(&pool_hist[P * kSelBins + lo + i], part);
+  }
 }
 
-// The first digits, by a workgroup per head, which adds the head's part to the pool's first histogram.  (With every workgroup
-// of the next launch searching through all heads instead: 8 heads x 3000 68.1 and 65.7 us of the whole pass, 16 x 9000 109.4
-// and 104.6, 8 x 50001 203.0 and 202.1, 32 x 9000 177 and 161.)
+// The first digits, by a workgroup per head.
 __global__ __launch_bounds__(kSelThreads) void k_adapt_first(AdaptArgs a) {
-  constexpr int PER = kSelBins / kSelThreads;
   __shared__ BinSearch<kSelThreads> s;
-  const int tid = threadIdx.x;
-  uint32_t* hist = a.hist + (size_t)blockIdx.x * 3 * kSelBins;
-  uint32_t* pool_hist = a.pool + (size_t)(blockIdx.x / a.H) * 3 * kSelBins;
-  uint32_t cnt[PER], part[PER], bin = kNoPrefix, rem = 0u;
-  load_bins<kSelThreads>(hist, cnt);
-  if (a.floor) find_bin<kSelThreads>(s, cnt, a.floor, &bin, &rem);
-  if (tid == 0) {
-    adapt_slot(hist, 0)[0] = bin;
-    adapt_slot(hist, 0)[1] = rem;
-  }
-#pragma unroll
-  for (int i = 0; i < PER; ++i) part[i] = 0u;
-  add_cut(part, cnt, bin, rem);
-#pragma unroll
-  for (int i = 0; i < PER; ++i)
-    if (part[i]) atomicAdd(&pool_hist[(kSelThreads - 1 - tid) * PER + i], part[i]);
+  adapt_cut<0>(a, blockIdx.x, a.hist + (size_t)blockIdx.x * 3 * kSelBins, a.pool + (size_t)(blockIdx.x / a.H) * 3 * kSelBins, 0u, a.floor, true, nullptr, s);
 }
 
-// second (P == 1) and third histogram of the heads, where their floors' thresholds are, and of the pool
+// Second (P == 1) and third histogram of the heads, where their floors' thresholds are, and of the pool.  The last block of a
+// head that has counted finds the head's digit and adds its part to the pool's histogram.
 template <int P>
 __global__ __launch_bounds__(kSelThreads) void k_adapt_hist(AdaptArgs a) {
   constexpr int SHIFT = P == 1 ? 21 : 10;
   __shared__ uint32_t s_own[kSelBins], s_pool[kSelBins];
-  __shared__ AdaptShared s;
+  __shared__ BinSearch<kSelThreads> s;
+  __shared__ uint32_t s_counted;
   const int tid = threadIdx.x, unit = blockIdx.x, b = unit / a.H, h = unit - b * a.H;
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)unit * a.n;
   const long long base = (long long)blockIdx.y * kSelBlock;
+  uint32_t* hist = a.hist + (size_t)unit * 3 * kSelBins;
+  uint32_t* pool_hist = a.pool + (size_t)b * 3 * kSelBins;
+  uint32_t cnt[kSelBins / kSelThreads];
+  load_bins<kSelThreads>(pool_hist + (P - 1) * kSelBins, cnt);
+  uint32_t own = kNoPrefix, own_rem = 0u, pool = 0u, pool_rem = a.rest;
+  if (a.floor) { own = adapt_slot(hist, P - 1)[0]; own_rem = adapt_slot(hist, P - 1)[1]; }
+  if (P == 2) { pool = adapt_slot(pool_hist, 0)[0]; pool_rem = adapt_slot(pool_hist, 0)[1]; }
   uint32_t u[kSelPer];
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) u[j] = sc[min(base + j * kSelThreads + tid, a.n - 1)];
   for (int i = tid; i < kSelBins; i += kSelThreads) s_own[i] = s_pool[i] = 0;
-  uint32_t* hist = a.hist + (size_t)unit * 3 * kSelBins;
-  uint32_t* pool = a.pool + (size_t)b * 3 * kSelBins;
-  AdaptPrefix x;
-  if constexpr (P == 1) {
-    uint32_t cnt[kSelBins / kSelThreads];
-    load_bins<kSelThreads>(pool, cnt);
-    x = AdaptPrefix{adapt_slot(hist, 0)[0], adapt_slot(hist, 0)[1], kNoPrefix, 0u, 0u};
-    if (a.rest) find_bin<kSelThreads>(s.pool, cnt, a.rest, &x.pool, &x.pool_rem);
+  if (a.rest) {
+    uint32_t bin;
+    find_bin<kSelThreads>(s, cnt, pool_rem, &bin, &pool_rem);
+    pool = (pool << 11) | bin;
   } else {
-    x = adapt_digit<1>(a, b, h, s);
+    pool = kNoPrefix;
   }
-  if (tid == 0 && blockIdx.y == 0) {                     // for the launches behind this one
-    if (P == 2) {
-      uint32_t* to = adapt_slot(hist, 1);
-      to[0] = x.own;
-      to[1] = x.own_rem;
-    }
-    if (h == 0) {
-      uint32_t* to = adapt_slot(pool, P - 1);
-      to[0] = x.pool;
-      to[1] = x.pool_rem;
-    }
+  if (tid == 0 && blockIdx.y == 0 && h == 0) {           // for the launches behind this one
+    adapt_slot(pool_hist, P - 1)[0] = pool;
+    adapt_slot(pool_hist, P - 1)[1] = pool_rem;
   }
   __syncthreads();
-  const bool own = a.floor != 0u, pooled = a.rest != 0u && x.own > x.pool;
+  const bool counted = a.floor != 0u, pooled = a.rest != 0u && own > pool;
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) {
     if (base + j * kSelThreads + tid < a.n) {
       const uint32_t digit = P == 1 ? (u[j] >> 10) & 2047u : u[j] & 1023u;
-      if (own && (u[j] >> SHIFT) == x.own) atomicAdd(&s_own[digit], 1u);
-      if (pooled && (u[j] >> SHIFT) == x.pool) atomicAdd(&s_pool[digit], 1u);
+      if (counted && (u[j] >> SHIFT) == own) atomicAdd(&s_own[digit], 1u);
+      if (pooled && (u[j] >> SHIFT) == pool) atomicAdd(&s_pool[digit], 1u);
     }
   }
   __syncthreads();
   for (int i = tid; i < kSelBins / P; i += kSelThreads) {
     const uint32_t c = s_own[i], d = s_pool[i];
-    if (c) atomicAdd(&hist[P * kSelBins + i], c);
-    if (d) atomicAdd(&pool[P * kSelBins + i], d);
+    if (c && a.nblk > 1) atomicAdd(&hist[P * kSelBins + i], c);
+    if (d) atomicAdd(&pool_hist[P * kSelBins + i], d);
   }
+  if (!counted) return;
+  const bool shared = a.rest != 0u && own == pool;
+  if (a.nblk == 1) {
+    adapt_cut<P>(a, unit, hist, pool_hist, own, own_rem, shared, s_own, s);
+    return;
+  }
+  // Every thread waits for its own counts, which are atomics of the whole chip and in their place when they are acknowledged; then
+  // the block's mark; and the last block reads past its caches.  (Fences of that reach write back and empty the dies' L2 for
+  // every block: select_adaptive, 32 heads x 32768, half of the budget by head, 52 us
+  // and 39.)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) s_counted = atomicAdd(hist + 2 * kSelBins + kCountedSlot + P, 1u);
+  __syncthreads();
+  if (s_counted != (uint32_t)a.nblk - 1u) return;
+  adapt_cut<P>(a, unit, hist, pool_hist, own, own_rem, shared, nullptr, s);
 }
 
 // The heads' lists and lengths, see k_sel_emit: blocks by ticket in the order of (head, block), waiting for lower ones only.
 __global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
   constexpr int W = kSelThreads / 64, U = 2;
-  __shared__ AdaptShared s;
+  constexpr int PER = kSelBins / 2 / kSelThreads;
+  __shared__ BinSearch<kSelThreads> s;
   __shared__ uint32_t s_w[2][W];
   __shared__ uint32_t s_front[4];
-  __shared__ uint32_t s_blk;
+  __shared__ uint32_t s_blk, s_share;
   const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x % a.B;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (tid == 0) s_blk = atomicAdd(a.pool + ((size_t)b * 3 + 2) * kSelBins + kEmitTicket, 1u);
+  uint32_t* pool_hist = a.pool + (size_t)b * 3 * kSelBins;
+  if (tid == 0) {
+    s_blk = atomicAdd(pool_hist + 2 * kSelBins + kEmitTicket, 1u);
+    s_share = 0u;
+  }
+  uint32_t cnt[PER];
+  load_bins<kSelThreads>(pool_hist + 2 * kSelBins, cnt);
+  uint32_t pool = adapt_slot(pool_hist, 1)[0], pool_rem = adapt_slot(pool_hist, 1)[1];
   __syncthreads();
   const int ticket = __builtin_amdgcn_readfirstlane((int)s_blk);
   if (ticket >= a.H * a.nblk) return;           // (a counter that did not start at zero)
@@ -722,8 +701,22 @@ __global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
     const int m = (int)min(max(left - 64 * j, 0ll), 64ll);
     return m >= 64 ? ~0ull : (1ull << m) - 1ull;
   };
-  const AdaptPrefix x = adapt_digit<2>(a, b, h, s);
-  const uint32_t T = __builtin_amdgcn_readfirstlane(min(x.own, x.pool));
+  uint32_t own = kNoPrefix, own_rem = 0u;
+  const uint2* owns = a.own + (size_t)b * a.H;           // of the sequence's first head
+  if (a.floor) { own = owns[h].x; own_rem = owns[h].y; }
+  if (a.rest) {
+    uint32_t bin;
+    find_bin<kSelThreads>(s, cnt, pool_rem, &bin, &pool_rem);
+    pool = (pool << 10) | bin;
+    const uint32_t lo = (uint32_t)((kSelThreads - 1 - tid) * PER);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (lo + i == bin && cnt[i] != pool_rem) s_share = 1u;     // not all of the pool's scores at its threshold are kept
+  } else {
+    pool = kNoPrefix;
+  }
+  const uint32_t T = __builtin_amdgcn_readfirstlane(min(own, pool));
+  const bool at_pool = a.rest != 0u && T == pool;
   uint32_t gt = 0, eq = 0;
 #pragma unroll
   for (int j = 0; j < kSelPer; ++j) {
@@ -736,7 +729,7 @@ __global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
   if (tid == 0) {
     uint32_t g = 0, e = 0;
     for (int w = 0; w < W; ++w) { g += s_w[0][w]; e += s_w[1][w]; }
-    __hip_atomic_store(&pub[ticket], kEmitSeen | (T == x.pool ? kEmitPool : 0u) | (e << 13) | g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&pub[ticket], kEmitSeen | (at_pool ? kEmitPool : 0u) | (e << 13) | g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // in the head's blocks in front of this one: above T and at T; in the heads in front: at the pool's threshold
   if (wave == 0) {
@@ -744,7 +737,10 @@ __global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
     int spin = 0;
     const int own0 = h * a.nblk;
     // (without a tie to share out the heads in front do not matter)
-    for (int j0 = (T == x.pool ? 0 : own0) + lane; j0 < ticket && spin < kEmitSpinLimit; j0 += U * 64) {
+    const bool share = at_pool && s_share != 0u;
+    if (share && a.floor)                                // at the pool's threshold, but of the floors of the heads in front
+      for (int g = lane; g < h; g += 64) pf -= owns[g].x == pool ? owns[g].y : 0u;
+    for (int j0 = (share ? 0 : own0) + lane; j0 < ticket && spin < kEmitSpinLimit; j0 += U * 64) {
       uint32_t word[U];
 #pragma unroll
       for (int y = 0; y < U; ++y)
@@ -774,11 +770,8 @@ __global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
   __syncthreads();
   if (!s_front[3]) return;
   // scores at T to keep: the floor's, and the pool's that the heads in front have left
-  uint32_t q = T == x.own ? x.own_rem : 0u;
-  if (T == x.pool) {
-    const uint32_t taken = s_front[2] - x.ties_front;
-    q += taken < x.pool_rem ? x.pool_rem - taken : 0u;
-  }
+  uint32_t q = T == own ? own_rem : 0u;
+  if (at_pool) q = s_share == 0u ? (uint32_t)a.n : q + (s_front[2] < pool_rem ? pool_rem - s_front[2] : 0u);
   q = __builtin_amdgcn_readfirstlane(q);
   uint32_t pos = s_front[0], eq_before = s_front[1];
   for (int w = 0; w < W; ++w) {
@@ -795,8 +788,8 @@ __global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
 }
 
 hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor, int32_t* idx,
-                                  int32_t* lengths, uint32_t* hist, uint32_t* pool_hist, uint32_t* blk, bool hist0_done,
-                                  hipStream_t st) {
+                                  int32_t* lengths, uint32_t* hist, uint32_t* pool_hist, uint32_t* blk, uint2* own,
+                                  bool hist0_done, hipStream_t st) {
   if (n_keep == 0) return launch_zero((uint32_t*)lengths, d.units(), st);
   const int nblk = (int)((n + kSelBlock - 1) / kSelBlock);
   AdaptArgs a;
@@ -806,6 +799,7 @@ hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n,
   a.rest = (uint32_t)((n_keep - floor) * d.Hkv);
   a.hist = hist;
   a.pool = pool_hist;
+  a.own = own;
   a.blk = blk;
   a.idx = idx;
   a.lengths = lengths;
