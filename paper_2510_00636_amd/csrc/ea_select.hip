@@ -323,11 +323,11 @@ __device__ __forceinline__ SmallShare small_share(int n) {
   return SmallShare{rows, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) * 64 * rows + ((int)threadIdx.x & 63)};
 }
 
-// The selection out of the registers of the workgroup.  HIST0: the caller's first histogram.
+// The selection out of the registers of the workgroup, to out[0 .. n_keep).  HIST0: the caller's first histogram; else s_hist0 is
+// LDS for it, kSelBins * kSelCopies words that are free again (`out` may be there) when the positions are written.
 template <int PER, bool HIST0>
-__device__ __forceinline__ void select_unit(const SelArgs& a, int unit, const uint32_t (&u)[PER]) {
+__device__ __forceinline__ void select_unit(const SelArgs& a, int unit, const uint32_t (&u)[PER], uint32_t* s_hist0, int32_t* out) {
   constexpr int NT = kSelSmallThreads;
-  __shared__ __align__(16) uint32_t s_hist0[HIST0 ? 1 : kSelBins * kSelCopies];
   __shared__ __align__(16) uint32_t s_hist1[kSelBins], s_hist2[kSelBins / 2];
   __shared__ BinSearch<NT> s_find[3];
   __shared__ uint32_t s_w[2][NT / 64];
@@ -398,7 +398,6 @@ __device__ __forceinline__ void select_unit(const SelArgs& a, int unit, const ui
   for (int w = 0; w < wave; ++w) { pos += s_w[0][w]; eq_before += s_w[1][w]; }
   pos = __builtin_amdgcn_readfirstlane(pos + (eq_before < q ? eq_before : q));
   eq_before = __builtin_amdgcn_readfirstlane(eq_before);
-  int32_t* out = a.idx + (size_t)unit * a.n_keep;
 #pragma unroll
   for (int it = 0; it < PER; ++it) emit_row(inside(it), u[it], T, q, pos, eq_before, out, a.n_keep, base + 64 * it);
 }
@@ -407,10 +406,11 @@ template <int PER, bool HIST0>
 __global__ __launch_bounds__(kSelSmallThreads) void k_sel_small(SelArgs a) {
   const SmallShare x = small_share((int)a.n);
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)blockIdx.x * a.n;
+  __shared__ __align__(16) uint32_t s_hist0[HIST0 ? 1 : kSelBins * kSelCopies];
   uint32_t u[PER];
 #pragma unroll
   for (int it = 0; it < PER; ++it) u[it] = sc[min(x.base + 64 * min(it, x.rows - 1), (int)a.n - 1)];
-  select_unit<PER, HIST0>(a, blockIdx.x, u);
+  select_unit<PER, HIST0>(a, blockIdx.x, u, s_hist0, a.idx + (size_t)blockIdx.x * a.n_keep);
 }
 
 // The finalize pass of a unit (k_finalize, the same numbers) in front of its selection.
@@ -463,7 +463,8 @@ __global__ __launch_bounds__(kSelSmallThreads) void k_finish_select(SelArgs a, c
     u[it] = __float_as_uint(sc);
     scores[(size_t)unit * n + at[it]] = sc;              // (rows past the share's end: its last one, or the head's, again)
   }
-  select_unit<PER, false>(a, unit, u);
+  __shared__ __align__(16) uint32_t s_hist0[kSelBins * kSelCopies];
+  select_unit<PER, false>(a, unit, u, s_hist0, a.idx + (size_t)unit * a.n_keep);
 }
 
 hipError_t launch_finish_select(const Dims& d, int64_t n, const void* logits, int logits_f64, const float* vnorm, const void* part,
@@ -787,11 +788,55 @@ __global__ __launch_bounds__(kSelThreads) void k_adapt_emit(AdaptArgs a) {
   if (blk == a.nblk - 1 && tid == kSelThreads - 1) a.lengths[unit] = (int32_t)pos;
 }
 
+// Short layers without a floor: the pooled list of a sequence by one workgroup, into LDS, and from there to the heads.
+// (select_adaptive, us, with the launches above and with this: 8 heads x 64 20.6 and 9.7, x 1000 21.2 and 10.8, 8 sequences of
+// them 21.3 and 11.2; compress_layer_adaptive, 8 x 64 40.0 and 29.5, x 1000 44.4 and 40.7.)
+constexpr int kAdaptSmallMax = kSelBins * kSelCopies, kAdaptSmallHeads = 2047;
+static_assert(kAdaptSmallMax <= 8 * kSelSmallThreads, "scores per thread");
+template <int PER>
+__global__ __launch_bounds__(kSelSmallThreads) void k_adapt_small(SelArgs a, int H, int n, int32_t* __restrict__ lengths) {
+  __shared__ __align__(16) uint32_t s_list[kAdaptSmallMax];
+  __shared__ int s_start[kAdaptSmallHeads + 1];          // of a head's part of the list
+  const int tid = threadIdx.x, b = blockIdx.x, kept = (int)a.n_keep;
+  const SmallShare x = small_share((int)a.n);
+  const uint32_t* sc = reinterpret_cast<const uint32_t*>(a.scores) + (size_t)b * a.n;
+  uint32_t u[PER];
+#pragma unroll
+  for (int it = 0; it < PER; ++it) u[it] = sc[min(x.base + 64 * min(it, x.rows - 1), (int)a.n - 1)];
+  const int* list = reinterpret_cast<const int*>(s_list);
+  select_unit<PER, false>(a, b, u, s_list, reinterpret_cast<int32_t*>(s_list));
+  __syncthreads();
+  for (int j = tid; j < kept; j += kSelSmallThreads) {
+    const int h = list[j] / n, before = j > 0 ? list[j - 1] / n : -1;
+    for (int g = before + 1; g <= h; ++g) s_start[g] = j;
+    if (j == kept - 1)
+      for (int g = h + 1; g <= H; ++g) s_start[g] = kept;
+  }
+  __syncthreads();
+  for (int j = tid; j < kept; j += kSelSmallThreads) {
+    const int h = list[j] / n;
+    a.idx[((size_t)b * H + h) * n + (j - s_start[h])] = list[j] - h * n;
+  }
+  for (int h = tid; h < H; h += kSelSmallThreads) lengths[(size_t)b * H + h] = s_start[h + 1] - s_start[h];
+}
+
 hipError_t launch_select_adaptive(const Dims& d, const float* scores, int64_t n, int64_t n_keep, int64_t floor, int32_t* idx,
                                   int32_t* lengths, uint32_t* hist, uint32_t* pool_hist, uint32_t* blk, uint2* own,
                                   bool hist0_done, hipStream_t st) {
   if (n_keep == 0) return launch_zero((uint32_t*)lengths, d.units(), st);
   const int nblk = (int)((n + kSelBlock - 1) / kSelBlock);
+  if (floor == 0 && d.Hkv * n <= kAdaptSmallMax && d.Hkv <= kAdaptSmallHeads) {
+    SelArgs f = {};
+    f.scores = scores;
+    f.n = d.Hkv * n;
+    f.n_keep = (uint32_t)(d.Hkv * n_keep);
+    f.idx = idx;
+    f.status = hist + 2 * kSelBins + kStatusSlot;
+    if (f.n <= 2 * kSelSmallThreads) k_adapt_small<2><<<d.B, kSelSmallThreads, 0, st>>>(f, d.Hkv, (int)n, lengths);
+    else if (f.n <= 4 * kSelSmallThreads) k_adapt_small<4><<<d.B, kSelSmallThreads, 0, st>>>(f, d.Hkv, (int)n, lengths);
+    else k_adapt_small<8><<<d.B, kSelSmallThreads, 0, st>>>(f, d.Hkv, (int)n, lengths);
+    return hipGetLastError();
+  }
   AdaptArgs a;
   a.scores = scores;
   a.n = n;

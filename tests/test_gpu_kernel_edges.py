@@ -561,13 +561,14 @@ def test_projection_blocks_of_whole_lines(w, dm, hq, hkv):
     P.check_stats(mu.cpu().numpy(), sg.cpu().numpy(), rmu, rsg)
 
 
-@pytest.mark.parametrize("hkv,n", [(3, 4096), (5, 4097), (16, 300), (17, 300), (40, 5000), (2, 25000), (130, 300), (70, 9000)])
+@pytest.mark.parametrize("hkv,n", [(3, 4096), (5, 4097), (16, 300), (17, 300), (40, 5000), (2, 25000), (130, 300), (70, 9000),
+                                   (1, 3), (1, 64), (2, 4096), (3, 2731), (2047, 4), (2048, 4)])
 @pytest.mark.parametrize("kind", ["spread", "ties", "equal", "special", "shared"])
 def test_adaptive_selection_shares_out_ties(hkv, n, kind):
     """Budgets shared by a layer's heads where the floor's threshold of a head lies above the pool's, at it and below it: few
     distinct values and a single one (all that decides is the order of heads and positions), zero, denormals and infinity,
-    and heads whose first digits agree and whose later ones do not; heads of one block and of several, and more heads than a
-    wavefront has lanes; floors of none, one, some and all of the budget.  Exactly the oracle's lists."""
+    and heads whose first digits agree and whose later ones do not; heads of one block and of several, more heads than a
+    wavefront has lanes, and layers on both sides of the limits (scores and heads) up to which one workgroup takes them; floors of none, one, some and all of the budget.  Exactly the oracle's lists."""
     import torch
     cfg = CONFIGS["c2"].with_(batch=2, n_kv_heads=hkv, n_q_heads=hkv)
     p = P.params_for(cfg)
