@@ -14,17 +14,26 @@ namespace ea {
 
 // Consecutive workgroups run on different dies, and with as many heads as dies a head's are on one: its fragments, which every
 // workgroup starts with, then come out of that die's L2, and its counters are near.  In the transposed order every head has
-// workgroups on all dies, and all of them share the heads evenly, which is what counts in a long call of several passes.
-// Operands + score, us, transposed and plain.  Register-fragment kernel, one pass: 8 x 20000 40.6 and 38.6, 32 x 8000 54.6 and
-// 51.4, 8 x 100000 108.6 and 104.9, 8 x 131072 even; two: 8 x 20000 58.2 and 55.6, 16 x 3000 33.7 and 28.9, but 8 x 131072 227
-// and 235; three heads of G = 12 x 40000 81.0 and 83.5.  LDS-fragment kernel, one pass: d = 256, G = 2, 8 x 3000 46.8 and 42.8,
-// 8 x 20000 73.1 and 70.1, 8 x 100000 of G = 1 164 and 167; d = 64, 16 x 8000 38.8 and 36.6, 32 x 32768 66.2 and 66.7, 2 x 100000 32.4 and 34.2; in
+// workgroups on all dies, and all of them share the heads evenly, which is what counts in a long call.
+// query_stats + score, us, transposed and plain; register-fragment kernel, G = 4: 8 x 20000 43.9 and 42.1, 16 x 3000 35.7 and 30.6,
+// 32 x 20000 99.7 and 95.0, 8 x 131072 138 and 135, 64 x 60000 475 and 465, 12 and 20 heads (that eight does not divide) x 131072
+// 196 and 197, 313 and 316; but 16 x 131072 246 and 249, 32 x 60000 241 and 244, x 131072 477 and 493; 8-bit rows 8 x 60000 67.1
+// and 65.4, 64 x 32768 227 and 220, but 8 x 131072 113 and 116, 16 x 131072 207 and 213, 32 x 131072 399 and 406; block pools 8 x
+// 60000 82.2 and 79.1, 32 x 60000 252 and 257.  Several passes: G = 6, 8 x 20000 60.9 and 58.5, 16 x 2000 38.9 and 35.4, but x 20000
+// 88.1 and 99.5; G = 12, three heads x 8000 39.6 and 41.4.
+// LDS-fragment kernel, one pass: d = 256, G = 1, 32 x 3000 54.1 and 53.3, 8 x 20000 59.5 and 60.4, 8 x 40000 81.1 and 83.0; G = 2, 8 x
+// 12000 66.3 and 62.7, x 20000 81.8 and 78.9, x 40000 118 and 117; d = 64, G = 4, 16 x 12000 36.3 and 33.6, x 30000 51.4 and 48.5,
+// 32 x 20000 60.5 and 59.1, x 32768 even; G = 8, 8 x 70000 70.9 and 71.7, 32 x 20000 79.2 and 79.4; in
 // several passes plain is up to 16 % slower (d = 64, G = 16, one x 100000 48.7 and 56.6; d = 256, G = 8, 8 x 8000 104 and 119).
 static bool transposed_order(const Dims& d, const ScorePlan& sp, int64_t n) {
   if (sp.spare) return false;                 // (their order is the order of coming)
   const int64_t units = d.units();
-  if (!sp.hw && !sp.five) return sp.passes > 1 || n > 40000 || units * n > (d.D == 64 ? 300000 : 100000);
-  return sp.passes > 1 && (units % 8 != 0 || units * sp.npart * sp.passes > 8500);
+  if (!sp.hw && !sp.five) {
+    if (d.D == 64) return sp.passes > 1 || n > 60000 || units * n > 600000;
+    return sp.passes > 1 || n > 40000 || units * n > (d.D == 256 && sp.GH == 2 ? 320000 : 100000);
+  }
+  if (sp.passes == 1) return units <= 32 && units * sp.npart > (d.kv_fp8 ? 16000 : 30000);
+  return units % 8 != 0 || units * sp.npart * sp.passes > 8500;
 }
 
 hipError_t launch_score_mfma(const Dims& d, const ScorePlan& sp, const void* k, const void* v,
