@@ -52,13 +52,17 @@ int main() {
             for (int64_t t = 0; t < ntiles; ++t) CHECK(seen[t] == 1, "n %ld: tile %ld", (long)n, (long)t);
           }
   CHECK(five > 100, "%d plans", five);
-  // shapes of which one kernel is the faster one by 3 % or more: G, units, keys, 8-bit, behind statistics, five
+  // shapes of which one kernel is the faster one by 3 % or more (G, units, keys, 8-bit, behind statistics, five),
   const struct { int G, units; int64_t n; int fp8, stats, five; } measured[] = {
       {5, 8, 20000, 0, 0, 1}, {5, 192, 4608, 0, 0, 1}, {5, 320, 1500, 0, 0, 1}, {9, 32, 4608, 0, 0, 1}, {9, 8, 60000, 0, 0, 0},
       {5, 32, 4608, 1, 0, 1}, {5, 32, 32768, 1, 0, 0}, {13, 4, 131072, 0, 0, 1}, {9, 8, 25000, 0, 1, 1}, {5, 8, 12000, 0, 1, 1},
       {4, 8, 20000, 0, 0, 0}, {3, 40, 5000, 0, 1, 0}, {5, 8, 63, 0, 0, 0}, {5, 16, 60000, 0, 0, 0}, {5, 150, 4608, 0, 0, 1},
       {5, 320, 6940, 0, 0, 0}, {5, 300, 9000, 0, 1, 0}, {14, 200, 4608, 0, 0, 0}, {18, 140, 4000, 0, 1, 0}, {14, 230, 3000, 0, 0, 1},
-      {18, 100, 5000, 0, 0, 1}};
+      {18, 100, 5000, 0, 0, 1},
+      // and those that the GPU test of this form means to reach it with, either way
+      {5, 36, 4100, 0, 0, 1}, {5, 36, 4097, 0, 1, 1}, {5, 300, 1030, 0, 0, 1}, {5, 40, 4160, 0, 1, 1}, {9, 9, 16449, 0, 0, 1},
+      {9, 9, 16449, 1, 0, 1}, {10, 9, 16449, 0, 0, 1}, {10, 9, 16449, 0, 1, 1}, {10, 9, 16449, 1, 0, 1}, {10, 100, 1030, 0, 0, 1},
+      {10, 100, 1030, 1, 0, 1}, {13, 200, 64, 0, 0, 1}, {13, 200, 64, 1, 0, 1}, {15, 150, 1030, 0, 1, 1}, {10, 64, 2049, 0, 0, 0}};
   for (const auto& m : measured) {
     ea_params p;
     memset(&p, 0, sizeof p);

@@ -123,9 +123,9 @@ def test_select_row_edges(n, kind):
 @pytest.mark.parametrize("n,n_keep,floor", [(4095, 2000, 1), (4096, 4000, 4000), (4097, 1500, 700), (5500, 5500, 17),
                                             (8193, 300, 300), (16385, 9000, 4097)])
 def test_adaptive_selection_block_edges(n, n_keep, floor):
-    """The copy that lifts every head's own best pairs, around its 4096-score blocks, with the pooled list in
-    one launch (3 n <= 16384) and in several: lists and lengths are exactly the oracle's.  The whole call is
-    made twice on one workspace: nothing of the first may be left in it."""
+    """Budgets shared by three heads of one block of 4096 scores and of a few, where every head's own digits are found
+    by its last block, with floors from one to all of the budget and scores of different scales: lists and lengths
+    are exactly the oracle's.  The whole call is made twice on one workspace: nothing of the first may be left in it."""
     import torch
     cfg = CONFIGS["c2"].with_(batch=2, n_kv_heads=3, n_q_heads=3)
     p = P.params_for(cfg)
@@ -146,11 +146,12 @@ def test_adaptive_selection_block_edges(n, n_keep, floor):
     assert ea.debug_status(p, n, 1, ws) == 0
 
 
-@pytest.mark.parametrize("n", [16385, 20480, 20481, 270000])
+@pytest.mark.parametrize("n", [16385, 20480, 20481, 24577, 28672, 28673, 270000])
 @pytest.mark.parametrize("kind", ["spread", "ties", "equal"])
 def test_select_blocks(n, kind):
-    """Selections of several launches: last blocks of one score and of 4096, more than 64 blocks, ties that
-    run across blocks; twice on one workspace, where the second call must not see the first one's counts."""
+    """Selections of several launches (from 24577 scores on) and long ones of one: last blocks of one score and of 4096,
+    more than 64 blocks, ties that run across blocks; several on one workspace, where a call must not see the counts of
+    the one before."""
     import torch
     rng = np.random.default_rng(n)
     cfg = CONFIGS["c1"].with_(n_q_heads=3, n_kv_heads=3)
@@ -341,11 +342,11 @@ def test_fused_statistics_behind_every_compress_call(form, d, hq, hkv, batch, w)
     _same_operands(d, hq * batch, got.cpu().numpy(), want.cpu().numpy())
 
 
-@pytest.mark.parametrize("n,w,floor", [(16385, 64, 300), (20481, 2, 300), (20481, 64, 0), (16385, 3, 6000)])
+@pytest.mark.parametrize("n,w,floor", [(16385, 64, 300), (20481, 2, 300), (20481, 64, 0), (16385, 3, 6000), (4096, 64, 0), (777, 20, 0)])
 def test_adaptive_pass_over_long_heads(n, w, floor):
-    """The whole adaptive call where the heads' selection takes several launches: the first digit of the heads'
-    and of the pooled lists counted on the way, everything cleared at the start of the call, also under
-    windows of a few samples (one or two workgroups for the table).  Two passes over different caches on one
+    """The whole adaptive call over heads of several blocks: their first digits counted on the way, everything cleared at
+    the start of the call, also under windows of a few samples (one or two workgroups for the table); and over short
+    layers without a floor, which one workgroup selects from.  Two passes over different caches on one
     workspace that starts with rubbish; lists, lengths and moved rows are exactly the oracle's for the
     call's own scores, and a NaN value row shows in the status word."""
     import torch
@@ -600,10 +601,12 @@ def test_adaptive_selection_shares_out_ties(hkv, n, kind):
         assert ea.debug_status(p, n, 1, ws) == 0
 
 
-@pytest.mark.parametrize("hq,batch,n", [(5, 36, 4100), (5, 36, 4097), (5, 300, 1030), (5, 40, 64 * 65), (9, 9, 16449), (10, 64, 2049)])
+@pytest.mark.parametrize("hq,batch,n", [(5, 36, 4100), (5, 36, 4097), (5, 300, 1030), (5, 40, 64 * 65), (9, 9, 16449), (10, 64, 2049),
+                                        (10, 9, 16449), (10, 100, 1030), (13, 200, 64), (15, 150, 1030)])
 def test_five_heads_per_pass_in_registers(hq, batch, n):
     """d = 128, passes of five query heads of which the wavefronts share the last: heads whose last tile of 64 keys holds 1, 4,
-    6 or all of them, spare workgroups, a second pass of four heads and of five, on contiguous tensors, 8-bit caches and the
+    6 or all of them, spare workgroups, a second pass of four heads and of five, three passes, both with spare workgroups (the
+    row of 64 sequences takes four heads per pass: the rule's other side), on contiguous tensors, 8-bit caches and the
     forms without a value side, and behind the statistics that make the operands tile by tile.  Against the oracle at the bf16
     tolerance (norms at half of it, a square root); twice with the same bits; a head's NaN stays its own."""
     import torch
@@ -644,7 +647,7 @@ def test_five_heads_per_pass_in_registers(hq, batch, n):
         torch.cuda.synchronize()
         real = [X.fp8_e4m3_decode(c) * s.astype(np.float64)[:, :, None, None] for c, s in ((k8, ks), (v8, vs))]
         P.check_scores(again.cpu().numpy(), O.scores(real[0], real[1], mu.astype(np.float64), sigma.astype(np.float64), eps), 2e-3)
-    for g in (0, 4):                                       # of the first sequence: all its scores, and no other sequence's
+    for g in (0, 4, hq - 1):                               # of the first sequence: all its scores, and no other sequence's
         bad = mu.copy()
         bad[0, g, 5] = np.nan
         ea.score(p, k, v, n, n, P.to_dev(bad), sgd, again, ws)
@@ -652,15 +655,18 @@ def test_five_heads_per_pass_in_registers(hq, batch, n):
         assert torch.isnan(again[0]).all() and torch.equal(again[1:], sc[1:]), g
 
 
-@pytest.mark.parametrize("dtype,n", [(t, n) for t in ("bf16", "f32") for n in (1, 63, 64, 1023, 1024, 1025, 2048, 2049, 3073, 4095, 4096, 4097)] +
-                         [("bf16", 5120), ("bf16", 5121)])
-def test_finalize_and_selection_in_one_launch(dtype, n):
+@pytest.mark.parametrize("dtype,n,heads", [(t, n, (5, 9)) for t in ("bf16", "f32") for n in (1, 63, 64, 1023, 1024, 1025, 2048, 2049, 3073, 4095, 4096, 4097)] +
+                         [("bf16", 5120, (5, 9)), ("bf16", 5121, (5, 9))] +
+                         [("bf16", 640, (17, 63, 64)), ("bf16", 641, (64,)), ("bf16", 2400, (16, 17)), ("f32", 336, (17, 64)), ("f32", 337, (64,)),
+                          ("f32", 1075, (20,))])
+def test_finalize_and_selection_in_one_launch(dtype, n, heads):
     """Compress calls around the rows per thread of the launch that finishes the scores of a head and selects from them, and on
-    both sides of its limits, with five and nine query heads per KV head (four are added up at a time).  The scores are the
+    both sides of its limits, with five and nine query heads per KV head (four are added up at a time) and with more of them
+    than its wavefronts, which then take several log-sum-exps each.  The scores are the
     score call's bit for bit where the operands are (fp32), the positions the stable top-k of the call's own scores, the
     rows moved accordingly, and a NaN value row shows in the status word."""
     import torch
-    for hq in (5, 9):
+    for hq in heads:
         cfg = CONFIGS["c2" if dtype == "bf16" else "c1"].with_(n_q_heads=hq, n_kv_heads=1, batch=2)
         w = min(n, 20)
         lay = make_layer(cfg, n=n, window=w)

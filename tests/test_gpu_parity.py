@@ -221,7 +221,7 @@ def test_score_c2_full_size():
                                       (32768, 30000), (32769, 1), (32769, 32768),
                                       (70000, 35000), (70001, 69999)])
 def test_select_exact(n, n_keep):
-    # heads of up to 16384 scores are selected by one workgroup out of LDS, longer ones by the
+    # heads of up to 24576 scores are selected by one workgroup out of its registers, longer ones by the
     # multi-launch histogram path: sizes on both sides of the switch
     cfg = CONFIGS["c2"].with_(batch=2, n_kv_heads=3, n_q_heads=3)
     r = np.random.default_rng(n * 7 + n_keep)
