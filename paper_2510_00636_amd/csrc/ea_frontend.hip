@@ -223,7 +223,8 @@ hipError_t launch_project(const Dims& d, const void* hidden, const void* wq, int
     // The more samples a workgroup takes, the less often W_Q is read: 64 where that leaves two workgroups per CU, else 32 (us
     // of statistics and the short pass behind them, 64 and 32 samples: 128 x 4096 hidden states, 32 heads 57.9 and 57.0; 128 x
     // 5120, 40 heads 73.2 and 70.3; 200 x 4096, 32 heads 68.3 and 69.3; 512 x 4096 99 and 104.6), and fewer where the
-    // workgroups would leave a quarter of the CUs without one (64 x 4096, 64 samples 55.0, 32 50.8).
+    // workgroups would leave a quarter of the CUs without one (64 x 4096, 64 samples 55.0, 32 50.8).  (Rows of less than two
+    // blocks gain nothing from the patch: 1024 samples x 72, 64 heads, 67 us straight into the operand layout and 73.)
     auto blocks = [&](int mt) { return (int64_t)((w + 16 * mt - 1) / (16 * mt)) * (d.Hq * d.D / 32) * d.B; };
     int mt = w > 32 ? 4 : w > 16 ? 2 : 1;
     if (mt == 4 && blocks(mt) < 2 * (int64_t)device_num_cu()) mt = 2;

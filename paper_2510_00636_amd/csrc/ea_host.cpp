@@ -178,8 +178,12 @@ static ScorePlan register_plan(const Dims& d, int64_t n, int num_cu) {
   return s;
 }
 
-// Which of the two kernels serves a call that both can: the lines are where operands + score take as long with either, over
-// 2400 shapes.  Figures: us with the LDS-fragment kernel and with this one, 8-bit rows behind the bar.
+// Which of the two kernels serves a call that both can: the lines are where operands + score took as long with either, over
+// 2400 shapes, when this kernel's workgroups stood in the transposed order (see transposed_order) and it alone had its operands
+// from the statistics.  Since then calls on both sides of them have become faster, and over 280 shapes most of those that
+// the other kernel would serve better by more than 3 % lie outside: compress, G = 3, 128 x 2585 111 and 97, 64 x 447 40 and 36,
+// 256 x 419 of G = 2 63 and 58; inside, 8-bit G = 10, 2 x 52097 82 and 88.
+// Figures: us with the LDS-fragment kernel and with this one, 8-bit rows behind the bar.
 static bool registers_serve(const Dims& d, int64_t n, int num_cu, const ScorePlan& lds, const ScorePlan& hw, bool from_stats) {
   // As many passes, and every wavefront (or all but the last pass's fourth) with a head: this one.  G = 4, 8 x 16384 38
   // and 31, 192 x 4608 150 and 140, 64 x 9000 85 and 86; G = 7, 8 x 45000 104 and 104; G = 12, 64 x 9000 186 and 175

@@ -25,7 +25,8 @@ hipError_t launch_stats(const Dims& d, const void* q_win, int w, const float2* t
 // way.  At d = 128 two workgroups that share a head each make the fragments of their own tiles of Sigma, in either score
 // kernel's layout (whole pass, 8 heads x 16384, 94.5 -> 91.2 us with the
 // histogram of the finalize pass, x 3000 57.3 -> 53.7; 32 x 9000 138 -> 132); from 192 heads on a head is one workgroup's
-// (decode-time shape, 960 heads, w = 512: 422 and 396).  At d = 256 Sigma's tiles stay apart.
+// (whole pass, n = 4608, w = 512, us, two workgroups per head and one: 32 query heads 45.8 and 49.6, 128 69.4 and 73.0, 160 82.4
+// and 80.0, 192 89.5 and 89.0, 288 125 and 121, 512 181 and 167, 960 308 and 281).  At d = 256 Sigma's tiles stay apart.
 // One workgroup: the same operands bit for bit.  Two: up to the power of two by which a head's M is scaled, which
 // comes from sums of squares there and from Sigma's diagonal else; where the largest entry lies within rounding of a power
 // of two they can differ by a factor of two, which moves only entries under 2^-26 of it (fp16 subnormals).
