@@ -240,8 +240,9 @@ ScorePlan choose_score_plan(const Dims& d, int64_t n, int num_cu, bool from_stat
 //   two passes over long heads: G = 9, 8 x 20000 73.0 and 71.6, 8 x 60000 138 and 143, 8-bit 128 and 129.
 // Nor where its two workgroups per job share out the chip worse than the other kernel's three, which takes heads of some length:
 //   one pass, jobs for every CU: 320 x 1500 170 and 168, x 4000 258 and 274, x 13000 610 and 684; 300 x 9000 441 and 498;
-//   several, a little more than two per CU: G = 14, 180 x 4608 465 and 483, 200 x 4608 491 and 517; G = 18, 140 x 4000 426 and 459
-//     (but G = 14, 230 x 3000 479 and 460).
+//   three and more, a little more than one per CU or than two: 280 to 320 jobs over heads x 6000 up to 12 % more, x 13000 17 % (G = 40,
+//     33 units; G = 20, 75), x 2500 even, 350 jobs even; G = 14, 180 x 4608 465 and 483, 200 x 4608 491 and 517; G = 18, 140 x 4000
+//     426 and 459 (but G = 14, 230 x 3000 479 and 460).
 // In a compress call it comes before the one of four heads per pass, whose lines are drawn further out there (registers_serve):
 // the whole pass, us, that one and this one: G = 5, 8 x 12000 73.2 and 69.7, 20 x 5000 73.5 and 68.7; G = 9, 8 x 25000 140 and
 // 131; G = 10, 16 x 12000 130 and 123.
@@ -252,7 +253,7 @@ ScorePlan serving_score_plan(const Dims& d, int64_t n, int num_cu, bool from_sta
   const bool filled = share == 0 || share * d.units() * 10 >= (int64_t)num_cu * 9;
   bool long_call = s.passes == 2 && tiles * 2 > 12000;
   if (s.passes == 1) long_call = (d.kv_fp8 && tiles > 2600) || (filled && tiles > 10000) || (jobs >= num_cu && n > 2000);
-  else if (s.passes > 2) long_call = n > 2000 && jobs > 2 * num_cu && jobs * 2 < 5 * num_cu;
+  else if (s.passes > 2) long_call = (n > 3000 && jobs > num_cu && jobs * 3 < 4 * num_cu) || (n > 2000 && jobs > 2 * num_cu && jobs * 2 < 5 * num_cu);
   if (s.hw || d.D != 128 || d.dtype != EA_BF16 || s.GH != 5 || n < kHwTile || long_call)
     return choose_score_plan(d, n, num_cu, from_stats);
   s.five = 1;

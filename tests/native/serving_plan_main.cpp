@@ -58,7 +58,7 @@ int main() {
       {5, 32, 4608, 1, 0, 1}, {5, 32, 32768, 1, 0, 0}, {13, 4, 131072, 0, 0, 1}, {9, 8, 25000, 0, 1, 1}, {5, 8, 12000, 0, 1, 1},
       {4, 8, 20000, 0, 0, 0}, {3, 40, 5000, 0, 1, 0}, {5, 8, 63, 0, 0, 0}, {5, 16, 60000, 0, 0, 0}, {5, 150, 4608, 0, 0, 1},
       {5, 320, 6940, 0, 0, 0}, {5, 300, 9000, 0, 1, 0}, {14, 200, 4608, 0, 0, 0}, {18, 140, 4000, 0, 1, 0}, {14, 230, 3000, 0, 0, 1},
-      {18, 100, 5000, 0, 0, 1},
+      {18, 100, 5000, 0, 0, 1}, {20, 72, 13303, 0, 1, 0}, {40, 33, 6000, 0, 0, 0}, {20, 75, 2500, 0, 0, 1}, {30, 63, 6000, 0, 0, 1},
       // and those that the GPU test of this form means to reach it with, either way
       {5, 36, 4100, 0, 0, 1}, {5, 36, 4097, 0, 1, 1}, {5, 300, 1030, 0, 0, 1}, {5, 40, 4160, 0, 1, 1}, {9, 9, 16449, 0, 0, 1},
       {9, 9, 16449, 1, 0, 1}, {10, 9, 16449, 0, 0, 1}, {10, 9, 16449, 0, 1, 1}, {10, 9, 16449, 1, 0, 1}, {10, 100, 1030, 0, 0, 1},
